@@ -1,5 +1,5 @@
 // Split-K reduction pass with the fused epilogue, and the guarded fallback GEMM for
-// shapes the MFMA path does not take (unaligned pointers or dimensions).
+// shapes neither the main kernel nor the ragged one takes.
 #include "launch.h"
 
 namespace fact {
@@ -149,8 +149,8 @@ hipError_t launch_splitk_reduce(const GemmArgs &args, hipStream_t stream)
 
 // ---- guarded fallback ---------------------------------------------------------------------
 // One thread per output element, ascending-k fp32 FMA.  No alignment or divisibility
-// requirement; every access is bounds-guarded.  Slow by design: it exists so that no
-// shape is silently wrong or rejected.
+// requirement; every access is bounds-guarded.  Slow by design: it serves rows shorter than
+// one 16-byte piece (the ragged kernel takes the rest) and is the reference result of the on-device sweep.
 template <bool TRANS_B>
 __global__ void __launch_bounds__(256) fallback_gemm_kernel(const GemmArgs p)
 {

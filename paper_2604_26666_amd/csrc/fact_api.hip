@@ -110,7 +110,7 @@ static int persistent_grid(const ConfigDesc &c, int64_t items)
 }
 
 struct Plan {
-    int cfg = -1;      // -1: fallback kernel
+    int cfg = -1;      // -1: no tile configuration of the main kernel serves it (ragged or guarded kernel)
     int split = 1;
     int group_m = 4;
 };
@@ -334,6 +334,10 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
 
     hipError_t e;
     if (pl.cfg < 0) {
+        if (cfg_id != FACT_CONFIG_GUARDED && ragged_serves(a, q.trans_b != 0)) {
+            e = launch_ragged_gemm(a, q.trans_b != 0, (int)q.batch, stream);
+            return e == hipSuccess ? FACT_OK : hip_fail(e, "ragged gemm launch");
+        }
         e = launch_fallback_gemm(a, q.trans_b != 0, (int)q.batch, stream);
         return e == hipSuccess ? FACT_OK : hip_fail(e, "fallback gemm launch");
     }

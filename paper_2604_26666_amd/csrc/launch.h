@@ -27,4 +27,8 @@ struct ConfigDesc {
 hipError_t launch_splitk_reduce(const GemmArgs &args, hipStream_t stream);
 hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
 
+// GEMM with operands of any alignment and size on the matrix cores (ragged.hip).
+bool ragged_serves(const GemmArgs &args, bool trans_b);
+hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
+
 }  // namespace fact

@@ -1,0 +1,343 @@
+// GEMM for operands the main kernel cannot take: rows that start at any 2-byte address, and any M, N, K
+// (odd leading dimensions, K or N no multiple of 8, unaligned pointers).  The main kernel moves operands
+// straight from global memory into LDS, which needs 16-byte aligned rows; here they pass through registers,
+// where a 16-byte global load may start at any 2-byte address (the unaligned-access mode that the compiler
+// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured cost of odd rows: 2000 x 1999 x
+// 1777 35.7 us, 2000 x 2000 x 1784 through the same kernel 30.9 us; the main kernel, which the latter takes, 24.4 us.
+#include "launch.h"
+#include <atomic>
+
+namespace fact {
+
+typedef u32x4_t u32x4_any __attribute__((aligned(2)));       // 16 bytes at any even address
+typedef u32x2_t u32x2_any __attribute__((aligned(2)));
+
+// 8 elements shifted down by s elements (element e <- element e + s), zeros from the top; s >= 8 gives zeros
+__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int s)
+{
+    const int w = s >> 1;
+    u32x4_t r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int j = i; j < 4; ++j) x = w == j - i ? v[j] : x;
+        r[i] = x;
+    }
+    if (s & 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (r[i] >> 16) | (i < 3 ? r[i < 3 ? i + 1 : 3] << 16 : 0u);
+    }
+    return r;
+}
+
+template <bool F16>
+__device__ __forceinline__ f32x4_t mfma_any(bf16x8_t a, bf16x8_t b, f32x4_t c)
+{
+    typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+    if constexpr (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ s16x4_t read_tr16(const char *lds)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)(lds));
+}
+
+// A work-group owns a BM x BN tile; its 4 KW waves form KW groups of WGM x WGN waves, and group g takes the 64-deep
+// K steps g, g + KW, ...  Each group keeps two LDS stages and two further steps of operands in registers on their
+// way there (the K loop is bound by the loads' latency: with one step in flight and one group per compute unit
+// 2000 x 1999 x 1777 took 45 us, as it stands 35.7 us = 398 TFLOP/s; the one-thread-per-element kernel 3416 us).  A 16-byte piece that would cross the end of a row (K-contiguous operand) or of the
+// matrix's columns (B as [K][N]) is loaded so that it ends there and shifted into place, so nothing outside the
+// matrices is ever read; a step past the end of K brings zeros.
+template <int BM, int BN, int WGM, int WGN, int KW, bool TRANS_B, bool F16>
+__global__ void __launch_bounds__(256 * KW, KW == 1 ? 2 : 1)
+ragged_kernel(const GemmArgs p)
+{
+    static_assert(WGM * WGN == 4, "four waves per group");
+    constexpr int WTM = BM / WGM, WTN = BN / WGN, MT = WTM / 16, NT = WTN / 16, HT = NT / 2;
+    static_assert(NT % 2 == 0, "a gated wave tile pairs gate and up tiles");
+    constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    constexpr int A_LD = BM / 32, B_LD = BN / 32;            // 16-byte pieces per thread and step
+    constexpr int NCH = BN / 8;                              // pieces per K-row of a [K][N] operand
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+
+    const int tid = threadIdx.x & 255, lane = tid & 63;
+    const int wave_all = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), group = wave_all >> 2, wave = wave_all & 3;
+    const int wm = wave / WGN, wn = wave % WGN, r16 = lane & 15, q = lane >> 4;
+    const bool gated = p.act == ACT_SILU_GATE;
+    const int nout = gated ? p.N >> 1 : p.N;
+    int tm, tn;
+    tile_coords(p, blockIdx.x, p.tiles_m * p.tiles_n, tm, tn);
+    const int m0 = tm * BM, n0 = tn * (gated ? BN / 2 : BN);
+    const int64_t z = blockIdx.z;
+    const int K = p.K;
+
+    // ---- global addresses: thread -> piece tid % 8 of rows tid / 8 + 32 i (K-contiguous), piece tid % NCH of K-rows
+    // tid / NCH + i * 256 / NCH ([K][N]).  Rows past the edge repeat the last one: their results are not stored.
+    const int kc = tid & 7;
+    const uint16_t *pa[A_LD], *pb[TRANS_B ? B_LD : 1];
+#pragma unroll
+    for (int i = 0; i < A_LD; ++i) {
+        const int m = m0 + (tid >> 3) + 32 * i;
+        pa[i] = (const uint16_t *)(p.A + z * p.stride_a) + (int64_t)(m < p.M ? m : p.M - 1) * p.lda;
+    }
+    constexpr int KR = 256 / NCH;                            // K-rows a round of loads covers
+    const int nc = tid % NCH, kr = tid / NCH;
+    int shift_n = 0;                                         // [K][N]: this thread's pieces end at column N and move down
+    if constexpr (TRANS_B) {
+#pragma unroll
+        for (int i = 0; i < B_LD; ++i) {
+            const int r = (tid >> 3) + 32 * i;               // LDS row; gated: a wave's rows are its gate columns, then the same up columns
+            const int in_wave = r % WTN, half = WTN / 2;
+            const int n = n0 + (gated ? (r / WTN) * half + in_wave % half : r);
+            const __bf16 *base = gated && in_wave >= half ? p.B_up : p.B;
+            pb[i] = (const uint16_t *)(base + z * p.stride_b) + (int64_t)(n < nout ? n : nout - 1) * p.ldb;
+        }
+    } else {
+        int n = n0 + nc * 8;
+        if (n > p.N - 8) { shift_n = n - (p.N - 8); n = p.N - 8; }
+        pb[0] = (const uint16_t *)(p.B + z * p.stride_b) + n;
+    }
+    const bool ragged_n = !TRANS_B && n0 + BN > p.N;         // uniform
+
+    // Loads of the group's step i: a piece that would pass K ends at K instead, a K-row past K repeats the last one;
+    // to_lds puts such pieces right (uniform branch, taken for the last steps only).
+    struct Step { u32x4_t a[A_LD], b[B_LD]; };
+    auto load = [&](Step &r, int i) __attribute__((always_inline)) {
+        const int k0 = (i * KW + group) * 64;
+        const int c = k0 + kc * 8, at = c < K - 8 ? c : K - 8;
+#pragma unroll
+        for (int x = 0; x < A_LD; ++x) r.a[x] = *(const u32x4_any *)(pa[x] + at);
+#pragma unroll
+        for (int x = 0; x < B_LD; ++x) {
+            if constexpr (TRANS_B) r.b[x] = *(const u32x4_any *)(pb[x] + at);
+            else {
+                const int k = k0 + kr + x * KR;
+                r.b[x] = *(const u32x4_any *)(pb[0] + (int64_t)(k < K ? k : K - 1) * p.ldb);
+            }
+        }
+    };
+    char *const ring = smem + group * 2 * STAGE;
+    auto to_lds = [&](Step &r, int i) __attribute__((always_inline)) {
+        char *s = ring + (i & 1) * STAGE;
+        const int k0 = (i * KW + group) * 64;
+        if (k0 + 64 > K) {
+            const int c = k0 + kc * 8, sh = c < K - 8 ? 0 : c - (K - 8);
+#pragma unroll
+            for (int x = 0; x < A_LD; ++x) r.a[x] = shift_down(r.a[x], sh);
+#pragma unroll
+            for (int x = 0; x < B_LD; ++x) {
+                if constexpr (TRANS_B) r.b[x] = shift_down(r.b[x], sh);
+                else if (k0 + kr + x * KR >= K) r.b[x] = u32x4_t{0u, 0u, 0u, 0u};
+            }
+        }
+        if (ragged_n) {
+#pragma unroll
+            for (int x = 0; x < B_LD; ++x) r.b[x] = shift_down(r.b[x], shift_n);
+        }
+#pragma unroll
+        for (int x = 0; x < A_LD; ++x) {
+            const int row = (tid >> 3) + 32 * x;
+            *(u32x4_t *)(s + row * 128 + ((kc ^ swz_k(row)) << 4)) = r.a[x];
+        }
+#pragma unroll
+        for (int x = 0; x < B_LD; ++x) {
+            if constexpr (TRANS_B) {
+                const int row = (tid >> 3) + 32 * x;
+                *(u32x4_t *)(s + A_BYTES + row * 128 + ((kc ^ swz_k(row)) << 4)) = r.b[x];
+            } else {
+                const int k = kr + x * KR;
+                *(u32x4_t *)(s + A_BYTES + k * (BN * 2) + ((nc ^ swz_n<BN>(k)) << 4)) = r.b[x];
+            }
+        }
+    };
+
+    f32x4_t acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    auto compute = [&](int slot) __attribute__((always_inline)) {
+        const char *s = ring + slot * STAGE;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            bf16x8_t a[MT], b[NT];
+            const int ch = ((4 * kk + q) ^ swz_k(r16)) << 4;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = *(const bf16x8_t *)(s + (wm * WTM + i * 16 + r16) * 128 + ch);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                if constexpr (TRANS_B) {
+                    b[j] = *(const bf16x8_t *)(s + A_BYTES + (wn * WTN + j * 16 + r16) * 128 + ch);
+                } else {
+                    // transposing reads (see the main kernel): lane 4 jj + c of a 16-lane group names K-row jj, columns 4c ..
+                    const int k = 32 * kk + 8 * q + ((lane >> 2) & 3), n = wn * WTN + j * 16 + 4 * (lane & 3);
+                    const char *at = s + A_BYTES + k * (BN * 2) + (((n >> 3) ^ swz_n<BN>(k)) << 4) + (lane & 1) * 8;
+                    const s16x4_t lo = read_tr16(at), hi = read_tr16(at + 4 * BN * 2);
+                    b[j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = mfma_any<F16>(b[j], a[i], acc[i][j]);
+        }
+    };
+
+    const int steps = ((K + 63) / 64 + KW - 1) / KW;         // per group, the same for all
+    Step r0, r1;
+    load(r0, 0);
+    load(r1, 1);
+    to_lds(r0, 0);
+    __syncthreads();
+    for (int i = 0; i < steps; i += 2) {
+        load(r0, i + 2);
+        compute(0);
+        to_lds(r1, i + 1);
+        __syncthreads();
+        if (i + 1 >= steps) break;
+        load(r1, i + 3);
+        compute(1);
+        to_lds(r0, i + 2);
+        __syncthreads();
+    }
+
+    // ---- sums of the K groups, through LDS: unit (i, j mod HT) of a wave tile (its tiles j and j + HT) is finished by
+    // group (i HT + j) mod KW, which adds the groups' sums in ascending order
+    if constexpr (KW > 1) {
+        f32x4_t *const sums = (f32x4_t *)smem;               // [unit][half][group][thread of the group]
+#pragma unroll
+        for (int u = 0; u < MT * HT; ++u)
+            if (u % KW != group) {
+                sums[((u * 2 + 0) * KW + group) * 256 + tid] = acc[u / HT][u % HT];
+                sums[((u * 2 + 1) * KW + group) * 256 + tid] = acc[u / HT][u % HT + HT];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MT * HT; ++u)
+            if (u % KW == group) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4_t own = acc[u / HT][u % HT + h * HT];
+                    f32x4_t v = group == 0 ? own : sums[((u * 2 + h) * KW) * 256 + tid];
+#pragma unroll
+                    for (int g = 1; g < KW; ++g) v += group == g ? own : sums[((u * 2 + h) * KW + g) * 256 + tid];
+                    acc[u / HT][u % HT + h * HT] = v;
+                }
+            }
+    }
+
+    // ---- epilogue: lane (r16, q) of tile (i, j) holds columns 4q .. 4q + 3 of row r16
+    const uint16_t *res = p.res ? (const uint16_t *)(p.res + z * p.stride_r) : nullptr;
+    uint16_t *C = (uint16_t *)(p.C + z * p.stride_c);
+    const uint16_t *bias = (const uint16_t *)p.bias;
+    const int n_wave = n0 + wn * (gated ? WTN / 2 : WTN);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        if (gated && j >= HT) break;
+        const int n = n_wave + j * 16 + 4 * q;
+        const bool full = n + 4 <= nout;
+        float bv[4] = {0.f, 0.f, 0.f, 0.f};
+        if (bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bv[e] = n + e < nout ? in16<F16>(bias[n + e]) : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            if (KW > 1 && (i * HT + j % HT) % KW != group) continue;
+            const int m = m0 + wm * WTM + i * 16 + r16;
+            if (m >= p.M || n >= nout) continue;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = acc[i][j][e];
+                if (gated) v[e] = silu(v[e]) * acc[i][j < HT ? j + HT : j][e];
+                if (bias) v[e] += bv[e];
+                if (p.act == ACT_GELU_TANH) v[e] = gelu_tanh(v[e]);
+            }
+            if (res) {
+                const uint16_t *rp = res + (int64_t)m * p.ldr + n;
+                if (full) {
+                    const u32x2_t w = *(const u32x2_any *)rp;
+                    v[0] += in16<F16>(w.x & 0xFFFFu); v[1] += in16<F16>(w.x >> 16);
+                    v[2] += in16<F16>(w.y & 0xFFFFu); v[3] += in16<F16>(w.y >> 16);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < nout) v[e] += in16<F16>(rp[e]);
+                }
+            }
+            uint16_t *cp = C + (int64_t)m * p.ldc + n;
+            if (full) {
+                *(u32x2_any *)cp = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < nout) cp[e] = (uint16_t)out16<F16>(v[e]);
+            }
+        }
+    }
+}
+
+template <int BM, int BN, int WGM, int WGN, int KW, bool TRANS_B, bool F16>
+static hipError_t launch_one(const GemmArgs &a, dim3 grid, hipStream_t stream)
+{
+    auto kern = ragged_kernel<BM, BN, WGM, WGN, KW, TRANS_B, F16>;
+    constexpr int lds = KW * 2 * (BM + BN) * 128;
+    static_assert(lds <= 160 * 1024 && (BM / WGM / 16) * (BN / WGN / 16) * KW * 4096 <= lds, "LDS: rings, then the groups' sums");
+    if constexpr (lds > 64 * 1024) {
+        static std::atomic<bool> attr_set[64];               // (two host threads may make a kernel's first launch at once: setting the limit twice is harmless)
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+        if (!attr_set[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set[dev].store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(256 * KW), lds, stream, a);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int WGM, int WGN, int KW>
+static hipError_t launch_tile(GemmArgs a, bool trans_b, int grid_z, hipStream_t stream)
+{
+    const bool gated = a.act == ACT_SILU_GATE;
+    const int nout = gated ? a.N / 2 : a.N, bn_out = gated ? BN / 2 : BN;
+    const int64_t tm = (a.M + (int64_t)BM - 1) / BM, tn = (nout + (int64_t)bn_out - 1) / bn_out;
+    if (tm * tn > 0x7FFFFFFF / 2) return hipErrorInvalidConfiguration;
+    a.tiles_m = (int)tm; a.tiles_n = (int)tn; a.group_m = 4;
+    const dim3 grid((unsigned)(tm * tn), 1, (unsigned)grid_z);
+    if (a.f16) return trans_b ? launch_one<BM, BN, WGM, WGN, KW, true, true>(a, grid, stream) : launch_one<BM, BN, WGM, WGN, KW, false, true>(a, grid, stream);
+    return trans_b ? launch_one<BM, BN, WGM, WGN, KW, true, false>(a, grid, stream) : launch_one<BM, BN, WGM, WGN, KW, false, false>(a, grid, stream);
+}
+
+// A row (or a K-row of a [K][N] operand) holds at least one 16-byte piece; shorter ones stay with the guarded kernel.
+bool ragged_serves(const GemmArgs &a, bool trans_b) { return a.K >= 8 && (trans_b || a.N >= 8); }
+
+// The largest tile that still gives most compute units a work-group, and several K groups per work-group where
+// K is long enough to share: what is short here is loads in flight, not matrix cores.  Measured (us, one launch,
+// operands in the memory-side cache; tile and K groups):
+//   2000 x 1999 x 1777   128/1 41.7   128/2 35.7   64/2 46.7   32x64/4 91.0   guarded kernel 3416
+//   1000 x  999 x 1777   128/2 31.4    64/1 17.6   64/2 14.5   32x64/4 24.0
+//    300 x  999 x  777    64/1 10.2    64/2  9.6   32x64/1 9.3   32x64/4  9.6
+//      7 x 2731 x 1284    64/1  9.9    64/4  9.5   32x64/1 8.5   32x64/4  8.2   guarded kernel  119
+//      1 x 4001 x 4001    64/1 26.3    64/4 20.5   32x64/1 23.1  32x64/4 16.5
+//   3850 x 1884 x   31   128/1 12.3   128/2 18.8    64/1 12.9
+//    858 x  133 x   33   128/1 11.6    64/1  5.4   32x64/1 4.4   32x64/4  6.5
+hipError_t launch_ragged_gemm(const GemmArgs &a, bool trans_b, int grid_z, hipStream_t stream)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return (a.M + bm - 1) / bm * ((a.N + bn - 1) / bn) * grid_z; };
+    if (tiles(128, 128) >= 160)
+        return a.K >= 512 && tiles(128, 128) < 512 ? launch_tile<128, 128, 2, 2, 2>(a, trans_b, grid_z, stream)
+                                                   : launch_tile<128, 128, 2, 2, 1>(a, trans_b, grid_z, stream);
+    if (tiles(64, 64) >= 160)
+        return a.K >= 256 ? launch_tile<64, 64, 2, 2, 2>(a, trans_b, grid_z, stream) : launch_tile<64, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+    return a.K >= 768 ? launch_tile<32, 64, 2, 2, 4>(a, trans_b, grid_z, stream) : launch_tile<32, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+}
+
+}  // namespace fact

@@ -1,0 +1,74 @@
+"""GEMMs on operands of any alignment (odd rows, widths that are no multiple of 8) on the matrix cores, held to the CPU
+oracle at the sizes where a tile, a K step or a K group ends: small integers keep every sum exact, so equal bits are
+demanded; the activations are held to the usual tolerance.  Padding is poisoned and must not be read."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_26666_amd as fact
+import workloads as wl
+from oracle import check, ref
+
+pytestmark = pytest.mark.gpu
+
+# one row per tile shape and K-group count of the dispatch rule (K above and below its line), and the smallest sizes
+SHAPES = [(1801, 1499, 521), (1801, 1499, 77), (700, 999, 300), (700, 999, 100), (37, 131, 777), (1, 9, 8), (33, 65, 71), (31, 8, 9), (65, 64, 1025)]
+
+
+def run(A, B, nk, bias=None, res=None, act=fact.ACT_NONE, f16=0):
+    """Rows padded to odd lengths with NaN, pointers 2-byte aligned only; returns the bits of C after checking its surroundings."""
+    dt = torch.float16 if f16 else torch.bfloat16
+
+    def odd(t):
+        r, c = t.shape
+        ld = c + 1 if c % 2 == 0 else c + 2
+        buf = torch.full((r * ld + 1,), float("nan"), dtype=dt, device="cuda")
+        torch.as_strided(buf, (r, c), (ld, 1), 1).copy_(t.cuda())
+        return buf, buf.data_ptr() + 2, ld
+
+    (M, K), N = A.shape, B.shape[0] if nk else B.shape[1]
+    nout = N // 2 if act == fact.ACT_SILU_GATE else N
+    Ab, ap, lda = odd(A)
+    Bb, bp, ldb = odd(B)
+    ldc = nout + 3
+    Cb = torch.full((M + 1, ldc), 77.0, dtype=dt, device="cuda")
+    keep = [None if t is None else t.cuda() for t in (bias, res)]
+    ep = fact.Epilogue(bias=keep[0], residual=keep[1], ldr=nout, act=act, f16=f16)
+    fact.binding.check(fact.fact_gemm(M, N, K, ap, lda, bp, ldb, nk, Cb, ldc, ep), f"{(M, N, K, nk)}")
+    torch.cuda.synchronize()
+    out = Cb.cpu()
+    assert (out[M] == 77.0).all() and (out[:, nout:] == 77.0).all(), "wrote outside C"
+    return wl.bits(out[:M, :nout].contiguous())
+
+
+@pytest.mark.parametrize("f16", [0, 1])
+@pytest.mark.parametrize("nk", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_exact_sums_bias_and_residual(shape, nk, f16):
+    M, N, K = shape
+    ints = wl.small_int_f16 if f16 else wl.small_int
+    fmt = "f16" if f16 else "bf16"
+    A, B = ints((M, K), -4, 4, f"rg.A.{shape}"), ints((N, K) if nk else (K, N), -4, 4, f"rg.B.{shape}.{nk}")
+    bias, res = ints((N,), -9, 9, "rg.bias"), ints((M, N), -9, 9, "rg.res")
+    rows = wl.choice_rows(M, 48, f"rg.rows.{shape}", edges=(0, 31, 32, 63, 64, 127, 128, M - 1))
+    got = run(A, B, nk, bias, res, f16=f16)
+    check.assert_bits_equal(got, ref.gemm_epilogue(A, B, nk, bias=bias, residual=res, rows=rows, fmt=fmt), rows="full", what=f"{shape} nk={nk}")
+
+
+@pytest.mark.parametrize("act", [fact.ACT_GELU_TANH, fact.ACT_SILU_GATE])
+@pytest.mark.parametrize("shape", [(1801, 1498, 521), (700, 998, 300), (37, 130, 777), (33, 66, 71)], ids=str)
+def test_activations(shape, act):
+    M, N, K = shape
+    A, B = wl.normal((M, K), 1.0, f"rg.a.{shape}"), wl.normal((N, K), K ** -0.5, f"rg.b.{shape}")
+    rows = wl.choice_rows(M, 32, f"rg.r.{shape}", edges=(0, M - 1))
+    got = run(A, B, 1, act=act)
+    check.assert_close(got, ref.gemm_epilogue(A, B, True, act=act, rows=rows), rows="full", what=f"{shape} act={act}")
+
+
+def test_a_row_of_infinities_stays_in_its_row():
+    # rows and columns past an edge repeat the last one and K past the end is zero on both sides: 0 x inf must not leak
+    A, B = wl.small_int((65, 73), -4, 4, "rg.inf.A").clone(), wl.small_int((73, 67), 1, 4, "rg.inf.B")
+    A[64] = float("inf")
+    got = run(A, B, 0)
+    check.assert_bits_equal(got, ref.gemm_epilogue(A, B, False, rows=np.arange(64)), rows="full", what="finite rows")
+    assert (wl.from_bits(got[64:]).float() == float("inf")).all()      # B is positive: no inf - inf, and no 0 x inf from past K
