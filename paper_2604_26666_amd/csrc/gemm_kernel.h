@@ -28,6 +28,10 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef u32x4_t u32x4_any __attribute__((aligned(2)));       // 16 (8) bytes at any even address: global accesses may be unaligned
+typedef u32x2_t u32x2_any __attribute__((aligned(2)));
+typedef f32x4_t f32x4_any __attribute__((aligned(4)));
+typedef f32x4_t f32x4_any __attribute__((aligned(4)));
 
 #define FACT_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
@@ -52,6 +56,7 @@ struct GemmArgs {
     int tiles_m, tiles_n;
     int group_m;            // tile rows walked together (L2 reuse)
     int vec_store;          // 1: C / residual / bias allow 16-byte vector access
+    int whole_lines;        // 1: every row of C begins on a 128-byte line
     int pf_sa, pf_sb;       // L2 prefetch: work-groups that share an A row-panel / a B column-panel (0: off; else a power of two)
     int pf_dist;            // L2 prefetch: K steps ahead of the step being loaded into LDS (>= 1)
     // Tail split (the last, partly filled round of tiles): work-groups [0, tail_first) own one tile
@@ -362,6 +367,12 @@ gemm_kernel(const GemmArgs p)
     // 8192 x 3072 x 768 + bias + GELU 45.3 -> 41.6 / 48.0 -> 41.7 us, 128 x 512^3 43.5 -> 42.5 / 51.5 -> 48.5 us,
     // 8192^3 713 -> 708 us; no shape slower.  (Write-through alone: better from the cache, worse from HBM.)
     constexpr int kStoreThrough = 19;
+    // ... where a row of C is whole 128-byte lines.  Otherwise the lines at the tiles' edges would go to memory in parts:
+    // plain stores then, which the L2 joins (1024 x 50256 x 768: 147 -> 92.7 us; 1024 x 50304 x 768, whole lines: 96.1 and 94.8).
+
+    // Interior tiles of a C whose rows are not 16-byte aligned or not whole lines take a register path of their own
+    // (8-wave work-groups and persistent launches do not have it: guarded path, or write-through stores).
+    constexpr bool REG_ANY = NWAVES <= 4 && !PERSIST;
 
     // ---- epilogue ---------------------------------------------------------------------------
     // Accumulator tile (mt, nt), lane (r16, q): output row mt*16 + r16, output columns
@@ -575,7 +586,8 @@ gemm_kernel(const GemmArgs p)
                     o[e] = pack2<F16>(f2);     // round to nearest even
                 }
                 // (scalar offset operand: the constant 0, see the note at the partial-tile stores below)
-                __builtin_amdgcn_raw_buffer_store_b128(o, rsrc_c, vo + j * step_c, 0, kStoreThrough);
+                if (p.whole_lines) __builtin_amdgcn_raw_buffer_store_b128(o, rsrc_c, vo + j * step_c, 0, kStoreThrough);
+                else __builtin_amdgcn_raw_buffer_store_b128(o, rsrc_c, vo + j * step_c, 0, 0);
             }
             vo += FU * step_c; vr += FU * step_r; src += FU * RPB * EPI_PITCH;
         }
@@ -687,7 +699,86 @@ gemm_kernel(const GemmArgs p)
             });
         });
     };
+    // The register path for C, bias or residual rows at any 2-byte address (odd leading dimensions such as a
+    // vocabulary's 50257), and for rows of C that are not whole 128-byte lines: the same exchange, then 16-byte
+    // accesses through pointers, which may be unaligned.
+    // What is added is looked at per group of columns at run time: one instance keeps the kernel's code small (it is
+    // fetched once per tile, and cold code runs at the speed of its fetch).  The stores are ordinary ones, so that the
+    // XCD's L2 joins the pieces of a line.  1024 x 50257 x 768: 162 -> 129 us (the guarded path before; C with
+    // rows of 50256, 16-byte stores: 92 us).  Staging the rows through LDS and cutting them where their 16-byte pieces
+    // of memory begin, with the ends of the rows as single elements, took 143 us.
+    auto reg_epilogue_any = [&](auto gated_tag) __attribute__((always_inline)) {
+        constexpr bool GATED = decltype(gated_tag)::value;
+        constexpr int OT = GATED ? NT / 2 : NT, NP = OT / 2;
+        static_assert(OT % 2 == 0, "tiles are exchanged in pairs");
+        const int n = n_wave + (q & 1) * 16 + (q >> 1) * 8;
+        const bool has_bias = p.bias != nullptr, has_res = R != nullptr, gelu = p.act == ACT_GELU_TANH;
+        u32x4_t bp[NP], rb[2][NP];
+        if (has_bias) {
+#pragma unroll
+            for (int pr = 0; pr < NP; ++pr) bp[pr] = *(const u32x4_any *)(p.bias + n + pr * 32);
+        }
+        const __bf16 *rrow = has_res ? R + (int64_t)(m_wave + r16) * p.ldr + n : nullptr;
+        __bf16 *crow = C + (int64_t)(m_wave + r16) * p.ldc + n;
+        auto load_res = [&](int mt) __attribute__((always_inline)) {
+            if (has_res) {
+#pragma unroll
+                for (int pr = 0; pr < NP; ++pr) rb[mt & 1][pr] = *(const u32x4_any *)(rrow + pr * 32);
+                rrow += 16 * p.ldr;
+            }
+        };
+        load_res(0);
+        static_for<MT>([&](auto mt_) __attribute__((always_inline)) {
+            constexpr int mt = decltype(mt_)::value;
+            if constexpr (mt + 1 < MT) load_res(mt + 1);
+            static_for<NP>([&](auto pr_) __attribute__((always_inline)) {
+                constexpr int pr = decltype(pr_)::value;
+                f32x4_t x0 = AccTile<mt * NT + 2 * pr>::get(), x1 = AccTile<mt * NT + 2 * pr + 1>::get();
+                if constexpr (GATED) {
+                    const f32x4_t u0 = AccTile<mt * NT + OT + 2 * pr>::get(), u1 = AccTile<mt * NT + OT + 2 * pr + 1>::get();
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { x0[e] = silu(x0[e]) * u0[e]; x1[e] = silu(x1[e]) * u1[e]; }
+                }
+                float z[8];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float a0 = x0[e], a1 = x1[e];
+                    const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a0), __builtin_bit_cast(uint32_t, a1), false, false);
+                    z[e] = __builtin_bit_cast(float, (uint32_t)sw[0]);
+                    z[4 + e] = __builtin_bit_cast(float, (uint32_t)sw[1]);
+                }
+                if (has_bias) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { z[2 * e] += in16<F16>(bp[pr][e] & 0xFFFFu); z[2 * e + 1] += in16<F16>(bp[pr][e] >> 16); }
+                }
+                if (gelu) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) z[e] = gelu_tanh(z[e]);
+                }
+                if (has_res) {
+                    const u32x4_t r4 = rb[mt & 1][pr];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { z[2 * e] += in16<F16>(r4[e] & 0xFFFFu); z[2 * e + 1] += in16<F16>(r4[e] >> 16); }
+                }
+                u32x4_t o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const f32x2_t f2 = {z[2 * e], z[2 * e + 1]};
+                    o[e] = pack2<F16>(f2);     // round to nearest even
+                }
+                *(u32x4_any *)(crow + pr * 32) = o;
+            });
+            crow += 16 * p.ldc;
+        });
+    };
     if constexpr (IN_REGS) {
+        if constexpr (REG_ANY) {
+            if (!p.vec_store || !p.whole_lines) {
+                if constexpr (NT % 4 == 0) { if (gated) { reg_epilogue_any(std::true_type{}); return; } }
+                reg_epilogue_any(std::false_type{});
+                return;
+            }
+        }
         const int what = (p.bias ? 1 : 0) | (p.act == ACT_GELU_TANH ? 2 : 0) | (R ? 4 : 0);
         constexpr std::true_type T{};
         constexpr std::false_type F{};
@@ -761,7 +852,7 @@ gemm_kernel(const GemmArgs p)
             if (gated) fast_pass(pass, std::true_type{}); else fast_pass(pass, std::false_type{});
             return;
         }
-        // General path (tile edges, unaligned C / bias / residual, split-K partials), every access
+        // General path (edge tiles of an unaligned C, of split-K partials and of fp32 output), every access
         // guarded.  Read-back in batches of EPI_U row-chunks per lane: first every LDS read and every
         // bias / residual load of the batch is issued, then the arithmetic and the stores follow,
         // so the global-load latency is paid once per batch, not once per chunk.  (The residual
@@ -771,7 +862,7 @@ gemm_kernel(const GemmArgs p)
             float v[EPI_U][8], u[EPI_U][8];
             u32x4_t rb[EPI_U], bb[EPI_U];
             int mm[EPI_U], nn[EPI_U];
-            bool live[EPI_U], vec[EPI_U], whole[EPI_U];       // whole: all 8 columns inside C, whatever their alignment
+            bool live[EPI_U], whole[EPI_U];                   // whole: all 8 columns inside C, whatever their alignment
 #pragma unroll
             for (int j = 0; j < EPI_U; ++j) {
                 const int idx = base + 64 * j;
@@ -780,7 +871,6 @@ gemm_kernel(const GemmArgs p)
                 nn[j] = n_wave + c8 * 8;
                 live[j] = idx < total && mm[j] < p.M && nn[j] < nout;
                 whole[j] = live[j] && (nn[j] + 7 < nout);
-                vec[j] = whole[j] && p.vec_store;
                 if (idx < total) {
                     const char *src = region + row * EPI_PITCH + c8 * 32;
                     const f32x4_t x0 = *(const f32x4_t *)src, x1 = *(const f32x4_t *)(src + 16);
@@ -805,9 +895,9 @@ gemm_kernel(const GemmArgs p)
                         }
                     }
                 }
-                if (!partial && vec[j]) {
-                    if (p.bias) bb[j] = *(const u32x4_t *)(p.bias + nn[j]);
-                    if (R) rb[j] = *(const u32x4_t *)(R + (int64_t)mm[j] * p.ldr + nn[j]);
+                if (!partial && whole[j]) {
+                    if (p.bias) bb[j] = *(const u32x4_any *)(p.bias + nn[j]);
+                    if (R) rb[j] = *(const u32x4_any *)(R + (int64_t)mm[j] * p.ldr + nn[j]);
                 }
             }
 #pragma unroll
@@ -840,16 +930,13 @@ gemm_kernel(const GemmArgs p)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) z[e] = gated ? silu(v[j][e]) * u[j][e] : v[j][e];
                 if (p.bias) {
-                    if (vec[j]) {
+                    if (whole[j]) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { z[2 * e] += in16<F16>(bb[j][e] & 0xFFFFu); z[2 * e + 1] += in16<F16>(bb[j][e] >> 16); }
-                    } else if (whole[j]) {                       // (unaligned rows, e.g. an odd leading dimension: element accesses, no guards)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) z[e] += (float)p.bias[n + e];
                     } else {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
-                            if (n + e < nout) z[e] += (float)p.bias[n + e];
+                            if (n + e < nout) z[e] += in16<F16>(((const uint16_t *)p.bias)[n + e]);
                     }
                 }
                 if (p.act == ACT_GELU_TANH) {
@@ -857,19 +944,14 @@ gemm_kernel(const GemmArgs p)
                     for (int e = 0; e < 8; ++e) z[e] = gelu_tanh(z[e]);
                 }
                 if (R) {
-                    if (vec[j]) {
+                    if (whole[j]) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { z[2 * e] += in16<F16>(rb[j][e] & 0xFFFFu); z[2 * e + 1] += in16<F16>(rb[j][e] >> 16); }
                     } else {
-                        const __bf16 *rp = R + (int64_t)m * p.ldr + n;
-                        if (whole[j]) {
+                        const uint16_t *rp = (const uint16_t *)(R + (int64_t)m * p.ldr + n);
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) z[e] += (float)rp[e];
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 8; ++e)
-                                if (n + e < nout) z[e] += (float)rp[e];
-                        }
+                        for (int e = 0; e < 8; ++e)
+                            if (n + e < nout) z[e] += in16<F16>(rp[e]);
                     }
                 }
                 if (tail_gave_up) {
@@ -878,12 +960,9 @@ gemm_kernel(const GemmArgs p)
                 }
                 if (p.c_f32) {
                     float *cf = Cf + (int64_t)m * p.ldc + n;
-                    if (vec[j]) {
-                        *(f32x4_t *)cf = f32x4_t{z[0], z[1], z[2], z[3]};
-                        *(f32x4_t *)(cf + 4) = f32x4_t{z[4], z[5], z[6], z[7]};
-                    } else if (whole[j]) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) cf[e] = z[e];
+                    if (whole[j]) {
+                        *(f32x4_any *)cf = f32x4_t{z[0], z[1], z[2], z[3]};
+                        *(f32x4_any *)(cf + 4) = f32x4_t{z[4], z[5], z[6], z[7]};
                     } else {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
@@ -892,15 +971,11 @@ gemm_kernel(const GemmArgs p)
                     continue;
                 }
                 __bf16 *cp = C + (int64_t)m * p.ldc + n;
-                if (vec[j]) {
+                if (whole[j]) {
                     u32x4_t o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = out16<F16>(z[2 * e]) | (out16<F16>(z[2 * e + 1]) << 16);
-                    *(u32x4_t *)cp = o;
-                } else if (whole[j]) {
-                    uint16_t *cs = (uint16_t *)cp;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) cs[e] = (uint16_t)out16<F16>(z[e]);
+                    *(u32x4_any *)cp = o;
                 } else {
                     uint16_t *cs = (uint16_t *)cp;
 #pragma unroll
@@ -1508,7 +1583,7 @@ gemm_kernel(const GemmArgs p)
         // (the same answer in every wave of the work-group: the two kinds of epilogue meet different
         // barriers and run at different points of a persistent work-group's loop)
         const bool inside = m0 + BM <= p_launch.M && n0 + (gated ? BN / 2 : BN) <= nout;
-        e_in_regs = !partial && p_launch.vec_store && inside && !in_tail && !p_launch.c_f32 && (!gated || NT % 4 == 0);
+        e_in_regs = !partial && (REG_ANY || p_launch.vec_store) && inside && !in_tail && !p_launch.c_f32 && (!gated || NT % 4 == 0);
     };
     // (a persistent work-group sets these before the K loop, so that nothing of the tile's set-up is needed after
     // it; an ordinary one after it, where its 8-wave form has the registers)

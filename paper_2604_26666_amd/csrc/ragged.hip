@@ -9,9 +9,6 @@
 
 namespace fact {
 
-typedef u32x4_t u32x4_any __attribute__((aligned(2)));       // 16 bytes at any even address
-typedef u32x2_t u32x2_any __attribute__((aligned(2)));
-
 // 8 elements shifted down by s elements (element e <- element e + s), zeros from the top; s >= 8 gives zeros
 __device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int s)
 {

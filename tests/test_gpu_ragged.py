@@ -72,3 +72,23 @@ def test_a_row_of_infinities_stays_in_its_row():
     got = run(A, B, 0)
     check.assert_bits_equal(got, ref.gemm_epilogue(A, B, False, rows=np.arange(64)), rows="full", what="finite rows")
     assert (wl.from_bits(got[64:]).float() == float("inf")).all()      # B is positive: no inf - inf, and no 0 x inf from past K
+
+
+@pytest.mark.parametrize("f16", [0, 1])
+@pytest.mark.parametrize("cfg", range(16))
+def test_odd_rows_of_c_in_every_configuration(cfg, f16):
+    # aligned operands, C, bias and residual at odd addresses: interior tiles (unaligned register path), ragged edges
+    tm, tn = fact.fact_config_info(cfg)[:2]
+    M, N, K = 2 * tm + 9, 2 * tn + 13, 72
+    ints, dt = (wl.small_int_f16, torch.float16) if f16 else (wl.small_int, torch.bfloat16)
+    A, B = ints((M, K), -4, 4, f"rg.oA.{M}"), ints((N, K), -4, 4, f"rg.oB.{N}")
+    bias, res = ints((N + 1,), -9, 9, "rg.ob"), ints((M, N), -9, 9, "rg.or")
+    Cb = torch.full((M + 1, N + 2), 77.0, dtype=dt, device="cuda")
+    bd, rd = bias.cuda(), res.cuda()
+    ep = fact.Epilogue(bias=bd.data_ptr() + 2, residual=rd, ldr=N, f16=f16)
+    fact.binding.check(fact.fact_gemm_ex(1, M, N, K, A.cuda(), K, 0, B.cuda(), K, 0, 1, Cb, N + 2, 0, ep, cfg, 1, 0, None, 0))
+    torch.cuda.synchronize()
+    out = Cb.cpu()
+    assert (out[M] == 77.0).all() and (out[:, N:] == 77.0).all(), "wrote outside C"
+    r = ref.gemm_epilogue(A, B, True, bias=bias[1:], residual=res, fmt="f16" if f16 else "bf16")
+    check.assert_bits_equal(wl.bits(out[:M, :N].contiguous()), r, what=f"cfg {cfg}")
