@@ -109,7 +109,9 @@ typedef struct fact_epilogue {
  * C[M][Nout] = epilogue(A[M][K] x B).  One data-parallel 2-D tiled launch (the paper's
  * "Data Parallel" grid schedule, Section 4.2 Action 2; Section 5.2.1).  ep may be NULL.
  * The tile configuration comes from the per-shape table (the shadow of the paper's
- * registry lookup, Section 4.2 Action 6).
+ * registry lookup, Section 4.2 Action 6).  Calls of at most 64 rows with trans_b == 1 that no
+ * registry or table entry names may take a kernel of their own for few rows instead, in every
+ * entry point that leaves the configuration to the library.
  */
 int fact_gemm(int64_t M, int64_t N, int64_t K,
               const void *A, int64_t lda,

@@ -113,6 +113,7 @@ struct Plan {
     int cfg = -1;      // -1: no tile configuration of the main kernel serves it (ragged or guarded kernel)
     int split = 1;
     int group_m = 4;
+    bool listed = false;   // from the registry or the table
 };
 
 // Estimated microseconds of a launch, for shapes the registry does not list.  A 64-deep K step of a
@@ -150,6 +151,7 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
         pl.cfg = r.cfg;
         pl.split = r.split == 0 ? 1 : r.split;             // negative: a tail split, which needs a workspace as well
         pl.group_m = r.group_m > 0 ? r.group_m : 4;
+        pl.listed = true;
     };
     {
         std::lock_guard<std::mutex> lock(g_registry_mutex);
@@ -383,6 +385,23 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
             a.k_per_split = (int)kps;
             a.P = (float *)ws;
         }
+    }
+    // Few rows against [N][K] weights, nothing about the launch asked for by the caller or the registry: the skinny
+    // kernel (whose rule says where it wins).  It needs no workspace; what the plan would have needed has been
+    // checked above all the same.
+    if (cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.listed && tail_g <= 1 && skinny_serves(a, q.trans_b != 0, a.splits > 1)) {
+        if (out_f32) {
+            if (a.splits <= 1) {
+                const size_t need = (size_t)q.M * (size_t)q.N * sizeof(float);
+                if (!ws) return FACT_ERR_WORKSPACE;
+                if (!aligned16(ws)) return FACT_ERR_ALIGN;
+                if (ws_bytes < need) return FACT_ERR_WORKSPACE;
+            }
+            a.out_f32 = 0; a.c_f32 = 1;
+        }
+        a.splits = 1; a.P = nullptr;
+        e = launch_skinny_gemm(a, (int)q.batch, stream);
+        return e == hipSuccess ? FACT_OK : hip_fail(e, "skinny gemm launch");
     }
     // L2 prefetch (see the kernel).  Many work-groups: the ones resident on an XCD (32 CUs) form a
     // block of gsz tile rows x (resident / gsz) tile columns that share panels; each touches its

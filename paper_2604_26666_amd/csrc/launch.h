@@ -27,6 +27,10 @@ struct ConfigDesc {
 hipError_t launch_splitk_reduce(const GemmArgs &args, hipStream_t stream);
 hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
 
+// GEMM of few rows against B as [N][K] (skinny.hip).
+bool skinny_serves(const GemmArgs &args, bool trans_b, bool plan_splits);
+hipError_t launch_skinny_gemm(const GemmArgs &args, int grid_z, hipStream_t stream);
+
 // GEMM with operands of any alignment and size on the matrix cores (ragged.hip).
 bool ragged_serves(const GemmArgs &args, bool trans_b);
 hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
