@@ -29,106 +29,139 @@ __device__ __forceinline__ uint32_t bf16_rne(float x)
     return u >> 16;
 }
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return bf16_rne(a) | (bf16_rne(b) << 16); }
+// sum over the wave, the same in every lane: rotations inside each 16-lane row, then exchanges of rows and halves, all on
+// the vector ALU (through LDS permutes the six dependent steps of a sum took 0.35 us)
+template <int CTRL>
+__device__ __forceinline__ float add_rotated(float v)
+{
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
-    return v;
+    v = add_rotated<0x128>(v);       // row_ror:8
+    v = add_rotated<0x124>(v);
+    v = add_rotated<0x122>(v);
+    v = add_rotated<0x121>(v);
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    v = __builtin_bit_cast(float, (uint32_t)s[0]) + __builtin_bit_cast(float, (uint32_t)s[1]);
+    const uint32_t w = __builtin_bit_cast(uint32_t, v);
+    const auto h = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return __builtin_bit_cast(float, (uint32_t)h[0]) + __builtin_bit_cast(float, (uint32_t)h[1]);
 }
 
-// One wave per row: the row is read once (16 bytes per lane and piece), kept in registers in fp32,
-// reduced across the wave, normalised and written once.  d <= 8192, a multiple of 8.
-// The number of 512-element pieces is a template parameter: a short row takes few registers, so
-// many waves fit on a SIMD and cover each other's memory latency.
-constexpr int kMaxPieces = 16;           // 16 pieces x 64 lanes x 8 elements
-template <bool RMS, int PIECES>
+// A row is read once (16 bytes per lane and piece), kept in registers in fp32, reduced, normalised and written once;
+// d <= 8192, a multiple of 8.  Bound by memory traffic where there are many rows and by one row's chain of latencies
+// where there are few, so gamma and beta are asked for before the sums need them, and a row wider than 1024 elements is
+// shared by the four waves of a work-group (their sums meet in LDS).  Operands
+// from HBM: 2048 x 4096 12.4 -> 8.6 us (3.9 TB/s), 16 x 4096 5.6 -> 2.2 us, 32768 x 4096 113 -> 92 us (5.8 TB/s), 8192 x 768
+// 9.9 -> 8.5 us (against a wave per row that asked for gamma and beta after its sums).
+// Narrower rows take a wave each.  The number of 512-element pieces per wave is a template parameter.
+constexpr int kMaxWidth = 8192;
+template <bool RMS, int WPR, int PIECES>
 __global__ void __launch_bounds__(256)
 norm_kernel(const uint16_t *X, int64_t ldx, const uint16_t *gamma, const uint16_t *beta, float eps,
             uint16_t *Y, int64_t ldy, int T, int d)
 {
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= T) return;
-    const uint16_t *x = X + (int64_t)row * ldx;
-    float v[PIECES][8];
-    float s = 0.f;
+    __shared__ float part[2][4];
+    const int wave = threadIdx.x >> 6;
+    const int64_t row = WPR == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (row >= T) return;                                    // (the whole work-group where it shares a row)
+    const int c0 = (WPR == 1 ? (int)threadIdx.x & 63 : (int)threadIdx.x) * 8;        // the lane's first column; pieces are WPR * 512 apart
+    auto over_row = [&](float v, int which) __attribute__((always_inline)) {
+        v = wave_sum(v);
+        if constexpr (WPR > 1) {
+            if ((threadIdx.x & 63) == 0) part[which][wave] = v;
+            __syncthreads();
+            v = (part[which][0] + part[which][1]) + (part[which][2] + part[which][3]);
+        }
+        return v;
+    };
+    const uint16_t *x = X + row * ldx;
+    u32x4_t w[PIECES], g[PIECES], b[PIECES];
 #pragma unroll
     for (int p = 0; p < PIECES; ++p) {
-        const int c = p * 512 + lane * 8;
-        if (c < d) {
-            const u32x4_t w = *(const u32x4_t *)(x + c);
+        const int c = p * WPR * 512 + c0;
+        w[p] = c < d ? *(const u32x4_t *)(x + c) : u32x4_t{0u, 0u, 0u, 0u};
+    }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { v[p][2 * e] = lo16(w[e]); v[p][2 * e + 1] = hi16(w[e]); }
-        } else {
+    for (int p = 0; p < PIECES; ++p) {
+        const int c = p * WPR * 512 + c0;
+        g[p] = c < d ? *(const u32x4_t *)(gamma + c) : u32x4_t{0u, 0u, 0u, 0u};
+        b[p] = !RMS && beta && c < d ? *(const u32x4_t *)(beta + c) : u32x4_t{0u, 0u, 0u, 0u};
+    }
+    float v[PIECES][8], s = 0.f, q = 0.f, mean = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[p][e] = 0.f;
-        }
-        if (!RMS) {
+    for (int p = 0; p < PIECES; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[p][2 * e] = lo16(w[p][e]); v[p][2 * e + 1] = hi16(w[p][e]); }
+    if constexpr (!RMS) {
+#pragma unroll
+        for (int p = 0; p < PIECES; ++p)
 #pragma unroll
             for (int e = 0; e < 8; ++e) s += v[p][e];
-        }
+        mean = over_row(s, 0) / (float)d;
     }
-    float mean = 0.f;
-    if (!RMS) mean = wave_sum(s) / (float)d;
-    float q = 0.f;
 #pragma unroll
-    for (int p = 0; p < PIECES; ++p) {
-        const int c = p * 512 + lane * 8;
-        if (c < d) {
+    for (int p = 0; p < PIECES; ++p)
+        if (p * WPR * 512 + c0 < d) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) { const float t = v[p][e] - mean; q += t * t; }
         }
-    }
-    const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
-    uint16_t *y = Y + (int64_t)row * ldy;
+    const float rstd = 1.0f / sqrtf(over_row(q, 1) / (float)d + eps);
+    uint16_t *y = Y + row * ldy;
 #pragma unroll
     for (int p = 0; p < PIECES; ++p) {
-        const int c = p * 512 + lane * 8;
+        const int c = p * WPR * 512 + c0;
         if (c < d) {
-            const u32x4_t g = *(const u32x4_t *)(gamma + c);
-            u32x4_t b = {0u, 0u, 0u, 0u};
-            if (!RMS && beta) b = *(const u32x4_t *)(beta + c);
             u32x4_t o;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                o[e] = pack2((v[p][2 * e] - mean) * rstd * lo16(g[e]) + lo16(b[e]),
-                             (v[p][2 * e + 1] - mean) * rstd * hi16(g[e]) + hi16(b[e]));
+                o[e] = pack2((v[p][2 * e] - mean) * rstd * lo16(g[p][e]) + lo16(b[p][e]),
+                             (v[p][2 * e + 1] - mean) * rstd * hi16(g[p][e]) + hi16(b[p][e]));
             *(u32x4_t *)(y + c) = o;
         }
     }
 }
 
-// Rotary embedding in place, "rotate-half" pairing: one thread takes 8 consecutive i < D/2 of one
-// (batch entry, token) - the 16-byte piece at i and the one at i + D/2 - and walks a group of up to
-// kRopeHeads heads (blockIdx.y), so the eight sines and cosines are computed once per group.
-constexpr int kRopeHeads = 8;
+// Rotary embedding in place, "rotate-half" pairing.  A work-group takes a few tokens and up to 256 of their angles
+// (blockIdx.y: further angles of a wider head); each thread computes one sine and cosine, once per token, into
+// LDS - the precise functions cost more than the traffic - and then walks 16-byte pieces of all heads: the piece at i
+// and the one at i + D/2.  2048 tokens of 40 heads of 128: 15.1 -> 11.4 us (3.7 TB/s), 16 tokens: 6.3 -> 3.1 us (against a
+// thread that computed eight angles and walked eight heads).
 __global__ void __launch_bounds__(256)
-rope_kernel(uint16_t *X, int64_t sb, int64_t st, int64_t sh, int B, int T, int H, int D, float log2_base)
+rope_kernel(uint16_t *X, int64_t sb, int64_t st, int64_t sh, int64_t tokens, int T, int H, int D, int per_wg, float log2_base)
 {
-    const int per_head = D / 16;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t total = (int64_t)B * T * per_head;
-    if (gid >= total) return;
-    const int piece = (int)(gid % per_head);
-    const int64_t bt = gid / per_head;
-    const int t = (int)(bt % T), b = (int)(bt / T);
-    float sn[8], cs[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int i = piece * 8 + e;
-        const float inv_freq = exp2f(-2.0f * (float)i / (float)D * log2_base);
-        sincosf((float)t * inv_freq, &sn[e], &cs[e]);
+    __shared__ float2 turn[256];
+    const int first = blockIdx.y * 256;                      // first angle of this work-group
+    const int angles = D / 2 - first < 256 ? D / 2 - first : 256, pieces = angles >> 3;
+    const int64_t bt0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * per_wg;
+    if (bt0 >= tokens) return;                               // (the whole work-group)
+    const int mine = tokens - bt0 < per_wg ? (int)(tokens - bt0) : per_wg;
+    {
+        const int k = threadIdx.x / angles, i = threadIdx.x - k * angles;        // token of the work-group, angle
+        if (k < mine) {
+            const float inv_freq = exp2f(-2.0f * (float)(first + i) / (float)D * log2_base);
+            float sn, cs;
+            sincosf((float)(int)((bt0 + k) % T) * inv_freq, &sn, &cs);
+            turn[threadIdx.x] = make_float2(cs, sn);
+        }
     }
-    const int h0 = blockIdx.y * kRopeHeads, h1 = h0 + kRopeHeads < H ? h0 + kRopeHeads : H;
-    uint16_t *p = X + (int64_t)b * sb + (int64_t)t * st + (int64_t)h0 * sh + piece * 8;
-    for (int h = h0; h < h1; ++h, p += sh) {
+    __syncthreads();
+    const int per_token = H * pieces;
+    for (int j = threadIdx.x; j < mine * per_token; j += 256) {
+        const int k = j / per_token, r = j - k * per_token, h = r / pieces, piece = r - h * pieces;
+        const int64_t bt = bt0 + k;
+        uint16_t *p = X + bt / T * sb + bt % T * st + (int64_t)h * sh + first + piece * 8;
+        const float2 *cs = turn + k * angles + piece * 8;
         const u32x4_t lo = *(const u32x4_t *)p, hi = *(const u32x4_t *)(p + D / 2);
         u32x4_t olo, ohi;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+            const float2 t0 = cs[2 * e], t1 = cs[2 * e + 1];
             const float a0 = lo16(lo[e]), a1 = hi16(lo[e]), c0 = lo16(hi[e]), c1 = hi16(hi[e]);
-            olo[e] = pack2(a0 * cs[2 * e] - c0 * sn[2 * e], a1 * cs[2 * e + 1] - c1 * sn[2 * e + 1]);
-            ohi[e] = pack2(c0 * cs[2 * e] + a0 * sn[2 * e], c1 * cs[2 * e + 1] + a1 * sn[2 * e + 1]);
+            olo[e] = pack2(a0 * t0.x - c0 * t0.y, a1 * t1.x - c1 * t1.y);
+            ohi[e] = pack2(c0 * t0.x + a0 * t0.y, c1 * t1.x + a1 * t1.y);
         }
         *(u32x4_t *)p = olo;
         *(u32x4_t *)(p + D / 2) = ohi;
@@ -192,16 +225,19 @@ int fact_norm(int64_t T, int64_t d, const void *X, int64_t ldx, const void *gamm
     if (T <= 0 || d <= 0 || ldx < d || ldy < d || T > 0x7FFFFFFF) return FACT_ERR_DIM;
     if (rms != 0 && rms != 1) return FACT_ERR_LAYOUT;
     if (rms && beta) return FACT_ERR_EPILOGUE;
-    if (d % 8 || d > 512 * kMaxPieces) return FACT_ERR_UNSUPPORTED;
+    if (d % 8 || d > kMaxWidth) return FACT_ERR_UNSUPPORTED;
     if (!aligned16(X) || !aligned16(Y) || !aligned16(gamma) || (beta && !aligned16(beta)) || (ldx & 7) || (ldy & 7)) return FACT_ERR_ALIGN;
     if (!(eps >= 0.f)) return FACT_ERR_DIM;
-    const unsigned grid = (unsigned)((T + 3) / 4);
+    const bool wide = d > 1024;                               // four waves per row
+    // (at most 2^20 work-groups along x: a grid's threads are counted in 32 bits)
+    const int64_t wgs = wide ? T : (T + 3) / 4, gx = wide && T > 1 << 20 ? 1 << 20 : wgs;
+    const dim3 grid((unsigned)gx, (unsigned)((wgs + gx - 1) / gx));
     hipStream_t s = (hipStream_t)stream;
-    const int pieces = (int)((d + 511) / 512);
-#define FACT_NORM_LAUNCH(R, P) hipLaunchKernelGGL((norm_kernel<R, P>), dim3(grid), dim3(256), 0, s, (const uint16_t *)X, ldx, \
+    const int pieces = (int)((d + (wide ? 2047 : 511)) / (wide ? 2048 : 512));
+#define FACT_NORM_LAUNCH(R, W, P) hipLaunchKernelGGL((norm_kernel<R, W, P>), grid, dim3(256), 0, s, (const uint16_t *)X, ldx, \
         (const uint16_t *)gamma, (const uint16_t *)(R ? nullptr : beta), eps, (uint16_t *)Y, ldy, (int)T, (int)d)
-#define FACT_NORM_PICK(R) do { if (pieces <= 1) FACT_NORM_LAUNCH(R, 1); else if (pieces <= 2) FACT_NORM_LAUNCH(R, 2); \
-        else if (pieces <= 4) FACT_NORM_LAUNCH(R, 4); else if (pieces <= 8) FACT_NORM_LAUNCH(R, 8); else FACT_NORM_LAUNCH(R, 16); } while (0)
+#define FACT_NORM_PICK(R) do { if (!wide && pieces == 1) FACT_NORM_LAUNCH(R, 1, 1); else if (!wide) FACT_NORM_LAUNCH(R, 1, 2); \
+        else if (pieces == 1) FACT_NORM_LAUNCH(R, 4, 1); else if (pieces == 2) FACT_NORM_LAUNCH(R, 4, 2); else FACT_NORM_LAUNCH(R, 4, 4); } while (0)
     if (rms) FACT_NORM_PICK(true); else FACT_NORM_PICK(false);
 #undef FACT_NORM_PICK
 #undef FACT_NORM_LAUNCH
@@ -217,10 +253,16 @@ int fact_rope(int64_t batch, int64_t T, int64_t n_heads, int64_t head_dim, void 
     if (head_dim <= 0 || head_dim % 16) return FACT_ERR_UNSUPPORTED;
     if (!aligned16(X) || (strides[0] & 7) || (strides[1] & 7) || (strides[2] & 7)) return FACT_ERR_ALIGN;
     if (!(base > 1.0f)) return FACT_ERR_DIM;
-    const int64_t total = batch * T * (head_dim / 16);
-    if (batch > 0x7FFFFFFF || T > 0x7FFFFFFF || n_heads > 65535 * kRopeHeads || (total + 255) / 256 > 0x7FFFFFFF) return FACT_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(rope_kernel, dim3((unsigned)((total + 255) / 256), (unsigned)((n_heads + kRopeHeads - 1) / kRopeHeads)), dim3(256), 0, (hipStream_t)stream, (uint16_t *)X,
-                       strides[0], strides[1], strides[2], (int)batch, (int)T, (int)n_heads, (int)head_dim, std::log2(base));
+    const int64_t tokens = batch * T;
+    if (batch > 0x7FFFFFFF || T > 0x7FFFFFFF || n_heads > 524280 || (tokens * (head_dim / 16) + 255) / 256 > 0x7FFFFFFF) return FACT_ERR_UNSUPPORTED;
+    const int64_t chunks = (head_dim / 2 + 255) / 256;
+    if (head_dim > 0x7FFFFFFF || chunks > 65535) return FACT_ERR_UNSUPPORTED;
+    // as many tokens per work-group as have their angles fit its 256 threads, one where there are few tokens
+    const int fit = head_dim >= 512 ? 1 : (int)(512 / head_dim), per_wg = tokens >= 1024 * (int64_t)fit ? fit : tokens >= 512 && fit > 1 ? 2 : 1;
+    const int64_t wgs = (tokens + per_wg - 1) / per_wg, gx = wgs > 1 << 20 ? 1 << 20 : wgs;       // (a grid's threads are counted in 32 bits)
+    if ((wgs + gx - 1) / gx > 65535) return FACT_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(rope_kernel, dim3((unsigned)gx, (unsigned)chunks, (unsigned)((wgs + gx - 1) / gx)), dim3(256), 0, (hipStream_t)stream, (uint16_t *)X,
+                       strides[0], strides[1], strides[2], tokens, (int)T, (int)n_heads, (int)head_dim, per_wg, std::log2(base));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? FACT_OK : fact::record_hip_failure(e, "rope launch");
 }

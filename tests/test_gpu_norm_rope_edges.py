@@ -1,0 +1,40 @@
+"""fact_norm and fact_rope at the sizes where their work splits change: rows of one wave and of four, the last piece of a
+row, few and many tokens per work-group, heads with more than 256 angles - against the block oracle, usual tolerance."""
+import pytest
+import torch
+
+import paper_2604_26666_amd as fact
+import workloads as wl
+from oracle import block as blk
+from oracle import check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rms", [0, 1])
+@pytest.mark.parametrize("T,d", [(1, 512), (3, 520), (5, 1024), (5, 1032), (2, 2048), (2, 2056), (7, 4104)])
+def test_norm_rows_of_one_and_four_waves(T, d, rms):
+    X = wl.normal((T, d), 2.0, f"ne.X.{T}.{d}") + wl.normal((T, 1), 3.0, f"ne.s.{T}.{d}")
+    g, b = wl.normal((d,), 1.0, f"ne.g.{d}"), wl.normal((d,), 0.5, f"ne.b.{d}")
+    Y = torch.full((T + 1, d), 77.0, dtype=torch.bfloat16, device="cuda")
+    fact.binding.check(fact.fact_norm(T, d, X.cuda(), d, g.cuda(), None if rms else b.cuda(), 1e-5, rms, Y, d))
+    torch.cuda.synchronize()
+    assert (Y[T] == 77.0).all()
+    r = blk.rmsnorm(wl.bits(X), wl.bits(g)) if rms else blk.layernorm(wl.bits(X), wl.bits(g), wl.bits(b))
+    check.assert_close(wl.bits(Y[:T].cpu().contiguous()), r, what=f"T={T} d={d} rms={rms}")
+
+
+@pytest.mark.parametrize("B,T,H,D", [(1, 1, 1, 16), (3, 171, 2, 64), (2, 1031, 3, 128), (1, 9, 2, 512), (1, 5, 2, 544), (40, 40, 1, 32)])
+def test_rope_token_groups_and_wide_heads(B, T, H, D):
+    base = 10000.0
+    X = wl.normal((B, T, H, D), 1.0, f"re.{B}.{T}.{H}.{D}")
+    Xd = X.cuda()
+    fact.binding.check(fact.fact_rope(B, T, H, D, Xd, (T * H * D, H * D, D), base))
+    torch.cuda.synchronize()
+    ang = torch.arange(T, dtype=torch.float64)[:, None] * base ** (-2.0 * torch.arange(D // 2, dtype=torch.float64) / D)
+    c, s, x = ang.cos()[None, :, None], ang.sin()[None, :, None], X.double()
+    lo, hi = x[..., : D // 2], x[..., D // 2:]
+    want = torch.cat([lo * c - hi * s, hi * c + lo * s], dim=-1)
+    # one rounding to bf16 (2^-8 of the value) and the angle's fp32 error, t * 2^-23 of a turned pair of size up to |x|
+    err = (Xd.cpu().double() - want).abs()
+    assert (err <= 2.0 ** -8 * want.abs() + T * 2.0 ** -22 * x.abs().max() + 1e-6).all(), err.max()
