@@ -28,7 +28,7 @@ static hipError_t launch(AttnArgs a, hipStream_t stream)
         if (e != hipSuccess) return e;
         attr_set[dev].store(true, std::memory_order_release);
     }
-    constexpr int BQ = NW * 64;
+    constexpr int BQ = NW * 32;
     a.q_blocks = (a.T + BQ - 1) / BQ;
     a.total = a.q_blocks * a.Hq * a.B;
     // Pairs per group of the work-group order (see the kernel): a multiple of 4, so that each of an
@@ -44,6 +44,14 @@ static hipError_t launch(AttnArgs a, hipStream_t stream)
             if (kv_heads * a.T * D * 4 <= (int64_t)4 << 20) best = r;
         }
         a.group = best ? best : smallest ? smallest : per;
+    }
+    // Work-groups of one residency round (see attn_fwd_kernel's launch bounds: 3 and 2 per compute unit) reach the
+    // compute units in layers of 32 per XCD; the last layer is folded back (1 x 2048 tokens, 32 heads of 128:
+    // 47.0 -> 44.4 us).
+    {
+        const bool split = (a.Hq * a.B & 7) == 0;
+        const int n = split ? a.total >> 3 : a.total, layer = split ? 32 : 256, layers = (n + layer - 1) / layer;
+        a.fold = a.causal && layers >= 2 && layers <= (D == 64 ? 3 : 2) ? (layers - 1) * layer : n;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)a.total), dim3(NW * 64), lds, stream, a);
     return hipGetLastError();
@@ -89,18 +97,9 @@ extern "C" int fact_attention(int64_t batch, int64_t T, int64_t n_q_heads, int64
     a.causal = causal;
     const float sc = scale > 0.f ? scale : 1.0f / std::sqrt((float)head_dim);
     a.scale_log2 = sc * 1.4426950408889634f;
-    a.q_blocks = 0; a.total = 0; a.group = 1;
+    a.q_blocks = 0; a.total = 0; a.group = 1; a.fold = 0;
 
-    // 128 queries per work-group (two waves; two work-groups share a compute unit, and fewer of a
-    // causal work-group's key blocks lie partly above the diagonal).  256 queries halve the K/V
-    // traffic into LDS per query, which pays only for long sequences of wide heads (measured: from
-    // T = 8192 at head_dim 128, 3-4%; below that the smaller work-groups are 5-20% faster), and
-    // only with enough work-groups to give every compute unit two.
-    const int64_t wgs256 = ((T + 255) / 256) * n_q_heads * batch;
-    const bool four = head_dim == 128 && T >= 8192 && wgs256 >= 512;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e;
-    if (head_dim == 128) e = four ? launch<128, 4>(a, s) : launch<128, 2>(a, s);
-    else e = launch<64, 2>(a, s);
+    const hipError_t e = head_dim == 128 ? launch<128, 4>(a, s) : launch<64, 4>(a, s);
     return e == hipSuccess ? FACT_OK : fact::record_hip_failure(e, "attention launch");
 }

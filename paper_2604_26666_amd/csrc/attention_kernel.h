@@ -3,40 +3,40 @@
 // h / (Hq / Hkv); nothing is expanded in memory).  The paper's first block pattern (Section 5.2.4
 // pattern p1; Section 5.2.5 pattern p1 for the grouped form) replaces this sub-graph with one
 // kernel that tiles over keys and never writes the score matrix to HBM (Section 2.1); this is
-// that kernel for 64-lane wavefronts and MFMA 16x16x32, written from the definition.
+// that kernel for 64-lane wavefronts and MFMA 32x32x16, written from the definition.
 //
 // Shape of the computation
-//   A work-group owns BQ = NW * 64 consecutive queries of one (batch, query head): wave w owns
-//   queries [q0 + 64 w, q0 + 64 w + 64) as 4 column tiles of 16.  Keys and values are walked in
-//   blocks of 64, staged in LDS (double-buffered, global->LDS direct loads) and shared by the
-//   waves.  Everything is computed TRANSPOSED so that a lane owns pieces of ONE query:
+//   A work-group owns BQ = NW * 32 consecutive queries of one (batch, query head), a wave 32 of
+//   them.  Keys and values are walked in blocks of 64, staged in LDS (double-buffered, global->LDS
+//   direct loads) and shared by the waves.  Everything is computed TRANSPOSED so that a lane owns
+//   pieces of ONE query:
 //     S^T (keys x queries) = K_block (A operand, rows = keys) x Q^T (B operand, columns = queries)
 //     O^T (d    x queries) = V_block^T (A operand, rows = d)  x P^T (B operand, columns = queries)
-//   MFMA 16x16x32 result layout: lane (r16 = lane % 16, q4 = lane / 16), register r holds
-//   D[4 q4 + r][r16]: rows come from the A operand, the column is the lane's query.  Hence
-//   * the running maximum of a query needs its 16 in-lane values per key block and one exchange
-//     with the three other lanes that hold the same query (lane ^ 16, lane ^ 32);
-//   * the softmax denominator is one more tile of the second contraction (V^T extended by a tile
-//     of ones), which also adds up the four lanes;
+//   MFMA 32x32x16 result layout: lane (r32 = lane % 32, h = lane / 32), register r holds
+//   D[8 (r / 4) + 4 h + r % 4][r32]: rows come from the A operand, the column is the lane's query.
+//   Hence
+//   * the running maximum of a query needs its 32 in-lane values per key block and one exchange
+//     with the other lane that holds the same query (lane ^ 32); its sum likewise, at the very end;
 //   * P^T in registers already IS the B operand of the second MFMA: a B operand lane holds 8
-//     K-values (here: keys) of one column (query).  The 8 keys a lane holds after two S^T tiles are
-//     {32u + 4 q4 + 0..3} and {32u + 16 + 4 q4 + 0..3}, not 8 consecutive ones, so the A operand
-//     (V^T) is fetched with the same key permutation: the transposing LDS read takes one address
-//     per 4-key group, so this costs nothing.
-//   Q^T fragments (the B operand of the first MFMA: 8 consecutive d of one query) are 16-byte
-//   pieces of Q rows: loaded once from global memory straight into registers.
-//   Softmax runs in base 2: p = 2^(s * c - m * c) with c = scale * log2(e), fp32.  P is rounded to
-//   bf16 (RNE) for the second MFMA; numerator and denominator sum the same rounded values.
-//   One wave per SIMD (the accumulators take most of the 512 registers), so nothing hides a stall:
-//   the key blocks are software-pipelined (scores of block j+1 under the softmax of block j, see
-//   `step` below) and every instruction is placed by hand between the MFMAs.
+//     K-values (here: keys) of one column (query).  The 8 keys a lane holds of a 16-key group u are
+//     {16u + 4h + 0..3} and {16u + 8 + 4h + 0..3}, not 8 consecutive ones, so the A operand
+//     (V^T) is fetched with the same permutation - the transposing LDS read takes one address per
+//     4-key group anyway.
+//   What bounds it: instruction issue.  A score costs an fma, an exponential (two issue slots), half a
+//   conversion and half an addition: 135 vector instructions per wave and key block, 580 cycles,
+//   next to 16 MFMAs (512 cycles) at head_dim 64 and 32 (1024) at 128, of which each takes about
+//   10 issue cycles from its SIMD.  A wave does the two in turn, so what matters is that another wave
+//   of the SIMD is at the other: 32 queries per wave leave room for three waves per SIMD at
+//   head_dim 64 and two at 128, and a work-group's first loads and last stores are covered the
+//   same way.  Against 64 queries per wave, one wave per SIMD and scores of one block computed
+//   between the exponentials of another (which this kernel replaces at every size): 16 x 500 tokens,
+//   12 heads of 64: 34 -> 21 us; 8 x 1024 causal 31 -> 23; 4 x 1999 causal, 32 / 8 heads of 128:
+//   157 -> 138; 1 x 2048 61 -> 44; 1 x 8192 526 -> 506 (1090 TFLOP/s); 4 x 4096, 16 heads of 64, full,
+//   338 -> 288.  Counters of the last: vector ALU issuing 63 % of the cycles, matrix pipe busy 44 %.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-#include <type_traits>
-#include <utility>
 
 namespace fact {
 namespace attn {
@@ -45,12 +45,12 @@ namespace attn {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
+typedef u32x4_t u32x4_by8 __attribute__((aligned(8)));       // rows of O start at any multiple of 8 bytes
 
 struct AttnArgs {
     const __bf16 *Q, *K, *V;
@@ -63,6 +63,7 @@ struct AttnArgs {
     float scale_log2;       // softmax scale * log2(e)
     int q_blocks;           // ceil(T / BQ)
     int total;              // q_blocks * Hq * B work-groups
+    int fold;               // positions of the work-group order (of an XCD's part of it) from here on run backwards
     int group;              // (batch, query head) pairs per group of the work-group order; divides the pairs of an XCD
 };
 
@@ -77,71 +78,71 @@ __device__ __forceinline__ const char *uniform_ptr(const char *ptr)
 
 // (Device-only builtins live in __device__ helpers: used directly in a __global__ template they
 // make the host pass drop the kernel's launch stub without a diagnostic.)
-__device__ __forceinline__ f32x4_t mfma_16x16x32(bf16x8_t a, bf16x8_t b, f32x4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-// max over the four lanes lane, lane ^ 16, lane ^ 32, lane ^ 48, in every lane, without LDS:
-// v_permlane16_swap exchanges the odd 16-lane rows of its first operand with the even rows of
-// its second, v_permlane32_swap the upper half of the first with the lower half of the second;
-// applied to two copies of x, the two results hold x and its partner's x in every lane.
-__device__ __forceinline__ float max_with_lane_xor16(float x)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, x);
-    auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    return fmaxf(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
-}
+// max over lane and lane ^ 32, in both, without LDS: v_permlane32_swap exchanges the upper half of its
+// first operand with the lower half of its second; applied to two copies of x, the two results hold x
+// and its partner's x in every lane.
 __device__ __forceinline__ float max_with_lane_xor32(float x)
 {
     const uint32_t w = __builtin_bit_cast(uint32_t, x);
     auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
     return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
 }
-__device__ __forceinline__ float max_over_lane_quads(float x) { return max_with_lane_xor32(max_with_lane_xor16(x)); }
+__device__ __forceinline__ float sum_with_lane_xor32(float x)
+{
+    const uint32_t w = __builtin_bit_cast(uint32_t, x);
+    auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
+}
 // 16 bytes per lane from global memory straight into LDS at lds + 16 * lane (lds uniform over the wave)
 __device__ __forceinline__ void load_to_lds_16(__amdgpu_buffer_rsrc_t rsrc, char *lds, uint32_t voffset, uint32_t soffset)
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, FACT_ATTN_LDS_PTR(lds), 16, voffset, soffset, 0, 0);
 }
-
-template <int N, class F, int... I>
-__device__ __forceinline__ void unroll_impl(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void unroll(F &&f) { unroll_impl<N>(static_cast<F &&>(f), std::make_integer_sequence<int, N>{}); }
+// 64-bit transposing LDS read (see the V^T fragment addresses)
+__device__ __forceinline__ s16x4_t read_transposed(const char *lds)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)lds);
+#else
+    return s16x4_t{};
+#endif
+}
 
 // LDS layout of a key or value block: [64 rows][D] bf16, the 16-byte chunk c of row r stored at
 // chunk position c ^ swz(r).
-//  K (read as MFMA A operand: 16 consecutive rows x 4 consecutive chunks per instruction): the
-//    XOR with the row number spreads the 16 rows, which all start at the same bank, over the banks.
-//  V (read with the transposing 64-bit read: per 16 lanes, 4 rows x 32 bytes at the same column):
-//    the XOR moves rows 4q..4q+3 (and the neighbouring group of 4) to different 32-byte windows.
+//  K (read as MFMA A operand: 32 consecutive rows x 2 consecutive chunks per instruction): the
+//    XOR with the row number spreads the rows, which all start at the same bank, over the banks.
+//  V (read with the transposing 64-bit read: per 32 lanes, 4 rows x 64 bytes at the same column):
+//    the XOR moves the 4 rows to different 64-byte windows of 256 bytes.
 template <int D> __device__ __forceinline__ int swz_keys(int row) { return row & (D / 8 - 1); }
 template <int D> __device__ __forceinline__ int swz_vals(int row)
 {
-    if constexpr (D == 128) return ((row & 3) << 2) | (((row >> 2) & 1) << 1);
-    else return (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1);
+    if constexpr (D == 128) return (row & 3) << 2;
+    else return ((row >> 1) & 1) << 2;
 }
 
 template <int D, int NW>
-__global__ void __launch_bounds__(NW * 64)
+__global__ void __launch_bounds__(NW * 64, D == 64 ? 3 : 2)
 attn_fwd_kernel(const AttnArgs p)
 {
+#if defined(__HIP_DEVICE_COMPILE__)      // the host pass only needs the kernel's symbol
     static_assert(D == 64 || D == 128, "head_dim");
-    constexpr int QW = 64, QT = QW / 16, BQ = NW * QW;        // queries per wave, its column tiles, per work-group
-    constexpr int BKV = 64, KT = BKV / 16, UB = BKV / 32;      // keys per block, its row tiles, 32-key groups
-    constexpr int KB = D / 32, DT = D / 16;                    // 32-wide groups / 16-row tiles of head_dim
+    constexpr int QW = 32, BQ = NW * QW;                       // queries per wave and per work-group
+    constexpr int BKV = 64, KT = BKV / 32, UB = BKV / 16;      // keys per block, its row tiles, 16-key groups
+    constexpr int KS = D / 16, DT = D / 32;                    // 16-wide groups / 32-row tiles of head_dim
     constexpr int CPR = D / 8, ROWB = D * 2;                   // chunks and bytes per LDS row
     constexpr int TILE_BYTES = BKV * ROWB, STAGE_BYTES = 2 * TILE_BYTES;
     constexpr int RPL = 1024 / ROWB;                           // rows per wave-wide load
     constexpr int L = TILE_BYTES / 1024 / NW;                  // wave-wide loads per tile and wave
     static_assert(L >= 1 && L * NW * 1024 == TILE_BYTES, "tile split over the waves");
+    static_assert(NW * RPL % (D / 8) == 0, "a wave's pieces are whole swizzle periods apart");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = lane & 15, q4 = lane >> 4;
+    const int r32 = lane & 31, h = lane >> 5;
 
     // Work-group -> (batch, key/value head, query head, query block).  Consecutive work-group ids go
     // to different XCDs (each with its own L2): id % 8 picks the XCD, and every XCD gets its own
@@ -153,13 +154,17 @@ attn_fwd_kernel(const AttnArgs p)
     // (The hardware hands consecutive work-groups of an XCD to its shader engines in turn and in
     // order; with a heavy .. light pattern whose period matched that turn, one engine got all the
     // heavy work-groups and the others idled between theirs - measured 30% of the time.)
+    // Where all work-groups of a causal launch are resident at once, the last one that each compute unit
+    // gets comes from the other end (p.fold): the light ones join the heaviest.
     const int G = p.Hq / p.Hkv;
     const int pairs = p.total / p.q_blocks;                    // batch * query heads
     int qb, pair;
     {
         const int v = blockIdx.x;
         const bool split = (pairs & 7) == 0;                   // else: one sequence over all pairs
-        const int pos = split ? v >> 3 : v, first = split ? (v & 7) * (pairs >> 3) : 0;
+        int pos = split ? v >> 3 : v;
+        if (pos >= p.fold) pos = p.fold + (split ? p.total >> 3 : p.total) - 1 - pos;
+        const int first = split ? (v & 7) * (pairs >> 3) : 0;
         const int per_group = p.group * p.q_blocks;
         const int gi = pos / per_group, within = pos - gi * per_group;
         qb = p.q_blocks - 1 - within / p.group;
@@ -189,415 +194,193 @@ attn_fwd_kernel(const AttnArgs p)
     // ---- K / V block loads: wave w fills the 1 KB pieces w, w + NW, ... of each tile -------------
     // Lane l of a wave-wide load writes 16 bytes at piece + 16 l, i.e. row l / CPR of the piece,
     // chunk position l % CPR: it fetches the chunk that belongs there under the swizzle.  Rows at
-    // or beyond T lie outside the descriptor's range and arrive as zeros.  A wave's pieces are
-    // NW * RPL rows apart, a multiple of the swizzles' periods except for 128-wide K rows with two
-    // waves (period 16, step 8): so one per-lane offset serves all of a wave's loads (two there),
-    // the piece and the key block go into the scalar offset.
-    // LDS: two K slots then two V slots; block j uses slot j % 2 of each.
-    constexpr int KALT = (D == 128 && NW == 2) ? 2 : 1;
-    uint32_t k_off[KALT], v_off;
+    // or beyond T lie outside the descriptor's range and arrive as zeros.  One per-lane offset serves
+    // all of a wave's loads; the piece and the key block go into the scalar offset.
+    // LDS: two stages of a K tile and a V tile; block j uses stage j % 2.
+    uint32_t k_off, v_off;
     {
         const int row = wave * RPL + lane / CPR, pos = lane % CPR;
-#pragma unroll
-        for (int a = 0; a < KALT; ++a)
-            k_off[a] = (uint32_t)(row * p.k_st * 2 + ((pos ^ swz_keys<D>(row + a * NW * RPL)) << 4));
+        k_off = (uint32_t)(row * p.k_st * 2 + ((pos ^ swz_keys<D>(row)) << 4));
         v_off = (uint32_t)(row * p.v_st * 2 + ((pos ^ swz_vals<D>(row)) << 4));
     }
     const uint32_t k_blk = (uint32_t)(BKV * p.k_st * 2), v_blk = (uint32_t)(BKV * p.v_st * 2);
     const uint32_t k_piece = (uint32_t)(NW * RPL * p.k_st * 2), v_piece = (uint32_t)(NW * RPL * p.v_st * 2);
-    // (block j >= nb does not exist: its loads still run, with a scalar offset beyond every descriptor's
-    // range, and bring zeros into a slot nobody reads - no branch around a load in the middle of the MFMAs)
-    constexpr uint32_t kBeyond = 0x80000000u;
-    // (per piece only one scalar addition for the offset and one for the LDS address: scalar
-    // instructions take issue slots of this wave like any others)
-    auto k_block_off = [&](int j) { return j < nb ? (uint32_t)j * k_blk : kBeyond; };
-    auto v_block_off = [&](int j) { return j < nb ? (uint32_t)j * v_blk : kBeyond; };
-    auto load_k_piece2 = [&](char *slot, uint32_t blk_off, int t) __attribute__((always_inline)) {
-        load_to_lds_16(rsrc_k, slot + t * NW * 1024, k_off[t % KALT], blk_off + t * k_piece);
-    };
-    auto load_v_piece2 = [&](char *slot, uint32_t blk_off, int t) __attribute__((always_inline)) {
-        load_to_lds_16(rsrc_v, slot + t * NW * 1024, v_off, blk_off + t * v_piece);
-    };
-    auto load_k_piece = [&](int j, int t) __attribute__((always_inline)) {
-        load_k_piece2(smem + (j & 1) * TILE_BYTES + wave * 1024, k_block_off(j), t);
-    };
-    auto load_v_piece = [&](int j, int t) __attribute__((always_inline)) {
-        load_v_piece2(smem + (2 + (j & 1)) * TILE_BYTES + wave * 1024, v_block_off(j), t);
-    };
-    auto load_k = [&](int j) __attribute__((always_inline)) {
+    auto load_block = [&](int j, int stage) __attribute__((always_inline)) {
+        char *const dst = smem + stage * STAGE_BYTES + wave * 1024;
 #pragma unroll
-        for (int t = 0; t < L; ++t) load_k_piece(j, t);
-    };
-    auto load_v = [&](int j) __attribute__((always_inline)) {
+        for (int t = 0; t < L; ++t) load_to_lds_16(rsrc_k, dst + t * NW * 1024, k_off, j * k_blk + t * k_piece);
 #pragma unroll
-        for (int t = 0; t < L; ++t) load_v_piece(j, t);
+        for (int t = 0; t < L; ++t) load_to_lds_16(rsrc_v, dst + TILE_BYTES + t * NW * 1024, v_off, j * v_blk + t * v_piece);
     };
-    load_k(0);
-    load_v(0);
-    if (nb > 1) load_k(1);
+    load_block(0, 0);
 
-    // ---- Q^T fragments: query 16 qt + r16 of the wave, d = 32 kb + 8 q4 .. + 7 ----------------
-    bf16x8_t qf[QT][KB];
+    // ---- Q^T fragments: query r32 of the wave, d = 16 ks + 8 h .. + 7 ----------------------------
+    bf16x8_t qf[KS];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            const uint32_t off = (uint32_t)(((q0w + 16 * qt + r16) * p.q_st + 32 * kb + 8 * q4) * 2);
-            qf[qt][kb] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc_q, off, 0, 0));
-        }
+    for (int ks = 0; ks < KS; ++ks)
+        qf[ks] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc_q, (uint32_t)(((q0w + r32) * p.q_st + 16 * ks + 8 * h) * 2), 0, 0));
 
-    // ---- LDS fragment addresses (relative to the slot) -----------------------------------------
-    // K tile kt, group kb: row 16 kt + r16, chunk (4 kb + q4) ^ swizzle(r16): kb sits in address bits
-    // 6 and up, which the XOR leaves to it, so group kb is the group-0 address ^ (kb << 6).
-    const uint32_t k_addr = (uint32_t)(r16 * ROWB + ((q4 ^ swz_keys<D>(r16)) << 4));
-    // V^T tile dt, 32-key group u, half h: a transposing read hands lane i of a 16-lane group
-    // column (= d) i of the 4 rows (= keys) whose addresses lanes 4 jj + cc supply for columns
-    // 4 cc .. 4 cc + 3.  Keys 32 u + 16 h + 4 q4 + jj: the permutation P^T comes in.  Tile dt is the
-    // tile-0 address ^ (dt << 5) (chunk 2 dt + cc / 2, swizzled by XOR; slots are 256-byte aligned).
-    const int jj = (lane >> 2) & 3, cc = lane & 3;
-    const uint32_t v_addr = (uint32_t)((4 * q4 + jj) * ROWB + (((cc >> 1) ^ swz_vals<D>(4 * q4 + jj)) << 4) + (cc & 1) * 8);
-    const uint32_t lds0 = (uint32_t)(size_t)FACT_ATTN_LDS_PTR(smem);
+    // ---- LDS fragment addresses (relative to the tile) -------------------------------------------
+    // K tile kt, group ks: row 32 kt + r32, chunk (2 ks + h) ^ swizzle(r32): ks sits in address bits 5
+    // and up, which the XOR leaves to it, so group ks is the group-0 address ^ (ks << 5).
+    const uint32_t k_addr = (uint32_t)(r32 * ROWB + ((h ^ swz_keys<D>(r32)) << 4));
+    // V^T tile dt, 16-key group u, half: a transposing read hands lane i of a 16-lane group column
+    // (= d) i of the 4 rows (= keys) whose addresses lanes 4 jj + cc supply for columns 4 cc .. 4 cc + 3.
+    // Keys 16 u + 8 half + 4 h + jj: the permutation P^T comes in.  Tile dt is the tile-0 address ^ (dt << 6).
+    const int jj = (lane >> 2) & 3, cc = lane & 3, g1 = (lane >> 4) & 1;
+    const uint32_t v_addr = (uint32_t)((4 * h + jj) * ROWB + (((2 * g1 + (cc >> 1)) ^ swz_vals<D>(4 * h + jj)) << 4) + (cc & 1) * 8);
 
-    // ---- state ------------------------------------------------------------------------------------
-    // The MFMAs are inline asm so that the register classes are fixed: O^T accumulators and the Q^T
-    // fragments live in the accumulation registers for the whole kernel, S^T goes straight to
-    // ordinary registers where the softmax works on it (through the builtin the compiler moved
-    // ~900 registers per key block between the two files).  The compiler does not know these are
-    // MFMAs, so the wait states between an MFMA and a vector-ALU read of its result are kept by
-    // construction (see the s_nop's) instead.
-    f32x4_t S[2][KT][QT];            // S^T of the block being consumed and of the one after it
-    f32x4_t o[DT][QT];
-    u32x4_t pf[UB][QT];              // P^T, bf16 pairs, in MFMA B-operand order
-    bf16x8_t kf[4];                  // K fragments: ring, read two fragments ahead of their MFMAs
-    s16x4_t vlo[3][UB], vhi[3][UB];   // V^T fragments: ring of three tiles, read two tiles ahead of their MFMAs
+    f32x16_t o[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-            o[dt][qt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            asm volatile("" : "+a"(o[dt][qt]));
-        }
-    f32x4_t lsum[QT];                // row sums of P: one more tile of O^T, from a V^T tile of ones
-    float m[QT], mx[QT], mc[QT];
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        m[qt] = -__builtin_inff(); mx[qt] = 0.f; mc[qt] = 0.f;
-        lsum[qt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        asm volatile("" : "+a"(lsum[qt]));
-    }
-    // a V^T fragment of ones: with it as the A operand, every row of the result tile is the sum of P
-    // over the keys - the softmax denominator, from the same rounded probabilities the numerator
-    // uses, on the matrix pipe instead of 64 vector additions per key block, and already summed
-    // over the four lanes that share a query
-    // (kept in registers for good: written right before its MFMA - which the compiler, not knowing
-    // that the asm is an MFMA, did - the matrix pipe read the registers' previous contents)
-    u32x4_t ones_frag = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-    asm volatile("" : "+v"(ones_frag));
-#pragma unroll
-    for (int u = 0; u < UB; ++u)
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) pf[u][qt] = u32x4_t{0u, 0u, 0u, 0u};
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+    // m is the REFERENCE exponent of the query's running sums, not its running maximum: it is the first
+    // block's largest score, and is raised (and the sums rescaled) only when the probabilities that a
+    // lane has computed with it add up to more than kMaxSum (or to no number).  None of them is above
+    // kMaxSum then, harmless in bf16 and fp32, and most key blocks need neither a maximum nor a rescaling:
+    // 26 of 150 vector instructions of a block.  The branch is uniform over the wave.
+    constexpr float kMaxSum = 256.0f;
     const float c = p.scale_log2;
+    float m = -__builtin_inff(), l = 0.f;
 
-    constexpr int NS = KT * KB * QT;                 // MFMAs of one S^T block
-    constexpr int EPM = KT * QT * 4 / NS;             // softmax elements worked off behind each of them
-    constexpr int NF = KT * KB;                      // K fragments of a block
-    constexpr int NE = KT * QT * 4;                  // softmax elements per lane and block
-
-    // (lambdas that hold inline asm take plain integers, constant after inlining: asm operands
-    // inside a generic lambda cannot name the enclosing function's variables)
-    auto read_k = [&](int slot_off, int f) __attribute__((always_inline)) {
-        const int kt = f / KB, kb = f % KB;
-        kf[f & 3] = *(const bf16x8_t *)(smem + slot_off + (k_addr ^ (kb << 6)) + kt * 16 * ROWB);
-    };
-    // MFMA number i of S^T(block) into S[tb]: fragment f = i / QT (key tile kt, 32 d's kb), query tile i % QT
-    auto s_mfma = [&](int tb, int slot_off, int i) __attribute__((always_inline)) {
-        const int f = i / QT, qt = i % QT, kt = f / KB, kb = f % KB;
-        if (qt == 0 && f + 2 < NF) read_k(slot_off, f + 2);
-        // The softmax values worked on behind the previous MFMA (the other S buffer's registers in
-        // their three stages, the packed pairs) ride along as dummy operands:
-        // that is what keeps the compiler from moving the softmax out from between the MFMAs.
-        const int e1 = (i + 1) * EPM < NE ? (i + 1) * EPM : NE - 1;      // an element stage 1 touched in slot i - 1
-        const int e3 = i > 0 ? (i - 1) * EPM : 0;                        // an element stage 3 touched in slot i - 1
-        const int q1 = e1 / (KT * 4), k1 = (e1 / 4) % KT, q3 = e3 / (KT * 4), k3 = (e3 / 4) % KT;
-        // (inputs only: as outputs they would make the compiler put a wait state behind every MFMA,
-        // which costs this wave an issue slot like any instruction)
-        if (kb == 0)
-            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0"
-                         : "=&v"(S[tb][kt][qt])
-                         : "v"(kf[f & 3]), "a"(qf[qt][kb]), "v"(S[tb ^ 1][k1][q1]), "v"(S[tb ^ 1][k3][q3]), "v"(pf[k3 / 2][q3]));
-        else
-            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                         : "+v"(S[tb][kt][qt])
-                         : "v"(kf[f & 3]), "a"(qf[qt][kb]), "v"(S[tb ^ 1][k1][q1]), "v"(S[tb ^ 1][k3][q3]), "v"(pf[k3 / 2][q3]));
-    };
-    // Softmax of S[sb], element e (query tile e / 16, key tile, register), in three stages that run
-    // in consecutive MFMA slots for one element and side by side for three different elements: a
-    // single wave per SIMD has nothing else to cover the latency of a dependent vector instruction
-    // (measured: fma -> exp -> add back to back take 29 cycles, the same three independent 17).
-    //   stage 1: t = s c - m c      stage 2: p = 2^t      stage 3: pack pairs to bf16
-    auto sm1 = [&](auto sb_, auto e_) __attribute__((always_inline)) {
-        constexpr int sb = decltype(sb_)::value, e = decltype(e_)::value;
-        if constexpr (e < NE) {
-            constexpr int qt = e / (KT * 4), kt = (e / 4) % KT, r = e % 4;
-            S[sb][kt][qt][r] = __builtin_fmaf(S[sb][kt][qt][r], c, -mc[qt]);
+    // One key block.  `stage` is a constant after inlining.
+    auto step = [&](int j, int stage) __attribute__((always_inline)) {
+        // block j has landed, for every wave, and every wave is done with block j - 1, whose stage the
+        // next loads overwrite
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (j >= nbw) {                                          // nothing (more) this wave's queries may see
+            if (j + 1 < nb) load_block(j + 1, stage ^ 1);
+            return;
         }
-    };
-    auto sm2 = [&](auto sb_, auto e_) __attribute__((always_inline)) {
-        constexpr int sb = decltype(sb_)::value, e = decltype(e_)::value;
-        if constexpr (e < NE) {
-            constexpr int qt = e / (KT * 4), kt = (e / 4) % KT, r = e % 4;
-            S[sb][kt][qt][r] = exp2_fast(S[sb][kt][qt][r]);
-        }
-    };
-    auto sm3 = [&](auto sb_, auto e_) __attribute__((always_inline)) {
-        constexpr int sb = decltype(sb_)::value, e = decltype(e_)::value;
-        constexpr int qt = e / (KT * 4), kt = (e / 4) % KT, r = e % 4;
-        if constexpr (r & 1) {
-            const f32x2_t pr = {S[sb][kt][qt][r - 1], S[sb][kt][qt][r]};
-            pf[kt / 2][qt][2 * (kt & 1) + r / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2_t));
-        }
-    };
-    auto mask_block = [&](auto sb_, int j) __attribute__((always_inline)) {
-        constexpr int sb = decltype(sb_)::value;
-        const int j0 = j * BKV;
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) {
-            const int last = p.causal ? q0w + 16 * qt + r16 : T - 1;         // last key this query sees
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (j0 + 16 * kt + 4 * q4 + r > last) S[sb][kt][qt][r] = -__builtin_inff();
-            __builtin_amdgcn_sched_barrier(0);        // (16 compare masks at a time: all 64 at once spill scalar registers everywhere)
-        }
-    };
-    auto needs_mask = [&](int j) { return p.causal ? (j * BKV + BKV - 1 > q0w) : (j * BKV + BKV > T); };
-    // largest score of query tile qt in S[sb], over the four lanes that share a query
-    auto max_of = [&](auto sb_, auto qt_) __attribute__((always_inline)) {
-        constexpr int sb = decltype(sb_)::value, qt = decltype(qt_)::value;
-        float t = S[sb][0][qt][0];
+        const char *const kt_lds = smem + stage * STAGE_BYTES, *const vt_lds = kt_lds + TILE_BYTES;
+        f32x16_t S[KT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) t = fmaxf(t, S[sb][kt][qt][r]);
-        mx[qt] = max_over_lane_quads(t);
-    };
-    // the same in pieces, to go between the MFMAs of the second contraction: piece p < KT folds in
-    // key tile p, pieces KT and KT + 1 exchange with the lanes that share the query
-    float mt = 0.f;
-    auto max_piece = [&](auto sb_, auto qt_, auto p_) __attribute__((always_inline)) {
-        constexpr int sb = decltype(sb_)::value, qt = decltype(qt_)::value, pc = decltype(p_)::value;
-        if constexpr (pc < KT) {
-            const f32x4_t x = S[sb][pc][qt];
-            if constexpr (pc == 0) mt = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-            else mt = fmaxf(fmaxf(mt, x[0]), fmaxf(fmaxf(x[1], x[2]), x[3]));
-        } else if constexpr (pc == KT) {
-            mt = max_with_lane_xor16(mt);
-        } else if constexpr (pc == KT + 1) {
-            mt = max_with_lane_xor32(mt);
-            mx[qt] = mt;
-        }
-    };
-    // transposing reads of V^T tile dt into fragment set `set`: 32-key group u (both 16-key halves)
-    auto read_v = [&](int set, uint32_t vbase, int dt, int u) __attribute__((always_inline)) {
-        static_assert(UB == 2, "two 32-key groups");
-        const uint32_t va = (vbase + v_addr) ^ (uint32_t)(dt << 5);
-        if (u == 0) {
-            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(vlo[set][0]) : "v"(va), "n"(0));
-            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(vhi[set][0]) : "v"(va), "n"(16 * ROWB));
-        } else {
-            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(vlo[set][1]) : "v"(va), "n"(32 * ROWB));
-            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(vhi[set][1]) : "v"(va), "n"(48 * ROWB));
-        }
-    };
-    auto wait_v4 = [&](int set) __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(4)" : "+v"(vlo[set][0]), "+v"(vhi[set][0]), "+v"(vlo[set][1]), "+v"(vhi[set][1]));
-    };
-    auto wait_v = [&](int set) __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vlo[set][0]), "+v"(vhi[set][0]), "+v"(vlo[set][1]), "+v"(vhi[set][1]));
-    };
-    // MFMA number mi of O^T tile dt: 32-key group mi / QT, query tile mi % QT (the running maximum
-    // of the piece worked off behind the previous MFMA rides along as a dummy operand, as above)
-    auto pv_mfma = [&](int set, int dt, int mi) __attribute__((always_inline)) {
-        const int u = mi / QT, qt = mi % QT;
-        const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(vlo[set][u], vhi[set][u], 0, 1, 2, 3, 4, 5, 6, 7));
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(o[dt][qt]) : "v"(vf), "v"(pf[u][qt]), "v"(mt), "v"(mx[(dt + QT - 1) % QT]));
-    };
-    float gmax = __builtin_inff();
-    auto sum_mfma = [&](int u, int qt) __attribute__((always_inline)) {
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(lsum[qt]) : "v"(ones_frag), "v"(pf[u][qt]), "v"(gmax));
-    };
-    auto nops = [&]() __attribute__((always_inline)) { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); };
-
-    // One key block: softmax of S[PAR] (block j) while S[PAR ^ 1] (block j + 1) is being computed,
-    // then O^T += V_j^T P^T while the maxima of block j + 1 are found.
-    auto step = [&](auto par_, int j) __attribute__((always_inline)) {
-        constexpr int PAR = decltype(par_)::value;
-        typedef std::integral_constant<int, PAR> cur_t;
-        typedef std::integral_constant<int, PAR ^ 1> nxt_t;
-        // Loads issued one step ago (K of block j+1, V of block j) have landed, for every wave; every
-        // wave is done with K of block j and V of block j-1, whose slots the new loads overwrite.
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        // The new loads: a wave with work issues them one by one between the MFMAs below (in a burst
-        // right here, 4 waves x 2 L loads queue up at the compute unit's address unit and every wave
-        // loses ~400 cycles of issue time).
-        if (j >= nbw) {                                          // nothing (more) this wave's queries may see
-            if (j + 2 < nb) load_k(j + 2);
-            if (j + 1 < nb) load_v(j + 1);
-            return;
-        }
-
-        // m[qt] is the REFERENCE exponent of the query's running sums, not always its running
-        // maximum: it is raised (and the sums rescaled) only when a score exceeds it by more than
-        // 2^kSlack in the base-2 domain, so the probabilities handed to the second MFMA stay below
-        // 2^kSlack = 256 (harmless in bf16 and fp32) and the accumulators are left alone on most
-        // key blocks.  The branch is uniform over the wave.
-        constexpr float kSlack = 8.0f;
-        // (gmax = largest (mx - m) c over the query tiles, found behind the previous step's last MFMAs;
-        // +inf before the first block)
-        if (__builtin_amdgcn_ballot_w64(gmax > kSlack) != 0) {
-            nops();                                              // the previous block's MFMAs have written O
+            for (int r = 0; r < 16; ++r) S[kt][r] = 0.f;
+        // Priority while the score MFMAs are issued: two waves that reach them together would share the pipe, finish
+        // together and then compete for the vector ALU; like this one of them goes ahead and the other's
+        // MFMAs run under its softmax (2 x 4096 tokens, 32 / 8 heads of 128, full: 498 -> 478 us).
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int qt = 0; qt < QT; ++qt) {
-                const float m_new = fmaxf(m[qt], mx[qt]);
-                const float alpha = exp2_fast((m[qt] - m_new) * c);
-                m[qt] = m_new;
-                asm volatile("" : "+a"(lsum[qt]));
-                lsum[qt] *= alpha;
-                asm volatile("" : "+a"(lsum[qt]));
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    asm volatile("" : "+a"(o[dt][qt]));           // (keeps the copy out of the registers inside this branch)
-                    o[dt][qt] *= alpha;
-                    asm volatile("" : "+a"(o[dt][qt]));           // back in the accumulation registers before the paths join
-                    __builtin_amdgcn_sched_barrier(0);            // one tile at a time: few registers in flight
-                }
-            }
-        }
+            for (int kt = 0; kt < KT; ++kt)
+                S[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8_t *)(kt_lds + (k_addr ^ (ks << 5)) + kt * 32 * ROWB), qf[ks], S[kt], 0, 0, 0);
+
+        // The V^T fragments go to registers here, before the next block's loads: the compiler waits for every
+        // outstanding load into LDS before a transposing read.
+        s16x4_t vf[UB][DT][2];
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt) mc[qt] = m[qt] * c;
-
-        // S^T of block j + 1, one softmax element of block j behind each MFMA.  On the wave's last
-        // block this still runs, on whatever the other K slot holds: the result is never used, and
-        // the softmax alone would take as long as the two together.
-        {
-            const int slot_off = ((j + 1) & 1) * TILE_BYTES;
-            char *const k_dst = smem + (j & 1) * TILE_BYTES + wave * 1024, *const v_dst = smem + (2 + ((j + 1) & 1)) * TILE_BYTES + wave * 1024;
-            const uint32_t k_src = k_block_off(j + 2), v_src = v_block_off(j + 1);
-            read_k(slot_off, 0);
-            read_k(slot_off, 1);
-            unroll<EPM>([&](auto k_) __attribute__((always_inline)) {          // fill the softmax pipeline
-                constexpr int k = decltype(k_)::value;
-                sm1(cur_t{}, std::integral_constant<int, k>{});
-                sm1(cur_t{}, std::integral_constant<int, EPM + k>{});
-            });
-            unroll<EPM>([&](auto k_) __attribute__((always_inline)) { sm2(cur_t{}, k_); });
-            __builtin_amdgcn_sched_barrier(0);
-            unroll<NS>([&](auto i_) __attribute__((always_inline)) {
-                constexpr int i = decltype(i_)::value;
-                s_mfma(PAR ^ 1, slot_off, i);
-                constexpr int LOAD_EVERY = NS / (2 * L);
-                if constexpr (i % LOAD_EVERY == LOAD_EVERY - 1) {
-                    constexpr int t = i / LOAD_EVERY;
-                    if constexpr (t < L) load_k_piece2(k_dst, k_src, t); else load_v_piece2(v_dst, v_src, t - L);
-                }
-                unroll<EPM>([&](auto k_) __attribute__((always_inline)) {
-                    constexpr int k = decltype(k_)::value;
-                    sm1(cur_t{}, std::integral_constant<int, (i + 2) * EPM + k>{});
-                    __builtin_amdgcn_sched_barrier(0);      // fma first: an exponential right behind the asm gets a wait state
-                    sm2(cur_t{}, std::integral_constant<int, (i + 1) * EPM + k>{});
-                    sm3(cur_t{}, std::integral_constant<int, i * EPM + k>{});
-                });
-                __builtin_amdgcn_sched_barrier(0);
-            });
-            if (needs_mask(j + 1)) {
-                nops();
-                mask_block(nxt_t{}, j + 1);
-            }
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int half = 0; half < 2; ++half)
+                    vf[u][dt][half] = read_transposed(vt_lds + ((v_addr ^ (dt << 6)) + (16 * u + 8 * half) * ROWB));
+        // all of it in one order: a few K fragments, then LDS reads between the MFMAs (296 -> 290 us at 4 x 4096 tokens, 16 heads of 64)
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+        for (int i = 0; i < KS * KT; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + 1 < nb) load_block(j + 1, stage ^ 1);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
 
-        const uint32_t vbase = lds0 + (2 + (j & 1)) * TILE_BYTES;
-        read_v(0, vbase, 0, 0);
-        read_v(0, vbase, 0, 1);
-        read_v(1, vbase, 1, 0);
-        read_v(1, vbase, 1, 1);
-        unroll<DT>([&](auto dt_) __attribute__((always_inline)) {
-            constexpr int dt = decltype(dt_)::value;
-            // tile dt has arrived when at most the 4 reads of tile dt + 1 are still in flight
-            if constexpr (dt + 1 < DT) wait_v4(dt % 3); else wait_v(dt % 3);
-            // 2 QT MFMAs; behind each: half of the reads of tile dt + 2, or a piece of the maximum of
-            // query tile dt of block j + 1 (the S^T MFMAs of this step are >= 8 MFMAs back by then)
-            unroll<UB * QT>([&](auto mi_) __attribute__((always_inline)) {
-                constexpr int mi = decltype(mi_)::value;
-                pv_mfma(dt % 3, dt, mi);
-                if constexpr (mi < 2) {
-                    if constexpr (dt + 2 < DT) read_v((dt + 2) % 3, vbase, dt + 2, mi);
-                } else if constexpr (dt < QT && mi - 2 < KT + 2) {
-                    max_piece(nxt_t{}, dt_, std::integral_constant<int, mi - 2>{});
+        if (p.causal ? (j * BKV + BKV - 1 > q0w) : (j * BKV + BKV > T)) {
+            const int last = (p.causal ? q0w + r32 : T - 1) - j * BKV - 4 * h;       // last key this query sees
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (32 * kt + 8 * (r / 4) + r % 4 > last) S[kt][r] = -__builtin_inff();
+        }
+        // the probabilities, and the lane's sum of them as rounded (the numerator uses the same), in fp32
+        u32x4_t pf[UB];
+        float lb = 0.f;
+        auto probabilities = [&]() __attribute__((always_inline)) {
+            const float mc = m * c;
+            const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3F803F80u);
+            lb = 0.f;
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 8 * (u & 1) + 2 * i;
+                    const f32x2_t pr = {exp2_fast(__builtin_fmaf(S[u / 2][r], c, -mc)), exp2_fast(__builtin_fmaf(S[u / 2][r + 1], c, -mc))};
+                    const bf16x2_t pb = __builtin_convertvector(pr, bf16x2_t);
+                    lb = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, lb, false);
+                    pf[u][i] = __builtin_bit_cast(uint32_t, pb);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            });
-        });
-        // the row-sum tile; behind its first MFMAs: how far the new maxima exceed the reference
-        unroll<UB * QT>([&](auto mi_) __attribute__((always_inline)) {
-            constexpr int mi = decltype(mi_)::value;
-            sum_mfma(mi / QT, mi % QT);
-            if constexpr (mi < QT) {
-                const float g = (mx[mi] - m[mi]) * c;
-                gmax = mi == 0 ? g : fmaxf(gmax, g);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        });
+        };
+        bool raise = j == 0;
+        if (!raise) {
+            probabilities();
+            raise = __builtin_amdgcn_ballot_w64(!(lb <= kMaxSum)) != 0;
+        }
+        if (raise) {
+            float mx = fmaxf(S[0][0], S[0][1]);
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) mx = fmaxf(fmaxf(mx, S[kt][r]), S[kt][r + 1]);
+            mx = max_with_lane_xor32(mx);
+            const float m_new = fmaxf(m, mx);
+            const float alpha = exp2_fast((m - m_new) * c);
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+            probabilities();
+        }
+        l += lb;
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, __builtin_shufflevector(vf[u][dt][0], vf[u][dt][1], 0, 1, 2, 3, 4, 5, 6, 7)),
+                                                                __builtin_bit_cast(bf16x8_t, pf[u]), o[dt], 0, 0, 0);
     };
-
-    // first block: S^T(0), its mask and maxima, nothing to overlap with yet
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (nbw > 0) {
-        read_k(0, 0);
-        read_k(0, 1);
-        unroll<NS>([&](auto i_) __attribute__((always_inline)) {
-            s_mfma(0, 0, decltype(i_)::value);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        nops();
-        if (needs_mask(0)) mask_block(std::integral_constant<int, 0>{}, 0);
-        unroll<QT>([&](auto qt_) __attribute__((always_inline)) { max_of(std::integral_constant<int, 0>{}, qt_); });
-    }
     for (int j = 0; j < nb; j += 2) {
-        step(std::integral_constant<int, 0>{}, j);
-        if (j + 1 < nb) step(std::integral_constant<int, 1>{}, j + 1);
+        step(j, 0);
+        if (j + 1 < nb) step(j + 1, 1);
     }
     if (nbw == 0) return;
-    nops();                                                      // the last MFMAs have written O
-    // (new values for the compiler, so that it cannot read the registers before the wait states)
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        asm volatile("" : "+a"(lsum[qt]));
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) asm volatile("" : "+a"(o[dt][qt]));
-    }
 
-    // ---- normalise and store: lane holds d = 16 dt + 4 q4 .. + 3 of query q0w + 16 qt + r16 ------
-    __bf16 *obase = p.O + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh;
+    // ---- normalise and store: lane holds d = 32 dt + 8 g + 4 h + 0..3 (g = 0..3) of query q0w + r32; the two
+    // lanes of a query trade halves, after which a lane holds 8 consecutive d -----------------------
+    const float inv = 1.0f / sum_with_lane_xor32(l);
+    const int query = q0w + r32;
+    __bf16 *row = p.O + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + (int64_t)query * p.o_st + 8 * h;
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const float inv = 1.0f / lsum[qt][0];
-        const int query = q0w + 16 * qt + r16;
-        if (query < T) {
-            __bf16 *row = obase + (int64_t)query * p.o_st + 4 * q4;
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const f32x2_t a = {o[dt][qt][0] * inv, o[dt][qt][1] * inv}, bq = {o[dt][qt][2] * inv, o[dt][qt][3] * inv};
-                u32x2_t w;
-                w.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2_t));
-                w.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(bq, bf16x2_t));
-                *(u32x2_t *)(row + 16 * dt) = w;
-            }
+        for (int g = 0; g < 4; g += 2) {
+            uint32_t w[2][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int r = 4 * (g + e) + 2 * i;
+                    const f32x2_t v = {o[dt][r] * inv, o[dt][r + 1] * inv};
+                    w[e][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+                }
+            const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+            if (query < T) *(u32x4_by8 *)(row + 32 * dt + 8 * g) = u32x4_t{(uint32_t)lo[0], (uint32_t)hi[0], (uint32_t)lo[1], (uint32_t)hi[1]};
         }
-    }
+#else
+    (void)p;
+#endif
 }
 
 }  // namespace attn
