@@ -114,6 +114,7 @@ struct Plan {
     int split = 1;
     int group_m = 4;
     bool listed = false;   // from the registry or the table
+    bool loaded = false;   // from a registry file read at run time
 };
 
 // Estimated microseconds of a launch, for shapes the registry does not list.  A 64-deep K step of a
@@ -156,7 +157,7 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
     {
         std::lock_guard<std::mutex> lock(g_registry_mutex);
         for (const TableRow &r : g_registry)
-            if (matches(r)) { take(r); return pl; }
+            if (matches(r)) { take(r); pl.loaded = true; return pl; }
     }
     for (const TableRow *r = g_table; r->cfg >= 0; ++r)
         if (matches(*r)) { take(*r); return pl; }
@@ -257,6 +258,40 @@ static TailPlan tail_plan(const ConfigDesc &c, int64_t tiles, int64_t K, int g)
     return t;
 }
 
+// Column split: a launch whose last round of work-groups is partly filled runs as two, the columns of the full rounds
+// on the plan's configuration and the rest on one that spreads them over the whole chip.
+struct ColumnSplit {
+    int64_t n1 = 0;        // output columns of the first launch (0: no split), a multiple of its tiles' width
+    int cfg = -1;          // configuration of the second
+};
+
+// Where: the model has to see 6.5 % after 3 us for the second launch.  Measured on 30 shapes of 2 to 4 rounds (us, one
+// launch -> two): 1024 x 50257 x 768 (3.08 rounds) 128.9 -> 102.4, 5018 x 6648 x 800 (2.03) 79.4 -> 70.8,
+// 7268 x 2536 x 2552 (1.59) 118.4 -> 109.2, 5053 x 7608 x 6080 (2.34) 364.7 -> 346.0, 2048 x 28672 x 4096 (3.50) 368.5 ->
+// 350.8; with less in it for the model the two are level or one launch is faster: 4980 x 8032 x 2936 (2.50) 221 -> 227,
+// 5421 x 7864 x 1744 (2.66) 143 -> 146.  Configurations of which two work-groups share a compute unit fill a last round better
+// than the model knows (8192 x 2304 x 768, 1.50 rounds: 31.2 -> 33.3) and are left alone; of those only the smallest tile
+// takes a rest.
+static ColumnSplit column_split(const Plan &pl, int64_t M, int64_t nout, int64_t K, int trans_b, bool gated)
+{
+    ColumnSplit sp;
+    const ConfigDesc &c = g_configs[pl.cfg];
+    if (wgs_per_cu(c) != 1) return sp;
+    const int64_t bn_out = gated ? c.bn / 2 : c.bn;
+    const int64_t tiles_m = (M + c.bm - 1) / c.bm, tiles = tiles_m * ((nout + bn_out - 1) / bn_out);
+    const int64_t n1 = (tiles - 1) / kNumCU * kNumCU / tiles_m * bn_out;
+    if (n1 <= 0 || n1 >= nout) return sp;
+    double rest = 0;
+    for (int i = 0; i < kNumConfigs; ++i) {
+        const ConfigDesc &d = g_configs[i];
+        if ((gated && !d.gate_capable()) || !d.serves(trans_b) || (wgs_per_cu(d) > 1 && d.bm * d.bn > 64 * 64)) continue;
+        const double t = model_time(d, 1, M, nout - n1, K, gated, 1);
+        if (sp.cfg < 0 || t < rest) { rest = t; sp.cfg = i; }
+    }
+    if (sp.cfg >= 0 && model_time(c, 1, M, n1, K, gated, 1) + rest + 3.0 <= 0.935 * model_time(c, 1, M, nout, K, gated, 1)) sp.n1 = n1;
+    return sp;
+}
+
 // ---- the one launch path every entry point goes through ----------------------------------------
 
 static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_table_split,
@@ -308,6 +343,28 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
         if (pl.split < 1) pl.split = 1;
         if (pl.split == 1) { c_f32 = true; out_f32 = false; }
         else if (q.batch != 1 || !allow_table_split) return FACT_ERR_UNSUPPORTED;
+    }
+
+    // (a registry file's choice, and persistent launches where they are asked for, are taken as they stand)
+    if (cfg_id < 0 && pl.cfg >= 0 && !pl.loaded && (split == 0 || split == 1) && group_m <= 0 && pl.split == 1 && tail_g <= 1 && q.batch == 1 &&
+        q.M > 64 && !g_persistent.load(std::memory_order_relaxed)) {
+        const ColumnSplit sp = column_split(pl, q.M, nout, q.K, q.trans_b, gated);
+        if (sp.n1 > 0) {
+            const int64_t n2 = nout - sp.n1;
+            const uint16_t *B = (const uint16_t *)q.B, *up = gated ? (q.B_up ? (const uint16_t *)q.B_up : B + nout * q.ldb) : nullptr;
+            const int64_t skip = q.trans_b ? sp.n1 * q.ldb : sp.n1;
+            Problem first = q, rest = q;
+            first.N = gated ? 2 * sp.n1 : sp.n1;
+            first.B_up = up;
+            rest.N = gated ? 2 * n2 : n2;
+            rest.B = B + skip;
+            rest.B_up = up ? up + skip : nullptr;
+            rest.C = (char *)q.C + sp.n1 * (q.ep.out_f32 ? 4 : 2);
+            if (q.ep.bias) rest.ep.bias = (const uint16_t *)q.ep.bias + sp.n1;
+            if (q.ep.residual) rest.ep.residual = (const uint16_t *)q.ep.residual + sp.n1;
+            rc = run(first, pl.cfg, 1, pl.group_m, allow_table_split, ws, ws_bytes, stream);
+            return rc != FACT_OK ? rc : run(rest, sp.cfg, 1, 0, allow_table_split, ws, ws_bytes, stream);
+        }
     }
 
     GemmArgs a;
