@@ -166,6 +166,10 @@ def _addr(x):
 def _stream(s):
     if s is None:
         import torch
+        # the current stream's handle itself: current_stream() builds a Stream object around it, 2.9 us of the 7.9 that a
+        # 512 x 512 x 512 call took to issue (0.2 this way; the call is then bound by the GPU, 5.4 us)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return int(torch.cuda.current_stream().cuda_stream)
     if isinstance(s, int):
         return s
