@@ -369,7 +369,7 @@ def time_blocks(steps=20, warmup=10):
         flops = 2.0 * Tt * d * (nq + 2 * nkv) + 2.0 * Tt * nq * d + 2.0 * Tt * d * dff * (3 if desc["act_gated"] else 2) \
             + 4.0 * B * desc["q_heads"] * desc["head_dim"] * (T * (T + 1) / 2.0)
         out[name] = {"ms": round(ms, 4), "tflops": round(flops / ms / 1e9, 1), "pct_mfma_peak": round(100 * flops / ms / 1e9 / PEAK_BF16_TFLOPS, 2),
-                     "launches": 10 if desc["rope"] else 9, "scratch_MB": round(need / 2 ** 20, 1)}
+                     "scratch_MB": round(need / 2 ** 20, 1)}
         del scratch, Xd, Y, b
     return out
 
