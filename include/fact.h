@@ -384,6 +384,27 @@ int fact_tail_timeouts(const void *ws, void *stream, int *gave_up);
  * every kernel still runs to its end.  Process-wide, applies to launches made after the call. */
 void fact_test_tail_poll_budget(int polls);
 
+/* Test hook (host logic only: nothing is launched, no pointer is followed, no GPU is needed): the kernels
+ * that fact_gemm_ex would launch for these arguments, in order.  ws == NULL: as the entry points
+ * without a workspace choose (fact_gemm, fact_gemm_batched, both with split_k = 1).  Writes at most
+ * max_launches kinds (FACT_ROUTE_*), tile configurations (-1 where none) and contraction columns
+ * (arrays, each may be NULL) and returns the number of launches, or the status the call would return. */
+enum {
+    FACT_ROUTE_TILES = 0,         /* the tile kernel */
+    FACT_ROUTE_TAIL = 1,          /* the tile kernel, its last round split along K */
+    FACT_ROUTE_PERSISTENT = 2,    /* the tile kernel's persistent form */
+    FACT_ROUTE_REDUCE = 3,        /* the reduction pass behind a split along K */
+    FACT_ROUTE_SKINNY = 4,        /* the kernel for few rows */
+    FACT_ROUTE_RAGGED = 5,        /* the kernel for rows of any alignment */
+    FACT_ROUTE_GUARDED = 6        /* one thread per element */
+};
+int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
+                    const void *A, int64_t lda, int64_t stride_a,
+                    const void *B, int64_t ldb, int64_t stride_b, int trans_b,
+                    void *C, int64_t ldc, int64_t stride_c,
+                    const fact_epilogue *ep, int config_id, int split_k, int group_m,
+                    void *ws, size_t ws_bytes, int max_launches, int *kinds, int *configs, int64_t *columns);
+
 /*
  * Persistent launches (the grid-level schedule of Section 4.2 Action 2 next to "Data Parallel" and
  * "Split-K"; Section 5.2.3 describes the persistent Stream-K form).  With mode 1, a launch with K

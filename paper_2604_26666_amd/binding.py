@@ -138,6 +138,8 @@ def lib():
         L.fact_tail_timeouts.restype = _int
         L.fact_test_tail_poll_budget.argtypes = [_int]
         L.fact_test_tail_poll_budget.restype = None
+        L.fact_test_route.argtypes = L.fact_gemm_ex.argtypes[:-1] + [_int, ip, ip, i64p]
+        L.fact_test_route.restype = _int
         L.fact_tune_persistent.argtypes = [_int]
         L.fact_tune_persistent.restype = _int
         L.fact_persistent_grid.argtypes = [_i64, _i64, _i64, _i64, _int, _int, _int]
@@ -304,6 +306,19 @@ def fact_tail_timeouts(ws, stream=None):
 
 def fact_test_tail_poll_budget(polls):
     lib().fact_test_tail_poll_budget(int(polls))
+
+
+ROUTES = ("tiles", "tail", "persistent", "reduce", "skinny", "ragged", "guarded")     # FACT_ROUTE_*
+
+
+def fact_test_route(batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, C, ldc, stride_c, ep,
+                    config_id=-1, split_k=1, group_m=0, ws=None, ws_bytes=0):
+    """[(kernel, tile configuration, columns), ...] of the launches that fact_gemm_ex would make (ws None: fact_gemm and
+    fact_gemm_batched), or the negative status it would return."""
+    k, c, n = (_int * 4)(), (_int * 4)(), (_i64 * 4)()
+    r = lib().fact_test_route(batch, M, N, K, _addr(A), lda, stride_a, _addr(B), ldb, stride_b, int(trans_b), _addr(C), ldc, stride_c,
+                              _ep(ep), int(config_id), int(split_k), int(group_m), _addr(ws), int(ws_bytes), 4, k, c, n)
+    return r if r < 0 else [(ROUTES[k[i]], c[i], n[i]) for i in range(r)]
 
 
 def fact_tune_persistent(mode):

@@ -294,8 +294,17 @@ static ColumnSplit column_split(const Plan &pl, int64_t M, int64_t nout, int64_t
 
 // ---- the one launch path every entry point goes through ----------------------------------------
 
+// How a call runs, for fact_test_route: with one of these run() notes each launch in place of making it.
+struct Route {
+    static constexpr int kMax = 4;
+    int launches = 0;
+    int kind[kMax], cfg[kMax];
+    int64_t columns[kMax];           // contraction columns of the launch
+    int add(int k, int c, int64_t n) { if (launches < kMax) { kind[launches] = k; cfg[launches] = c; columns[launches] = n; } ++launches; return FACT_OK; }
+};
+
 static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_table_split,
-               void *ws, size_t ws_bytes, hipStream_t stream)
+               void *ws, size_t ws_bytes, hipStream_t stream, Route *route = nullptr)
 {
     int rc = validate(q);
     if (rc != FACT_OK) return rc;
@@ -362,8 +371,8 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
             rest.C = (char *)q.C + sp.n1 * (q.ep.out_f32 ? 4 : 2);
             if (q.ep.bias) rest.ep.bias = (const uint16_t *)q.ep.bias + sp.n1;
             if (q.ep.residual) rest.ep.residual = (const uint16_t *)q.ep.residual + sp.n1;
-            rc = run(first, pl.cfg, 1, pl.group_m, allow_table_split, ws, ws_bytes, stream);
-            return rc != FACT_OK ? rc : run(rest, sp.cfg, 1, 0, allow_table_split, ws, ws_bytes, stream);
+            rc = run(first, pl.cfg, 1, pl.group_m, allow_table_split, ws, ws_bytes, stream, route);
+            return rc != FACT_OK ? rc : run(rest, sp.cfg, 1, 0, allow_table_split, ws, ws_bytes, stream, route);
         }
     }
 
@@ -396,9 +405,11 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     hipError_t e;
     if (pl.cfg < 0) {
         if (cfg_id != FACT_CONFIG_GUARDED && ragged_serves(a, q.trans_b != 0)) {
+            if (route) return route->add(FACT_ROUTE_RAGGED, -1, q.N);
             e = launch_ragged_gemm(a, q.trans_b != 0, (int)q.batch, stream);
             return e == hipSuccess ? FACT_OK : hip_fail(e, "ragged gemm launch");
         }
+        if (route) return route->add(FACT_ROUTE_GUARDED, -1, q.N);
         e = launch_fallback_gemm(a, q.trans_b != 0, (int)q.batch, stream);
         return e == hipSuccess ? FACT_OK : hip_fail(e, "fallback gemm launch");
     }
@@ -457,6 +468,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
             a.out_f32 = 0; a.c_f32 = 1;
         }
         a.splits = 1; a.P = nullptr;
+        if (route) return route->add(FACT_ROUTE_SKINNY, -1, q.N);
         e = launch_skinny_gemm(a, (int)q.batch, stream);
         return e == hipSuccess ? FACT_OK : hip_fail(e, "skinny gemm launch");
     }
@@ -502,6 +514,10 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     }
     // (the kernel numbers (K range or batch entry, tile) pairs with 32-bit integers)
     if (tiles_m * tiles_n * (a.splits > 1 ? (int64_t)a.splits : q.batch) > INT32_MAX / 2) return FACT_ERR_DIM;
+    if (route) {
+        route->add(a.tail_g > 1 ? FACT_ROUTE_TAIL : a.persist_items > 0 ? FACT_ROUTE_PERSISTENT : FACT_ROUTE_TILES, pl.cfg, q.N);
+        return a.splits > 1 || out_f32 ? route->add(FACT_ROUTE_REDUCE, -1, q.N) : FACT_OK;
+    }
     e = c.launch(a, q.trans_b != 0, a.splits > 1 ? a.splits : (int)q.batch, stream);
     if (e != hipSuccess) return hip_fail(e, "gemm launch");
     if (a.splits > 1 || out_f32) {
@@ -617,6 +633,25 @@ int fact_gemm_ex(int64_t batch, int64_t M, int64_t N, int64_t K,
 {
     Problem q{batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, nullptr, C, ldc, stride_c, ep_or_none(ep)};
     return run(q, config_id, split_k, group_m, true, ws, ws_bytes, (hipStream_t)stream);
+}
+
+int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
+                    const void *A, int64_t lda, int64_t stride_a,
+                    const void *B, int64_t ldb, int64_t stride_b, int trans_b,
+                    void *C, int64_t ldc, int64_t stride_c,
+                    const fact_epilogue *ep, int config_id, int split_k, int group_m,
+                    void *ws, size_t ws_bytes, int max_launches, int *kinds, int *configs, int64_t *columns)
+{
+    Problem q{batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, nullptr, C, ldc, stride_c, ep_or_none(ep)};
+    Route route;
+    const int rc = run(q, config_id, split_k, group_m, ws != nullptr, ws, ws_bytes, nullptr, &route);
+    if (rc != FACT_OK) return rc;
+    for (int i = 0; i < route.launches && i < max_launches && i < Route::kMax; ++i) {
+        if (kinds) kinds[i] = route.kind[i];
+        if (configs) configs[i] = route.cfg[i];
+        if (columns) columns[i] = route.columns[i];
+    }
+    return route.launches;
 }
 
 size_t fact_block_mlp_workspace_bytes(int64_t T, int64_t d_model, int64_t d_ff, int act)

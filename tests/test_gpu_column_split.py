@@ -14,6 +14,12 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1024, 50257, 768, 1), (5018, 6648, 800, 0), (7268, 2536, 2552, 1)]
 
 
+def assert_two_launches(M, N, K, nk, act=fact.ACT_NONE):
+    p, nout = 1 << 16, N // 2 if act == fact.ACT_SILU_GATE else N
+    r = fact.fact_test_route(1, M, N, K, p, K, 0, p, K if nk else N, 0, nk, p, nout, 0, fact.Epilogue(act=act))
+    assert [x[0] for x in r] == ["tiles", "tiles"], r
+
+
 def tensor(shape, dt, seed, std=1.0):
     g = torch.Generator(device="cuda").manual_seed(seed)
     return (torch.randn(shape, generator=g, device="cuda") * std).to(dt)
@@ -23,6 +29,7 @@ def tensor(shape, dt, seed, std=1.0):
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_same_bits_as_one_launch(shape, f16, f32):
     M, N, K, nk = shape
+    assert_two_launches(M, N, K, nk)
     dt, odt = (torch.float16 if f16 else torch.bfloat16), (torch.float32 if f32 else torch.float16 if f16 else torch.bfloat16)
     A, B = tensor((M, K), dt, 1), tensor((N, K) if nk else (K, N), dt, 2, K ** -0.5)
     bias, res = tensor((N,), dt, 3), tensor((M, N), dt, 4)
@@ -43,6 +50,7 @@ def test_same_bits_as_one_launch(shape, f16, f32):
 @pytest.mark.parametrize("halves", [False, True])
 def test_gated_rest_takes_both_weight_matrices_at_an_offset(halves):
     T, d, dff = 2048, 4096, 14336
+    assert_two_launches(T, 2 * dff, d, 1, fact.ACT_SILU_GATE)
     X, W = tensor((T, d), torch.bfloat16, 5), tensor((2 * dff, d), torch.bfloat16, 6, 0.02)
     ep = fact.Epilogue(act=fact.ACT_SILU_GATE)
     H, D = (torch.full((T, dff), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
@@ -61,6 +69,7 @@ def test_gated_rest_takes_both_weight_matrices_at_an_offset(halves):
 
 def test_against_the_oracle_around_the_seam():
     M, N, K = 1024, 50257, 768
+    assert_two_launches(M, N, K, 1)
     A, B = wl.small_int((M, K), -4, 4, "cs.A"), wl.small_int((N, K), -4, 4, "cs.B")
     Ad, Bd = A.cuda(), B.cuda()
     C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
