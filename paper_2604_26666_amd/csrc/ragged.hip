@@ -313,8 +313,14 @@ static hipError_t launch_tile(GemmArgs a, bool trans_b, int grid_z, hipStream_t 
     return trans_b ? launch_one<BM, BN, WGM, WGN, KW, true, false>(a, grid, stream) : launch_one<BM, BN, WGM, WGN, KW, false, false>(a, grid, stream);
 }
 
-// A row (or a K-row of a [K][N] operand) holds at least one 16-byte piece; shorter ones stay with the guarded kernel.
-bool ragged_serves(const GemmArgs &a, bool trans_b) { return a.K >= 8 && (trans_b || a.N >= 8); }
+// Operands whose rows hold at least one 16-byte piece; shorter ones stay with the guarded kernel.  So do sizes of which the
+// edge of a last tile, or the step that a last K group loads ahead (3 x 4 x 64 past K), would leave the kernel's 32-bit
+// indexes: a wrapped one is negative, which its clamps take for inside.
+bool ragged_serves(const GemmArgs &a, bool trans_b)
+{
+    constexpr int kLast = INT32_MAX - 4096;
+    return a.K >= 8 && (trans_b || a.N >= 8) && a.M <= kLast && a.N <= kLast && a.K <= kLast;
+}
 
 // The largest tile that still gives most compute units a work-group, and several K groups per work-group where
 // K is long enough to share: what is short here is loads in flight, not matrix cores.  Measured (us, one launch,

@@ -43,3 +43,16 @@ def test_column_split(M, N, K, nk, act):
 
 def test_a_call_that_is_refused_has_no_route():
     assert route(0, 8, 8, 1) == -2 and route(8, 8, 8, 1, cfg=99) == -7 and route(8, 8, 8, 1, a=None) == -1
+
+
+# 32-bit indexes: a step loaded ahead, or a tile's edge, must not pass 2^31 (the guarded kernel counts K one by one)
+@pytest.mark.parametrize("nk", [0, 1])
+def test_ragged_kernel_keeps_its_indexes_in_range(nk):
+    top, last = 2 ** 31 - 1, 2 ** 31 - 1 - 4096
+    for K in (top, top - 63, top - 960, last + 1):
+        assert kernels(1, 8, K, nk) == ["guarded"], K
+    # groups x steps ahead x depth, all below the margin, and a tile's edge
+    assert 3 * 4 * 64 + 4 * 64 + 64 < 4096 and kernels(1, 8, last, nk) == ["ragged"]
+    for K in (9, 999, 2 ** 21 + 8):               # short rows, odd ones, and aligned ones past the tile kernel's leading dimensions
+        assert kernels(3, 9, K, nk) == ["ragged"], K
+    assert kernels(last + 1, 9, 9, nk) == ["guarded"] and kernels(1, last + 2, 9, nk) == ["guarded"] and kernels(1, last, 9, nk) == ["ragged"]
