@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(256) fallback_gemm_kernel(const GemmArgs p)
 hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream)
 {
     const int nout = args.act == ACT_SILU_GATE ? args.N / 2 : args.N;
-    const int64_t blocks = (int64_t)((nout + 15) / 16) * ((args.M + 15) / 16);
+    const int64_t blocks = ((int64_t)nout + 15) / 16 * (((int64_t)args.M + 15) / 16);
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
     dim3 grid((unsigned)blocks, 1, (unsigned)grid_z);
     if (trans_b)

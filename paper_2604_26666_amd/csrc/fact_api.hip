@@ -70,7 +70,8 @@ static bool fast_dims_ok(int64_t M, int64_t N, int64_t K, int trans_b)
 {
     if (K % 8) return false;
     if (!trans_b && N % 8) return false;
-    if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX - 64) return false;
+    // (the kernel's rows and columns of a tile's edge, and k of a step ahead, are 32-bit: a wrapped edge would count as inside)
+    if (M > INT32_MAX - 256 || N > INT32_MAX - 256 || K > INT32_MAX - 64) return false;
     return true;
 }
 

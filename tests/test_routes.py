@@ -56,3 +56,12 @@ def test_ragged_kernel_keeps_its_indexes_in_range(nk):
     for K in (9, 999, 2 ** 21 + 8):               # short rows, odd ones, and aligned ones past the tile kernel's leading dimensions
         assert kernels(3, 9, K, nk) == ["ragged"], K
     assert kernels(last + 1, 9, 9, nk) == ["guarded"] and kernels(1, last + 2, 9, nk) == ["guarded"] and kernels(1, last, 9, nk) == ["ragged"]
+
+
+def test_tile_kernel_keeps_its_edges_in_range():
+    # a last tile of up to 256 rows or columns must not reach past 2^31
+    edge = 2 ** 31 - 1 - 256
+    assert kernels(edge, 8, 8, 0) == ["tiles"] and kernels(72, edge, 8, 1) == ["tiles"]
+    for over in (edge + 1, 2 ** 31 - 1):
+        assert kernels(over, 8, 8, 0) == ["guarded"] and kernels(72, over, 8, 1) == ["guarded"]
+        assert route(over, 8, 8, 0, cfg=0) == -7
