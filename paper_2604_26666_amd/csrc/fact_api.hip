@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -293,6 +294,42 @@ static ColumnSplit column_split(const Plan &pl, int64_t M, int64_t nout, int64_t
     return sp;
 }
 
+// Few rows against [N][K] weights: the skinny kernel, or the plan?  model_time prices full chips; with at most 64 rows a
+// launch of the tile kernel is one or two rounds of work-groups that each wait for their loads: a K step is a load's latency
+// or 60 GB/s per compute unit, the weights come at 5.0 TB/s (4.7 where their rows are no whole lines), and a split along K adds a launch of 5 us and its partial sums.
+static double few_rows_us(const ConfigDesc &c, int64_t batch, int64_t M, int64_t N, int64_t nout, int64_t K, bool gated, int splits, bool whole_lines)
+{
+    const int64_t bn_out = gated ? c.bn / 2 : c.bn, tiles_n = (nout + bn_out - 1) / bn_out;
+    const double tiles = (double)((M + c.bm - 1) / c.bm) * tiles_n * batch * splits;
+    const int fit = wgs_per_cu(c);
+    const double rounds = tiles > 256.0 * fit ? tiles / (256.0 * fit) : 1.0;
+    const double sharing = tiles < 256.0 ? 1.0 : tiles / 256.0 < fit ? tiles / 256.0 : fit;
+    const double bytes = 128.0 * ((M < c.bm ? M : c.bm) + (N < c.bn ? N : c.bn)), step = sharing * bytes / 60e3;
+    const double latency = c.bm == 64 ? 0.2 : 0.5 * std::sqrt((double)c.bm * c.bn / 65536.0);
+    const int64_t ksteps = ((K + splits - 1) / splits + 63) / 64;
+    const double chain = 3.2 + 0.0086 * tiles + rounds * (double)ksteps * (step > latency ? step : latency);
+    const double memory = 3.2 + (double)batch * K * 2.0 * (N + (double)(tiles_n < 8 ? tiles_n : 8) * M) / (whole_lines ? 5.0e6 : 4.7e6);
+    return (chain > memory ? chain : memory) + (splits > 1 ? 5.0 + (double)M * N * 8.0 * splits / 1e7 : 0.0);
+}
+
+// Where the skinny kernel's estimate is below the plan's.  Both estimates were fitted to 1100 calls of 1 to 64 rows, 16 to
+// 36000 columns, K of 64 to 131072 and batches up to 128, with and without a workspace, operands from HBM; the choice costs
+// 0.4 % over the better kernel of every call on average; in 29 of them the one it takes is more than 3 % slower, by 25 % at most
+// but for three (45 to 52 %).  Some of the calls (us, plan -> skinny; * the plan is kept):
+//    M x N x K:  16 x 4096 x 14336  59.6 -> 25.6     16 x 768 x 3072  9.5 -> 6.3       64 x 3072 x 768  5.3 -> 4.4
+//                16 x 16384 x 8192  62.6 -> 52.0     16 x 16384 x 256  5.4 -> 6.6 *    32 x 16384 x 1024  9.6 -> 11.2 *
+//    with a workspace, so that the plan may split K:
+//                16 x 64 x 8192  11.7 -> 10.3        16 x 64 x 32768  12.0 -> 34.9 *   64 x 64 x 131072  16.6 -> 315 *
+//    without:    16 x 64 x 8192  23.7 -> 10.4        64 x 64 x 32768  134 -> 51        64 x 64 x 131072  559 -> 318
+//    batches:    8 x (16 x 256 x 1024)  6.7 -> 4.1   128 x (32 x 64 x 4096)  24.8 -> 37.2 *   128 x (64 x 512 x 1024)  33.1 -> 75.4 *
+static bool skinny_serves(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c)
+{
+    if (!skinny_takes(a, trans_b)) return false;
+    const bool gated = a.act == FACT_ACT_SILU_GATE;
+    const bool lines = ((uintptr_t)a.B & 127u) == 0 && a.ldb % 64 == 0 && (batch == 1 || a.stride_b % 64 == 0);
+    return skinny_us(a, batch, lines) < few_rows_us(c, batch, a.M, a.N, gated ? a.N / 2 : a.N, a.K, gated, a.splits, lines);
+}
+
 // ---- the one launch path every entry point goes through ----------------------------------------
 
 // How a call runs, for fact_test_route: with one of these run() notes each launch in place of making it.
@@ -456,9 +493,9 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
         }
     }
     // Few rows against [N][K] weights, nothing about the launch asked for by the caller or the registry: the skinny
-    // kernel (whose rule says where it wins).  It needs no workspace; what the plan would have needed has been
+    // kernel where it is the faster one.  It needs no workspace; what the plan would have needed has been
     // checked above all the same.
-    if (cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.listed && tail_g <= 1 && skinny_serves(a, q.trans_b != 0, a.splits > 1)) {
+    if (cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.listed && tail_g <= 1 && skinny_serves(a, q.trans_b != 0, q.batch, c)) {
         if (out_f32) {
             if (a.splits <= 1) {
                 const size_t need = (size_t)q.M * (size_t)q.N * sizeof(float);

@@ -27,8 +27,10 @@ struct ConfigDesc {
 hipError_t launch_splitk_reduce(const GemmArgs &args, hipStream_t stream);
 hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
 
-// GEMM of few rows against B as [N][K] (skinny.hip).
-bool skinny_serves(const GemmArgs &args, bool trans_b, bool plan_splits);
+// GEMM of few rows against B as [N][K] (skinny.hip): the calls it can take, and its estimated microseconds
+// (whole_lines: every row of B begins on a 128-byte line).
+bool skinny_takes(const GemmArgs &args, bool trans_b);
+double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
 hipError_t launch_skinny_gemm(const GemmArgs &args, int grid_z, hipStream_t stream);
 
 // GEMM with operands of any alignment and size on the matrix cores (ragged.hip).

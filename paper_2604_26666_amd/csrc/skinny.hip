@@ -202,30 +202,46 @@ static hipError_t launch_tile(const GemmArgs &a, int grid_z, hipStream_t stream)
     return a.f16 ? launch_skinny_as<MT, NT, NW, S, true>(a, grid_z, stream) : launch_skinny_as<MT, NT, NW, S, false>(a, grid_z, stream);
 }
 
-// Which calls: measured against the main kernel's best plan (us, operands from HBM; M x N x K: main kernel -> this one):
-//    1 x 4096 x 14336 58.9 -> 22.4   16: 59.6 -> 25.6   32: 61.7 -> 33.7   64: 73.0 -> 43.6   (22.4 us = 5.2 TB/s)
-//    1 x 4096 x  4096 15.7 ->  8.5   16: 17.3 ->  9.7   32: 17.9 -> 11.7   64: 19.4 -> 15.0
-//    1 x 3072 x   768  5.4 ->  3.5   16:  5.4 ->  4.0   32:  5.6 ->  4.4   64:  5.3 ->  4.4
-//    1 x  768 x  3072  9.5 ->  5.4   16:  9.5 ->  6.3   32:  9.7 ->  7.8   64:  9.3 -> 10.9 (13 where the plan splits K)
-//    1 x 8192 x  1024  7.0 ->  5.9   16:  7.1 ->  5.9   32:  7.3 ->  6.3   64:  7.3 ->  7.6
-// Up to 32 rows it always wins.  Up to 64 every work-group reads four times its weights' bytes of A, which pays where
-// the main kernel has few work-groups (columns) or two launches.  Gated calls (two weight matrices per column) are level
-// at 32 rows: 2 x 14336 x 4096 46 -> 42-45 us at 1-16 rows, 59 -> 57 us at 32.
-bool skinny_serves(const GemmArgs &a, bool trans_b, bool plan_splits)
+// One 16-column tile per work-group (two for gated calls, one of each half, and for many columns of 17-32 rows: half the
+// reads of A); four waves and three or four stages, so that two or three work-groups share a compute unit.  Up to 64 rows
+// eight waves and all of the LDS.
+struct Tile { int mt, nt, waves, stages; };
+static Tile tile_of(const GemmArgs &a)
 {
-    if (!trans_b || a.M > 64) return false;
-    if (a.M <= 32) return true;
-    return a.act != ACT_SILU_GATE && a.N <= 6144 && (a.K <= 1024 || a.N >= 2048 || plan_splits);
+    if (a.act == ACT_SILU_GATE) return a.M <= 16 ? Tile{1, 2, 4, 3} : Tile{2, 2, 4, 4};
+    if (a.M <= 16) return {1, 1, 4, 4};
+    if (a.M <= 32) return a.N > 6144 ? Tile{2, 2, 4, 4} : Tile{2, 1, 4, 3};
+    return {4, 1, 8, 2};
 }
 
-// One 16-column tile per work-group (two for gated calls, one of each half, and for many columns of 17-32 rows: half the
-// reads of A); four waves and three or four stages, so that two or three work-groups share a compute unit.
+bool skinny_takes(const GemmArgs &a, bool trans_b) { return trans_b && a.M <= (a.act == ACT_SILU_GATE ? 32 : 64); }
+
+// Estimated microseconds: a work-group's K steps one after the other, each at least a load's latency and at most 60 GB/s per
+// compute unit, in as many rounds as the work-groups need; a start and an end per round, which nothing covers where
+// only one work-group fits a compute unit; never faster than HBM delivers the weights, and A to each XCD.  Rows of weights that
+// are no whole 128-byte lines cost more: each 128-byte piece lies on two lines (16 x 4096 x 14336 24.0 us, K = 14344 32.6).
+double skinny_us(const GemmArgs &a, int64_t batch, bool whole_lines)
+{
+    const Tile t = tile_of(a);
+    const bool gated = a.act == ACT_SILU_GATE;
+    const int nout = gated ? a.N / 2 : a.N, cols = 16 * (gated ? t.nt / 2 : t.nt);
+    const double wx = (double)((nout + (int64_t)cols - 1) / cols), wgs = wx * ((a.M + 16 * t.mt - 1) / (16 * t.mt)) * (double)batch;
+    const int fit = 160 * 1024 / (t.waves * t.stages * (t.mt + t.nt) * 2048), blocks = (int)(((int64_t)a.K + 63) / 64);
+    const double rounds = wgs > 256.0 * fit ? wgs / (256.0 * fit) : 1.0;
+    const double sharing = wgs < 256.0 ? 1.0 : wgs / 256.0 < fit ? wgs / 256.0 : fit;
+    const double rows_a = 0.5 * (16 * t.mt + (a.M < 16 * t.mt ? a.M : 16 * t.mt));       // (rows past M are not fetched, but their zeros are written)
+    const double bytes = 128.0 * t.waves * (rows_a + 16 * t.nt), step = sharing * bytes / (whole_lines ? 60e3 : 50e3);
+    const double chain = 1.4 + 0.004 * wgs + rounds * (0.8 + (blocks + t.waves - 1) / t.waves * (step > 0.2 ? step : 0.2)) + (fit == 1 ? 2.0 * (rounds - 1.0) : 0.0);
+    const double memory = 1.4 + (double)batch * a.K * 2.0 * (a.N + (wx < 8.0 ? wx : 8.0) * a.M) / (whole_lines ? 5.4e6 : 4.7e6);
+    return chain > memory ? chain : memory;
+}
+
 hipError_t launch_skinny_gemm(const GemmArgs &a, int grid_z, hipStream_t stream)
 {
-    if (a.act == ACT_SILU_GATE) return a.M <= 16 ? launch_tile<1, 2, 4, 3>(a, grid_z, stream) : launch_tile<2, 2, 4, 4>(a, grid_z, stream);
-    if (a.M <= 16) return launch_tile<1, 1, 4, 4>(a, grid_z, stream);
-    if (a.M <= 32) return a.N > 6144 ? launch_tile<2, 2, 4, 4>(a, grid_z, stream) : launch_tile<2, 1, 4, 3>(a, grid_z, stream);
-    return launch_tile<4, 1, 8, 2>(a, grid_z, stream);
+    const Tile t = tile_of(a);
+    if (t.mt == 4) return launch_tile<4, 1, 8, 2>(a, grid_z, stream);
+    if (t.mt == 2) return t.nt == 2 ? launch_tile<2, 2, 4, 4>(a, grid_z, stream) : launch_tile<2, 1, 4, 3>(a, grid_z, stream);
+    return t.nt == 2 ? launch_tile<1, 2, 4, 3>(a, grid_z, stream) : launch_tile<1, 1, 4, 4>(a, grid_z, stream);
 }
 
 }  // namespace fact

@@ -84,3 +84,15 @@ def test_batches():
     torch.cuda.synchronize()
     for b in range(5):
         check.assert_bits_equal(wl.bits(C[b].cpu()), ref.gemm_epilogue(A[b], W[b], True), what=f"batch {b}")
+
+
+@pytest.mark.parametrize("M,N,K,pad", [(1, 16, 16384 + 72, 8), (16, 64, 32768, 0), (33, 64, 16384 + 8, 0), (64, 100, 65536, 8)])
+def test_long_k_and_few_columns(M, N, K, pad):
+    # without a workspace the skinny kernel walks all of K; with one the plan splits K over the chip.  Both exact on integers
+    A, W = wl.small_int((M, K), -2, 2, f"sk.lA.{M}.{K}"), wl.small_int((N, K), -2, 2, f"sk.lW.{N}.{K}")
+    r = ref.gemm_epilogue(A, W, True)
+    p = 1 << 16
+    route = lambda ws, split: [x[0] for x in fact.fact_test_route(1, M, N, K, p, K + pad, 0, p, K + pad, 0, 1, p, N, 0, None, -1, split, 0, ws, 1 << 40)]
+    assert route(None, 1) == ["skinny"] and route(p, 0) == ["tiles", "reduce"]
+    for entry in ("gemm", "splitk"):
+        check.assert_bits_equal(wl.bits(run(A, W, pad=pad, entry=entry)), r, what=f"{(M, N, K, entry)}")

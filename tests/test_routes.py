@@ -65,3 +65,27 @@ def test_tile_kernel_keeps_its_edges_in_range():
     for over in (edge + 1, 2 ** 31 - 1):
         assert kernels(over, 8, 8, 0) == ["guarded"] and kernels(72, over, 8, 1) == ["guarded"]
         assert route(over, 8, 8, 0, cfg=0) == -7
+
+
+# Few rows against [N][K] weights.  (M, N, K, batch, with a workspace): the skinny kernel where it measured faster than the plan,
+# the plan (here one that splits K over the whole chip, or tiles) where the skinny kernel has a handful of work-groups for
+# a long K, or more of them than weights to share A
+@pytest.mark.parametrize("M,N,K,batch,ws,want", [
+    (16, 4096, 14336, 1, False, "skinny"), (16, 4096, 14336, 1, True, "skinny"), (1, 3072, 768, 1, True, "skinny"), (64, 3072, 768, 1, False, "skinny"),
+    (16, 768, 3072, 1, True, "skinny"), (16, 64, 8192, 1, True, "skinny"), (16, 16384, 8192, 1, True, "skinny"), (16, 256, 1024, 8, False, "skinny"),
+    (16, 64, 32768, 1, False, "skinny"), (64, 64, 131072, 1, False, "skinny"),
+    (64, 64, 131072, 1, True, "tiles"), (16, 64, 65536, 1, True, "tiles"), (16, 128, 131072, 1, True, "tiles"), (1, 16, 32768, 1, True, "tiles"),
+    (32, 256, 32768, 1, True, "tiles"), (48, 512, 8192, 1, True, "tiles"), (64, 256, 8192, 1, True, "tiles"),
+    (16, 16384, 256, 1, False, "tiles"), (32, 16384, 1024, 1, False, "tiles"), (64, 8192, 1024, 1, False, "tiles"),
+    (64, 512, 1024, 128, False, "tiles"), (32, 64, 4096, 128, False, "tiles"), (48, 4096, 1024, 8, False, "tiles")])
+def test_few_rows(M, N, K, batch, ws, want):
+    got = kernels(M, N, K, 1, batch=batch, ws=ws)
+    plan = fact.fact_select_config(batch, M, N, K, 1, 0)
+    assert got == (["skinny"] if want == "skinny" else ["tiles", "reduce"] if ws and plan[2] > 1 else ["tiles"])
+
+
+def test_few_rows_only_where_nothing_else_was_asked_for():
+    assert kernels(16, 4096, 4096, 1) == ["skinny"]
+    assert kernels(16, 4096, 4096, 0) == ["tiles"] and kernels(65, 4096, 4096, 1) == ["tiles"]
+    assert kernels(16, 4096, 4096, 1, cfg=6) == ["tiles"] and kernels(16, 4096, 4096, 1, ws=True, split=4) == ["tiles", "reduce"]
+    assert kernels(16, 4096, 4096, 1, a=P + 2) == ["ragged"]
