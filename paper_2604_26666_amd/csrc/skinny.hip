@@ -214,7 +214,8 @@ static Tile tile_of(const GemmArgs &a)
     return {4, 1, 8, 2};
 }
 
-bool skinny_takes(const GemmArgs &a, bool trans_b) { return trans_b && a.M <= (a.act == ACT_SILU_GATE ? 32 : 64); }
+// (a grid's threads are counted in 32 bits: 32 for each column here)
+bool skinny_takes(const GemmArgs &a, bool trans_b) { return trans_b && a.M <= (a.act == ACT_SILU_GATE ? 32 : 64) && a.N < 1 << 27; }
 
 // Estimated microseconds: a work-group's K steps one after the other, each at least a load's latency and at most 60 GB/s per
 // compute unit, in as many rounds as the work-groups need; a start and an end per round, which nothing covers where

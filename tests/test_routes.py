@@ -89,3 +89,9 @@ def test_few_rows_only_where_nothing_else_was_asked_for():
     assert kernels(16, 4096, 4096, 0) == ["tiles"] and kernels(65, 4096, 4096, 1) == ["tiles"]
     assert kernels(16, 4096, 4096, 1, cfg=6) == ["tiles"] and kernels(16, 4096, 4096, 1, ws=True, split=4) == ["tiles", "reduce"]
     assert kernels(16, 4096, 4096, 1, a=P + 2) == ["ragged"]
+
+
+def test_few_rows_of_more_columns_than_a_grid_counts():
+    # (such weights would be 500 GB and more: the pricing alone does not rule them out)
+    assert kernels(1, 2 ** 27 - 16, 2048, 1) == ["skinny"]
+    assert kernels(1, 2 ** 28, 2048, 1) == ["tiles"] and kernels(16, 2 ** 28, 1024, 1, fact.ACT_SILU_GATE) == ["tiles"]
