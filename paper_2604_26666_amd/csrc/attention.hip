@@ -53,7 +53,9 @@ static hipError_t launch(AttnArgs a, hipStream_t stream)
         const int n = split ? a.total >> 3 : a.total, layer = split ? 32 : 256, layers = (n + layer - 1) / layer;
         a.fold = a.causal && layers >= 2 && layers <= (D == 64 ? 3 : 2) ? (layers - 1) * layer : n;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.total), dim3(NW * 64), lds, stream, a);
+    // (a grid's threads are counted in 32 bits: more than 2^20 work-groups go into further rows of the grid)
+    a.grid_x = a.total > 1 << 20 ? 1 << 20 : a.total;
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.grid_x, (unsigned)(((int64_t)a.total + a.grid_x - 1) / a.grid_x)), dim3(NW * 64), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -97,7 +99,7 @@ extern "C" int fact_attention(int64_t batch, int64_t T, int64_t n_q_heads, int64
     a.causal = causal;
     const float sc = scale > 0.f ? scale : 1.0f / std::sqrt((float)head_dim);
     a.scale_log2 = sc * 1.4426950408889634f;
-    a.q_blocks = 0; a.total = 0; a.group = 1; a.fold = 0;
+    a.q_blocks = 0; a.total = 0; a.grid_x = 0; a.group = 1; a.fold = 0;
 
     hipStream_t s = (hipStream_t)stream;
     const hipError_t e = head_dim == 128 ? launch<128, 4>(a, s) : launch<64, 4>(a, s);

@@ -63,6 +63,7 @@ struct AttnArgs {
     float scale_log2;       // softmax scale * log2(e)
     int q_blocks;           // ceil(T / BQ)
     int total;              // q_blocks * Hq * B work-groups
+    int grid_x;             // work-groups in a row of the grid, a multiple of 8 where there is more than one row
     int fold;               // positions of the work-group order (of an XCD's part of it) from here on run backwards
     int group;              // (batch, query head) pairs per group of the work-group order; divides the pairs of an XCD
 };
@@ -166,7 +167,8 @@ attn_fwd_kernel(const AttnArgs p)
     const int pairs = p.total / p.q_blocks;                    // batch * query heads
     int qb, pair;
     {
-        const int v = blockIdx.x;
+        const int v = (int)(blockIdx.y * (uint32_t)p.grid_x + blockIdx.x);
+        if (v >= p.total) return;                              // (the whole work-group)
         const bool split = (pairs & 7) == 0;                   // else: one sequence over all pairs
         int pos = split ? v >> 3 : v;
         if (pos >= p.fold) pos = p.fold + (split ? p.total >> 3 : p.total) - 1 - pos;

@@ -74,3 +74,15 @@ def test_falling_scores_keep_the_first_reference(D):
     q[..., 0] = 1.0
     k[..., 0] = (-(torch.arange(T, device="cuda") // 64) * 40.0).bfloat16()[None, :, None]
     check(run(q, k, v, 0, 1.0), q, k, v, 0, [(0, 0), (0, 1)], 1.0)
+
+
+def test_more_work_groups_than_one_grid_row_counts():
+    # 2^24 + 8 work-groups of 256 threads pass the 32-bit thread count of a grid's row: single tokens, whose result is V itself.
+    # The batch stride of Q, K and V is 0, so only the output is large (2 GB)
+    B, H, D = 2 ** 21 + 1, 8, 64
+    q, k, v = tensors(1, 1, H, H, D, 11)
+    O = torch.full((B, H, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    fact.binding.check(fact.fact_attention(B, 1, H, H, D, q, (0, H * D, D), k, (0, H * D, D), v, (0, H * D, D), O, (H * D, H * D, D), 0, 0.0))
+    torch.cuda.synchronize()
+    for part in O.split(1 << 19):
+        assert torch.equal(part, v[0].expand_as(part))
