@@ -65,7 +65,7 @@ norm_kernel(const uint16_t *X, int64_t ldx, const uint16_t *gamma, const uint16_
 {
     __shared__ float part[2][4];
     const int wave = threadIdx.x >> 6;
-    const int64_t row = WPR == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, row = WPR == 1 ? wg * 4 + wave : wg;
     if (row >= T) return;                                    // (the whole work-group where it shares a row)
     const int c0 = (WPR == 1 ? (int)threadIdx.x & 63 : (int)threadIdx.x) * 8;        // the lane's first column; pieces are WPR * 512 apart
     auto over_row = [&](float v, int which) __attribute__((always_inline)) {
@@ -230,7 +230,7 @@ int fact_norm(int64_t T, int64_t d, const void *X, int64_t ldx, const void *gamm
     if (!(eps >= 0.f)) return FACT_ERR_DIM;
     const bool wide = d > 1024;                               // four waves per row
     // (at most 2^20 work-groups along x: a grid's threads are counted in 32 bits)
-    const int64_t wgs = wide ? T : (T + 3) / 4, gx = wide && T > 1 << 20 ? 1 << 20 : wgs;
+    const int64_t wgs = wide ? T : (T + 3) / 4, gx = wgs > 1 << 20 ? 1 << 20 : wgs;
     const dim3 grid((unsigned)gx, (unsigned)((wgs + gx - 1) / gx));
     hipStream_t s = (hipStream_t)stream;
     const int pieces = (int)((d + (wide ? 2047 : 511)) / (wide ? 2048 : 512));

@@ -38,3 +38,19 @@ def test_rope_token_groups_and_wide_heads(B, T, H, D):
     # one rounding to bf16 (2^-8 of the value) and the angle's fp32 error, t * 2^-23 of a turned pair of size up to |x|
     err = (Xd.cpu().double() - want).abs()
     assert (err <= 2.0 ** -8 * want.abs() + T * 2.0 ** -22 * x.abs().max() + 1e-6).all(), err.max()
+
+
+@pytest.mark.parametrize("T,d", [(2 ** 26 + 8, 8), (2 ** 22 + 5, 64), (2 ** 20 + 3, 1032)])
+def test_more_rows_than_one_grid_row_holds(T, d):
+    # every work-group's row is written, also past the first row of the grid (2^26 rows of one wave each are 2^32 threads).
+    # A row of +-c is normed to +-c / sqrt(c^2 + eps): c = 1, 2, 3, 4 in turn
+    c = (torch.arange(T, device="cuda") % 4 + 1).bfloat16()
+    X = torch.ones((1, d), dtype=torch.bfloat16, device="cuda")
+    X[0, ::2] = -1
+    X = c[:, None] * X
+    g = torch.full((d,), 2.0, dtype=torch.bfloat16, device="cuda")
+    Y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    fact.binding.check(fact.fact_norm(T, d, X, d, g, None, 0.0, 1, Y, d))
+    torch.cuda.synchronize()
+    for x, y in zip(X.split(1 << 23), Y.split(1 << 23)):
+        assert torch.equal(y, x.sign() * 2)
