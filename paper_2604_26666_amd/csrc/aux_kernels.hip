@@ -156,11 +156,15 @@ __global__ void __launch_bounds__(256) fallback_gemm_kernel(const GemmArgs p)
 {
     const bool gated = p.act == ACT_SILU_GATE;
     const int nout = gated ? (p.N >> 1) : p.N;
-    const int tiles_n = (nout + 15) >> 4;
-    const int n = (int)(blockIdx.x % tiles_n) * 16 + (threadIdx.x & 15);
-    const int m = (int)(blockIdx.x / tiles_n) * 16 + (threadIdx.x >> 4);
+    const uint32_t tiles_n = ((uint32_t)nout + 15u) >> 4;
+    int64_t row = blockIdx.x / tiles_n, column = blockIdx.x % tiles_n;
+    if (gridDim.y > 1) {                                     // large outputs: further rows of the grid
+        const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+        row = block / tiles_n; column = block % tiles_n;
+    }
+    if (row * 16 + (threadIdx.x >> 4) >= p.M || column * 16 + (threadIdx.x & 15) >= nout) return;
+    const int n = (int)column * 16 + (threadIdx.x & 15), m = (int)row * 16 + (threadIdx.x >> 4);
     const int z = blockIdx.z;
-    if (m >= p.M || n >= nout) return;
     const uint16_t *A = (const uint16_t *)(p.A + z * p.stride_a) + (int64_t)m * p.lda;
     const uint16_t *B = (const uint16_t *)(p.B + z * p.stride_b);
     float acc = 0.f, acc_up = 0.f;
@@ -188,8 +192,9 @@ hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, 
 {
     const int nout = args.act == ACT_SILU_GATE ? args.N / 2 : args.N;
     const int64_t blocks = ((int64_t)nout + 15) / 16 * (((int64_t)args.M + 15) / 16);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)blocks, 1, (unsigned)grid_z);
+    const int64_t gx = blocks > 1 << 20 ? 1 << 20 : blocks, gy = (blocks + gx - 1) / gx;       // (a grid's threads are counted in 32 bits)
+    if (gy > 65535) return hipErrorInvalidConfiguration;
+    dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)grid_z);
     if (trans_b)
         hipLaunchKernelGGL(fallback_gemm_kernel<true>, grid, dim3(256), 0, stream, args);
     else

@@ -92,3 +92,19 @@ def test_odd_rows_of_c_in_every_configuration(cfg, f16):
     assert (out[M] == 77.0).all() and (out[:, N:] == 77.0).all(), "wrote outside C"
     r = ref.gemm_epilogue(A, B, True, bias=bias[1:], residual=res, fmt="f16" if f16 else "bf16")
     check.assert_bits_equal(wl.bits(out[:M, :N].contiguous()), r, what=f"cfg {cfg}")
+
+
+@pytest.mark.parametrize("nk", [0, 1])
+def test_guarded_kernel_on_more_elements_than_a_grid_row_counts(nk):
+    # one thread per element: 2^32 elements and more go into further rows of the grid.  Small integers, exact in bf16
+    M, N, K = 65536 + 24, 65536 + 8, 3
+    A, B = (torch.randint(-4, 5, s, device="cuda").bfloat16() for s in ((M, K), (N, K) if nk else (K, N)))
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    p = fact.fact_test_route(1, M, N, K, A, K, 0, B, K if nk else N, 0, nk, C, N, 0, None)
+    assert [x[0] for x in p] == ["guarded"]
+    fact.binding.check(fact.fact_gemm(M, N, K, A, K, B, K if nk else N, nk, C, N, None))
+    torch.cuda.synchronize()
+    Bk = (B.t() if nk else B).float()
+    for a, c in zip(A.split(8192), C.split(8192)):
+        want = sum(a[:, k:k + 1].float() * Bk[k:k + 1] for k in range(K))
+        assert torch.equal(c.float(), want)
