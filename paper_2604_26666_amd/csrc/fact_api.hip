@@ -111,6 +111,14 @@ static int persistent_grid(const ConfigDesc &c, int64_t items)
     return items > slots && items <= INT32_MAX / 2 ? (int)slots : 0;
 }
 
+// A grid's threads are counted in 32 bits along x, and a larger count is cut without an error.
+static bool grid_fits(const ConfigDesc &c, int64_t tiles) { return tiles <= (int64_t)UINT32_MAX / c.threads(); }
+static int64_t tiles_of(const ConfigDesc &c, int64_t M, int64_t nout, bool gated)
+{
+    const int64_t bn_out = gated ? c.bn / 2 : c.bn;
+    return (M + c.bm - 1) / c.bm * ((nout + bn_out - 1) / bn_out);
+}
+
 struct Plan {
     int cfg = -1;      // -1: no tile configuration of the main kernel serves it (ragged or guarded kernel)
     int split = 1;
@@ -168,7 +176,7 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
     for (int i = 0; i < kNumConfigs; ++i) {
         const ConfigDesc &c = g_configs[i];
         if (gated && !c.gate_capable()) continue;
-        if (!c.serves(trans_b)) continue;
+        if (!c.serves(trans_b) || !grid_fits(c, tiles_of(c, M, nout, gated))) continue;
         int max_split = 1;
         if (allow_split && batch == 1) {
             max_split = (int)(K / 1024);
@@ -287,6 +295,7 @@ static ColumnSplit column_split(const Plan &pl, int64_t M, int64_t nout, int64_t
     for (int i = 0; i < kNumConfigs; ++i) {
         const ConfigDesc &d = g_configs[i];
         if ((gated && !d.gate_capable()) || !d.serves(trans_b) || (wgs_per_cu(d) > 1 && d.bm * d.bn > 64 * 64)) continue;
+        if (!grid_fits(d, tiles_of(d, M, nout - n1, gated))) continue;
         const double t = model_time(d, 1, M, nout - n1, K, gated, 1);
         if (sp.cfg < 0 || t < rest) { rest = t; sp.cfg = i; }
     }
@@ -550,6 +559,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
         const int grid = persistent_grid(c, tiles_m * tiles_n * q.batch);
         if (grid > 0) { a.persist_items = (int)(tiles_m * tiles_n * q.batch); a.persist_z = (int)q.batch; a.persist_grid = grid; }
     }
+    if (!grid_fits(c, a.tail_g > 1 ? a.tail_first + (tiles_m * tiles_n - a.tail_first) * a.tail_g : tiles_m * tiles_n)) return FACT_ERR_DIM;
     // (the kernel numbers (K range or batch entry, tile) pairs with 32-bit integers)
     if (tiles_m * tiles_n * (a.splits > 1 ? (int64_t)a.splits : q.batch) > INT32_MAX / 2) return FACT_ERR_DIM;
     if (route) {

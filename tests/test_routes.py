@@ -95,3 +95,17 @@ def test_few_rows_of_more_columns_than_a_grid_counts():
     # (such weights would be 500 GB and more: the pricing alone does not rule them out)
     assert kernels(1, 2 ** 27 - 16, 2048, 1) == ["skinny"]
     assert kernels(1, 2 ** 28, 2048, 1) == ["tiles"] and kernels(16, 2 ** 28, 1024, 1, fact.ACT_SILU_GATE) == ["tiles"]
+
+
+def test_a_grid_never_has_more_threads_than_it_counts():
+    # 2^32 threads and more along x would be cut to 32 bits without an error
+    for M, N in ((2 ** 30 - 8, 64), (2 ** 30, 8), (2 ** 30 + 64, 64), (2 ** 31 - 300, 8)):
+        for nk in (0, 1):
+            (kind, cfg, _), = route(M, N, 8, nk)
+            bm, bn, wm, wn, _ = fact.fact_config_info(cfg)
+            assert kind == "tiles" and -(-M // bm) * -(-N // bn) * wm * wn * 64 < 2 ** 32, (M, N, nk, cfg)
+            for c in range(fact.fact_num_configs()):
+                bm, bn, wm, wn, _ = fact.fact_config_info(c)
+                if nk or bn != 192:
+                    fits = -(-M // bm) * -(-N // bn) * wm * wn * 64 < 2 ** 32
+                    assert kernels(M, N, 8, nk, cfg=c) == (["tiles"] if fits else -2), (M, N, c)
