@@ -451,7 +451,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
 
     hipError_t e;
     if (pl.cfg < 0) {
-        if (cfg_id != FACT_CONFIG_GUARDED && ragged_serves(a, q.trans_b != 0)) {
+        if (cfg_id != FACT_CONFIG_GUARDED && ragged_serves(a, q.trans_b != 0, q.batch)) {
             if (route) return route->add(FACT_ROUTE_RAGGED, -1, q.N);
             e = launch_ragged_gemm(a, q.trans_b != 0, (int)q.batch, stream);
             return e == hipSuccess ? FACT_OK : hip_fail(e, "ragged gemm launch");

@@ -34,7 +34,7 @@ double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
 hipError_t launch_skinny_gemm(const GemmArgs &args, int grid_z, hipStream_t stream);
 
 // GEMM with operands of any alignment and size on the matrix cores (ragged.hip).
-bool ragged_serves(const GemmArgs &args, bool trans_b);
+bool ragged_serves(const GemmArgs &args, bool trans_b, int64_t batch);
 hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
 
 }  // namespace fact

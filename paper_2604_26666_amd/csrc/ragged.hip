@@ -316,10 +316,24 @@ static hipError_t launch_tile(GemmArgs a, bool trans_b, int grid_z, hipStream_t 
 // Operands whose rows hold at least one 16-byte piece; shorter ones stay with the guarded kernel.  So do sizes of which the
 // edge of a last tile, or the step that a last K group loads ahead (3 x 4 x 64 past K), would leave the kernel's 32-bit
 // indexes: a wrapped one is negative, which its clamps take for inside.
-bool ragged_serves(const GemmArgs &a, bool trans_b)
+// And so does a K of a few elements where the guarded kernel has little to do, or where a tile here is mostly edge (us, guarded
+// and this kernel, K = 9 unless said): 8 x 8 2.1 / 2.7, 1 x 1000 2.5 / 3.3, 300 x 300 2.8 / 3.3 (K = 13 3.2 / 3.2, 17 3.7 / 3.3),
+// 100000 x 9 8.7 / 17.2 (K = 17 13.5 / 17.3, with [N][K] 20.4 / 16.6), 9 x 100000 12.4 / 13.6 (K = 13 16.0 / 13.7);
+// but 1000 x 1000 6.9 / 4.3, 4000 x 300 8.0 / 5.2, 100000 x 33 26.9 / 20.5.
+static bool guarded_is_faster(const GemmArgs &a, bool trans_b, int64_t batch)
+{
+    if (a.K > 24) return false;
+    const int nout = a.act == ACT_SILU_GATE ? a.N / 2 : a.N;
+    const int64_t blocks = ((int64_t)a.M + 15) / 16 * (((int64_t)nout + 15) / 16) * batch;      // the guarded kernel's work-groups
+    if (blocks * a.K <= 4096) return a.K <= 13;
+    if (nout <= 16) return a.K <= 13 || (!trans_b && blocks >= 2048);
+    return a.M <= 16 && a.K <= 9;
+}
+
+bool ragged_serves(const GemmArgs &a, bool trans_b, int64_t batch)
 {
     constexpr int kLast = INT32_MAX - 4096;
-    return a.K >= 8 && (trans_b || a.N >= 8) && a.M <= kLast && a.N <= kLast && a.K <= kLast;
+    return a.K >= 8 && (trans_b || a.N >= 8) && a.M <= kLast && a.N <= kLast && a.K <= kLast && !guarded_is_faster(a, trans_b, batch);
 }
 
 // The largest tile that still gives most compute units a work-group, and several K groups per work-group where

@@ -12,7 +12,8 @@ from oracle import check, ref
 pytestmark = pytest.mark.gpu
 
 # one row per tile shape and K-group count of the dispatch rule (K above and below its line), and the smallest sizes
-SHAPES = [(1801, 1499, 521), (1801, 1499, 77), (700, 999, 300), (700, 999, 100), (37, 131, 777), (1, 9, 8), (33, 65, 71), (31, 8, 9), (65, 64, 1025)]
+# (few rows or columns with a K of up to 13 run on the guarded kernel)
+SHAPES = [(601, 1003, 8), (1003, 601, 9), (1801, 1499, 521), (1801, 1499, 77), (700, 999, 300), (700, 999, 100), (37, 131, 777), (1, 9, 8), (33, 65, 71), (31, 8, 9), (65, 64, 1025)]
 
 
 def run(A, B, nk, bias=None, res=None, act=fact.ACT_NONE, f16=0):

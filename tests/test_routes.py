@@ -53,9 +53,9 @@ def test_ragged_kernel_keeps_its_indexes_in_range(nk):
         assert kernels(1, 8, K, nk) == ["guarded"], K
     # groups x steps ahead x depth, all below the margin, and a tile's edge
     assert 3 * 4 * 64 + 4 * 64 + 64 < 4096 and kernels(1, 8, last, nk) == ["ragged"]
-    for K in (9, 999, 2 ** 21 + 8):               # short rows, odd ones, and aligned ones past the tile kernel's leading dimensions
+    for K in (25, 999, 2 ** 21 + 8):              # odd rows, and aligned ones past the tile kernel's leading dimensions
         assert kernels(3, 9, K, nk) == ["ragged"], K
-    assert kernels(last + 1, 9, 9, nk) == ["guarded"] and kernels(1, last + 2, 9, nk) == ["guarded"] and kernels(1, last, 9, nk) == ["ragged"]
+    assert kernels(last + 1, 9, 25, nk) == ["guarded"] and kernels(1, last + 2, 25, nk) == ["guarded"] and kernels(1, last, 25, nk) == ["ragged"]
 
 
 def test_tile_kernel_keeps_its_edges_in_range():
@@ -109,3 +109,13 @@ def test_a_grid_never_has_more_threads_than_it_counts():
                 if nk or bn != 192:
                     fits = -(-M // bm) * -(-N // bn) * wm * wn * 64 < 2 ** 32
                     assert kernels(M, N, 8, nk, cfg=c) == (["tiles"] if fits else -2), (M, N, c)
+
+
+# rows of any alignment with a short K: the guarded kernel where it has little to do or the ragged kernel's tiles are mostly edge
+@pytest.mark.parametrize("M,N,K,nk,batch,want", [
+    (8, 8, 9, 0, 1, "guarded"), (1, 1000, 9, 1, 1, "guarded"), (300, 300, 9, 0, 1, "guarded"), (150, 50, 13, 1, 1, "guarded"), (100000, 9, 9, 1, 1, "guarded"),
+    (100000, 9, 17, 0, 1, "guarded"), (9, 100000, 9, 0, 1, "guarded"),
+    (8, 8, 17, 0, 1, "ragged"), (300, 300, 17, 1, 1, "ragged"), (1000, 1000, 9, 0, 1, "ragged"), (4000, 300, 9, 1, 1, "ragged"), (100000, 33, 9, 0, 1, "ragged"),
+    (100000, 9, 17, 1, 1, "ragged"), (9, 100000, 13, 0, 1, "ragged"), (100, 100, 9, 0, 64, "ragged"), (8, 8, 25, 0, 1, "ragged"), (8, 8, 7, 1, 1, "guarded")])
+def test_short_k_of_any_alignment(M, N, K, nk, batch, want):
+    assert kernels(M, N, K, nk, batch=batch) == [want]
