@@ -52,8 +52,8 @@ __device__ __forceinline__ float wave_sum(float v)
 
 // A row is read once (16 bytes per lane and piece), kept in registers in fp32, reduced, normalised and written once;
 // d <= 8192, a multiple of 8.  Bound by memory traffic where there are many rows and by one row's chain of latencies
-// where there are few, so gamma and beta are asked for before the sums need them, and a row wider than 1024 elements is
-// shared by the four waves of a work-group (their sums meet in LDS).  Operands
+// where there are few, so gamma and beta are asked for before the sums need them, and a wide row is shared by the four
+// waves of a work-group (their sums meet in LDS; the launch says which rows).  Operands
 // from HBM: 2048 x 4096 12.4 -> 8.6 us (3.9 TB/s), 16 x 4096 5.6 -> 2.2 us, 32768 x 4096 113 -> 92 us (5.8 TB/s), 8192 x 768
 // 9.9 -> 8.5 us (against a wave per row that asked for gamma and beta after its sums).
 // Narrower rows take a wave each.  The number of 512-element pieces per wave is a template parameter.
@@ -228,7 +228,11 @@ int fact_norm(int64_t T, int64_t d, const void *X, int64_t ldx, const void *gamm
     if (d % 8 || d > kMaxWidth) return FACT_ERR_UNSUPPORTED;
     if (!aligned16(X) || !aligned16(Y) || !aligned16(gamma) || (beta && !aligned16(beta)) || (ldx & 7) || (ldy & 7)) return FACT_ERR_ALIGN;
     if (!(eps >= 0.f)) return FACT_ERR_DIM;
-    const bool wide = d > 1024;                               // four waves per row
+    // Four waves per row from 2048 elements on, and from 1032 on where there are few rows; with many a wave takes up to 2040 elements
+    // by itself, since four waves leave lanes idle (us, four waves -> one; LayerNorm: 262144 x 1152 340 -> 210, 16384 x 1536
+    // 23.8 -> 21.1, 4096 x 1032 8.7 -> 7.1, 4096 x 1792 9.4 -> 9.3, 65536 x 2040 100 -> 101; RMSNorm: 65536 x 2048 86 -> 91;
+    // 1024 x 1544 3.9 -> 4.3, 16 x 1544 2.2 -> 3.1).
+    const bool wide = d > 1024 && (d >= 2048 || T < 2048);
     // (at most 2^20 work-groups along x: a grid's threads are counted in 32 bits)
     const int64_t wgs = wide ? T : (T + 3) / 4, gx = wgs > 1 << 20 ? 1 << 20 : wgs;
     const dim3 grid((unsigned)gx, (unsigned)((wgs + gx - 1) / gx));
@@ -236,7 +240,8 @@ int fact_norm(int64_t T, int64_t d, const void *X, int64_t ldx, const void *gamm
     const int pieces = (int)((d + (wide ? 2047 : 511)) / (wide ? 2048 : 512));
 #define FACT_NORM_LAUNCH(R, W, P) hipLaunchKernelGGL((norm_kernel<R, W, P>), grid, dim3(256), 0, s, (const uint16_t *)X, ldx, \
         (const uint16_t *)gamma, (const uint16_t *)(R ? nullptr : beta), eps, (uint16_t *)Y, ldy, (int)T, (int)d)
-#define FACT_NORM_PICK(R) do { if (!wide && pieces == 1) FACT_NORM_LAUNCH(R, 1, 1); else if (!wide) FACT_NORM_LAUNCH(R, 1, 2); \
+#define FACT_NORM_PICK(R) do { if (!wide && pieces == 1) FACT_NORM_LAUNCH(R, 1, 1); else if (!wide && pieces == 2) FACT_NORM_LAUNCH(R, 1, 2); \
+        else if (!wide && pieces == 3) FACT_NORM_LAUNCH(R, 1, 3); else if (!wide) FACT_NORM_LAUNCH(R, 1, 4); \
         else if (pieces == 1) FACT_NORM_LAUNCH(R, 4, 1); else if (pieces == 2) FACT_NORM_LAUNCH(R, 4, 2); else FACT_NORM_LAUNCH(R, 4, 4); } while (0)
     if (rms) FACT_NORM_PICK(true); else FACT_NORM_PICK(false);
 #undef FACT_NORM_PICK

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rms", [0, 1])
-@pytest.mark.parametrize("T,d", [(1, 512), (3, 520), (5, 1024), (5, 1032), (2, 2048), (2, 2056), (7, 4104)])
+@pytest.mark.parametrize("T,d", [(1, 512), (3, 520), (5, 1024), (5, 1032), (2, 2048), (2, 2056), (7, 4104),
+                                 (2047, 1032), (2049, 1032), (2048, 1536), (2050, 1544), (2051, 2040), (2048, 2048)])
 def test_norm_rows_of_one_and_four_waves(T, d, rms):
     X = wl.normal((T, d), 2.0, f"ne.X.{T}.{d}") + wl.normal((T, 1), 3.0, f"ne.s.{T}.{d}")
     g, b = wl.normal((d,), 1.0, f"ne.g.{d}"), wl.normal((d,), 0.5, f"ne.b.{d}")
