@@ -370,7 +370,7 @@ gemm_kernel(const GemmArgs p)
     // ... where a row of C is whole 128-byte lines.  Otherwise the lines at the tiles' edges would go to memory in parts:
     // plain stores then, which the L2 joins (1024 x 50256 x 768: 147 -> 92.7 us; 1024 x 50304 x 768, whole lines: 96.1 and 94.8).
 
-    // Interior tiles of a C whose rows are not 16-byte aligned or not whole lines take a register path of their own
+    // Tiles of a C whose rows are not 16-byte aligned, and interior ones where they are not whole lines, take a register path of their own
     // (8-wave work-groups and persistent launches do not have it: guarded path, or write-through stores).
     constexpr bool REG_ANY = NWAVES <= 4 && !PERSIST;
 
@@ -408,7 +408,7 @@ gemm_kernel(const GemmArgs p)
     const int lanes_per_row = out_w / 8;
     const int e_n0 = e_tn * (gated ? BN / 2 : BN);              // first OUTPUT column of the tile
     const int n_wave = e_n0 + wn * out_w;                       // first output column of this wave
-    const int m_wave = e_tm * BM + wm * WTM;
+    const int e_m0 = e_tm * BM, m_wave = e_m0 + wm * WTM;
     float *P = partial ? p.P + (int64_t)e_z * p.M * p.N : nullptr;       // split-K: this K range's plane of partials
     const bool batched = !e_in_tail && p.splits <= 1;            // e_z is a batch entry (a K range otherwise)
     __bf16 *C = p.C + (batched ? e_z * p.stride_c : 0);
@@ -709,23 +709,40 @@ gemm_kernel(const GemmArgs p)
     // XCD's L2 joins the pieces of a line.  1024 x 50257 x 768: 162 -> 129 us (the guarded path before; C with
     // rows of 50256, 16-byte stores: 92 us).  Staging the rows through LDS and cutting them where their 16-byte pieces
     // of memory begin, with the ends of the rows as single elements, took 143 us.
-    auto reg_epilogue_any = [&](auto gated_tag) __attribute__((always_inline)) {
-        constexpr bool GATED = decltype(gated_tag)::value;
+    // Edge tiles of such a C take it too, with every access guarded.  (In the LDS-staged general path, which a launch's interior
+    // tiles do not run, they fetched cold code of their own: 3547 x 2369 x 328, of which a seventh of the tiles are edges, 31.9 us
+    // when all tiles took that path, 33.7 when the edges alone did, 24.1 like this; 2726 x 30276 x 376 204, 156 and 124 us.)
+    auto reg_epilogue_any = [&](auto gated_tag, auto edge_tag) __attribute__((always_inline)) {
+        constexpr bool GATED = decltype(gated_tag)::value, EDGE = decltype(edge_tag)::value;
         constexpr int OT = GATED ? NT / 2 : NT, NP = OT / 2;
         static_assert(OT % 2 == 0, "tiles are exchanged in pairs");
         const int n = n_wave + (q & 1) * 16 + (q >> 1) * 8;
         const bool has_bias = p.bias != nullptr, has_res = R != nullptr, gelu = p.act == ACT_GELU_TANH;
         u32x4_t bp[NP], rb[2][NP];
+        // 8 elements from column n + pr * 32 on, zeros past the last column (an edge tile's: element by element there)
+        auto load8 = [&](const __bf16 *from, int pr) __attribute__((always_inline)) -> u32x4_t {
+            const int left = nout - (n + pr * 32);
+            if (!EDGE || left >= 8) return *(const u32x4_any *)(from + pr * 32);
+            u32x4_t v = {0u, 0u, 0u, 0u};
+            const uint16_t *at = (const uint16_t *)(from + pr * 32);
+#pragma unroll
+            for (int e = 0; e < 7; ++e)
+                if (e < left) v[e / 2] |= (uint32_t)at[e] << (16 * (e & 1));
+            return v;
+        };
         if (has_bias) {
 #pragma unroll
-            for (int pr = 0; pr < NP; ++pr) bp[pr] = *(const u32x4_any *)(p.bias + n + pr * 32);
+            for (int pr = 0; pr < NP; ++pr) bp[pr] = load8(p.bias + n, pr);
         }
+        const int row = m_wave + r16;
         const __bf16 *rrow = has_res ? R + (int64_t)(m_wave + r16) * p.ldr + n : nullptr;
         __bf16 *crow = C + (int64_t)(m_wave + r16) * p.ldc + n;
         auto load_res = [&](int mt) __attribute__((always_inline)) {
             if (has_res) {
+                if (!EDGE || row + 16 * mt < p.M) {
 #pragma unroll
-                for (int pr = 0; pr < NP; ++pr) rb[mt & 1][pr] = *(const u32x4_any *)(rrow + pr * 32);
+                    for (int pr = 0; pr < NP; ++pr) rb[mt & 1][pr] = load8(rrow, pr);
+                }
                 rrow += 16 * p.ldr;
             }
         };
@@ -768,16 +785,32 @@ gemm_kernel(const GemmArgs p)
                     const f32x2_t f2 = {z[2 * e], z[2 * e + 1]};
                     o[e] = pack2<F16>(f2);     // round to nearest even
                 }
-                *(u32x4_any *)(crow + pr * 32) = o;
+                if constexpr (EDGE) {
+                    const int left = nout - (n + pr * 32);
+                    if (row + 16 * mt < p.M) {
+                        if (left >= 8) *(u32x4_any *)(crow + pr * 32) = o;
+                        else {
+                            uint16_t *at = (uint16_t *)(crow + pr * 32);
+#pragma unroll
+                            for (int e = 0; e < 7; ++e)
+                                if (e < left) at[e] = (uint16_t)(o[e / 2] >> (16 * (e & 1)));
+                        }
+                    }
+                } else {
+                    *(u32x4_any *)(crow + pr * 32) = o;
+                }
             });
             crow += 16 * p.ldc;
         });
     };
     if constexpr (IN_REGS) {
         if constexpr (REG_ANY) {
-            if (!p.vec_store || !p.whole_lines) {
-                if constexpr (NT % 4 == 0) { if (gated) { reg_epilogue_any(std::true_type{}); return; } }
-                reg_epilogue_any(std::false_type{});
+            if (__builtin_expect(!p.vec_store || !p.whole_lines, 0)) {       // (laid out behind the common forms)
+                const bool edge = e_m0 + BM > p.M || e_n0 + (gated ? BN / 2 : BN) > nout;
+                if constexpr (NT % 4 == 0) {
+                    if (gated) { if (edge) reg_epilogue_any(std::true_type{}, std::true_type{}); else reg_epilogue_any(std::true_type{}, std::false_type{}); return; }
+                }
+                if (edge) reg_epilogue_any(std::false_type{}, std::true_type{}); else reg_epilogue_any(std::false_type{}, std::false_type{});
                 return;
             }
         }
@@ -863,7 +896,7 @@ gemm_kernel(const GemmArgs p)
             if (gated) fast_pass(pass, std::true_type{}); else fast_pass(pass, std::false_type{});
             return;
         }
-        // General path (edge tiles of an unaligned C, of split-K partials and of fp32 output), every access
+        // General path (edge tiles of split-K partials and of fp32 output; of an unaligned C where there is no register path for them), every access
         // guarded.  Read-back in batches of EPI_U row-chunks per lane: first every LDS read and every
         // bias / residual load of the batch is issued, then the arithmetic and the stores follow,
         // so the global-load latency is paid once per batch, not once per chunk.  (The residual
@@ -1589,12 +1622,12 @@ gemm_kernel(const GemmArgs p)
     auto hand_over = [&]() __attribute__((always_inline)) {
         e_tm = tm; e_tn = tn; e_z = z;
         e_in_tail = in_tail; e_tail_seg = tail_seg; e_tail_tile = tail_tile;
-        // register epilogue: the whole tile inside C, bf16 output, no hand-over; gated tiles only where a
-        // wave's output tiles pair up
+        // register epilogue: the whole tile inside C (or C's rows at any address, where edge tiles have it too), 16-bit
+        // output, no hand-over; gated tiles only where a wave's output tiles pair up
         // (the same answer in every wave of the work-group: the two kinds of epilogue meet different
         // barriers and run at different points of a persistent work-group's loop)
         const bool inside = m0 + BM <= p_launch.M && n0 + (gated ? BN / 2 : BN) <= nout;
-        e_in_regs = !partial && (REG_ANY || p_launch.vec_store) && inside && !in_tail && !p_launch.c_f32 && (!gated || NT % 4 == 0);
+        e_in_regs = !partial && (inside ? REG_ANY || p_launch.vec_store : REG_ANY && !p_launch.vec_store) && !in_tail && !p_launch.c_f32 && (!gated || NT % 4 == 0);
     };
     // (a persistent work-group sets these before the K loop, so that nothing of the tile's set-up is needed after
     // it; an ordinary one after it, where its 8-wave form has the registers)

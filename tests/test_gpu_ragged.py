@@ -95,6 +95,27 @@ def test_odd_rows_of_c_in_every_configuration(cfg, f16):
     check.assert_bits_equal(wl.bits(out[:M, :N].contiguous()), r, what=f"cfg {cfg}")
 
 
+@pytest.mark.parametrize("act", [fact.ACT_GELU_TANH, fact.ACT_SILU_GATE])
+@pytest.mark.parametrize("cfg", range(16))
+def test_activations_on_odd_rows_of_c_in_every_configuration(cfg, act):
+    # the same tiles with the activations, a residual at odd addresses, and edges of one row and of one column
+    tm, tn = fact.fact_config_info(cfg)[:2]
+    gated = act == fact.ACT_SILU_GATE
+    for M, nout in ((tm + 1, (tn // 2 if gated else tn) + 1), (tm - 3, 2 * tn - 5)):
+        N, K = 2 * nout if gated else nout, 72
+        A, B = wl.normal((M, K), 1.0, f"rg.eA.{M}"), wl.normal((N, K), K ** -0.5, f"rg.eB.{N}")
+        res, bias = wl.normal((M, nout + 1), 1.0, f"rg.er.{M}.{nout}"), None if gated else wl.normal((nout,), 1.0, f"rg.eb.{nout}")
+        Cb = torch.full((M + 1, nout + 2), 77.0, dtype=torch.bfloat16, device="cuda")
+        rd, bd = res.cuda(), None if bias is None else bias.cuda()
+        ep = fact.Epilogue(bias=bd, residual=rd.data_ptr() + 2, ldr=nout + 1, act=act)
+        fact.binding.check(fact.fact_gemm_ex(1, M, N, K, A.cuda(), K, 0, B.cuda(), K, 0, 1, Cb, nout + 2, 0, ep, cfg, 1, 0, None, 0))
+        torch.cuda.synchronize()
+        out = Cb.cpu()
+        assert (out[M] == 77.0).all() and (out[:, nout:] == 77.0).all(), "wrote outside C"
+        r = ref.gemm_epilogue(A, B, True, bias=bias, act=act, residual=res[:, 1:].contiguous())
+        check.assert_close(wl.bits(out[:M, :nout].contiguous()), r, what=f"cfg {cfg} {M} x {nout}")
+
+
 @pytest.mark.parametrize("nk", [0, 1])
 def test_guarded_kernel_on_more_elements_than_a_grid_row_counts(nk):
     # one thread per element: 2^32 elements and more go into further rows of the grid.  Small integers, exact in bf16
