@@ -126,17 +126,20 @@ norm_kernel(const uint16_t *X, int64_t ldx, const uint16_t *gamma, const uint16_
 
 // Rotary embedding in place, "rotate-half" pairing.  A work-group takes a few tokens and up to 256 of their angles
 // (blockIdx.y: further angles of a wider head); each thread computes one sine and cosine, once per token, into
-// LDS - the precise functions cost more than the traffic - and then walks 16-byte pieces of all heads: the piece at i
-// and the one at i + D/2.  2048 tokens of 40 heads of 128: 15.1 -> 11.4 us (3.7 TB/s), 16 tokens: 6.3 -> 3.1 us (against a
+// LDS - the precise functions cost more than the traffic - and then walks 16-byte pieces of its heads: the piece at i
+// and the one at i + D/2.  Many heads of few tokens are shared by several work-groups (4096 heads of 128, one token: 100 -> 3.7 us).  2048 tokens of 40 heads of 128: 15.1 -> 11.4 us (3.7 TB/s), 16 tokens: 6.3 -> 3.1 us (against a
 // thread that computed eight angles and walked eight heads).
+template <bool GROUPS>
 __global__ void __launch_bounds__(256)
-rope_kernel(uint16_t *X, int64_t sb, int64_t st, int64_t sh, int64_t tokens, int T, int H, int D, int per_wg, float log2_base)
+rope_kernel(uint16_t *X, int64_t sb, int64_t st, int64_t sh, int64_t tokens, int T, int H, int D, int per_wg, int per_group, float log2_base)
 {
     __shared__ float2 turn[256];
     const int first = blockIdx.y * 256;                      // first angle of this work-group
+    // blockIdx.z: the group of heads, or (all heads in one work-group) further rows of the grid
+    const int h0 = GROUPS ? (int)blockIdx.z * per_group : 0, heads = GROUPS && H - h0 > per_group ? per_group : H - h0;
     const int angles = D / 2 - first < 256 ? D / 2 - first : 256, pieces = angles >> 3;
-    const int64_t bt0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * per_wg;
-    if (bt0 >= tokens) return;                               // (the whole work-group)
+    const int64_t bt0 = (GROUPS ? (int64_t)blockIdx.x : (int64_t)blockIdx.z * gridDim.x + blockIdx.x) * per_wg;
+    if (bt0 >= tokens || (GROUPS && heads <= 0)) return;     // (the whole work-group)
     const int mine = tokens - bt0 < per_wg ? (int)(tokens - bt0) : per_wg;
     {
         const int k = threadIdx.x / angles, i = threadIdx.x - k * angles;        // token of the work-group, angle
@@ -148,11 +151,11 @@ rope_kernel(uint16_t *X, int64_t sb, int64_t st, int64_t sh, int64_t tokens, int
         }
     }
     __syncthreads();
-    const int per_token = H * pieces;
+    const int per_token = heads * pieces;
     for (int j = threadIdx.x; j < mine * per_token; j += 256) {
         const int k = j / per_token, r = j - k * per_token, h = r / pieces, piece = r - h * pieces;
         const int64_t bt = bt0 + k;
-        uint16_t *p = X + bt / T * sb + bt % T * st + (int64_t)h * sh + first + piece * 8;
+        uint16_t *p = X + bt / T * sb + bt % T * st + (int64_t)(h0 + h) * sh + first + piece * 8;
         const float2 *cs = turn + k * angles + piece * 8;
         const u32x4_t lo = *(const u32x4_t *)p, hi = *(const u32x4_t *)(p + D / 2);
         u32x4_t olo, ohi;
@@ -312,8 +315,16 @@ int fact_rope(int64_t batch, int64_t T, int64_t n_heads, int64_t head_dim, void 
     if (tokens >= 1024 * (int64_t)fit) per_wg = fit;
     const int64_t wgs = (tokens + per_wg - 1) / per_wg, gx = wgs > 1 << 20 ? 1 << 20 : wgs;
     if ((wgs + gx - 1) / gx > 65535) return FACT_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(rope_kernel, dim3((unsigned)gx, (unsigned)chunks, (unsigned)((wgs + gx - 1) / gx)), dim3(256), 0, (hipStream_t)stream, (uint16_t *)X,
-                       strides[0], strides[1], strides[2], tokens, (int)T, (int)n_heads, (int)head_dim, per_wg, std::log2(base));
+    // heads are shared where they give every thread more than two pieces and the chip has room
+    const int64_t pieces = (head_dim < 512 ? head_dim : 512) / 16;
+    int64_t groups = n_heads * pieces * per_wg / 512;
+    if (groups > 1024 / (wgs * chunks)) groups = 1024 / (wgs * chunks);
+    if (groups > 1)
+        hipLaunchKernelGGL(rope_kernel<true>, dim3((unsigned)wgs, (unsigned)chunks, (unsigned)groups), dim3(256), 0, (hipStream_t)stream, (uint16_t *)X,
+                           strides[0], strides[1], strides[2], tokens, (int)T, (int)n_heads, (int)head_dim, per_wg, (int)((n_heads + groups - 1) / groups), std::log2(base));
+    else
+        hipLaunchKernelGGL(rope_kernel<false>, dim3((unsigned)gx, (unsigned)chunks, (unsigned)((wgs + gx - 1) / gx)), dim3(256), 0, (hipStream_t)stream, (uint16_t *)X,
+                           strides[0], strides[1], strides[2], tokens, (int)T, (int)n_heads, (int)head_dim, per_wg, (int)n_heads, std::log2(base));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? FACT_OK : fact::record_hip_failure(e, "rope launch");
 }

@@ -27,7 +27,9 @@ def test_norm_rows_of_one_and_four_waves(T, d, rms):
 
 @pytest.mark.parametrize("B,T,H,D", [(1, 1, 1, 16), (3, 171, 2, 64), (2, 1031, 3, 128), (1, 9, 2, 512), (1, 5, 2, 544), (40, 40, 1, 32),
                                      # few heads: a thread per 8 angles and token; work-groups of an intermediate number of tokens
-                                     (1, 12501, 1, 64), (3, 7001, 3, 128), (2, 1031, 1, 16), (1, 2100, 1, 544), (40, 60, 1, 32), (1, 16387, 2, 16)])
+                                     (1, 12501, 1, 64), (3, 7001, 3, 128), (2, 1031, 1, 16), (1, 2100, 1, 544), (40, 60, 1, 32), (1, 16387, 2, 16),
+                                     # heads shared by several work-groups, the last group short
+                                     (1, 1, 300, 128), (3, 5, 257, 64), (1, 2, 70, 1024), (16, 1, 129, 96)])
 def test_rope_token_groups_and_wide_heads(B, T, H, D):
     base = 10000.0
     X = wl.normal((B, T, H, D), 1.0, f"re.{B}.{T}.{H}.{D}")
