@@ -129,9 +129,26 @@ def sweep_case(case, steps=20, warmup=20, groups=(1, 2, 4, 8, 16), splits=(2, 4,
     return results, failures
 
 
-def entries_for(case, results):
-    """Registry entries of a swept case: the best launch and, if that one needs a workspace, the best with K whole."""
-    if not results:
+def automatic_ms(case, steps=20, warmup=20):
+    """Mean ms of the call with nothing chosen for it, timed as the candidates are, or None where it fails the parity gate."""
+    case.alloc()
+    got = guarded_reference(case)
+    if got is None:
+        return None
+    rows, ref = got
+    case.t["C"].fill_(0)
+    if case.splitk:
+        ms, _ = wb.time_case_rotating(case, steps=steps, warmup=warmup, copies=wb.operand_copies(case), min_warm_ms=6.0, min_timed_ms=8.0)
+    else:
+        ms = wb.time_case(case, steps, warmup, min_warm_ms=6.0, min_timed_ms=8.0)
+    return ms if ms is not None and _close(_on_rows(case.t["C"], rows), ref) else None
+
+
+def entries_for(case, results, auto_ms=None):
+    """Registry entries of a swept case: the best launch and, if that one needs a workspace, the best with K whole.  None where
+    the call left to itself is more than 3 % faster than every candidate (auto_ms): it then runs on kernels that an entry
+    cannot name - the one for few rows, two launches over the columns - and that an entry would switch off."""
+    if not results or (auto_ms is not None and auto_ms < 0.97 * results[0]["ms"]):
         return []
     build = f"v{fact.fact_version()}"
     gated = 1 if case.act == fact.ACT_SILU_GATE else 0
@@ -154,14 +171,18 @@ def main(argv):
     new, log = [], {}
     for case in wb.cases(names):
         res, fail = sweep_case(case)
+        auto = automatic_ms(case)
         case.free()
         if not res:
             print(f"{case.name}: no configuration was accepted ({len(fail)} failures)", flush=True)
             log[case.name] = {"failed": fail}
             continue
-        ents = entries_for(case, res)
+        best, ents = res[0], entries_for(case, res, auto)
+        if not ents:
+            print(f"{case.name}: the call left to itself takes {auto:.4f} ms, the best of {len(res)} candidates {best['ms']:.4f} ms: no entry", flush=True)
+            log[case.name] = {"best": best, "automatic_ms": auto, "accepted": len(res), "failed": fail}
+            continue
         new += ents
-        best = res[0]
         print(f"{case.name}: best cfg {best['cfg']} {fact.fact_config_info(best['cfg'])} split {best['split']} "
               f"group_m {best['group_m']}: {ents[0].tflops} TFLOP/s; {len(res)} accepted, {len(fail)} failed", flush=True)
         log[case.name] = {"best": best, "top": res[:8], "accepted": len(res), "failed": fail}

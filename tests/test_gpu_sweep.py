@@ -78,3 +78,15 @@ def test_guarded_reference_on_sampled_rows_of_a_large_shape(monkeypatch):
     check.assert_close(wl.bits(out.cpu()), r, what="guarded reference, sampled rows")
     res, fail = sweep.sweep_case(case, steps=3, warmup=2, groups=(4,), tails=(), configs=(3,))
     assert len(res) == 1 and not fail
+
+
+def test_sweep_leaves_a_shape_alone_that_other_kernels_serve_faster():
+    # a decode-sized call runs on the kernel for few rows, which no configuration names and an entry would switch off
+    M, N, K = 16, 4096, 4096
+    X, W = wl.normal((M, K), 1.0, "swd.X"), wl.normal((N, K), 0.02, "swd.W")
+    case = workbench.Case("swd.case", M, N, K, 1, maker=lambda: {"A": X, "B": W})
+    res, fail = sweep.sweep_case(case, steps=5, warmup=5, groups=(4,), tails=(), configs=(3, 6, 8))
+    auto = sweep.automatic_ms(case)
+    assert len(res) == 3 and auto is not None and auto < 0.97 * res[0]["ms"], (auto, res)
+    assert sweep.entries_for(case, res, auto) == []
+    assert len(sweep.entries_for(case, res, res[0]["ms"])) == 1          # level: the entry is written
