@@ -171,7 +171,10 @@ def _stream(s):
         # the current stream's handle itself: current_stream() builds a Stream object around it, 2.9 us of the 7.9 that a
         # 512 x 512 x 512 call took to issue (0.2 this way; the call is then bound by the GPU, 5.4 us)
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:                       # (not part of torch's public interface)
+                pass
         return int(torch.cuda.current_stream().cuda_stream)
     if isinstance(s, int):
         return s

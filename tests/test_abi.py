@@ -163,3 +163,12 @@ def test_two_per_compute_unit_configuration_and_fp16_field_host_logic():
     assert fact.fact_gemm_ex(1, 8192, 2496, 4096, p, 4096, 0, p, 4096, 0, 1, p, 2496, 0, ep, 14, -2, 4, None, 0, 0) == -6
     assert fact.fact_gemm(64, 64, 64, p, 64, p, 64, 0, p, 64, fact.Epilogue(f16=2), 0) == -5
     assert fact.fact_gemm(64, 64, 64, p, 64, p, 64, 0, p, 64, fact.Epilogue(f16=-1), 0) == -5
+
+
+def test_default_stream_without_torchs_private_names(monkeypatch):
+    import torch
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 1234})())
+    assert fact.binding._stream(None) == 1234 and fact.binding._stream(77) == 77
