@@ -59,8 +59,7 @@ def test_head_grouping(Hq, Hkv):
 
 
 def test_many_query_blocks_ragged_length():
-    # several query blocks per head, T not a multiple of anything (the 256-query work-groups that
-    # long sequences of 128-wide heads get are covered by the full-size tests)
+    # several query blocks per head, T not a multiple of anything
     got, r = run_packed(2, 1000, 16, 4, 128, 1, std=1.28, name="qb4")
     check.assert_close(got, r, what="attention 2 x 1000 tokens, 16/4 heads of 128")
     got, r = run_packed(1, 1000, 4, 4, 64, 1, std=0.55, name="qb2")

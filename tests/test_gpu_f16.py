@@ -203,13 +203,13 @@ def test_batched_entries_and_guarded_kernel():
     torch.cuda.synchronize()
     for z in range(batch):
         check.assert_close(wl.bits(C[z].cpu().contiguous()), ref.gemm_epilogue(A[z], B[z], False, fmt="f16"), what=f"batch {z}")
-    for (m, n, k) in [(5, 7, 3), (33, 20, 100)]:                       # K % 8 != 0: the guarded kernel
+    for (m, n, k) in [(5, 7, 3), (33, 20, 100)]:                       # K % 8 != 0: the guarded and the ragged kernel
         a = wl.small_int_f16((m, k), -40, 40, f"hf.A{m}")
         b = wl.small_int_f16((k, n), -40, 40, f"hf.B{m}")
         bias = wl.small_int_f16((n,), -3, 3, "hf.bias")
         res = wl.small_int_f16((m, n), -3, 3, "hf.res")
         r = ref.gemm_epilogue(a, b, False, bias=bias, residual=res, fmt="f16")
-        check.assert_bits_equal(gemm16(a, b, 0, bias=bias, residual=res, pad=3), r, what=f"guarded {(m, n, k)}")
+        check.assert_bits_equal(gemm16(a, b, 0, bias=bias, residual=res, pad=3), r, what=f"unaligned {(m, n, k)}")
 
 
 def test_bf16_calls_are_untouched_by_the_field():

@@ -95,8 +95,12 @@ def test_rounding_ties_through_the_mfma_path_and_the_fallback():
 
 
 @pytest.mark.parametrize("trans_b", [0, 1])
-def test_tiny_and_unaligned_shapes_use_the_guarded_kernel(trans_b):
+def test_tiny_and_unaligned_shapes_with_the_guarded_kernel_and_left_to_themselves(trans_b):
+    # left to themselves: the guarded kernel, from K = 14 on the ragged one; then each on the guarded kernel by request
+    p = 1 << 16
     for (M, N, K) in [(1, 1, 1), (2, 3, 5), (5, 7, 3), (17, 33, 9), (33, 20, 100)]:
+        route = fact.fact_test_route(1, M, N, K, p, K, 0, p, K if trans_b else N, 0, trans_b, p, N, 0, None)
+        assert [x[0] for x in route] == ["ragged" if K > 13 else "guarded"]
         A = wl.small_int((M, K), -3, 3, f"gt.A{M}{N}{K}")
         B = wl.small_int((K, N), -3, 3, f"gt.B{M}{N}{K}")
         Bs = B if not trans_b else B.t().contiguous()
@@ -105,16 +109,20 @@ def test_tiny_and_unaligned_shapes_use_the_guarded_kernel(trans_b):
         r = ref.gemm_epilogue(A, Bs, bool(trans_b), bias=bias, residual=res)
         got = G().gemm(A, Bs, trans_b, bias=bias, residual=res, pad=3)
         check.assert_bits_equal(got, r, what=f"{(M, N, K)}")
+        got = G().gemm(A, Bs, trans_b, bias=bias, residual=res, pad=3, cfg=fact.CONFIG_GUARDED, split=1, entry="ex")
+        check.assert_bits_equal(got, r, what=f"{(M, N, K)} guarded")
 
 
 def test_guarded_kernel_gated_epilogue_and_batches():
-    # K = 9 is served by the guarded kernel only.  Small integers keep the gate and up sums exact, so
+    # so small an output with K = 9 is served by the guarded kernel.  Small integers keep the gate and up sums exact, so
     # the only inexact step is SiLU in fp32: the output is held to the usual tolerance and to a much
     # tighter one that an up-weight matrix taken from another batch entry cannot meet.
     M, K, I = 13, 9, 11
     rc, cfg, _ = fact.fact_select_config(1, M, 2 * I, K, 1, fact.ACT_SILU_GATE)
-    assert cfg < 0, "this shape is meant for the guarded kernel"
     for batch in (1, 3):
+        p = 1 << 16
+        route = fact.fact_test_route(batch, M, 2 * I, K, p, K, M * K, p, K, 2 * I * K, 1, p, I, M * I, fact.Epilogue(act=fact.ACT_SILU_GATE))
+        assert cfg < 0 and [x[0] for x in route] == ["guarded"], "this shape is meant for the guarded kernel"
         X = wl.small_int((batch, M, K), -2, 2, f"gg.X{batch}")
         W = wl.small_int((batch, 2 * I, K), -2, 2, f"gg.W{batch}")        # distinct gate and up rows in every batch entry
         C = G().poisoned(batch * M, I).view(batch, M, I)

@@ -66,6 +66,50 @@ def test_activations(shape, act):
     check.assert_close(got, ref.gemm_epilogue(A, B, True, act=act, rows=rows), rows="full", what=f"{shape} act={act}")
 
 
+@pytest.mark.parametrize("act,nk,f16", [(fact.ACT_SILU_GATE, 1, 1), (fact.ACT_GELU_TANH, 0, 0), (fact.ACT_GELU_TANH, 0, 1)])
+@pytest.mark.parametrize("shape", [(700, 998, 300), (37, 130, 777)], ids=str)
+def test_activations_in_fp16_and_with_row_major_weights(shape, act, nk, f16):
+    M, N, K = shape
+    normal, fmt = (wl.normal_f16, "f16") if f16 else (wl.normal, "bf16")
+    A, B = normal((M, K), 1.0, f"rg.fa.{shape}"), normal((N, K) if nk else (K, N), K ** -0.5, f"rg.fb.{shape}.{nk}")
+    rows = wl.choice_rows(M, 32, f"rg.fr.{shape}", edges=(0, M - 1))
+    got = run(A, B, nk, act=act, f16=f16)
+    check.assert_close(got, ref.gemm_epilogue(A, B, bool(nk), act=act, rows=rows, fmt=fmt), rows="full", what=f"{shape} act={act}")
+
+
+@pytest.mark.parametrize("nk", [0, 1])
+def test_batches_of_odd_strides(nk):
+    # every operand of a batch entry begins at an odd element, rows and entries padded with NaN
+    b, M, N, K = 3, 45, 71, 99
+    A, B = wl.small_int((b, M, K), -4, 4, "rg.bA"), wl.small_int((b, N, K) if nk else (b, K, N), -4, 4, f"rg.bB.{nk}")
+    bias, res = wl.small_int((N,), -9, 9, "rg.bb"), wl.small_int((b, M, N), -9, 9, "rg.br")
+
+    def odd(t):
+        r, c = t.shape[1:]
+        ld = c + 1 + c % 2                                       # odd
+        stride = r * ld + 1 + (r * ld) % 2                       # odd as well
+        buf = torch.full((b * stride + 1,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        torch.as_strided(buf, (b, r, c), (stride, ld, 1), 1).copy_(t.cuda())
+        return buf, buf.data_ptr() + 2, ld, stride
+
+    (Ab, ap, lda, sa), (Bb, bp, ldb, sb), (Rb, rp, ldr, sr) = odd(A), odd(B), odd(res)
+    ldc = N + 2
+    sc = M * ldc + 1
+    Cb = torch.full((b * sc + 1,), 77.0, dtype=torch.bfloat16, device="cuda")
+    bd = bias.cuda()
+    ep = fact.Epilogue(bias=bd, residual=rp, ldr=ldr, stride_r=sr)
+    assert fact.fact_test_route(b, M, N, K, ap, lda, sa, bp, ldb, sb, nk, Cb.data_ptr() + 2, ldc, sc, ep)[0][0] == "ragged"
+    fact.binding.check(fact.fact_gemm_batched(b, M, N, K, ap, lda, sa, bp, ldb, sb, nk, Cb.data_ptr() + 2, ldc, sc, ep))
+    torch.cuda.synchronize()
+    out = torch.as_strided(Cb, (b, M, N), (sc, ldc, 1), 1).cpu()
+    for z in range(b):
+        r = ref.gemm_epilogue(A[z], B[z], bool(nk), bias=bias, residual=res[z])
+        check.assert_bits_equal(wl.bits(out[z].contiguous()), r, what=f"batch entry {z}")
+    written = torch.zeros(Cb.numel(), dtype=torch.bool)
+    torch.as_strided(written, (b, M, N), (sc, ldc, 1), 1).fill_(True)
+    assert (Cb.cpu()[~written] == 77.0).all(), "wrote outside C"
+
+
 def test_a_row_of_infinities_stays_in_its_row():
     # rows and columns past an edge repeat the last one and K past the end is zero on both sides: 0 x inf must not leak
     A, B = wl.small_int((65, 73), -4, 4, "rg.inf.A").clone(), wl.small_int((73, 67), 1, 4, "rg.inf.B")
