@@ -447,7 +447,8 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
                   (!q.ep.residual || (aligned16(q.ep.residual) && q.ep.ldr % 8 == 0 && q.ep.stride_r % 8 == 0)) &&
                   q.ldc < ((int64_t)1 << 21) && q.ep.ldr < ((int64_t)1 << 21);     // a tile's rows within 2^31 bytes: 32-bit row offsets in the epilogue
 
-    a.whole_lines = ((uintptr_t)q.C & 127u) == 0 && q.ldc % 64 == 0 && (q.batch == 1 || q.stride_c % 64 == 0);
+    const int unit = gated ? 64 : 32;                 // elements of C between the addresses that rows may begin at (see kStoreThrough)
+    a.store_through = ((uintptr_t)q.C & (uintptr_t)(2 * unit - 1)) == 0 && q.ldc % unit == 0 && (q.batch == 1 || q.stride_c % unit == 0);
 
     hipError_t e;
     if (pl.cfg < 0) {

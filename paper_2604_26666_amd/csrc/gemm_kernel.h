@@ -56,7 +56,7 @@ struct GemmArgs {
     int tiles_m, tiles_n;
     int group_m;            // tile rows walked together (L2 reuse)
     int vec_store;          // 1: C / residual / bias allow 16-byte vector access
-    int whole_lines;        // 1: every row of C begins on a 128-byte line
+    int store_through;      // 1: 16-byte stores of C are written through the L2 (see kStoreThrough)
     int pf_sa, pf_sb;       // L2 prefetch: work-groups that share an A row-panel / a B column-panel (0: off; else a power of two)
     int pf_dist;            // L2 prefetch: K steps ahead of the step being loaded into LDS (>= 1)
     // Tail split (the last, partly filled round of tiles): work-groups [0, tail_first) own one tile
@@ -367,10 +367,14 @@ gemm_kernel(const GemmArgs p)
     // 8192 x 3072 x 768 + bias + GELU 45.3 -> 41.6 / 48.0 -> 41.7 us, 128 x 512^3 43.5 -> 42.5 / 51.5 -> 48.5 us,
     // 8192^3 713 -> 708 us; no shape slower.  (Write-through alone: better from the cache, worse from HBM.)
     constexpr int kStoreThrough = 19;
-    // ... where a row of C is whole 128-byte lines.  Otherwise the lines at the tiles' edges would go to memory in parts:
-    // plain stores then, which the L2 joins (1024 x 50256 x 768: 147 -> 92.7 us; 1024 x 50304 x 768, whole lines: 96.1 and 94.8).
+    // ... where every row of C begins on a 64-byte boundary.  Rows at other addresses would send the lines at the tiles' edges to
+    // memory in pieces of 16 or 32 bytes: plain stores then, which the L2 joins (us, through -> plain; 1024 x 50256 x 768 147 ->
+    // 92.7, 1611 x 9840 x 456 41.7 -> 28.8; but rows at odd multiples of 64 bytes 2726 x 30304 x 376 98 -> 122, 4096 x 4128 x 4096
+    // 127 -> 145, 1611 x 9824 x 456 27.0 -> 28.8, and whole lines 1024 x 50304 x 768 94.8 -> 96.1).  A gated wave tile is half as
+    // wide, so that with odd multiples of 64 bytes it holds no whole line: plain stores there (521 x 53568 x 272 43.5 -> 38.9, 4096
+    // x 16448 x 512 85 -> 88), and whole lines, or halves of them at the edges of 192-wide tiles, are written through.
 
-    // Tiles of a C whose rows are not 16-byte aligned, and interior ones where they are not whole lines, take a register path of their own
+    // Tiles of a C whose rows are not 16-byte aligned, and interior ones that are not written through, take a register path of their own
     // (8-wave work-groups and persistent launches do not have it: guarded path, or write-through stores).
     constexpr bool REG_ANY = NWAVES <= 4 && !PERSIST;
 
@@ -702,7 +706,7 @@ gemm_kernel(const GemmArgs p)
         });
     };
     // The register path for C, bias or residual rows at any 2-byte address (odd leading dimensions such as a
-    // vocabulary's 50257), and for rows of C that are not whole 128-byte lines: the same exchange, then 16-byte
+    // vocabulary's 50257), and for rows of C that are not written through: the same exchange, then 16-byte
     // accesses through pointers, which may be unaligned.
     // What is added is looked at per group of columns at run time: one instance keeps the kernel's code small (it is
     // fetched once per tile, and cold code runs at the speed of its fetch).  The stores are ordinary ones, so that the
@@ -805,7 +809,7 @@ gemm_kernel(const GemmArgs p)
     };
     if constexpr (IN_REGS) {
         if constexpr (REG_ANY) {
-            if (__builtin_expect(!p.vec_store || !p.whole_lines, 0)) {       // (laid out behind the common forms)
+            if (__builtin_expect(!p.vec_store || !p.store_through, 0)) {       // (laid out behind the common forms)
                 const bool edge = e_m0 + BM > p.M || e_n0 + (gated ? BN / 2 : BN) > nout;
                 if constexpr (NT % 4 == 0) {
                     if (gated) { if (edge) reg_epilogue_any(std::true_type{}, std::true_type{}); else reg_epilogue_any(std::true_type{}, std::false_type{}); return; }
@@ -850,7 +854,7 @@ gemm_kernel(const GemmArgs p)
                 compact_pass(decltype(pass_)::value, gated_tag, through_tag);
             });
         };
-        if (p.whole_lines) { if (gated) all(std::true_type{}, std::true_type{}); else all(std::false_type{}, std::true_type{}); }
+        if (p.store_through) { if (gated) all(std::true_type{}, std::true_type{}); else all(std::false_type{}, std::true_type{}); }
         else if (gated) all(std::true_type{}, std::false_type{}); else all(std::false_type{}, std::false_type{});
     } else
     static_for<WTM / EPI_ROWS>([&](auto pass_) __attribute__((always_inline)) {
