@@ -504,8 +504,8 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     }
     // Few rows against [N][K] weights, nothing about the launch asked for by the caller or the registry: the skinny
     // kernel where it is the faster one.  It needs no workspace; what the plan would have needed has been
-    // checked above all the same.
-    if (cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.listed && tail_g <= 1 && skinny_serves(a, q.trans_b != 0, q.batch, c)) {
+    // checked above all the same.  (Persistent launches where they are asked for are taken as they stand.)
+    if (!(a.splits <= 1 && !a.f16 && persistent_grid(c, tiles_m * tiles_n * q.batch) > 0) && cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.listed && tail_g <= 1 && skinny_serves(a, q.trans_b != 0, q.batch, c)) {
         if (out_f32) {
             if (a.splits <= 1) {
                 const size_t need = (size_t)q.M * (size_t)q.N * sizeof(float);

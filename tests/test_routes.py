@@ -119,3 +119,16 @@ def test_a_grid_never_has_more_threads_than_it_counts():
     (100000, 9, 17, 1, 1, "ragged"), (9, 100000, 13, 0, 1, "ragged"), (100, 100, 9, 0, 64, "ragged"), (8, 8, 25, 0, 1, "ragged"), (8, 8, 7, 1, 1, "guarded")])
 def test_short_k_of_any_alignment(M, N, K, nk, batch, want):
     assert kernels(M, N, K, nk, batch=batch) == [want]
+
+
+def test_persistent_launches_are_taken_as_they_stand():
+    M, N, K = 16, 131072, 4096
+    grid = fact.fact_persistent_grid(1, M, N, K, 1)
+    assert grid == 0 and kernels(M, N, K, 1) == ["skinny"]
+    was = fact.fact_tune_persistent(1)
+    try:
+        assert fact.fact_persistent_grid(1, M, N, K, 1) > 0 and kernels(M, N, K, 1) == ["persistent"]
+        assert kernels(M, 4096, K, 1) == ["skinny"]                         # every tile is resident: no persistent launch to take
+        assert kernels(1024, 50257, 768, 1) == ["persistent"]              # and none is split into two
+    finally:
+        fact.fact_tune_persistent(was)
