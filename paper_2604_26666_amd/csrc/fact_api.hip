@@ -118,6 +118,8 @@ static int64_t tiles_of(const ConfigDesc &c, int64_t M, int64_t nout, bool gated
     const int64_t bn_out = gated ? c.bn / 2 : c.bn;
     return (M + c.bm - 1) / c.bm * ((nout + bn_out - 1) / bn_out);
 }
+// Outputs that no configuration needs so many tiles for (at least 64 x 32 each, 512 threads at most): nothing to count.
+static bool any_grid_fits(int64_t M, int64_t nout) { return M < 1 << 24 && nout < 1 << 24 && M * nout < (int64_t)1 << 33; }
 
 struct Plan {
     int cfg = -1;      // -1: no tile configuration of the main kernel serves it (ragged or guarded kernel)
@@ -172,11 +174,12 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
     for (const TableRow *r = g_table; r->cfg >= 0; ++r)
         if (matches(*r)) { take(*r); return pl; }
     const int64_t nout = gated ? N / 2 : N;
+    const bool all_fit = any_grid_fits(M, nout);
     double best = 0;
     for (int i = 0; i < kNumConfigs; ++i) {
         const ConfigDesc &c = g_configs[i];
         if (gated && !c.gate_capable()) continue;
-        if (!c.serves(trans_b) || !grid_fits(c, tiles_of(c, M, nout, gated))) continue;
+        if (!c.serves(trans_b) || (!all_fit && !grid_fits(c, tiles_of(c, M, nout, gated)))) continue;
         int max_split = 1;
         if (allow_split && batch == 1) {
             max_split = (int)(K / 1024);
@@ -291,11 +294,12 @@ static ColumnSplit column_split(const Plan &pl, int64_t M, int64_t nout, int64_t
     const int64_t tiles_m = (M + c.bm - 1) / c.bm, tiles = tiles_m * ((nout + bn_out - 1) / bn_out);
     const int64_t n1 = (tiles - 1) / kNumCU * kNumCU / tiles_m * bn_out;
     if (n1 <= 0 || n1 >= nout) return sp;
+    const bool all_fit = any_grid_fits(M, nout);
     double rest = 0;
     for (int i = 0; i < kNumConfigs; ++i) {
         const ConfigDesc &d = g_configs[i];
         if ((gated && !d.gate_capable()) || !d.serves(trans_b) || (wgs_per_cu(d) > 1 && d.bm * d.bn > 64 * 64)) continue;
-        if (!grid_fits(d, tiles_of(d, M, nout - n1, gated))) continue;
+        if (!all_fit && !grid_fits(d, tiles_of(d, M, nout - n1, gated))) continue;
         const double t = model_time(d, 1, M, nout - n1, K, gated, 1);
         if (sp.cfg < 0 || t < rest) { rest = t; sp.cfg = i; }
     }
