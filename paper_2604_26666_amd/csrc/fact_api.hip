@@ -327,8 +327,8 @@ static double few_rows_us(const ConfigDesc &c, int64_t batch, int64_t M, int64_t
 
 // Where the skinny kernel's estimate is below the plan's.  Both estimates were fitted to 1100 calls of 1 to 64 rows, 16 to
 // 36000 columns, K of 64 to 131072 and batches up to 128, with and without a workspace, operands from HBM; the choice costs
-// 0.4 % over the better kernel of every call on average; in 29 of them the one it takes is more than 3 % slower, by 25 % at most
-// but for three (45 to 52 %).  Some of the calls (us, plan -> skinny; * the plan is kept):
+// 0.4 % over the better kernel of every call on average; in 28 of them the one it takes is more than 3 % slower, by 25 % at most
+// but for two (46 and 49 %).  Some of the calls (us, plan -> skinny; * the plan is kept):
 //    M x N x K:  16 x 4096 x 14336  59.6 -> 25.6     16 x 768 x 3072  9.5 -> 6.3       64 x 3072 x 768  5.3 -> 4.4
 //                16 x 16384 x 8192  62.6 -> 52.0     16 x 16384 x 256  5.4 -> 6.6 *    32 x 16384 x 1024  9.6 -> 11.2 *
 //    with a workspace, so that the plan may split K:

@@ -231,7 +231,7 @@ double skinny_us(const GemmArgs &a, int64_t batch, bool whole_lines)
     const double rounds = wgs > 256.0 * fit ? wgs / (256.0 * fit) : 1.0;
     const double sharing = wgs < 256.0 ? 1.0 : wgs / 256.0 < fit ? wgs / 256.0 : fit;
     const double rows_a = 0.5 * (16 * t.mt + (a.M < 16 * t.mt ? a.M : 16 * t.mt));       // (rows past M are not fetched, but their zeros are written)
-    const double bytes = 128.0 * t.waves * (rows_a + 16 * t.nt), step = sharing * bytes / (whole_lines ? 60e3 : 50e3);
+    const double bytes = 128.0 * (blocks < t.waves ? blocks : t.waves) * (rows_a + 16 * t.nt), step = sharing * bytes / (whole_lines ? 60e3 : 50e3);
     const double chain = 1.4 + 0.004 * wgs + rounds * (0.8 + (blocks + t.waves - 1) / t.waves * (step > 0.2 ? step : 0.2)) + (fit == 1 ? 2.0 * (rounds - 1.0) : 0.0);
     const double memory = 1.4 + (double)batch * a.K * 2.0 * (a.N + (wx < 8.0 ? wx : 8.0) * a.M) / (whole_lines ? 5.4e6 : 4.7e6);
     return chain > memory ? chain : memory;
