@@ -1,7 +1,7 @@
 // One tile configuration's kernels (both B layouts).  Built once per row of configs.def with
 // -DFACT_ID=.. -DFACT_BM=.. -DFACT_BN=.. -DFACT_WM=.. -DFACT_WN=.. -DFACT_BK=.. -DFACT_STAGES=..
 #include "launch.h"
-#include <atomic>
+#include "lds_limit.h"
 
 namespace fact {
 
@@ -22,22 +22,9 @@ static hipError_t launch_one(const GemmArgs &args, int grid_z, hipStream_t strea
     const bool persist = CAN_PERSIST && args.persist_items > 0;
     if (args.persist_items > 0 && (!CAN_PERSIST || args.f16)) return hipErrorInvalidConfiguration;     // (the host side never asks for it)
     constexpr int lds = lds_total(FACT_BM, FACT_BN, FACT_WM, FACT_WN, FACT_BK, FACT_STAGES);
-    static std::atomic<bool> attr_set[64];         // (two host threads may make a kernel's first launch at once: setting the limit twice is harmless)
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, lds, {(const void *)kern, (const void *)kern_p, (const void *)kern_h});     // (kern_p is kern where no persistent form exists)
     if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    if (!attr_set[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        if (CAN_PERSIST) {
-            e = hipFuncSetAttribute((const void *)kern_p, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-        }
-        e = hipFuncSetAttribute((const void *)kern_h, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        attr_set[dev].store(true, std::memory_order_release);
-    }
     const int tiles = args.tiles_m * args.tiles_n;
     const int grid_x = args.tail_g > 1 ? args.tail_first + (tiles - args.tail_first) * args.tail_g : tiles;
     dim3 grid((unsigned)grid_x, 1, (unsigned)grid_z);

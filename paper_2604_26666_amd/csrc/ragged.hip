@@ -5,7 +5,7 @@
 // targets on this architecture), and go to LDS in the same swizzled layouts.  Measured cost of odd rows: 2000 x 1999 x
 // 1777 35.7 us, 2000 x 2000 x 1784 through the same kernel 30.9 us; the main kernel, which the latter takes, 24.4 us.
 #include "launch.h"
-#include <atomic>
+#include "lds_limit.h"
 
 namespace fact {
 
@@ -285,16 +285,9 @@ static hipError_t launch_one(const GemmArgs &a, dim3 grid, hipStream_t stream)
     constexpr int lds = KW * 2 * (BM + BN) * 128;
     static_assert(lds <= 160 * 1024 && (BM / WGM / 16) * (BN / WGN / 16) * KW * 4096 <= lds, "LDS: rings, then the groups' sums");
     if constexpr (lds > 64 * 1024) {
-        static std::atomic<bool> attr_set[64];               // (two host threads may make a kernel's first launch at once: setting the limit twice is harmless)
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
+        static LdsLimit limit;
+        const hipError_t e = raise_lds_limit(limit, lds, {(const void *)kern});
         if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-        if (!attr_set[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-            attr_set[dev].store(true, std::memory_order_release);
-        }
     }
     hipLaunchKernelGGL(kern, grid, dim3(256 * KW), lds, stream, a);
     return hipGetLastError();

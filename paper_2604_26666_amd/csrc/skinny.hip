@@ -8,7 +8,7 @@
 // 64 bytes or as whole lines with the halves exchanged between lanes, stay at 23 and 33 GB/s per compute unit however
 // many are in flight: 16 x 4096 x 14336 took 38 and 33 us, this form 25.6 us.)
 #include "launch.h"
-#include <atomic>
+#include "lds_limit.h"
 
 namespace fact {
 
@@ -181,16 +181,9 @@ static hipError_t launch_skinny_as(const GemmArgs &a, int grid_z, hipStream_t st
     constexpr int lds = NW * S * (MT + NT) * 2048;
     static_assert(lds <= 160 * 1024 && MT * NT * 1024 <= S * (MT + NT) * 2048, "LDS: rings, then the waves' sums");
     if constexpr (lds > 64 * 1024) {
-        static std::atomic<bool> attr_set[64];               // (two host threads may make a kernel's first launch at once: setting the limit twice is harmless)
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
+        static LdsLimit limit;
+        const hipError_t e = raise_lds_limit(limit, lds, {(const void *)kern});
         if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-        if (!attr_set[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-            attr_set[dev].store(true, std::memory_order_release);
-        }
     }
     hipLaunchKernelGGL(kern, grid, dim3(64 * NW), lds, stream, a);
     return hipGetLastError();
