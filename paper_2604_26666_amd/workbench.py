@@ -335,6 +335,22 @@ def time_attention(steps=30, warmup=30):
     return out
 
 
+def block_launches(B, T, desc):
+    """Kernels that fact_block_forward launches for this block: the norms, rotary, attention and those of its four GEMMs."""
+    p, Tt, d, dff, gated = 1 << 16, B * T, desc["d_model"], desc["d_ff"], desc["act_gated"]
+    nq, nkv = desc["q_heads"] * desc["head_dim"], desc["kv_heads"] * desc["head_dim"]
+
+    def gemm(N, K, act=fact.ACT_NONE, split=0):
+        # as the block calls it: the workspace is the block's own; the first feed-forward GEMM never splits K
+        nout = N // 2 if act == fact.ACT_SILU_GATE else N
+        r = fact.fact_test_route(1, Tt, N, K, p, K, 0, p, K, 0, 1, p, nout, 0, fact.Epilogue(act=act), -1, split, 0, p if split == 0 else None, 1 << 40)
+        return len(r)
+
+    act = fact.ACT_SILU_GATE if gated else fact.ACT_GELU_TANH
+    whole = fact.fact_block_mlp_workspace_bytes(Tt, d, dff, act) == 0
+    return 3 + int(bool(desc["rope"])) + gemm(nq + 2 * nkv, d) + gemm(d, nq) + gemm(2 * dff if gated else dff, d, act, 1) + gemm(d, dff, split=1 if whole else 0)
+
+
 def time_blocks(steps=20, warmup=10):
     """Whole decoder blocks through fact_block_forward: ms per block and the TFLOP/s of its matrix
     work (the four projections' 2 M N K plus the attention's causal half)."""
@@ -369,7 +385,7 @@ def time_blocks(steps=20, warmup=10):
         flops = 2.0 * Tt * d * (nq + 2 * nkv) + 2.0 * Tt * nq * d + 2.0 * Tt * d * dff * (3 if desc["act_gated"] else 2) \
             + 4.0 * B * desc["q_heads"] * desc["head_dim"] * (T * (T + 1) / 2.0)
         out[name] = {"ms": round(ms, 4), "tflops": round(flops / ms / 1e9, 1), "pct_mfma_peak": round(100 * flops / ms / 1e9 / PEAK_BF16_TFLOPS, 2),
-                     "scratch_MB": round(need / 2 ** 20, 1)}
+                     "launches": block_launches(B, T, desc), "scratch_MB": round(need / 2 ** 20, 1)}
         del scratch, Xd, Y, b
     return out
 

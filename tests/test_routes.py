@@ -132,3 +132,11 @@ def test_persistent_launches_are_taken_as_they_stand():
         assert kernels(1024, 50257, 768, 1) == ["persistent"]              # and none is split into two
     finally:
         fact.fact_tune_persistent(was)
+
+
+def test_launches_of_a_block():
+    from paper_2604_26666_amd import workbench
+    gpt = {"d_model": 768, "q_heads": 12, "kv_heads": 12, "head_dim": 64, "d_ff": 3072, "act_gated": False, "rope": False}
+    llama = {"d_model": 4096, "q_heads": 32, "kv_heads": 8, "head_dim": 128, "d_ff": 14336, "act_gated": True, "rope": True}
+    assert workbench.block_launches(8, 1024, gpt) == 2 + 1 + 4                  # norms, attention, one launch per GEMM
+    assert workbench.block_launches(1, 2048, llama) == 2 + 1 + 1 + 5            # rotary as well, and the gate / up GEMM over columns in two
