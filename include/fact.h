@@ -36,8 +36,9 @@
  *   - Shapes: any positive M, N, K.  The MFMA path needs 16-byte aligned A and B
  *     with lda, ldb and K multiples of 8 (and N a multiple of 8 when trans_b == 0);
  *     anything else runs kernels with the same results contract that stage unaligned rows through
- *     registers (K >= 8, and N >= 8 when trans_b == 0; about 2/3 of the aligned kernels' rate at
- *     2000^3) or, below that, compute one element per thread.
+ *     registers (K >= 8, and N >= 8 when trans_b == 0; about 3/4 of the aligned kernels' rate at
+ *     2000^3) or compute one element per thread: rows shorter than that, a K of a few elements
+ *     where that is faster, and M, N or K within 4096 of 2^31.
  */
 #ifndef FACT_H
 #define FACT_H
@@ -106,12 +107,15 @@ typedef struct fact_epilogue {
 /* ---- entry points --------------------------------------------------------------------- */
 
 /*
- * C[M][Nout] = epilogue(A[M][K] x B).  One data-parallel 2-D tiled launch (the paper's
+ * C[M][Nout] = epilogue(A[M][K] x B).  Data-parallel 2-D tiled (the paper's
  * "Data Parallel" grid schedule, Section 4.2 Action 2; Section 5.2.1).  ep may be NULL.
  * The tile configuration comes from the per-shape table (the shadow of the paper's
- * registry lookup, Section 4.2 Action 6).  Calls of at most 64 rows with trans_b == 1 that no
- * registry or table entry names may take a kernel of their own for few rows instead, in every
- * entry point that leaves the configuration to the library.
+ * registry lookup, Section 4.2 Action 6).  One launch, or two over the columns where the last
+ * round of tiles would be nearly empty (the columns of the full rounds on the table's configuration,
+ * the others on one that spreads them over the GPU; same bits as one launch; not for an entry of a
+ * registry file loaded at run time).  Calls of at most 64 rows with trans_b == 1 that no registry or
+ * table entry names take a kernel of their own for few rows where it is estimated to be faster.
+ * Both hold in every entry point that leaves the configuration to the library.
  */
 int fact_gemm(int64_t M, int64_t N, int64_t K,
               const void *A, int64_t lda,
@@ -139,8 +143,9 @@ int fact_gemm_batched(int64_t batch, int64_t M, int64_t N, int64_t K,
  * order; W is 1, 2, 4 or 8, the least that puts some 2048 waves to work on the M x N output
  * with at least four ranges each: a function of M, N and split_k alone), applies the epilogue
  * and rounds once.  split_k == 0 lets the table choose; split_k == 1 (or a
- * choice of 1) runs the plain kernel and needs no workspace.  Bit-reproducible: the
- * order of additions is fixed.
+ * choice of 1) runs the plain kernel and needs no workspace.  Few rows may keep K whole on the kernel
+ * for few rows (see fact_gemm) although the table splits it; the workspace is asked for all the same.
+ * Bit-reproducible: the order of additions is fixed.
  * ws: device pointer, 16-byte aligned, at least
  * fact_gemm_splitk_workspace_bytes(M, N, K, split_k) bytes; contents are scratch.
  */
@@ -303,8 +308,10 @@ int fact_config_info(int id, int *tile_m, int *tile_n, int *waves_m, int *waves_
 /* The table's choice for a shape (host logic only, no GPU needed): writes the tile
  * configuration id and the split-K factor (>= 1; -g for a tail split of g ranges, see
  * fact_gemm_ex).  batch >= 1.  Returns FACT_OK, or an
- * error if the shape is invalid.  config_id is -1 when the shape can only run on the
- * guarded fallback kernel (unaligned dimensions). */
+ * error if the shape is invalid.  config_id is -1 when no tile configuration serves the
+ * shape (unaligned dimensions: the kernel for rows of any alignment, or one element per thread).
+ * Where a call takes the kernel for few rows, or runs as two launches (see fact_gemm), this is
+ * the choice that it was weighed against; fact_test_route names the kernels that run. */
 int fact_select_config(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act,
                        int *config_id, int *split_k);
 
@@ -418,7 +425,8 @@ int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
  */
 int fact_tune_persistent(int mode);
 /* Work-groups a launch of this problem with K whole uses when it is persistent, else 0 (config_id < 0:
- * the table's or the model's configuration; 0 as well when that choice splits K). */
+ * the table's or the model's configuration; 0 as well when that choice splits K).  While mode 1 is
+ * set such a launch takes the place of the kernel for few rows and of two launches over the columns. */
 int fact_persistent_grid(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, int config_id);
 
 /* ---- misc ------------------------------------------------------------------------------- */

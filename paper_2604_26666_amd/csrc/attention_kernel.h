@@ -22,7 +22,7 @@
 //     {16u + 4h + 0..3} and {16u + 8 + 4h + 0..3}, not 8 consecutive ones, so the A operand
 //     (V^T) is fetched with the same permutation - the transposing LDS read takes one address per
 //     4-key group anyway.
-//   What bounds it: instruction issue.  A score costs an fma, an exponential (two issue slots), half a
+//   What it spends its cycles on: vector ALU and matrix pipe, mostly in turn.  A score costs an fma, an exponential (two issue slots), half a
 //   conversion and half an addition: 135 vector instructions per wave and key block, 580 cycles,
 //   next to 16 MFMAs (512 cycles) at head_dim 64 and 32 (1024) at 128, of which each takes about
 //   10 issue cycles from its SIMD.  A wave does the two in turn, so what matters is that another wave
@@ -30,9 +30,9 @@
 //   head_dim 64 and two at 128, and a work-group's first loads and last stores are covered the
 //   same way.  Against 64 queries per wave, one wave per SIMD and scores of one block computed
 //   between the exponentials of another (which this kernel replaces at every size): 16 x 500 tokens,
-//   12 heads of 64: 34 -> 21 us; 8 x 1024 causal 31 -> 23; 4 x 1999 causal, 32 / 8 heads of 128:
-//   157 -> 138; 1 x 2048 61 -> 44; 1 x 8192 526 -> 506 (1090 TFLOP/s); 4 x 4096, 16 heads of 64, full,
-//   338 -> 288.  Counters of the last: vector ALU issuing 63 % of the cycles, matrix pipe busy 44 %.
+//   12 heads of 64: 33 -> 19.8 us; 8 x 1024 causal 31 -> 23; 4 x 1999 causal, 32 / 8 heads of 128:
+//   156 -> 144; 1 x 2048 61 -> 44; 1 x 8192 563 -> 507 (1085 TFLOP/s); 4 x 4096, 16 heads of 64, full,
+//   338 -> 288.  Counters of the last: vector ALU issuing 61 % of the cycles, matrix pipe busy 49 %.
 #pragma once
 
 #include <hip/hip_runtime.h>

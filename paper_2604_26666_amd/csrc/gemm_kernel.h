@@ -31,7 +31,6 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef u32x4_t u32x4_any __attribute__((aligned(2)));       // 16 (8) bytes at any even address: global accesses may be unaligned
 typedef u32x2_t u32x2_any __attribute__((aligned(2)));
 typedef f32x4_t f32x4_any __attribute__((aligned(4)));
-typedef f32x4_t f32x4_any __attribute__((aligned(4)));
 
 #define FACT_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 

@@ -3,7 +3,7 @@
 // straight from global memory into LDS, which needs 16-byte aligned rows; here they pass through registers,
 // where a 16-byte global load may start at any 2-byte address (the unaligned-access mode that the compiler
 // targets on this architecture), and go to LDS in the same swizzled layouts.  Measured cost of odd rows: 2000 x 1999 x
-// 1777 35.7 us, 2000 x 2000 x 1784 through the same kernel 30.9 us; the main kernel, which the latter takes, 24.4 us.
+// 1777 33.0 us, 2000 x 2000 x 1784 through the same kernel 30.9 us; the main kernel, which the latter takes, 24.4 us.
 #include "launch.h"
 #include "lds_limit.h"
 
@@ -44,7 +44,7 @@ __device__ __forceinline__ s16x4_t read_tr16(const char *lds)
 // A work-group owns a BM x BN tile; its 4 KW waves form KW groups of WGM x WGN waves, and group g takes the 64-deep
 // K steps g, g + KW, ...  Each group keeps two LDS stages and two further steps of operands in registers on their
 // way there (the K loop is bound by the loads' latency: with one step in flight and one group per compute unit
-// 2000 x 1999 x 1777 took 45 us, as it stands 35.7 us = 398 TFLOP/s; the one-thread-per-element kernel 3416 us).  A 16-byte piece that would cross the end of a row (K-contiguous operand) or of the
+// 2000 x 1999 x 1777 took 45 us, as it stands 33.0 us = 430 TFLOP/s; the one-thread-per-element kernel 3416 us).  A 16-byte piece that would cross the end of a row (K-contiguous operand) or of the
 // matrix's columns (B as [K][N]) is loaded so that it ends there and shifted into place, so nothing outside the
 // matrices is ever read; a step past the end of K brings zeros.
 template <int BM, int BN, int WGM, int WGN, int KW, bool TRANS_B, bool F16>
