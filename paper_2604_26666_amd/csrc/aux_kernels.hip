@@ -44,13 +44,21 @@ __global__ void __launch_bounds__(64 * kReduceWaves) splitk_reduce_kernel(const 
         }
         float v[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f};
         const float *src = p.P + (int64_t)m * p.N + n + (int64_t)s_begin * plane;
-        const bool full = n + 3 < nout;
+        const bool full = n + 3 < nout, vec_e = full && p.vec_store;
         const int cnt = live ? s_end - s_begin : 0;
+        // the first wave's bias and residual travel with the partials
+        u32x2_t bias4 = {0u, 0u}, res4 = {0u, 0u};
+        if (wave == 0 && live && vec_e) {
+            if (p.bias) bias4 = *(const u32x2_t *)((const uint16_t *)p.bias + n);
+            if (p.res) res4 = *(const u32x2_t *)((const uint16_t *)p.res + (int64_t)m * p.ldr + n);
+        }
         if (full && vec_p) {
-            // whole batches with every load issued before the first add, then the rest one by one
-            constexpr int NB = 8;
+            // Batches of 8, 4, 2 and 1 ranges, in each every load issued before the first add: a wave is bound by its trips to
+            // memory, and with a trip per range past the last 8, and one each for bias and residual after the sums, 4 ranges of
+            // 208 x 4096 took 11.4 us, like this 7.7 (GEMM and reduction: 192 x 64 x 10112 11.1 -> 9.7, 384 x 256 x 69120 38.9 -> 36.4).
             int s0 = 0;
-            for (; s0 + NB <= cnt; s0 += NB) {
+            auto batch = [&](auto nb_) __attribute__((always_inline)) {
+                constexpr int NB = decltype(nb_)::value;
                 f32x4_t a[NB], b[NB];
 #pragma unroll
                 for (int j = 0; j < NB; ++j) a[j] = *(const f32x4_t *)(src + (s0 + j) * plane);
@@ -64,12 +72,12 @@ __global__ void __launch_bounds__(64 * kReduceWaves) splitk_reduce_kernel(const 
 #pragma unroll
                     for (int j = 0; j < NB; ++j) { u[0] += b[j].x; u[1] += b[j].y; u[2] += b[j].z; u[3] += b[j].w; }
                 }
-            }
-            for (; s0 < cnt; ++s0) {
-                const f32x4_t a = *(const f32x4_t *)(src + s0 * plane);
-                v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-                if (gated) { const f32x4_t b = *(const f32x4_t *)(src + s0 * plane + nout); u[0] += b.x; u[1] += b.y; u[2] += b.z; u[3] += b.w; }
-            }
+                s0 += NB;
+            };
+            while (s0 + 8 <= cnt) batch(std::integral_constant<int, 8>{});
+            if (s0 + 4 <= cnt) batch(std::integral_constant<int, 4>{});
+            if (s0 + 2 <= cnt) batch(std::integral_constant<int, 2>{});
+            if (s0 < cnt) batch(std::integral_constant<int, 1>{});
         } else {
             for (int s0 = 0; s0 < cnt; ++s0)
                 for (int e = 0; e < 4; ++e)
@@ -90,18 +98,19 @@ __global__ void __launch_bounds__(64 * kReduceWaves) splitk_reduce_kernel(const 
             for (int w = 0; w < kReduceWaves - 1; ++w)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { v[e] += part[w][0][e][lane]; u[e] += part[w][1][e][lane]; }
+#pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (n + e >= nout) continue;
                 float zv = v[e];
                 if (gated) zv = silu(zv) * u[e];
-                if (p.bias) zv += in16_rt(p.f16, ((const uint16_t *)p.bias)[n + e]);
+                if (p.bias) zv += in16_rt(p.f16, vec_e ? (bias4[e / 2] >> (16 * (e & 1))) & 0xFFFFu : ((const uint16_t *)p.bias)[n + e]);
                 if (p.act == ACT_GELU_TANH) zv = gelu_tanh(zv);
-                if (p.res) zv += in16_rt(p.f16, ((const uint16_t *)p.res)[(int64_t)m * p.ldr + n + e]);
+                if (p.res) zv += in16_rt(p.f16, vec_e ? (res4[e / 2] >> (16 * (e & 1))) & 0xFFFFu : ((const uint16_t *)p.res)[(int64_t)m * p.ldr + n + e]);
                 v[e] = zv;
             }
             if (p.out_f32) {                                   // fp32 output: no rounding at all
                 float *cf = (float *)p.C + (int64_t)m * p.ldc + n;
-                if (full && p.vec_store) {
+                if (vec_e) {
                     *(f32x4_t *)cf = f32x4_t{v[0], v[1], v[2], v[3]};
                 } else {
                     for (int e = 0; e < 4; ++e)
@@ -109,7 +118,7 @@ __global__ void __launch_bounds__(64 * kReduceWaves) splitk_reduce_kernel(const 
                 }
             } else {
                 __bf16 *cp = p.C + (int64_t)m * p.ldc + n;
-                if (full && p.vec_store) {
+                if (vec_e) {
                     *(u32x2_t *)cp = u32x2_t{out16_rt(p.f16, v[0]) | (out16_rt(p.f16, v[1]) << 16), out16_rt(p.f16, v[2]) | (out16_rt(p.f16, v[3]) << 16)};
                 } else {
                     uint16_t *cs = (uint16_t *)cp;
