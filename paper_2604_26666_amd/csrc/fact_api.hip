@@ -335,12 +335,41 @@ static double few_rows_us(const ConfigDesc &c, int64_t batch, int64_t M, int64_t
 //                16 x 64 x 8192  11.7 -> 10.3        16 x 64 x 32768  12.0 -> 34.9 *   64 x 64 x 131072  16.6 -> 315 *
 //    without:    16 x 64 x 8192  23.7 -> 10.4        64 x 64 x 32768  134 -> 51        64 x 64 x 131072  559 -> 318
 //    batches:    8 x (16 x 256 x 1024)  6.7 -> 4.1   128 x (32 x 64 x 4096)  24.8 -> 37.2 *   128 x (64 x 512 x 1024)  33.1 -> 75.4 *
-static bool skinny_serves(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c)
+// The plan's time where the chip has few work-groups of it: model_time prices full chips.  Fitted to the same calls as
+// small_us, of which those with more than 64 rows or B as [K][N] ran the tile kernel (mean error 13 and 6 %).
+static double small_plan_us(const ConfigDesc &c, bool trans_b, int64_t batch, int64_t M, int64_t N, int64_t K, int splits)
 {
-    if (!skinny_takes(a, trans_b)) return false;
-    const bool gated = a.act == FACT_ACT_SILU_GATE;
+    const int64_t tiles_n = (N + c.bn - 1) / c.bn;
+    const double tiles = (double)((M + c.bm - 1) / c.bm) * tiles_n * batch * splits;
+    const int fit = wgs_per_cu(c);
+    const double rounds = tiles > 256.0 * fit ? tiles / (256.0 * fit) : 1.0;
+    const double sharing = tiles < 256.0 ? 1.0 : tiles / 256.0 < fit ? tiles / 256.0 : fit;
+    const double area = (double)c.bm * c.bn / 65536.0, latency = c.bm == 64 ? (trans_b ? 0.124 : 0.184) : 0.5 * std::sqrt(area);
+    const double step = sharing * 128.0 * ((M < c.bm ? M : c.bm) + (N < c.bn ? N : c.bn)) / (trans_b ? 84.1e3 : 71.4e3);
+    const int64_t ksteps = ((K + splits - 1) / splits + 63) / 64;
+    const double start = trans_b ? 3.06 : 4.16;
+    const double chain = start + 0.004 * tiles + rounds * ((trans_b ? 14.7 : 8.2) * area + (double)ksteps * (step > latency ? step : latency));
+    const double memory = start + (double)batch * K * 2.0 * (N + (double)(tiles_n < 8 ? tiles_n : 8) * M) / 5.0e6;
+    return (chain > memory ? chain : memory) + (splits > 1 ? 4.0 + (double)M * N * 8.0 * splits / 1e7 : 0.0);
+}
+
+// Which form of the skinny kernel runs in the plan's place: kFewRows, a tile of small_us, or kNoSkinny.
+// Small outputs (small_us) where the estimate is 8 % below the plan's (us, plan -> skinny; M x N x K): B as [K][N] 43 x 2736 x 80 5.3 -> 3.6, 1 x 32 x 3688
+// 15.0 -> 5.7, 22 x 176 x 3920 16.0 -> 7.6, 120 x 112 x 6280 31.3 -> 13.3, 610 x 344 x 7272 36.3 -> 23.7; but 159 x 5840 x 928 12.2 -> 16.8; [N][K]
+// 67 x 56 x 256 4.7 -> 3.3, 425 x 104 x 1352 7.2 -> 4.5, 180 x 1920 x 600 6.0 -> 5.1; but 572 x 1552 x 2128 14.8 -> 25.  Over the 650 calls with more than 64
+// rows or B as [K][N] the choice is 1.29 and 1.50 times as fast as the plan alone, the better kernel of every call 1.34 and 1.55 times;
+// 4 of them lose more than 3 %, 12 % at most.
+static constexpr int kNoSkinny = -2, kFewRows = -1;
+static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c)
+{
+    const bool gated = a.act == FACT_ACT_SILU_GATE, few = skinny_takes(a, trans_b);
     const bool lines = ((uintptr_t)a.B & 127u) == 0 && a.ldb % 64 == 0 && (batch == 1 || a.stride_b % 64 == 0);
-    return skinny_us(a, batch, lines) < few_rows_us(c, batch, a.M, a.N, gated ? a.N / 2 : a.N, a.K, gated, a.splits, lines);
+    int tile = -1;
+    const double small = small_us(a, trans_b, batch, &tile);
+    if (!few) return tile >= 0 && small < 0.92 * small_plan_us(c, trans_b, batch, a.M, a.N, a.K, a.splits) ? tile : kNoSkinny;
+    const double rows = skinny_us(a, batch, lines), plan = few_rows_us(c, batch, a.M, a.N, gated ? a.N / 2 : a.N, a.K, gated, a.splits, lines);
+    if (rows < plan || (a.splits <= 1 && tile >= 0 && small < 0.92 * plan)) return tile >= 0 && small < rows ? tile : kFewRows;
+    return kNoSkinny;
 }
 
 // ---- the one launch path every entry point goes through ----------------------------------------
@@ -506,10 +535,12 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
             a.P = (float *)ws;
         }
     }
-    // Few rows against [N][K] weights, nothing about the launch asked for by the caller or the registry: the skinny
-    // kernel where it is the faster one.  It needs no workspace; what the plan would have needed has been
-    // checked above all the same.  (Persistent launches where they are asked for are taken as they stand.)
-    if (!(a.splits <= 1 && !a.f16 && persistent_grid(c, tiles_m * tiles_n * q.batch) > 0) && cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.listed && tail_g <= 1 && skinny_serves(a, q.trans_b != 0, q.batch, c)) {
+    // Few rows against [N][K] weights or a small output, nothing about the launch asked for by the caller or the registry: the
+    // skinny kernel where it is the faster one.  It needs no workspace; what the plan would have needed has been
+    // checked above all the same.  (Persistent launches where they are asked for, and a registry file's choice, are taken as
+    // they stand; a row of the compiled-in table names the best tile configuration: 512^3 5.5 us there, 4.0 here.)
+    if (!(a.splits <= 1 && !a.f16 && persistent_grid(c, tiles_m * tiles_n * q.batch) > 0) && cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.loaded && tail_g <= 1)
+        if (const int tile = skinny_choice(a, q.trans_b != 0, q.batch, c); tile != kNoSkinny) {
         if (out_f32) {
             if (a.splits <= 1) {
                 const size_t need = (size_t)q.M * (size_t)q.N * sizeof(float);
@@ -521,7 +552,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
         }
         a.splits = 1; a.P = nullptr;
         if (route) return route->add(FACT_ROUTE_SKINNY, -1, q.N);
-        e = launch_skinny_gemm(a, (int)q.batch, stream);
+        e = launch_skinny_gemm(a, q.trans_b != 0, tile, (int)q.batch, stream);
         return e == hipSuccess ? FACT_OK : hip_fail(e, "skinny gemm launch");
     }
     // L2 prefetch (see the kernel).  Many work-groups: the ones resident on an XCD (32 CUs) form a

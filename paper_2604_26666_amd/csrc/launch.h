@@ -27,11 +27,13 @@ struct ConfigDesc {
 hipError_t launch_splitk_reduce(const GemmArgs &args, hipStream_t stream);
 hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
 
-// GEMM of few rows against B as [N][K] (skinny.hip): the calls it can take, and its estimated microseconds
-// (whole_lines: every row of B begins on a 128-byte line).
+// GEMM of few rows against B as [N][K], and small GEMMs of either layout (skinny.hip): the calls of few rows it can take and
+// their estimated microseconds (whole_lines: every row of B begins on a 128-byte line); the estimate for a small GEMM with the
+// tile that gives it (-1: none serves it); the launch (tile -1: few rows).
 bool skinny_takes(const GemmArgs &args, bool trans_b);
 double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
-hipError_t launch_skinny_gemm(const GemmArgs &args, int grid_z, hipStream_t stream);
+double small_us(const GemmArgs &args, bool trans_b, int64_t batch, int *tile);
+hipError_t launch_skinny_gemm(const GemmArgs &args, bool trans_b, int tile, int grid_z, hipStream_t stream);
 
 // GEMM with operands of any alignment and size on the matrix cores (ragged.hip).
 bool ragged_serves(const GemmArgs &args, bool trans_b, int64_t batch);

@@ -1,5 +1,6 @@
-// GEMM of few rows against weights as a linear layer stores them (B as [N][K]): decode steps, a handful of tokens.
-// Such a call reads N x K weights once and does next to nothing with them, so it is bound by how many bytes the
+// GEMM with little to do for each work-group: few rows against weights as a linear layer stores them (B as [N][K]; decode
+// steps, a handful of tokens), and small outputs of either layout of B.
+// A call of few rows reads N x K weights once and does next to nothing with them, so it is bound by how many bytes the
 // whole chip has in flight.  The main kernel's tiles give it too few work-groups (64 of 64 x 64 for 4096 columns) that
 // each walk all of K through a ring of LDS stages with a barrier per step.  Here a work-group owns 16 NT columns and
 // its NW waves split K between them, 64 values at a time in turn.  Each wave has a ring of S stages in LDS to itself,
@@ -20,14 +21,54 @@ __device__ __forceinline__ f32x4_t mfma_skinny(u32x4_t a, u32x4_t b, f32x4_t c)
     else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
+// LDS layout of a block of a [K][N] operand: 64 K-rows of 16 NT columns as in memory, the 16-byte piece c of K-row k at
+// position c ^ swz_cols(k).  A transposing read takes 4 K-rows x 32 bytes per 16 lanes: rows of 128 bytes (NT = 4) would put
+// the four into the same banks, so they are spread over the four 32-byte slots of a row; shorter rows are apart as they are.
+template <int NT> __device__ __forceinline__ int swz_cols(int k) { return NT == 4 ? (k & 3) << 1 : 0; }
+// The fragments of such a block: [column tile][32 K-values], lane (r16, q) gets K-values 8q .. 8q + 7 of column r16.  Reads
+// and wait in one statement: the compiler does not track what inline assembly loads.  (Through the builtin it would wait for
+// all loads into LDS before each read.)
+template <int NT>
+__device__ __forceinline__ void columns_of(uint32_t block, int lane, u32x4_t (&f)[NT][2])
+{
+    const int q = lane >> 4, jj = (lane >> 2) & 3, c = lane & 3;
+    const uint32_t row = block + (8 * q + jj) * (NT * 32) + (c & 1) * 8;
+    u32x2_t lo[NT][2], hi[NT][2];
+    uint32_t at[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) at[j] = row + (((2 * j + (c >> 1)) ^ swz_cols<NT>(jj)) << 4);
+    constexpr int ROW4 = 4 * NT * 32, ROW32 = 32 * NT * 32;      // 4 K-rows on: the lane's upper half; 32: the second sub-step
+    if constexpr (NT == 1) {
+        asm volatile("ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:%5\n\tds_read_b64_tr_b16 %2, %4 offset:%6\n\t"
+                     "ds_read_b64_tr_b16 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo[0][0]), "=&v"(hi[0][0]), "=&v"(lo[0][1]), "=&v"(hi[0][1])
+                     : "v"(at[0]), "n"(ROW4), "n"(ROW32), "n"(ROW32 + ROW4) : "memory");
+    } else {
+#pragma unroll
+        for (int j = 0; j < NT; j += 2)
+            asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%10\n\tds_read_b64_tr_b16 %2, %8 offset:%11\n\t"
+                         "ds_read_b64_tr_b16 %3, %8 offset:%12\n\tds_read_b64_tr_b16 %4, %9\n\tds_read_b64_tr_b16 %5, %9 offset:%10\n\t"
+                         "ds_read_b64_tr_b16 %6, %9 offset:%11\n\tds_read_b64_tr_b16 %7, %9 offset:%12\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(lo[j][0]), "=&v"(hi[j][0]), "=&v"(lo[j][1]), "=&v"(hi[j][1]),
+                           "=&v"(lo[j + 1][0]), "=&v"(hi[j + 1][0]), "=&v"(lo[j + 1][1]), "=&v"(hi[j + 1][1])
+                         : "v"(at[j]), "v"(at[j + 1]), "n"(ROW4), "n"(ROW32), "n"(ROW32 + ROW4) : "memory");
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) f[j][kk] = u32x4_t{lo[j][kk].x, lo[j][kk].y, hi[j][kk].x, hi[j][kk].y};
+}
+
 // MT x NT tiles of 16 x 16; gated: the first NT / 2 column tiles are gate columns, the others the same up columns.
-template <int MT, int NT, int NW, int S, bool F16>
+// STREAM: B is asked for as non-temporal data, which leaves no copy of it in the memory-side cache (see kStreamBytes).
+template <int MT, int NT, int NW, int S, bool TRANS_B, bool STREAM, bool F16>
 __global__ void __launch_bounds__(64 * NW)
 skinny_kernel(const GemmArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)      // the host pass only needs the kernel's symbol
     constexpr int STAGE = (MT + NT) * 2048, L = (MT + NT) * 2;       // bytes and loads of a stage
     static_assert((S - 1) * L <= 63, "vmcnt range");
+    constexpr int kPolicyB = STREAM ? 2 : 0;                         // cache-policy bit nt
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     f32x4_t *const sums = (f32x4_t *)smem;                           // [tile][wave][lane], once the rings are done with
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -48,13 +89,28 @@ skinny_kernel(const GemmArgs p)
     };
     const int chunk = (lane & 7) ^ (lane >> 3);
     const __amdgpu_buffer_rsrc_t rsrc_a = rsrc_of(p.A + z * p.stride_a, m0, p.M - m0, p.lda, 16 * MT);
-    const __amdgpu_buffer_rsrc_t rsrc_b = rsrc_of(p.B + z * p.stride_b, n0, nout - n0, p.ldb, 16 * OT);
-    const __amdgpu_buffer_rsrc_t rsrc_u = rsrc_of((gated ? p.B_up : p.B) + z * p.stride_b, n0, nout - n0, p.ldb, 16 * OT);
+    __amdgpu_buffer_rsrc_t rsrc_b, rsrc_u;
     uint32_t va[2 * MT], vb[2 * NT];
 #pragma unroll
     for (int i = 0; i < 2 * MT; ++i) va[i] = (uint32_t)(((8 * i + (lane >> 3)) * p.lda + chunk * 8) * 2);
+    // B as [K][N]: a block's 64 K-rows of 16 NT columns, RPL rows to a load; the descriptor moves with the block, so that its
+    // range ends with the last K-row, and pieces past the last column are pushed beyond it (N is a multiple of 8).
+    constexpr int CPR = 2 * NT, RPL = 64 / CPR;              // 16-byte pieces of a K-row, K-rows of a load
+    const char *slab = nullptr;
+    int64_t slab_bytes = 0;
+    if constexpr (TRANS_B) {
+        rsrc_b = rsrc_of(p.B + z * p.stride_b, n0, nout - n0, p.ldb, 16 * OT);
+        rsrc_u = rsrc_of((gated ? p.B_up : p.B) + z * p.stride_b, n0, nout - n0, p.ldb, 16 * OT);
 #pragma unroll
-    for (int j = 0; j < 2 * NT; ++j) vb[j] = (uint32_t)(((8 * (gated && j >= NT ? j - NT : j) + (lane >> 3)) * p.ldb + chunk * 8) * 2);
+        for (int j = 0; j < 2 * NT; ++j) vb[j] = (uint32_t)(((8 * (gated && j >= NT ? j - NT : j) + (lane >> 3)) * p.ldb + chunk * 8) * 2);
+    } else {
+        slab = (const char *)(p.B + z * p.stride_b + (int64_t)wave * 64 * p.ldb + n0);
+        slab_bytes = (int64_t)NW * 64 * p.ldb * 2;
+        const int nc = (lane % CPR) ^ swz_cols<NT>(lane / CPR);
+        const uint32_t past = n0 + nc * 8 < p.N ? 0u : kOobOffset;
+#pragma unroll
+        for (int j = 0; j < 2 * NT; ++j) vb[j] = (uint32_t)(((j * RPL + lane / CPR) * p.ldb + nc * 8) * 2) | past;
+    }
     const int blocks = (p.K + 63) >> 6;
     const int mine = blocks > wave ? (blocks - wave + NW - 1) / NW : 0;
     char *const ring = smem + wave * S * STAGE;
@@ -63,10 +119,17 @@ skinny_kernel(const GemmArgs p)
         const uint32_t beyond = i >= mine || k + chunk * 8 >= p.K ? kOobOffset : 0u;
         const int soff = i < mine ? k * 2 : 0;
         char *dst = ring + slot * STAGE;
+        if constexpr (!TRANS_B) {
+            const int rows = i < mine ? (p.K - k < 64 ? p.K - k : 64) : 0;
+            rsrc_b = __builtin_amdgcn_make_buffer_rsrc((void *)wave_uniform(slab + i * slab_bytes), 0,
+                                                       wave_uniform((uint32_t)(rows > 0 ? ((int64_t)(rows - 1) * p.ldb + (p.N - n0)) * 2 : 0)), kBufferFlags);
+#pragma unroll
+            for (int j = 0; j < 2 * NT; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, FACT_LDS_PTR(dst + (2 * MT + j) * 1024), 16, vb[j], 0, 0, kPolicyB);
+        } else
 #pragma unroll
         for (int j = 0; j < 2 * NT; ++j) {
-            if (gated && j >= NT) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_u, FACT_LDS_PTR(dst + (2 * MT + j) * 1024), 16, vb[j] | beyond, soff, 0, 2);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, FACT_LDS_PTR(dst + (2 * MT + j) * 1024), 16, vb[j] | beyond, soff, 0, 2);
+            if (gated && j >= NT) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_u, FACT_LDS_PTR(dst + (2 * MT + j) * 1024), 16, vb[j] | beyond, soff, 0, kPolicyB);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_b, FACT_LDS_PTR(dst + (2 * MT + j) * 1024), 16, vb[j] | beyond, soff, 0, kPolicyB);
         }
 #pragma unroll
         for (int t = 0; t < 2 * MT; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, FACT_LDS_PTR(dst + t * 1024), 16, va[t] | beyond, soff, 0, 0);
@@ -84,6 +147,8 @@ skinny_kernel(const GemmArgs p)
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * L) : "memory");
         load(i + S - 1, fill);
         const char *s = ring + slot * STAGE;
+        u32x4_t bt[TRANS_B ? 1 : NT][2];
+        if constexpr (!TRANS_B) columns_of<NT>((uint32_t)(size_t)FACT_LDS_PTR(s + MT * 2048), lane, bt);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             const int at = r16 * 128 + (((4 * kk + q) ^ (r16 & 7)) << 4);
@@ -91,7 +156,10 @@ skinny_kernel(const GemmArgs p)
 #pragma unroll
             for (int t = 0; t < MT; ++t) a[t] = *(const u32x4_t *)(s + t * 2048 + at);
 #pragma unroll
-            for (int j = 0; j < NT; ++j) b[j] = *(const u32x4_t *)(s + (MT + j) * 2048 + at);
+            for (int j = 0; j < NT; ++j) {
+                if constexpr (TRANS_B) b[j] = *(const u32x4_t *)(s + (MT + j) * 2048 + at);
+                else b[j] = bt[j][kk];
+            }
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -171,13 +239,13 @@ skinny_kernel(const GemmArgs p)
 #endif
 }
 
-template <int MT, int NT, int NW, int S, bool F16>
+template <int MT, int NT, int NW, int S, bool TRANS_B, bool STREAM, bool F16>
 static hipError_t launch_skinny_as(const GemmArgs &a, int grid_z, hipStream_t stream)
 {
     const bool gated = a.act == ACT_SILU_GATE;
     const int nout = gated ? a.N / 2 : a.N, cols = 16 * (gated ? NT / 2 : NT);
     const dim3 grid((unsigned)((nout + (int64_t)cols - 1) / cols), (unsigned)((a.M + 16 * MT - 1) / (16 * MT)), (unsigned)grid_z);
-    auto kern = skinny_kernel<MT, NT, NW, S, F16>;
+    auto kern = skinny_kernel<MT, NT, NW, S, TRANS_B, STREAM, F16>;
     constexpr int lds = NW * S * (MT + NT) * 2048;
     static_assert(lds <= 160 * 1024 && MT * NT * 1024 <= S * (MT + NT) * 2048, "LDS: rings, then the waves' sums");
     if constexpr (lds > 64 * 1024) {
@@ -189,22 +257,38 @@ static hipError_t launch_skinny_as(const GemmArgs &a, int grid_z, hipStream_t st
     return hipGetLastError();
 }
 
-template <int MT, int NT, int NW, int S>
+// B larger than this is asked for as non-temporal data (us per feed-forward block of 16 rows, three sets of weights in turn,
+// cached -> non-temporal; megabytes of the two products' weights: 24 x 2 4096 x 14336, 352 MB: 73.3 -> 70.7; 2048 x 5632, 69 MB: 17.7 ->
+// 23.0; 1024 x 4096, 17 MB: 10.4 -> 12.0; 768 x 3072: 8.8 -> 10.4).  A fourth of the memory-side cache: several such matrices
+// are found there again, larger ones push each other out.
+constexpr int64_t kStreamBytes = (int64_t)64 << 20;
+static bool streams(const GemmArgs &a, int64_t batch) { return (int64_t)a.N * a.K * 2 * batch > kStreamBytes; }
+
+template <int MT, int NT, int NW, int S, bool TRANS_B, bool STREAM>
 static hipError_t launch_tile(const GemmArgs &a, int grid_z, hipStream_t stream)
 {
-    return a.f16 ? launch_skinny_as<MT, NT, NW, S, true>(a, grid_z, stream) : launch_skinny_as<MT, NT, NW, S, false>(a, grid_z, stream);
+    return a.f16 ? launch_skinny_as<MT, NT, NW, S, TRANS_B, STREAM, true>(a, grid_z, stream) : launch_skinny_as<MT, NT, NW, S, TRANS_B, STREAM, false>(a, grid_z, stream);
 }
 
-// One 16-column tile per work-group (two for gated calls, one of each half, and for many columns of 17-32 rows: half the
-// reads of A); four waves and three or four stages, so that two or three work-groups share a compute unit.  Up to 64 rows
-// eight waves and all of the LDS.
 struct Tile { int mt, nt, waves, stages; };
-static Tile tile_of(const GemmArgs &a)
+static constexpr Tile kTiles[] = {{1, 1, 4, 4}, {2, 1, 4, 3}, {2, 2, 4, 2}, {1, 2, 4, 4}, {1, 4, 4, 3}, {4, 1, 8, 2}, {2, 2, 4, 4}, {1, 2, 4, 3}};
+static int64_t groups_of(const Tile &t, const GemmArgs &a, int64_t batch)
 {
-    if (a.act == ACT_SILU_GATE) return a.M <= 16 ? Tile{1, 2, 4, 3} : Tile{2, 2, 4, 4};
-    if (a.M <= 16) return {1, 1, 4, 4};
-    if (a.M <= 32) return a.N > 6144 ? Tile{2, 2, 4, 4} : Tile{2, 1, 4, 3};
-    return {4, 1, 8, 2};
+    const bool gated = a.act == ACT_SILU_GATE;
+    const int64_t cols = 16 * (gated ? t.nt / 2 : t.nt), nout = gated ? a.N / 2 : a.N;
+    return (nout + cols - 1) / cols * (((int64_t)a.M + 16 * t.mt - 1) / (16 * t.mt)) * batch;
+}
+static int resident(const Tile &t) { return 160 * 1024 / (t.waves * t.stages * (t.mt + t.nt) * 2048); }       // work-groups of a compute unit
+
+// At most 64 rows (32 gated) of [N][K] weights, whatever their size: one 16-column tile per work-group (two for gated calls, one of
+// each half, and for many columns of 17-32 rows: half the reads of A); four waves and three or four stages, so that two or
+// three work-groups share a compute unit.  Up to 64 rows eight waves and all of the LDS.
+static int row_tile(const GemmArgs &a)
+{
+    if (a.act == ACT_SILU_GATE) return a.M <= 16 ? 7 : 6;
+    if (a.M <= 16) return 0;
+    if (a.M <= 32) return a.N > 6144 ? 6 : 1;
+    return 5;
 }
 
 // (a grid's threads are counted in 32 bits: 32 for each column here)
@@ -216,11 +300,11 @@ bool skinny_takes(const GemmArgs &a, bool trans_b) { return trans_b && a.M <= (a
 // are no whole 128-byte lines cost more: each 128-byte piece lies on two lines (16 x 4096 x 14336 24.0 us, K = 14344 32.6).
 double skinny_us(const GemmArgs &a, int64_t batch, bool whole_lines)
 {
-    const Tile t = tile_of(a);
+    const Tile &t = kTiles[row_tile(a)];
     const bool gated = a.act == ACT_SILU_GATE;
     const int nout = gated ? a.N / 2 : a.N, cols = 16 * (gated ? t.nt / 2 : t.nt);
-    const double wx = (double)((nout + (int64_t)cols - 1) / cols), wgs = wx * ((a.M + 16 * t.mt - 1) / (16 * t.mt)) * (double)batch;
-    const int fit = 160 * 1024 / (t.waves * t.stages * (t.mt + t.nt) * 2048), blocks = (int)(((int64_t)a.K + 63) / 64);
+    const double wx = (double)((nout + (int64_t)cols - 1) / cols), wgs = (double)groups_of(t, a, batch);
+    const int fit = resident(t), blocks = (int)(((int64_t)a.K + 63) / 64);
     const double rounds = wgs > 256.0 * fit ? wgs / (256.0 * fit) : 1.0;
     const double sharing = wgs < 256.0 ? 1.0 : wgs / 256.0 < fit ? wgs / 256.0 : fit;
     const double rows_a = 0.5 * (16 * t.mt + (a.M < 16 * t.mt ? a.M : 16 * t.mt));       // (rows past M are not fetched, but their zeros are written)
@@ -230,12 +314,65 @@ double skinny_us(const GemmArgs &a, int64_t batch, bool whole_lines)
     return chain > memory ? chain : memory;
 }
 
-hipError_t launch_skinny_gemm(const GemmArgs &a, int grid_z, hipStream_t stream)
+// Small outputs of any number of rows and either layout of B, B from the caches: the tile with the least estimated microseconds,
+// among those whose work-groups are all resident at once.  Against the tile kernel, which such a call reaches with a fraction of
+// the compute units, a work-group here has a quarter of K per wave, no barrier in the loop, a start and an end 2 us shorter, and
+// there are more of them.  The estimate: 3 us, the K steps one after the other at 84 (B as [K][N]) or 108 GB/s per compute unit;
+// never faster than the 8.2 or 11.2 TB/s at which the L2s deliver what the work-groups ask for together, nor than B arrives
+// once in each XCD that asks for a piece of its lines (as [K][N], a work-group's 16 NT columns are a part of 128-byte lines).
+// Fitted to 900 calls of 1 to 1536 rows, 32 to 8192 columns, K of 64 to 8192 (mean error 9 and 12 %).
+double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
 {
-    const Tile t = tile_of(a);
-    if (t.mt == 4) return launch_tile<4, 1, 8, 2>(a, grid_z, stream);
-    if (t.mt == 2) return t.nt == 2 ? launch_tile<2, 2, 4, 4>(a, grid_z, stream) : launch_tile<2, 1, 4, 3>(a, grid_z, stream);
-    return t.nt == 2 ? launch_tile<1, 2, 4, 3>(a, grid_z, stream) : launch_tile<1, 1, 4, 4>(a, grid_z, stream);
+    double best = 0.0;
+    *tile = -1;
+    if (a.act == ACT_SILU_GATE || a.N > 8192 || streams(a, batch)) return best;
+    if (!trans_b && (int64_t)a.N * a.K >= 1 << 24) return best;      // (from 32 MB of [K][N] on both are bound by memory: 4 x 3928 x 7208 25.9 / 22.7, 3 x 7856 x 4152 17.8 / 18.7)
+    const int64_t blocks = ((int64_t)a.K + 63) / 64;
+    for (int i = 0; i < 5; ++i) {
+        const Tile &t = kTiles[i];
+        if (trans_b ? t.nt > t.mt : i == 1) continue;
+        const int64_t wgs = groups_of(t, a, batch);
+        const int fit = resident(t);
+        if (wgs > 256 * fit || ((int64_t)a.M + 16 * t.mt - 1) / (16 * t.mt) > 65535) continue;
+        const double sharing = wgs > 256 ? wgs / 256.0 : 1.0;
+        const double rows_a = 0.5 * (16 * t.mt + (a.M < 16 * t.mt ? a.M : 16 * t.mt));
+        const double cols = 16 * t.nt * (trans_b ? 1.0 : t.nt == 1 ? 1.48 : t.nt == 2 ? 1.25 : 1.0);       // (a line's lookups for less than a line)
+        double step = sharing * 128.0 * (blocks < t.waves ? blocks : t.waves) * (rows_a + cols) / (trans_b ? 107.7e3 : 83.6e3);
+        if (!trans_b && step < 0.2) step = 0.2;
+        const double chain = 3.07 + (trans_b ? 0.0015 : 0.002) * wgs + (blocks + t.waves - 1) / t.waves * step;
+        const int64_t wx = ((int64_t)a.N + 16 * t.nt - 1) / (16 * t.nt);
+        const double memory = 3.0 + (double)batch * a.K * 2.0 * (a.N * (trans_b ? 1.0 : 4.0 / t.nt) + (wx < 8 ? wx : 8) * (double)a.M) / (trans_b ? 4.42e6 : 5.38e6);
+        const double pull = 3.0 + (double)wgs * blocks * 128.0 * (rows_a + cols) / (trans_b ? 11.2e6 : 8.2e6);
+        double us = chain > memory ? chain : memory;
+        if (pull > us) us = pull;
+        if (*tile < 0 || us < best) { best = us; *tile = i; }
+    }
+    return best;
+}
+
+// tile: small_us's choice, or -1 for the tile of few rows (skinny_us)
+hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int tile, int grid_z, hipStream_t stream)
+{
+    const bool nt = streams(a, grid_z);
+    if (tile < 0) tile = row_tile(a);
+    if (!trans_b) {
+        switch (tile) {
+        case 0: return launch_tile<1, 1, 4, 4, false, false>(a, grid_z, stream);
+        case 2: return launch_tile<2, 2, 4, 2, false, false>(a, grid_z, stream);
+        case 3: return launch_tile<1, 2, 4, 4, false, false>(a, grid_z, stream);
+        case 4: return launch_tile<1, 4, 4, 3, false, false>(a, grid_z, stream);
+        default: return hipErrorInvalidConfiguration;
+        }
+    }
+    switch (tile) {
+    case 0: return nt ? launch_tile<1, 1, 4, 4, true, true>(a, grid_z, stream) : launch_tile<1, 1, 4, 4, true, false>(a, grid_z, stream);
+    case 1: return nt ? launch_tile<2, 1, 4, 3, true, true>(a, grid_z, stream) : launch_tile<2, 1, 4, 3, true, false>(a, grid_z, stream);
+    case 2: return launch_tile<2, 2, 4, 2, true, false>(a, grid_z, stream);
+    case 5: return nt ? launch_tile<4, 1, 8, 2, true, true>(a, grid_z, stream) : launch_tile<4, 1, 8, 2, true, false>(a, grid_z, stream);
+    case 6: return nt ? launch_tile<2, 2, 4, 4, true, true>(a, grid_z, stream) : launch_tile<2, 2, 4, 4, true, false>(a, grid_z, stream);
+    case 7: return nt ? launch_tile<1, 2, 4, 3, true, true>(a, grid_z, stream) : launch_tile<1, 2, 4, 3, true, false>(a, grid_z, stream);
+    default: return hipErrorInvalidConfiguration;
+    }
 }
 
 }  // namespace fact
