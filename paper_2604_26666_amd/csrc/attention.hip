@@ -13,11 +13,11 @@ int record_hip_failure(hipError_t e, const char *what);      // fact_api.hip: te
 
 namespace attn {
 
-template <int D, int NW>
+template <int D, int NW, int KG, int BKV>
 static hipError_t launch(AttnArgs a, hipStream_t stream)
 {
-    auto kern = attn_fwd_kernel<D, NW>;
-    constexpr int lds = 2 * 2 * 64 * D * 2;                   // two stages of a K and a V block
+    auto kern = attn_fwd_kernel<D, NW, KG, BKV>;
+    constexpr int lds = lds_bytes(D, NW, KG, BKV);
     static LdsLimit limit;
     const hipError_t e = raise_lds_limit(limit, lds, {(const void *)kern});
     if (e != hipSuccess) return e;
@@ -44,12 +44,50 @@ static hipError_t launch(AttnArgs a, hipStream_t stream)
     {
         const bool split = (a.Hq * a.B & 7) == 0;
         const int n = split ? a.total >> 3 : a.total, layer = split ? 32 : 256, layers = (n + layer - 1) / layer;
-        a.fold = a.causal && layers >= 2 && layers <= (D == 64 ? 3 : 2) ? (layers - 1) * layer : n;
+        a.fold = a.causal && layers >= 2 && layers <= (KG > 1 ? 1 : D == 64 ? 3 : 2) ? (layers - 1) * layer : n;
     }
     // (a grid's threads are counted in 32 bits: more than 2^20 work-groups go into further rows of the grid)
     a.grid_x = a.total > 1 << 20 ? 1 << 20 : a.total;
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.grid_x, (unsigned)(((int64_t)a.total + a.grid_x - 1) / a.grid_x)), dim3(NW * 64), lds, stream, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.grid_x, (unsigned)(((int64_t)a.total + a.grid_x - 1) / a.grid_x)), dim3(NW * KG * 64), lds, stream, a);
     return hipGetLastError();
+}
+
+// Which shape of work-group: query groups of 32, key groups, keys of a block.  With few work-groups, above all causal ones of
+// which the last walks all the keys, a launch lasts as long as its longest work-group, at one wave per SIMD: key groups shorten
+// that chain and put more waves on a compute unit, fewer queries per work-group make more of them; each costs more K and V from
+// the L2 per query.  Key blocks of 32 leave four waves per SIMD at head_dim 64 in place of three.  us, 4 x 1 x 64 -> the choice
+// (batch x tokens, query heads): head_dim 64 causal 1 x 616, 12 10.6 -> 6.8 (1 x 4 x 32), 1 x 2656, 16 36.2 -> 24.1 (2 x 2 x 64), 36 x 208, 12 14.7 -> 11.8
+// (4 x 1 x 32), full 1 x 509, 16 9.2 -> 6.5; head_dim 128 causal 1 x 1172, 16 24.1 -> 19.1, 1 x 1152, 32 27.0 -> 22.6 (2 x 2 x 32).
+// The estimate in us: a start, then the longer of one chain (`chain` per step of the longest work-group) and the chip's throughput
+// (`step` and `group` per step and work-group, over 256 compute units); with one key group, where work-groups of all lengths
+// share a compute unit, the two overlap badly (the fourth root of the fourth powers' sum).  Fitted to 460 calls, mean error
+// 6-8 %; a shape other than 4 x 1 x 64 is taken where it is 3 % below: over those calls 5.4 % (head_dim 64) and 1.5 % (128) faster, 10 % slower at
+// worst.  `resident`: work-groups of the chip at once (LDS); beyond that shapes with key groups do not serve.
+struct Shape { int nw, kg, bkv, resident; double start, chain, step, group; };
+static constexpr Shape kShapes64[4] = {{4, 1, 64, 0, 3.52, 0.775, 0.56, 1.36}, {4, 1, 32, 0, 3.46, 0.45, 0.289, 1.12},
+                                       {2, 2, 64, 512, 3.63, 0.932, 0.592, 1.734}, {1, 4, 32, 512, 3.4, 0.86, 0.404, 1.511}};
+static constexpr Shape kShapes128[3] = {{4, 1, 64, 0, 3.96, 1.07, 0.97, 1.91}, {2, 2, 32, 512, 4.29, 0.823, 0.55, 2.11},
+                                        {1, 4, 32, 256, 3.54, 1.61, 1.04, 3.4}};
+template <int N>
+static int choose(const AttnArgs &a, const Shape (&shapes)[N])
+{
+    if (a.T <= 64) return 0;                                 // (one key block: nothing to share)
+    const double pairs = (double)a.B * a.Hq;
+    int best = 0;
+    double least = 0.0;
+    for (int i = 0; i < N; ++i) {
+        const Shape &s = shapes[i];
+        const int bq = s.nw * 32, rows = s.kg * s.bkv;
+        const double blocks = (a.T + bq - 1) / bq, longest = (a.T + rows - 1) / rows;
+        if (s.resident && blocks * pairs > s.resident) continue;
+        // steps of all query blocks of a head: the first ends at key bq, the last at T
+        const double steps = a.causal ? blocks * (bq > rows ? (double)bq / rows + longest : 1.0 + longest) / 2.0 : blocks * longest;
+        const double x = longest * s.chain, y = pairs * (steps * s.step + blocks * s.group) / 256.0;
+        const double us = s.start + (s.kg > 1 ? (x > y ? x : y) : std::sqrt(std::sqrt(x * x * x * x + y * y * y * y)));
+        if (i == 0) least = 0.97 * us;
+        else if (us < least) { least = us; best = i; }
+    }
+    return best;
 }
 
 }  // namespace attn
@@ -95,6 +133,20 @@ extern "C" int fact_attention(int64_t batch, int64_t T, int64_t n_q_heads, int64
     a.q_blocks = 0; a.total = 0; a.grid_x = 0; a.group = 1; a.fold = 0;
 
     hipStream_t s = (hipStream_t)stream;
-    const hipError_t e = head_dim == 128 ? launch<128, 4>(a, s) : launch<64, 4>(a, s);
+    hipError_t e;
+    if (head_dim == 128) {
+        switch (choose(a, kShapes128)) {
+        case 0: e = launch<128, 4, 1, 64>(a, s); break;
+        case 1: e = launch<128, 2, 2, 32>(a, s); break;
+        default: e = launch<128, 1, 4, 32>(a, s); break;
+        }
+    } else {
+        switch (choose(a, kShapes64)) {
+        case 0: e = launch<64, 4, 1, 64>(a, s); break;
+        case 1: e = launch<64, 4, 1, 32>(a, s); break;
+        case 2: e = launch<64, 2, 2, 64>(a, s); break;
+        default: e = launch<64, 1, 4, 32>(a, s); break;
+        }
+    }
     return e == hipSuccess ? FACT_OK : fact::record_hip_failure(e, "attention launch");
 }

@@ -7,8 +7,10 @@
 //
 // Shape of the computation
 //   A work-group owns BQ = NW * 32 consecutive queries of one (batch, query head), a wave 32 of
-//   them.  Keys and values are walked in blocks of 64, staged in LDS (double-buffered, global->LDS
-//   direct loads) and shared by the waves.  Everything is computed TRANSPOSED so that a lane owns
+//   them.  Keys and values are walked in blocks of BKV (64 or 32), staged in LDS (double-buffered, global->LDS
+//   direct loads) and shared by the waves.  With KG key groups each 32 queries have KG waves, which take the blocks of a
+//   step (KG of them) one each and add their sums up at the end: a shorter chain where a launch has few work-groups
+//   (the rule and its figures stand at the launch).  Everything is computed TRANSPOSED so that a lane owns
 //   pieces of ONE query:
 //     S^T (keys x queries) = K_block (A operand, rows = keys) x Q^T (B operand, columns = queries)
 //     O^T (d    x queries) = V_block^T (A operand, rows = d)  x P^T (B operand, columns = queries)
@@ -28,7 +30,7 @@
 //   10 issue cycles from its SIMD.  A wave does the two in turn, so what matters is that another wave
 //   of the SIMD is at the other: 32 queries per wave leave room for three waves per SIMD at
 //   head_dim 64 and two at 128, and a work-group's first loads and last stores are covered the
-//   same way.  Against 64 queries per wave, one wave per SIMD and scores of one block computed
+//   same way.  (Blocks of 32 keys need 110 registers at head_dim 64: four waves.)  Against 64 queries per wave, one wave per SIMD and scores of one block computed
 //   between the exponentials of another (which this kernel replaces at every size): 16 x 500 tokens,
 //   12 heads of 64: 33 -> 19.8 us; 8 x 1024 causal 31 -> 23; 4 x 1999 causal, 32 / 8 heads of 128:
 //   156 -> 144; 1 x 2048 61 -> 44; 1 x 8192 563 -> 507 (1085 TFLOP/s); 4 x 4096, 16 heads of 64, full,
@@ -129,26 +131,34 @@ template <int D> __device__ __forceinline__ int swz_vals(int row)
     else return ((row >> 1) & 1) << 2;
 }
 
-template <int D, int NW>
-__global__ void __launch_bounds__(NW * 64, D == 64 ? 3 : 2)
+// LDS of a work-group: two stages of the groups' K and V blocks, afterwards the sums that the key groups exchange
+constexpr int lds_bytes(int d, int nw, int kg, int bkv)
+{
+    const int stages = 2 * 2 * kg * bkv * d * 2, sums = d / 32 * (kg - 1) * nw * 4096 + nw * kg * 512;
+    return kg > 1 && sums > stages ? sums : stages;
+}
+
+template <int D, int NW, int KG, int BKV>
+__global__ void __launch_bounds__(NW * KG * 64, D == 64 && KG == 1 ? 3 : 2)
 attn_fwd_kernel(const AttnArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)      // the host pass only needs the kernel's symbol
     static_assert(D == 64 || D == 128, "head_dim");
-    constexpr int QW = 32, BQ = NW * QW;                       // queries per wave and per work-group
-    constexpr int BKV = 64, KT = BKV / 32, UB = BKV / 16;      // keys per block, its row tiles, 16-key groups
+    constexpr int QW = 32, BQ = NW * QW, NT = NW * KG;         // queries per wave and per work-group, waves
+    constexpr int KT = BKV / 32, UB = BKV / 16, ROWS = KG * BKV;       // a wave's key block: row tiles, 16-key groups; keys of a step
     constexpr int KS = D / 16, DT = D / 32;                    // 16-wide groups / 32-row tiles of head_dim
     constexpr int CPR = D / 8, ROWB = D * 2;                   // chunks and bytes per LDS row
-    constexpr int TILE_BYTES = BKV * ROWB, STAGE_BYTES = 2 * TILE_BYTES;
+    constexpr int TILE_BYTES = ROWS * ROWB, STAGE_BYTES = 2 * TILE_BYTES;
     constexpr int RPL = 1024 / ROWB;                           // rows per wave-wide load
-    constexpr int L = TILE_BYTES / 1024 / NW;                  // wave-wide loads per tile and wave
-    static_assert(L >= 1 && L * NW * 1024 == TILE_BYTES, "tile split over the waves");
-    static_assert(NW * RPL % 16 == 0, "a wave's pieces are whole swizzle periods apart");
+    constexpr int L = TILE_BYTES / 1024 / NT;                  // wave-wide loads per tile and wave
+    static_assert(L >= 1 && L * NT * 1024 == TILE_BYTES, "tile split over the waves");
+    static_assert(NT * RPL % 16 == 0 && BKV % 16 == 0, "a wave's pieces, and the groups' blocks, are whole swizzle periods apart");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qw = KG > 1 ? wave % NW : wave, kg = KG > 1 ? wave / NW : 0;      // the wave's queries, its key group
     const int r32 = lane & 31, h = lane >> 5;
 
     // Work-group -> (batch, key/value head, query head, query block).  Consecutive work-group ids go
@@ -181,15 +191,14 @@ attn_fwd_kernel(const AttnArgs p)
     const int kv = pair / G;
     const int b = kv / p.Hkv, hk = kv - b * p.Hkv;
     const int hq = hk * G + (pair - kv * G);
-    const int q0 = qb * BQ, q0w = q0 + wave * QW;
+    const int q0 = qb * BQ, q0w = q0 + qw * QW;
     const int T = p.T;
 
-    // key blocks this work-group walks, and how many of them this wave needs
+    // steps this work-group walks, and the keys this wave's queries see
     const int kend = p.causal ? (q0 + BQ < T ? q0 + BQ : T) : T;
-    const int nb = (kend + BKV - 1) / BKV;
-    int nbw = nb;
-    if (p.causal) { const int e = q0w + QW < T ? q0w + QW : T; nbw = (e + BKV - 1) / BKV; }
-    if (q0w >= T) nbw = 0;
+    const int nb = (kend + ROWS - 1) / ROWS;
+    int kend_w = p.causal && q0w + QW < T ? q0w + QW : T;
+    if (q0w >= T) kend_w = 0;
 
     auto make_rsrc = [&](const __bf16 *base, int64_t st) {
         return __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr((const char *)base), 0,
@@ -199,7 +208,7 @@ attn_fwd_kernel(const AttnArgs p)
     const __amdgpu_buffer_rsrc_t rsrc_k = make_rsrc(p.K + (int64_t)b * p.k_sb + (int64_t)hk * p.k_sh, p.k_st);
     const __amdgpu_buffer_rsrc_t rsrc_v = make_rsrc(p.V + (int64_t)b * p.v_sb + (int64_t)hk * p.v_sh, p.v_st);
 
-    // ---- K / V block loads: wave w fills the 1 KB pieces w, w + NW, ... of each tile -------------
+    // ---- K / V block loads: wave w fills the 1 KB pieces w, w + NT, ... of each tile -------------
     // Lane l of a wave-wide load writes 16 bytes at piece + 16 l, i.e. row l / CPR of the piece,
     // chunk position l % CPR: it fetches the chunk that belongs there under the swizzle.  Rows at
     // or beyond T lie outside the descriptor's range and arrive as zeros.  One per-lane offset serves
@@ -211,14 +220,14 @@ attn_fwd_kernel(const AttnArgs p)
         k_off = (uint32_t)(row * p.k_st * 2 + ((pos ^ swz_keys<D>(row)) << 4));
         v_off = (uint32_t)(row * p.v_st * 2 + ((pos ^ swz_vals<D>(row)) << 4));
     }
-    const uint32_t k_blk = (uint32_t)(BKV * p.k_st * 2), v_blk = (uint32_t)(BKV * p.v_st * 2);
-    const uint32_t k_piece = (uint32_t)(NW * RPL * p.k_st * 2), v_piece = (uint32_t)(NW * RPL * p.v_st * 2);
+    const uint32_t k_blk = (uint32_t)(ROWS * p.k_st * 2), v_blk = (uint32_t)(ROWS * p.v_st * 2);
+    const uint32_t k_piece = (uint32_t)(NT * RPL * p.k_st * 2), v_piece = (uint32_t)(NT * RPL * p.v_st * 2);
     auto load_block = [&](int j, int stage) __attribute__((always_inline)) {
         char *const dst = smem + stage * STAGE_BYTES + wave * 1024;
 #pragma unroll
-        for (int t = 0; t < L; ++t) load_to_lds_16(rsrc_k, dst + t * NW * 1024, k_off, j * k_blk + t * k_piece);
+        for (int t = 0; t < L; ++t) load_to_lds_16(rsrc_k, dst + t * NT * 1024, k_off, j * k_blk + t * k_piece);
 #pragma unroll
-        for (int t = 0; t < L; ++t) load_to_lds_16(rsrc_v, dst + TILE_BYTES + t * NW * 1024, v_off, j * v_blk + t * v_piece);
+        for (int t = 0; t < L; ++t) load_to_lds_16(rsrc_v, dst + TILE_BYTES + t * NT * 1024, v_off, j * v_blk + t * v_piece);
     };
     load_block(0, 0);
 
@@ -258,11 +267,12 @@ attn_fwd_kernel(const AttnArgs p)
         // next loads overwrite
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (j >= nbw) {                                          // nothing (more) this wave's queries may see
+        const int k0 = j * ROWS + kg * BKV;                      // the wave's key block
+        if (k0 >= kend_w) {                                      // nothing (more) this wave's queries may see
             if (j + 1 < nb) load_block(j + 1, stage ^ 1);
             return;
         }
-        const char *const kt_lds = smem + stage * STAGE_BYTES, *const vt_lds = kt_lds + TILE_BYTES;
+        const char *const kt_lds = smem + stage * STAGE_BYTES + kg * BKV * ROWB, *const vt_lds = kt_lds + TILE_BYTES;
         f32x16_t S[KT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
@@ -302,8 +312,8 @@ attn_fwd_kernel(const AttnArgs p)
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
 
-        if (p.causal ? (j * BKV + BKV - 1 > q0w) : (j * BKV + BKV > T)) {
-            const int last = (p.causal ? q0w + r32 : T - 1) - j * BKV - 4 * h;       // last key this query sees
+        if (p.causal ? (k0 + BKV - 1 > q0w) : (k0 + BKV > T)) {
+            const int last = (p.causal ? q0w + r32 : T - 1) - k0 - 4 * h;       // last key this query sees
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -362,7 +372,51 @@ attn_fwd_kernel(const AttnArgs p)
         step(j, 0);
         if (j + 1 < nb) step(j + 1, 1);
     }
-    if (nbw == 0) return;
+
+    // ---- the key groups' sums: group g finishes the d tiles g, g + KG, ... of its queries and gets the other groups' sums of them
+    // through LDS, with their reference exponents.  Added in ascending group order: the result is bit-reproducible.
+    if constexpr (KG > 1) {
+        typedef float f32x4_t __attribute__((ext_vector_type(4)));
+        f32x4_t *const tiles = (f32x4_t *)smem;                                    // [d tile][sender's rank][query group][quarter][lane]
+        f32x2_t *const refs = (f32x2_t *)(smem + DT * (KG - 1) * NW * 4096);       // [group][query group][lane]
+        static_assert(DT * (KG - 1) * NW * 4096 + NT * 512 <= lds_bytes(D, NW, KG, BKV), "LDS");
+        __syncthreads();                                                           // every wave is done with the key blocks
+        refs[(kg * NW + qw) * 64 + lane] = f32x2_t{m, l};
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+            if (dt % KG != kg) {
+                f32x4_t *const to = tiles + ((dt * (KG - 1) + (kg + KG - dt % KG) % KG - 1) * NW + qw) * 256 + lane;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) to[i * 64] = f32x4_t{o[dt][4 * i], o[dt][4 * i + 1], o[dt][4 * i + 2], o[dt][4 * i + 3]};
+            }
+        __syncthreads();
+        f32x2_t of[KG];
+        float m_all = m;
+#pragma unroll
+        for (int g = 0; g < KG; ++g) { of[g] = refs[(g * NW + qw) * 64 + lane]; m_all = fmaxf(m_all, of[g].x); }
+        l = 0.f;
+#pragma unroll
+        for (int g = 0; g < KG; ++g) { of[g].x = exp2_fast((of[g].x - m_all) * c); l += of[g].x * of[g].y; }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+            if (dt % KG == kg) {
+                f32x16_t sum;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+#pragma unroll
+                for (int g = 0; g < KG; ++g) {
+                    const f32x4_t *const from = tiles + ((dt * (KG - 1) + (g + KG - dt % KG) % KG - 1) * NW + qw) * 256 + lane;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const f32x4_t other = g == kg ? f32x4_t{o[dt][4 * i], o[dt][4 * i + 1], o[dt][4 * i + 2], o[dt][4 * i + 3]} : from[i * 64];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[4 * i + e] += of[g].x * other[e];
+                    }
+                }
+                o[dt] = sum;
+            }
+    }
+    if (q0w >= T) return;
 
     // ---- normalise and store: lane holds d = 32 dt + 8 g + 4 h + 0..3 (g = 0..3) of query q0w + r32; the two
     // lanes of a query trade halves, after which a lane holds 8 consecutive d -----------------------
@@ -370,7 +424,8 @@ attn_fwd_kernel(const AttnArgs p)
     const int query = q0w + r32;
     __bf16 *row = p.O + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + (int64_t)query * p.o_st + 8 * h;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int dt = 0; dt < DT; ++dt) {
+        if (KG > 1 && dt % KG != kg) continue;
 #pragma unroll
         for (int g = 0; g < 4; g += 2) {
             uint32_t w[2][2];
@@ -386,6 +441,7 @@ attn_fwd_kernel(const AttnArgs p)
             const auto hi = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
             if (query < T) *(u32x4_by8 *)(row + 32 * dt + 8 * g) = u32x4_t{(uint32_t)lo[0], (uint32_t)hi[0], (uint32_t)lo[1], (uint32_t)hi[1]};
         }
+    }
 #else
     (void)p;
 #endif

@@ -1,0 +1,45 @@
+"""fact_attention in every shape of work-group that its rule can choose (query groups x key groups x keys of a block), at lengths
+where a query group, a key block or a key group's share ends, some of them with key groups that see no key: against 64-bit
+attention, with the tolerance of test_gpu_attention.py."""
+import pytest
+import torch
+
+from test_gpu_attention_order import check, run, tensors
+
+pytestmark = pytest.mark.gpu
+
+# (B, T, Hq, Hkv, D): the shapes that few and many work-groups of these lengths take
+FULL = [(8, 97, 12, 12, 64), (3, 200, 32, 8, 64), (2, 127, 96, 96, 64)]                                      # 4 x 1 x 64
+SHORT = [(3, 65, 32, 8, 64), (8, 129, 12, 12, 64), (8, 160, 16, 4, 64), (3, 96, 32, 32, 64)]                 # 4 x 1 x 32
+PAIRS = [(2, 65, 32, 8, 64), (3, 97, 16, 16, 64), (2, 129, 32, 32, 64), (3, 200, 16, 4, 64), (2, 300, 32, 8, 64)]       # 2 x 2 x 64
+SINGLE = [(1, 65, 2, 1, 64), (1, 96, 4, 4, 64), (1, 97, 2, 2, 64), (2, 127, 4, 2, 64), (3, 129, 2, 2, 64), (1, 417, 2, 1, 64), (1, 900, 2, 2, 64)]       # 1 x 4 x 32
+WIDE = [(3, 97, 12, 4, 128), (8, 70, 16, 4, 128), (3, 127, 32, 8, 128)]                                      # head_dim 128: 4 x 1 x 64
+WIDE_PAIRS = [(1, 129, 2, 2, 128), (2, 160, 2, 1, 128), (3, 200, 12, 4, 128), (1, 257, 32, 8, 128)]          # 2 x 2 x 32
+WIDE_SINGLE = [(1, 65, 2, 1, 128), (1, 96, 2, 2, 128), (1, 97, 2, 2, 128), (3, 127, 2, 2, 128), (2, 65, 4, 4, 128)]     # 1 x 4 x 32
+
+
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("B,T,Hq,Hkv,D", FULL + SHORT + PAIRS + SINGLE + WIDE + WIDE_PAIRS + WIDE_SINGLE)
+def test_lengths(B, T, Hq, Hkv, D, causal):
+    q, k, v = tensors(B, T, Hq, Hkv, D, 21)
+    check(run(q, k, v, causal), q, k, v, causal, [(0, 0), (0, Hq - 1), (B - 1, Hq // 2)])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,T", [(2, 96), (2, 337), (32, 289)])
+@pytest.mark.parametrize("last", [False, True])
+def test_one_group_holds_all_the_weight(D, H, T, last):
+    # one key outweighs all others by far: the groups' reference exponents differ by hundreds, and all but one sum vanish
+    q, k, v = tensors(1, T, H, H, D, 23)
+    q.mul_(0.25)
+    k.mul_(0.25)
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    k[:, T - 1 if last else T // 2, :, 0] = 400.0
+    check(run(q, k, v, 0, 1.0), q, k, v, 0, [(0, 0), (0, H - 1)], 1.0)
+
+
+def test_the_same_bits_again():
+    for B, T, H, D in ((1, 900, 2, 64), (2, 300, 32, 64), (1, 257, 32, 128), (3, 127, 2, 128)):
+        q, k, v = tensors(B, T, H, H, D, 25)
+        assert torch.equal(run(q, k, v, 1).view(torch.int16), run(q, k, v, 1).view(torch.int16))
