@@ -157,6 +157,29 @@ def lib():
     return _lib
 
 
+_fast = None
+
+
+def _fast_calls():
+    """The launching calls' marshalling in C (csrc/pycall.cpp), bound to the loaded library's functions."""
+    global _fast
+    if _fast is None:
+        L = lib()
+        try:
+            from . import _pycall
+        except ImportError as e:
+            raise FactError(f"{e}: build it with `python -m paper_2604_26666_amd.build` (or __graft_entry__.build())") from e
+        import torch
+        try:
+            streams = (torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        except AttributeError:                               # (not part of torch's public interface)
+            streams = None
+        names = ("fact_gemm", "fact_gemm_batched", "fact_gemm_splitk", "fact_block_mlp", "fact_block_mlp_f16", "fact_attention", "fact_block_forward")
+        _pycall.init({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, Epilogue, Block, streams)
+        _fast = _pycall
+    return _fast
+
+
 def _addr(x):
     if x is None:
         return None
@@ -192,16 +215,25 @@ def check(rc, what="fact call"):
 
 
 def fact_gemm(M, N, K, A, lda, B, ldb, trans_b, C, ldc, ep=None, stream=None):
+    rc = (_fast or _fast_calls()).gemm(M, N, K, A, lda, B, ldb, trans_b, C, ldc, ep, stream)
+    if rc is not None:
+        return rc
     return lib().fact_gemm(M, N, K, _addr(A), lda, _addr(B), ldb, int(trans_b), _addr(C), ldc, _ep(ep), _stream(stream))
 
 
 def fact_gemm_batched(batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, C, ldc, stride_c,
                       ep=None, stream=None):
+    rc = (_fast or _fast_calls()).gemm_batched(batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, C, ldc, stride_c, ep, stream)
+    if rc is not None:
+        return rc
     return lib().fact_gemm_batched(batch, M, N, K, _addr(A), lda, stride_a, _addr(B), ldb, stride_b, int(trans_b),
                                    _addr(C), ldc, stride_c, _ep(ep), _stream(stream))
 
 
 def fact_gemm_splitk(M, N, K, A, lda, B, ldb, trans_b, C, ldc, ep, split_k, ws, ws_bytes, stream=None):
+    rc = (_fast or _fast_calls()).gemm_splitk(M, N, K, A, lda, B, ldb, trans_b, C, ldc, ep, split_k, ws, ws_bytes, stream)
+    if rc is not None:
+        return rc
     return lib().fact_gemm_splitk(M, N, K, _addr(A), lda, _addr(B), ldb, int(trans_b), _addr(C), ldc, _ep(ep),
                                   int(split_k), _addr(ws), int(ws_bytes), _stream(stream))
 
@@ -228,12 +260,18 @@ def fact_gemm_f32out_workspace_bytes(M, N, K, split_k):
 
 
 def fact_block_mlp(T, d_model, d_ff, X, W1, W1u, b1, act, W2, b2, R, H, Y, ws, ws_bytes, stream=None):
+    rc = (_fast or _fast_calls()).block_mlp(T, d_model, d_ff, X, W1, W1u, b1, act, W2, b2, R, H, Y, ws, ws_bytes, stream)
+    if rc is not None:
+        return rc
     return lib().fact_block_mlp(T, d_model, d_ff, _addr(X), _addr(W1), _addr(W1u), _addr(b1), int(act),
                                 _addr(W2), _addr(b2), _addr(R), _addr(H), _addr(Y), _addr(ws), int(ws_bytes),
                                 _stream(stream))
 
 
 def fact_block_mlp_f16(T, d_model, d_ff, X, W1, W1u, b1, act, W2, b2, R, H, Y, ws, ws_bytes, stream=None):
+    rc = (_fast or _fast_calls()).block_mlp_f16(T, d_model, d_ff, X, W1, W1u, b1, act, W2, b2, R, H, Y, ws, ws_bytes, stream)
+    if rc is not None:
+        return rc
     return lib().fact_block_mlp_f16(T, d_model, d_ff, _addr(X), _addr(W1), _addr(W1u), _addr(b1), int(act),
                                     _addr(W2), _addr(b2), _addr(R), _addr(H), _addr(Y), _addr(ws), int(ws_bytes),
                                     _stream(stream))
@@ -253,6 +291,9 @@ def fact_gemm_ex(batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, C,
 def fact_attention(batch, T, n_q_heads, n_kv_heads, head_dim, Q, q_strides, K, k_strides, V, v_strides,
                    O, o_strides, causal=1, scale=0.0, stream=None):
     """Strides are sequences of three element strides (batch entry, token, head)."""
+    rc = (_fast or _fast_calls()).attention(batch, T, n_q_heads, n_kv_heads, head_dim, Q, q_strides, K, k_strides, V, v_strides, O, o_strides, causal, scale, stream)
+    if rc is not None:
+        return rc
     arr = lambda s: (_i64 * 3)(*[int(x) for x in s])
     return lib().fact_attention(batch, T, n_q_heads, n_kv_heads, head_dim, _addr(Q), arr(q_strides), _addr(K), arr(k_strides),
                                 _addr(V), arr(v_strides), _addr(O), arr(o_strides), int(causal), float(scale), _stream(stream))
@@ -279,6 +320,9 @@ def fact_block_scratch_offsets(blk):
 
 
 def fact_block_forward(blk, X, Y, scratch, scratch_bytes, stream=None):
+    rc = (_fast or _fast_calls()).block_forward(blk, X, Y, scratch, scratch_bytes, stream)
+    if rc is not None:
+        return rc
     return lib().fact_block_forward(ctypes.byref(blk._c()), _addr(X), _addr(Y), _addr(scratch), int(scratch_bytes), _stream(stream))
 
 

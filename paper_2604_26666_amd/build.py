@@ -7,12 +7,14 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfact_gemm.so")
+PYCALL = os.path.join(HERE, "_pycall.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -197,11 +199,19 @@ def write_acc_regs(path=os.path.join(CSRC, "acc_regs.inc")):
     return path
 
 
+def build_pycall(path=PYCALL):
+    """The binding's argument marshalling (csrc/pycall.cpp): host code for the running interpreter."""
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "pycall.cpp"), "-o", path])
+    return path
+
+
 def build(jobs=None, verbose=False, extra_flags=(), lib=LIB, obj_dir=OBJ):
     """extra_flags / lib / obj_dir exist for experiments (a variant library beside the product one)."""
     write_acc_regs()
     OBJ = obj_dir
     LIB = lib
+    build_pycall()
     FLAGS = list(globals()["FLAGS"]) + list(extra_flags)
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)

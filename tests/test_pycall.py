@@ -1,0 +1,136 @@
+"""The launching calls' argument marshalling in C against the general way through ctypes: both reach the library with the same
+arguments (a recording stand-in here, so no GPU), and what the first does not know goes the second way."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_26666_amd as fact
+from paper_2604_26666_amd import binding
+
+NAMES = ("fact_gemm", "fact_gemm_batched", "fact_gemm_splitk", "fact_block_mlp", "fact_block_mlp_f16", "fact_attention", "fact_block_forward")
+
+
+class General:
+    """In the place of the C functions: nothing is known, every call goes through ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+@pytest.fixture(scope="module")
+def recorded():
+    if not os.path.exists(fact.lib_path()):
+        from paper_2604_26666_amd import build
+        build.build()
+    real, fast = binding.lib(), binding._fast_calls()
+    calls, keep = [], []
+
+    def value(x):
+        if isinstance(x, ctypes.POINTER(binding._CEpilogue)):
+            return tuple(getattr(x[0], f) for f, _ in binding._CEpilogue._fields_) if x else None
+        if isinstance(x, ctypes.POINTER(binding._CBlock)):
+            return tuple(getattr(x[0], f) for f, _ in binding._CBlock._fields_)
+        if isinstance(x, ctypes.POINTER(ctypes.c_int64)):
+            return tuple(x[:3])
+        return x
+
+    class Stub:
+        pass
+
+    stub, table = Stub(), {}
+    for n in NAMES:
+        proto = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(real, n).argtypes)
+        f = proto(lambda *a, n=n: calls.append((n,) + tuple(value(x) for x in a)) or 7)
+        keep.append(f)
+        setattr(stub, n, f)
+        table[n] = ctypes.cast(f, ctypes.c_void_p).value
+    streams = (torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    fast.init(table, fact.Epilogue, fact.Block, streams)
+    binding._lib = stub
+
+    def run(name, *a, **k):
+        calls.clear()
+        out = []
+        for way in (fast, General()):
+            binding._fast = way
+            assert getattr(fact, name)(*a, **k) == 7
+            out.append(calls[-1])
+        assert len(calls) == 2
+        binding._fast = fast
+        return out
+
+    yield run
+    binding._lib, binding._fast = real, None
+    binding._fast_calls()
+
+
+T = lambda *s: torch.zeros(*s, dtype=torch.bfloat16)
+S = 0x7F00DEADBEE0
+
+
+def test_gemm(recorded):
+    A, B, C, bias = T(3, 5), T(5, 7), T(3, 7), T(7)
+    ep = fact.Epilogue(bias=bias, residual=C, ldr=7, stride_r=2 ** 40, act=1, out_f32=1, f16=1)
+    for e in (None, ep, fact.Epilogue(residual=0x1000)):
+        for tb in (0, 1, True):
+            one, two = recorded("fact_gemm", 3, 7, 5, A, 5, B, 7, tb, C, 7, e, S)
+            assert one == two and one[4] == A.data_ptr() and one[8] == int(tb) and one[12] == S
+    one, two = recorded("fact_gemm", -1, 2 ** 62, 0, None, 1, 2 ** 63 + 8, 1, 0, None, 1, stream=0)
+    assert one == two
+    one, two = recorded("fact_gemm_batched", 2, 3, 7, 5, A, 5, 15, B, 7, 35, 0, C, 7, 21, ep, S)
+    assert one == two and len(one) == 17
+    for split in (0, 9):
+        one, two = recorded("fact_gemm_splitk", 3, 7, 5, A, 5, B, 7, 0, C, 7, ep, split, bias, 2 ** 40, S)
+        assert one == two
+
+
+def test_blocks_and_attention(recorded):
+    t = [T(4) for _ in range(13)]
+    for name in ("fact_block_mlp", "fact_block_mlp_f16"):
+        one, two = recorded(name, 2, 3, 4, t[0], t[1], None, t[2], 1, t[3], t[4], None, t[5], t[6], t[7], 99, S)
+        assert one == two and one[0] == name
+    a = (1, 2, 3, 1, 64, t[0].data_ptr(), (1, 2, 3), t[1], [4, 5, 6], t[2], (7, 8, 9), t[3], (10, 11, 12))
+    one, two = recorded("fact_attention", *a, 0, 0.25, S)
+    assert one == two and one[7] == (1, 2, 3) and one[13] == (10, 11, 12)
+    one, two = recorded("fact_attention", *a, stream=S)
+    assert one == two
+    names = ("norm1_g", "norm1_b", "Wqkv", "bqkv", "Wo", "bo", "norm2_g", "norm2_b", "W1", "W1u", "b1", "W2", "b2")
+    b = fact.Block(1, 2, 3, 4, 5, 64, 7, 1, 2, rope=1, eps=1e-5, rope_base=500000.0, **dict(zip(names, t)))
+    some = fact.Block(1, 2, 3, 4, 5, 64, 7, 0, 1, Wqkv=t[0], Wo=None, b2=0x2000)
+    for blk in (b, some):
+        one, two = recorded("fact_block_forward", blk, t[0], t[1], t[2], 77, S)
+        assert one == two and one[0] == "fact_block_forward"
+
+
+def test_what_c_does_not_know_goes_through_ctypes(recorded):
+    A = T(4)
+
+    class Wrapped:                                           # data_ptr() of a number that is no int
+        def data_ptr(self):
+            return np.int64(A.data_ptr())
+
+    class Stream:
+        cuda_stream = S
+
+    class Ep(fact.Epilogue):
+        pass
+
+    one, two = recorded("fact_gemm", 3, 7, 5, Wrapped(), 5, A, 7, np.int32(1), A, 7, Ep(bias=A), Stream())
+    assert one == two and one[4] == A.data_ptr() and one[12] == S and one[8] == 1
+    one, two = recorded("fact_attention", 1, 2, 3, 1, 64, A, np.array([1, 2, 3]), A, (4, 5, 6), A, (7, 8, 9), A, (10, 11, 12), 1, 1, S)
+    assert one == two and one[7] == (1, 2, 3)
+    one, two = recorded("fact_block_forward", fact.Block(1, 2, 3, 4, 5, 64, 7, 0, 1, eps=1, Wqkv=A), A, A, A, 77, S)
+    assert one == two
+
+
+def test_the_same_errors(recorded):
+    A = T(4)
+    for bad, error in (((3, 7, 5, "A", 5, A, 7, 1, A, 7), AttributeError), ((3.0, 7, 5, A, 5, A, 7, 1, A, 7), ctypes.ArgumentError),
+                       ((3, 7, 5, A, 5, A, 7, None, A, 7), TypeError)):
+        with pytest.raises(error):
+            fact.fact_gemm(*bad, None, S)
+    with pytest.raises(TypeError):
+        fact.fact_gemm(3, 7, 5, A)
