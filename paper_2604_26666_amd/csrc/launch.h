@@ -35,6 +35,10 @@ double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
 double small_us(const GemmArgs &args, bool trans_b, int64_t batch, int *tile);
 hipError_t launch_skinny_gemm(const GemmArgs &args, bool trans_b, int tile, int grid_z, hipStream_t stream);
 
+// The same kernel's form for operands of any alignment: its estimate with the tile that gives it (-1: none), the launch.
+double small_any_us(const GemmArgs &args, bool trans_b, int64_t batch, int *tile);
+hipError_t launch_small_any(const GemmArgs &args, bool trans_b, int tile, int grid_z, hipStream_t stream);
+
 // GEMM with operands of any alignment and size on the matrix cores (ragged.hip).
 bool ragged_serves(const GemmArgs &args, bool trans_b, int64_t batch);
 hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);

@@ -6,27 +6,9 @@
 // 1777 33.0 us, 2000 x 2000 x 1784 through the same kernel 30.9 us; the main kernel, which the latter takes, 24.4 us.
 #include "launch.h"
 #include "lds_limit.h"
+#include "shift_down.h"
 
 namespace fact {
-
-// 8 elements shifted down by s elements (element e <- element e + s), zeros from the top; s >= 8 gives zeros
-__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int s)
-{
-    const int w = s >> 1;
-    u32x4_t r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t x = 0;
-#pragma unroll
-        for (int j = i; j < 4; ++j) x = w == j - i ? v[j] : x;
-        r[i] = x;
-    }
-    if (s & 1) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = (r[i] >> 16) | (i < 3 ? r[i < 3 ? i + 1 : 3] << 16 : 0u);
-    }
-    return r;
-}
 
 template <bool F16>
 __device__ __forceinline__ f32x4_t mfma_any(bf16x8_t a, bf16x8_t b, f32x4_t c)
@@ -339,15 +321,38 @@ bool ragged_serves(const GemmArgs &a, bool trans_b, int64_t batch)
 //      1 x 4001 x 4001    64/1 26.3    64/4 20.5   32x64/1 23.1  32x64/4 16.5
 //   3850 x 1884 x   31   128/1 12.3   128/2 18.8    64/1 12.9
 //    858 x  133 x   33   128/1 11.6    64/1  5.4   32x64/1 4.4   32x64/4  6.5
+struct RaggedTile { int bm, bn, groups; };
+static RaggedTile ragged_tile(const GemmArgs &a, int64_t batch)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return (a.M + bm - 1) / bm * ((a.N + bn - 1) / bn) * batch; };
+    if (tiles(128, 128) >= 160) return {128, 128, a.K >= 512 && tiles(128, 128) < 512 ? 2 : 1};
+    if (tiles(64, 64) >= 160) return {64, 64, a.K >= 256 ? 2 : 1};
+    return {32, 64, a.K >= 768 ? 4 : 1};
+}
+
+// Its estimated microseconds where there are few work-groups (fitted to the calls of small_any_us, mean error 5 and 8 %).
+static double ragged_us(const GemmArgs &a, bool trans_b, int64_t batch)
+{
+    const RaggedTile t = ragged_tile(a, batch);
+    const double wgs = (double)((a.M + (int64_t)t.bm - 1) / t.bm * ((a.N + (int64_t)t.bn - 1) / t.bn) * batch);
+    const int64_t blocks = ((int64_t)a.K + 63) / 64;
+    const double load = (wgs > 256 ? wgs / 256.0 : 1.0) * 128.0 * t.groups * (t.bm + t.bn) / (trans_b ? 55.6e3 : 43.7e3);
+    const double step = !trans_b && load < 0.376 ? 0.376 : load;
+    return (trans_b ? 2.44 : 2.71) + 0.0021 * wgs + (trans_b ? 2.07 : 1.51) * t.bm * t.bn / 4096.0 + (double)((blocks + t.groups - 1) / t.groups) * step;
+}
+
+// Small outputs go to the kernel whose waves split K where that is the faster one by its estimate (us, this kernel -> that one; M x N x K: 1 x 34 x 1917
+// [N][K] 11.1 -> 4.9, 9 x 83 x 1443 [N][K] 9.0 -> 4.3, 273 x 53 x 3855 [K][N] 21.5 -> 10.7, 45 x 2916 x 3331 [N][K] 18.0 -> 12.8; but 304 x 3477 x 246 [N][K]
+// 6.4 -> 9.2, 137 x 3402 x 334 [K][N] 6.2 -> 8.6).  Over the 420 calls the choice is 1.23 times as fast, the better kernel of every call 1.25.
 hipError_t launch_ragged_gemm(const GemmArgs &a, bool trans_b, int grid_z, hipStream_t stream)
 {
-    auto tiles = [&](int64_t bm, int64_t bn) { return (a.M + bm - 1) / bm * ((a.N + bn - 1) / bn) * grid_z; };
-    if (tiles(128, 128) >= 160)
-        return a.K >= 512 && tiles(128, 128) < 512 ? launch_tile<128, 128, 2, 2, 2>(a, trans_b, grid_z, stream)
-                                                   : launch_tile<128, 128, 2, 2, 1>(a, trans_b, grid_z, stream);
-    if (tiles(64, 64) >= 160)
-        return a.K >= 256 ? launch_tile<64, 64, 2, 2, 2>(a, trans_b, grid_z, stream) : launch_tile<64, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
-    return a.K >= 768 ? launch_tile<32, 64, 2, 2, 4>(a, trans_b, grid_z, stream) : launch_tile<32, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+    int small = -1;
+    const double us = small_any_us(a, trans_b, grid_z, &small);
+    if (small >= 0 && us < 0.96 * ragged_us(a, trans_b, grid_z)) return launch_small_any(a, trans_b, small, grid_z, stream);
+    const RaggedTile t = ragged_tile(a, grid_z);
+    if (t.bm == 128) return t.groups == 2 ? launch_tile<128, 128, 2, 2, 2>(a, trans_b, grid_z, stream) : launch_tile<128, 128, 2, 2, 1>(a, trans_b, grid_z, stream);
+    if (t.bm == 64) return t.groups == 2 ? launch_tile<64, 64, 2, 2, 2>(a, trans_b, grid_z, stream) : launch_tile<64, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+    return t.groups == 4 ? launch_tile<32, 64, 2, 2, 4>(a, trans_b, grid_z, stream) : launch_tile<32, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
 }
 
 }  // namespace fact

@@ -10,6 +10,7 @@
 // many are in flight: 16 x 4096 x 14336 took 38 and 33 us, this form 25.6 us.)
 #include "launch.h"
 #include "lds_limit.h"
+#include "shift_down.h"
 
 namespace fact {
 
@@ -57,6 +58,78 @@ __device__ __forceinline__ void columns_of(uint32_t block, int lane, u32x4_t (&f
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) f[j][kk] = u32x4_t{lo[j][kk].x, lo[j][kk].y, hi[j][kk].x, hi[j][kk].y};
+}
+
+// The waves' sums, added in ascending wave order (a fixed order: the result is bit-reproducible), the epilogue, the store.
+template <int MT, int NT, int NW, bool F16>
+__device__ __forceinline__ void finish(const GemmArgs &p, const f32x4_t (&acc)[MT][NT], f32x4_t *sums, int wave, int lane, int m0, int n0, int64_t z)
+{
+    const int r16 = lane & 15, q = lane >> 4;
+    const bool gated = p.act == ACT_SILU_GATE;
+    const int nout = gated ? p.N >> 1 : p.N;
+    const int OT = gated ? NT / 2 : NT;                      // output column tiles
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) sums[((t * NT + j) * NW + wave) * 64 + lane] = acc[t][j];
+    __syncthreads();
+    const uint16_t *res = p.res ? (const uint16_t *)(p.res + z * p.stride_r) : nullptr;
+    const uint16_t *bias = (const uint16_t *)p.bias;
+    for (int o = wave; o < MT * OT; o += NW) {
+        const int t = o / OT, j = o - t * OT;
+        const int m = m0 + 16 * t + r16, n = n0 + 16 * j + 4 * q;         // the lane's four columns
+        auto total = [&](int tile) __attribute__((always_inline)) {
+            f32x4_t v = sums[tile * NW * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += sums[(tile * NW + w) * 64 + lane];
+            return v;
+        };
+        f32x4_t v = total(t * NT + j);
+        if (gated) {
+            const f32x4_t u = total(t * NT + NT / 2 + j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = silu(v[e]) * u[e];
+        }
+        if (m >= p.M || n >= nout) continue;
+        const bool full = n + 4 <= nout;
+        if (full) {
+            if (bias) {
+                const u32x2_t w = *(const u32x2_any *)(bias + n);
+                v[0] += in16<F16>(w.x & 0xFFFFu); v[1] += in16<F16>(w.x >> 16); v[2] += in16<F16>(w.y & 0xFFFFu); v[3] += in16<F16>(w.y >> 16);
+            }
+            if (p.act == ACT_GELU_TANH) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
+            }
+            if (res) {
+                const u32x2_t w = *(const u32x2_any *)(res + (int64_t)m * p.ldr + n);
+                v[0] += in16<F16>(w.x & 0xFFFFu); v[1] += in16<F16>(w.x >> 16); v[2] += in16<F16>(w.y & 0xFFFFu); v[3] += in16<F16>(w.y >> 16);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (n + e >= nout) continue;
+                if (bias) v[e] += in16<F16>(bias[n + e]);
+                if (p.act == ACT_GELU_TANH) v[e] = gelu_tanh(v[e]);
+                if (res) v[e] += in16<F16>(res[(int64_t)m * p.ldr + n + e]);
+            }
+        }
+        if (p.c_f32) {
+            float *c = (float *)p.C + z * p.stride_c + (int64_t)m * p.ldc + n;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < nout) c[e] = v[e];
+        } else {
+            uint16_t *c = (uint16_t *)(p.C + z * p.stride_c) + (int64_t)m * p.ldc + n;
+            if (full) {
+                *(u32x2_any *)c = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < nout) c[e] = (uint16_t)out16<F16>(v[e]);
+            }
+        }
+    }
 }
 
 // MT x NT tiles of 16 x 16; gated: the first NT / 2 column tiles are gate columns, the others the same up columns.
@@ -170,73 +243,141 @@ skinny_kernel(const GemmArgs p)
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // loads past the last block still write LDS
     __syncthreads();
-
-    // the waves' sums, added in ascending wave order (a fixed order: the result is bit-reproducible)
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) sums[((t * NT + j) * NW + wave) * 64 + lane] = acc[t][j];
-    __syncthreads();
-    const uint16_t *res = p.res ? (const uint16_t *)(p.res + z * p.stride_r) : nullptr;
-    const uint16_t *bias = (const uint16_t *)p.bias;
-    for (int o = wave; o < MT * OT; o += NW) {
-        const int t = o / OT, j = o - t * OT;
-        const int m = m0 + 16 * t + r16, n = n0 + 16 * j + 4 * q;         // the lane's four columns
-        auto total = [&](int tile) __attribute__((always_inline)) {
-            f32x4_t v = sums[tile * NW * 64 + lane];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) v += sums[(tile * NW + w) * 64 + lane];
-            return v;
-        };
-        f32x4_t v = total(t * NT + j);
-        if (gated) {
-            const f32x4_t u = total(t * NT + NT / 2 + j);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = silu(v[e]) * u[e];
-        }
-        if (m >= p.M || n >= nout) continue;
-        const bool full = n + 4 <= nout;
-        if (full) {
-            if (bias) {
-                const u32x2_t w = *(const u32x2_any *)(bias + n);
-                v[0] += in16<F16>(w.x & 0xFFFFu); v[1] += in16<F16>(w.x >> 16); v[2] += in16<F16>(w.y & 0xFFFFu); v[3] += in16<F16>(w.y >> 16);
-            }
-            if (p.act == ACT_GELU_TANH) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
-            }
-            if (res) {
-                const u32x2_t w = *(const u32x2_any *)(res + (int64_t)m * p.ldr + n);
-                v[0] += in16<F16>(w.x & 0xFFFFu); v[1] += in16<F16>(w.x >> 16); v[2] += in16<F16>(w.y & 0xFFFFu); v[3] += in16<F16>(w.y >> 16);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (n + e >= nout) continue;
-                if (bias) v[e] += in16<F16>(bias[n + e]);
-                if (p.act == ACT_GELU_TANH) v[e] = gelu_tanh(v[e]);
-                if (res) v[e] += in16<F16>(res[(int64_t)m * p.ldr + n + e]);
-            }
-        }
-        if (p.c_f32) {
-            float *c = (float *)p.C + z * p.stride_c + (int64_t)m * p.ldc + n;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (n + e < nout) c[e] = v[e];
-        } else {
-            uint16_t *c = (uint16_t *)(p.C + z * p.stride_c) + (int64_t)m * p.ldc + n;
-            if (full) {
-                *(u32x2_any *)c = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n + e < nout) c[e] = (uint16_t)out16<F16>(v[e]);
-            }
-        }
-    }
+    finish<MT, NT, NW, F16>(p, acc, sums, wave, lane, m0, n0, z);
 #else
     (void)p;
 #endif
+}
+
+// The same for rows that start at any 2-byte address and any M, N, K of at least a piece (not gated): the pieces pass through
+// registers, D blocks of 64 K-values ahead, into an LDS block of the wave's own, still without a barrier until the sums meet.  A
+// piece that would cross the end of a row, or the last column of a [K][N] operand, is loaded so that it ends there and
+// moved down; K-values past K are zeros, so that every wave may run whole rounds of D blocks.
+template <int MT, int NT, int NW, int D, bool TRANS_B, bool F16>
+__global__ void __launch_bounds__(64 * NW)
+skinny_any_kernel(const GemmArgs p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int STAGE = (MT + NT) * 2048, CPR = 2 * NT, RPL = 64 / CPR;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int r16 = lane & 15, q = lane >> 4, K = p.K;
+    const int n0 = blockIdx.x * 16 * NT, m0 = blockIdx.y * 16 * MT;
+    const int64_t z = blockIdx.z;
+    // lane -> piece lane % 8 of rows lane / 8 + 8 i (K-contiguous), piece lane % CPR of K-rows lane / CPR + RPL j ([K][N]); rows past
+    // the edge repeat the last one: their results are not stored
+    const int kc = lane & 7;
+    const uint16_t *pa[2 * MT], *pb[TRANS_B ? 2 * NT : 1];
+#pragma unroll
+    for (int i = 0; i < 2 * MT; ++i) {
+        const int m = m0 + 8 * i + (lane >> 3);
+        pa[i] = (const uint16_t *)(p.A + z * p.stride_a) + (int64_t)(m < p.M ? m : p.M - 1) * p.lda;
+    }
+    int shift_n = 0;
+    if constexpr (TRANS_B) {
+#pragma unroll
+        for (int j = 0; j < 2 * NT; ++j) {
+            const int n = n0 + 8 * j + (lane >> 3);
+            pb[j] = (const uint16_t *)(p.B + z * p.stride_b) + (int64_t)(n < p.N ? n : p.N - 1) * p.ldb;
+        }
+    } else {
+        int n = n0 + (lane % CPR) * 8;
+        if (n > p.N - 8) { shift_n = n - (p.N - 8); n = p.N - 8; }
+        pb[0] = (const uint16_t *)(p.B + z * p.stride_b) + n;
+    }
+    const bool ragged_n = !TRANS_B && n0 + 16 * NT > p.N;
+    struct Block { u32x4_t a[2 * MT], b[2 * NT]; } r[D];
+    auto fetch = [&](Block &t, int i) __attribute__((always_inline)) {
+        const int k = (wave + i * NW) * 64, c = k + kc * 8, at = c < K - 8 ? c : K - 8;
+#pragma unroll
+        for (int j = 0; j < 2 * NT; ++j) {
+            if constexpr (TRANS_B) t.b[j] = *(const u32x4_any *)(pb[j] + at);
+            else {
+                const int row = k + j * RPL + lane / CPR;
+                t.b[j] = *(const u32x4_any *)(pb[0] + (int64_t)(row < K ? row : K - 1) * p.ldb);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 2 * MT; ++x) t.a[x] = *(const u32x4_any *)(pa[x] + at);
+    };
+    char *const s = smem + wave * STAGE;
+    auto put = [&](Block &t, int i) __attribute__((always_inline)) {
+        const int k = (wave + i * NW) * 64;
+        if (k + 64 > K) {
+            const int c = k + kc * 8, by = c < K - 8 ? 0 : c - (K - 8);
+#pragma unroll
+            for (int x = 0; x < 2 * MT; ++x) t.a[x] = shift_down(t.a[x], by);
+#pragma unroll
+            for (int j = 0; j < 2 * NT; ++j) {
+                if constexpr (TRANS_B) t.b[j] = shift_down(t.b[j], by);
+                else if (k + j * RPL + lane / CPR >= K) t.b[j] = u32x4_t{0u, 0u, 0u, 0u};
+            }
+        }
+        if (ragged_n) {
+#pragma unroll
+            for (int j = 0; j < 2 * NT; ++j) t.b[j] = shift_down(t.b[j], shift_n);
+        }
+        const int at = (lane >> 3) * 128 + ((kc ^ (lane >> 3)) << 4);        // (rows 8 apart: the same swizzle)
+#pragma unroll
+        for (int x = 0; x < 2 * MT; ++x) *(u32x4_t *)(s + x * 1024 + at) = t.a[x];
+#pragma unroll
+        for (int j = 0; j < 2 * NT; ++j) {
+            if constexpr (TRANS_B) *(u32x4_t *)(s + (2 * MT + j) * 1024 + at) = t.b[j];
+            else {
+                const int row = j * RPL + lane / CPR;
+                *(u32x4_t *)(s + MT * 2048 + row * (NT * 32) + (((lane % CPR) ^ swz_cols<NT>(row)) << 4)) = t.b[j];
+            }
+        }
+    };
+    f32x4_t acc[MT][NT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int blocks = (K + 63) >> 6;
+    const int mine = blocks > wave ? (blocks - wave + NW - 1) / NW : 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) fetch(r[d], d);
+    for (int i = 0; i < mine; i += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            put(r[d], i + d);
+            fetch(r[d], i + d + D);
+            u32x4_t bt[TRANS_B ? 1 : NT][2];
+            if constexpr (!TRANS_B) columns_of<NT>((uint32_t)(size_t)FACT_LDS_PTR(s + MT * 2048), lane, bt);
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const int at = r16 * 128 + (((4 * kk + q) ^ (r16 & 7)) << 4);
+                u32x4_t a[MT], b[NT];
+#pragma unroll
+                for (int t = 0; t < MT; ++t) a[t] = *(const u32x4_t *)(s + t * 2048 + at);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    if constexpr (TRANS_B) b[j] = *(const u32x4_t *)(s + (MT + j) * 2048 + at);
+                    else b[j] = bt[j][kk];
+                }
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) acc[t][j] = mfma_skinny<F16>(b[j], a[t], acc[t][j]);
+            }
+        }
+    }
+    __syncthreads();
+    finish<MT, NT, NW, F16>(p, acc, (f32x4_t *)smem, wave, lane, m0, n0, z);
+#else
+    (void)p;
+#endif
+}
+
+template <int MT, int NT, int NW, int D, bool TRANS_B, bool F16>
+static hipError_t launch_any_as(const GemmArgs &a, int grid_z, hipStream_t stream)
+{
+    const dim3 grid((unsigned)((a.N + (int64_t)16 * NT - 1) / (16 * NT)), (unsigned)((a.M + 16 * MT - 1) / (16 * MT)), (unsigned)grid_z);
+    constexpr int lds = NW * (MT + NT) * 2048;
+    static_assert(lds <= 64 * 1024 && MT * NT * 1024 <= (MT + NT) * 2048, "LDS: the waves' blocks, then their sums");
+    hipLaunchKernelGGL((skinny_any_kernel<MT, NT, NW, D, TRANS_B, F16>), grid, dim3(64 * NW), lds, stream, a);
+    return hipGetLastError();
 }
 
 template <int MT, int NT, int NW, int S, bool TRANS_B, bool STREAM, bool F16>
@@ -373,6 +514,41 @@ hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int tile, int gri
     case 7: return nt ? launch_tile<1, 2, 4, 3, true, true>(a, grid_z, stream) : launch_tile<1, 2, 4, 3, true, false>(a, grid_z, stream);
     default: return hipErrorInvalidConfiguration;
     }
+}
+
+// Operands of any alignment: the estimate of small_us with what loads at odd addresses reach (16 bytes per lane from half a
+// word run at 36 GB/s per compute unit, from whole words at 99), for a tile of 16 x 16 and one of 32 x 32; fitted to 445 calls of 1 to 3000
+// rows, 16 to 4096 columns, K of 16 to 4096 (mean error 6-9 %).
+struct AnyTile { int mt, nt; double start[2], group[2], latency[2], rate[2], pull[2]; };       // [B as [K][N], as [N][K]]
+static constexpr AnyTile kAnyTiles[2] = {{1, 1, {3.38, 3.25}, {0.0006, 0.0007}, {0.255, 0.196}, {42.6e3, 78.3e3}, {6.26e6, 10.5e6}},
+                                         {2, 2, {4.33, 3.87}, {0.0009, 0.0014}, {0.025, 0.012}, {59.1e3, 75.0e3}, {6.76e6, 9.6e6}}};
+double small_any_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
+{
+    double best = 0.0;
+    *tile = -1;
+    if (a.act == ACT_SILU_GATE) return best;
+    const int64_t blocks = ((int64_t)a.K + 63) / 64;
+    for (int i = 0; i < 2; ++i) {
+        const AnyTile &t = kAnyTiles[i];
+        const int64_t wgs = ((int64_t)a.N + 16 * t.nt - 1) / (16 * t.nt) * (((int64_t)a.M + 16 * t.mt - 1) / (16 * t.mt)) * batch;
+        if (wgs > 8192) continue;
+        const double rows = 128.0 * 16 * (t.mt + t.nt), sharing = wgs > 256 ? wgs / 256.0 : 1.0;
+        const double load = sharing * rows * (blocks < 4 ? blocks : 4) / t.rate[trans_b], step = load > t.latency[trans_b] ? load : t.latency[trans_b];
+        const double chain = t.start[trans_b] + t.group[trans_b] * wgs + (blocks + 3) / 4 * step, pull = t.start[trans_b] + (double)wgs * blocks * rows / t.pull[trans_b];
+        const double us = chain > pull ? chain : pull;
+        if (*tile < 0 || us < best) { best = us; *tile = i; }
+    }
+    return best;
+}
+
+hipError_t launch_small_any(const GemmArgs &a, bool trans_b, int tile, int grid_z, hipStream_t stream)
+{
+    auto pick = [&](auto tb, auto half) {
+        constexpr bool T = decltype(tb)::value, F16 = decltype(half)::value;
+        return tile == 0 ? launch_any_as<1, 1, 4, 2, T, F16>(a, grid_z, stream) : launch_any_as<2, 2, 4, 2, T, F16>(a, grid_z, stream);
+    };
+    if (a.f16) return trans_b ? pick(std::true_type{}, std::true_type{}) : pick(std::false_type{}, std::true_type{});
+    return trans_b ? pick(std::true_type{}, std::false_type{}) : pick(std::false_type{}, std::false_type{});
 }
 
 }  // namespace fact
