@@ -28,9 +28,37 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef u32x4_t u32x4_words __attribute__((aligned(4)));
+typedef uint32_t u32x3_words __attribute__((ext_vector_type(3), aligned(4)));
 typedef u32x4_t u32x4_any __attribute__((aligned(2)));       // 16 (8) bytes at any even address: global accesses may be unaligned
 typedef u32x2_t u32x2_any __attribute__((aligned(2)));
 typedef f32x4_t f32x4_any __attribute__((aligned(4)));
+
+// 8 elements of a row of C that begins at any 2-byte address.  A 16-byte store to half a word runs at less than half the rate of
+// one to a whole word (2048 x 8192 x 512, rows of 8193 elements: 32.3 us, of 8194: 22.1), so on such a row every lane
+// stores from its second element to the first one of the lane that holds the next 8 (follow): 32.3 -> 23.7 us, 4096 x 4096 x 1024
+// with rows of 4097 42.7 -> 33.5, 1024 x 50257 x 768 105 -> 94.  Where the wave's columns of the row begin and end (starts,
+// ends) the first element is stored by itself and the last 7 in two parts.  left: elements from here to the row's end.
+__device__ __forceinline__ void store_few(uint16_t *at, u32x4_t o, int from, int left)
+{
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+        if (e >= from && e < left) at[e] = (uint16_t)(o[e / 2] >> (16 * (e & 1)));
+}
+template <bool EDGE>
+__device__ __forceinline__ void store8_of_row(uint16_t *at, u32x4_t o, uint32_t follow, bool starts, bool ends, int left)
+{
+    const int odd = (int)((size_t)at >> 1 & 1);
+    u32x4_t w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_alignbit(e < 3 ? o[e < 3 ? e + 1 : 3] : follow, o[e], 16 * odd);
+    uint16_t *const to = at + odd;
+    if (!EDGE || left >= 8) {
+        if (odd && (ends || (EDGE && left == 8))) { *(u32x3_words *)to = u32x3_words{w[0], w[1], w[2]}; at[7] = (uint16_t)(o[3] >> 16); }
+        else *(u32x4_words *)to = w;
+    } else store_few(at, o, odd, left);
+    if (starts && odd && (!EDGE || left > 0)) at[0] = (uint16_t)o[0];
+}
 
 #define FACT_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
@@ -706,17 +734,19 @@ gemm_kernel(const GemmArgs p)
     };
     // The register path for C, bias or residual rows at any 2-byte address (odd leading dimensions such as a
     // vocabulary's 50257), and for rows of C that are not written through: the same exchange, then 16-byte
-    // accesses through pointers, which may be unaligned.
+    // stores through pointers, moved by one element along the row where that begins at half a word (store8_of_row).
     // What is added is looked at per group of columns at run time: one instance keeps the kernel's code small (it is
     // fetched once per tile, and cold code runs at the speed of its fetch).  The stores are ordinary ones, so that the
-    // XCD's L2 joins the pieces of a line.  1024 x 50257 x 768: 162 -> 129 us (the guarded path before; C with
-    // rows of 50256, 16-byte stores: 92 us).  Staging the rows through LDS and cutting them where their 16-byte pieces
-    // of memory begin, with the ends of the rows as single elements, took 143 us.
+    // XCD's L2 joins the pieces of a line.  1024 x 50257 x 768: 162 -> 129 us (the guarded path before).  Staging the rows
+    // through LDS and cutting them where their 16-byte pieces of memory begin, with the ends of the rows as single elements,
+    // took 143 us.
     // Edge tiles of such a C take it too, with every access guarded.  (In the LDS-staged general path, which a launch's interior
     // tiles do not run, they fetched cold code of their own: 3547 x 2369 x 328, of which a seventh of the tiles are edges, 31.9 us
     // when all tiles took that path, 33.7 when the edges alone did, 24.1 like this; 2726 x 30276 x 376 204, 156 and 124 us.)
-    auto reg_epilogue_any = [&](auto gated_tag, auto edge_tag) __attribute__((always_inline)) {
-        constexpr bool GATED = decltype(gated_tag)::value, EDGE = decltype(edge_tag)::value;
+    // (Rows at half a word run through instances of their own, not gated, the columns in descending order so that a lane's next
+    // element is there: as a branch of one instance they cost 4648 x 7208 x 64 on whole words 34.5 us for 32.7.)
+    auto reg_epilogue_any = [&](auto gated_tag, auto edge_tag, auto odd_tag) __attribute__((always_inline)) {
+        constexpr bool GATED = decltype(gated_tag)::value, EDGE = decltype(edge_tag)::value, ODD = decltype(odd_tag)::value;
         constexpr int OT = GATED ? NT / 2 : NT, NP = OT / 2;
         static_assert(OT % 2 == 0, "tiles are exchanged in pairs");
         const int n = n_wave + (q & 1) * 16 + (q >> 1) * 8;
@@ -740,6 +770,7 @@ gemm_kernel(const GemmArgs p)
         const int row = m_wave + r16;
         const __bf16 *rrow = has_res ? R + (int64_t)(m_wave + r16) * p.ldr + n : nullptr;
         __bf16 *crow = C + (int64_t)(m_wave + r16) * p.ldc + n;
+        const int next_lane = (((0x0132 >> (q * 4)) & 3) * 16 + r16) * 4;
         auto load_res = [&](int mt) __attribute__((always_inline)) {
             if (has_res) {
                 if (!EDGE || row + 16 * mt < p.M) {
@@ -754,8 +785,9 @@ gemm_kernel(const GemmArgs p)
             constexpr int mt = decltype(mt_)::value;
             if constexpr (EDGE && BN != 192) { if (m_wave + 16 * mt >= p.M) return; }           // (rows past the last one, for the whole wave)
             if constexpr (mt + 1 < MT) load_res(mt + 1);
+            uint32_t first = 0;
             static_for<NP>([&](auto pr_) __attribute__((always_inline)) {
-                constexpr int pr = decltype(pr_)::value;
+                constexpr int pr = ODD ? NP - 1 - decltype(pr_)::value : decltype(pr_)::value;
                 if constexpr (EDGE && BN != 192) { if (n_wave + 32 * pr >= nout) return; }      // (columns likewise)
                 f32x4_t x0 = AccTile<mt * NT + 2 * pr>::get(), x1 = AccTile<mt * NT + 2 * pr + 1>::get();
                 if constexpr (GATED) {
@@ -790,19 +822,17 @@ gemm_kernel(const GemmArgs p)
                     const f32x2_t f2 = {z[2 * e], z[2 * e + 1]};
                     o[e] = pack2<F16>(f2);     // round to nearest even
                 }
-                if constexpr (EDGE) {
-                    const int left = nout - (n + pr * 32);
-                    if (row + 16 * mt < p.M) {
-                        if (left >= 8) *(u32x4_any *)(crow + pr * 32) = o;
-                        else {
-                            uint16_t *at = (uint16_t *)(crow + pr * 32);
-#pragma unroll
-                            for (int e = 0; e < 7; ++e)
-                                if (e < left) at[e] = (uint16_t)(o[e / 2] >> (16 * (e & 1)));
-                        }
-                    }
-                } else {
-                    *(u32x4_any *)(crow + pr * 32) = o;
+                uint16_t *at = (uint16_t *)(crow + pr * 32);
+                const int left = EDGE ? nout - (n + pr * 32) : 9;
+                const bool live = !EDGE || row + 16 * mt < p.M;
+                if constexpr (ODD) {
+                    // (column order of the lanes: q = 0, 2, 1, 3, past the last one the next 32 columns' first, which is done already)
+                    const uint32_t follow = (uint32_t)__builtin_amdgcn_ds_bpermute(next_lane, (int)(q == 0 ? first : o[0]));
+                    first = o[0];
+                    if (live) store8_of_row<EDGE>(at, o, follow, pr == 0 && q == 0, pr == NP - 1 && q == 3, left);
+                } else if (live) {
+                    if (left >= 8) *(u32x4_any *)at = o;
+                    else store_few(at, o, 0, left);
                 }
             });
             crow += 16 * p.ldc;
@@ -816,10 +846,13 @@ gemm_kernel(const GemmArgs p)
             if constexpr (BN == 192) any = __builtin_expect(any, 0);
             if (any) {
                 const bool edge = e_m0 + BM > p.M || e_n0 + (gated ? BN / 2 : BN) > nout;
+                constexpr std::true_type T{};
+                constexpr std::false_type F{};
                 if constexpr (NT % 4 == 0) {
-                    if (gated) { if (edge) reg_epilogue_any(std::true_type{}, std::true_type{}); else reg_epilogue_any(std::true_type{}, std::false_type{}); return; }
+                    if (gated) { if (edge) reg_epilogue_any(T, T, F); else reg_epilogue_any(T, F, F); return; }
                 }
-                if (edge) reg_epilogue_any(std::false_type{}, std::true_type{}); else reg_epilogue_any(std::false_type{}, std::false_type{});
+                if ((p.ldc & 1) | ((size_t)C >> 1 & 1)) { if (edge) reg_epilogue_any(F, T, T); else reg_epilogue_any(F, F, T); }
+                else if (edge) reg_epilogue_any(F, T, F); else reg_epilogue_any(F, F, F);
                 return;
             }
         }

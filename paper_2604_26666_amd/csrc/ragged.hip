@@ -2,8 +2,9 @@
 // (odd leading dimensions, K or N no multiple of 8, unaligned pointers).  The main kernel moves operands
 // straight from global memory into LDS, which needs 16-byte aligned rows; here they pass through registers,
 // where a 16-byte global load may start at any 2-byte address (the unaligned-access mode that the compiler
-// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured cost of odd rows: 2000 x 1999 x
-// 1777 33.0 us, 2000 x 2000 x 1784 through the same kernel 30.9 us; the main kernel, which the latter takes, 24.4 us.
+// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured: 2000 x 1999 x 1777 34-35 us (rows that all
+// begin at whole words 29, all at half words 36-40); the main kernel on 2000 x 2000 x 1784 24.4.  Two steps of loads in flight,
+// with the order of loads and matrix products fixed, were slower (37.4), so the loop's order is the compiler's.
 #include "launch.h"
 #include "lds_limit.h"
 #include "shift_down.h"
@@ -67,10 +68,9 @@ ragged_kernel(const GemmArgs p)
     if constexpr (TRANS_B) {
 #pragma unroll
         for (int i = 0; i < B_LD; ++i) {
-            const int r = (tid >> 3) + 32 * i;               // LDS row; gated: a wave's rows are its gate columns, then the same up columns
-            const int in_wave = r % WTN, half = WTN / 2;
-            const int n = n0 + (gated ? (r / WTN) * half + in_wave % half : r);
-            const __bf16 *base = gated && in_wave >= half ? p.B_up : p.B;
+            const int r = (tid >> 3) + 32 * i;               // LDS row; gated: 16 gate columns, the same 16 up columns, and so on
+            const int n = n0 + (gated ? (r >> 5) * 16 + (r & 15) : r);
+            const __bf16 *base = gated && (r & 16) ? p.B_up : p.B;
             pb[i] = (const uint16_t *)(base + z * p.stride_b) + (int64_t)(n < nout ? n : nout - 1) * p.ldb;
         }
     } else {
@@ -183,27 +183,27 @@ ragged_kernel(const GemmArgs p)
         __syncthreads();
     }
 
-    // ---- sums of the K groups, through LDS: unit (i, j mod HT) of a wave tile (its tiles j and j + HT) is finished by
-    // group (i HT + j) mod KW, which adds the groups' sums in ascending order
+    // ---- sums of the K groups, through LDS: unit (i, j) of a wave tile (its tiles 2 j and 2 j + 1 of row i) is finished by
+    // group i mod KW, which adds the groups' sums in ascending order
     if constexpr (KW > 1) {
         f32x4_t *const sums = (f32x4_t *)smem;               // [unit][half][group][thread of the group]
 #pragma unroll
         for (int u = 0; u < MT * HT; ++u)
-            if (u % KW != group) {
-                sums[((u * 2 + 0) * KW + group) * 256 + tid] = acc[u / HT][u % HT];
-                sums[((u * 2 + 1) * KW + group) * 256 + tid] = acc[u / HT][u % HT + HT];
+            if (u / HT % KW != group) {
+                sums[((u * 2 + 0) * KW + group) * 256 + tid] = acc[u / HT][u % HT * 2];
+                sums[((u * 2 + 1) * KW + group) * 256 + tid] = acc[u / HT][u % HT * 2 + 1];
             }
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < MT * HT; ++u)
-            if (u % KW == group) {
+            if (u / HT % KW == group) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const f32x4_t own = acc[u / HT][u % HT + h * HT];
+                    const f32x4_t own = acc[u / HT][u % HT * 2 + h];
                     f32x4_t v = group == 0 ? own : sums[((u * 2 + h) * KW) * 256 + tid];
 #pragma unroll
                     for (int g = 1; g < KW; ++g) v += group == g ? own : sums[((u * 2 + h) * KW + g) * 256 + tid];
-                    acc[u / HT][u % HT + h * HT] = v;
+                    acc[u / HT][u % HT * 2 + h] = v;
                 }
             }
     }
@@ -213,48 +213,99 @@ ragged_kernel(const GemmArgs p)
     uint16_t *C = (uint16_t *)(p.C + z * p.stride_c);
     const uint16_t *bias = (const uint16_t *)p.bias;
     const int n_wave = n0 + wn * (gated ? WTN / 2 : WTN);
+    if (gated) {
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        if (gated && j >= HT) break;
-        const int n = n_wave + j * 16 + 4 * q;
-        const bool full = n + 4 <= nout;
-        float bv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (bias) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bv[e] = n + e < nout ? in16<F16>(bias[n + e]) : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (KW > 1 && (i * HT + j % HT) % KW != group) continue;
-            const int m = m0 + wm * WTM + i * 16 + r16;
+        for (int u = 0; u < MT * HT; ++u) {
+            if (KW > 1 && u / HT % KW != group) continue;
+            const int i = u / HT, j = u % HT, n = n_wave + j * 16 + 4 * q, m = m0 + wm * WTM + i * 16 + r16;
             if (m >= p.M || n >= nout) continue;
+            const bool full = n + 4 <= nout;
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                v[e] = acc[i][j][e];
-                if (gated) v[e] = silu(v[e]) * acc[i][j < HT ? j + HT : j][e];
-                if (bias) v[e] += bv[e];
-                if (p.act == ACT_GELU_TANH) v[e] = gelu_tanh(v[e]);
+                v[e] = silu(acc[i][2 * j][e]) * acc[i][2 * j + 1][e];
+                if (bias && n + e < nout) v[e] += in16<F16>(bias[n + e]);
             }
             if (res) {
                 const uint16_t *rp = res + (int64_t)m * p.ldr + n;
-                if (full) {
-                    const u32x2_t w = *(const u32x2_any *)rp;
-                    v[0] += in16<F16>(w.x & 0xFFFFu); v[1] += in16<F16>(w.x >> 16);
-                    v[2] += in16<F16>(w.y & 0xFFFFu); v[3] += in16<F16>(w.y >> 16);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (n + e < nout) v[e] += in16<F16>(rp[e]);
-                }
-            }
-            uint16_t *cp = C + (int64_t)m * p.ldc + n;
-            if (full) {
-                *(u32x2_any *)cp = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
-            } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
+                    if (n + e < nout) v[e] += in16<F16>(rp[e]);
+            }
+            uint16_t *cp = C + (int64_t)m * p.ldc + n;
+            if (full) *(u32x2_any *)cp = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
+            else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
                     if (n + e < nout) cp[e] = (uint16_t)out16<F16>(v[e]);
+            }
+        }
+        return;
+    }
+    // 8 columns of a row to a lane: two tiles' rows change places between lanes 16 apart; store8_of_row moves them to whole words
+    // (before: 4 columns at any 2-byte address, the bias element by element; with a bias 2000 x 1999 x 1777 36.9 -> 35.1 us,
+    // 1859 x 1658 x 92 13.1 -> 9.9, 1445 x 3347 x 349 23.7 -> 20.8, 3404 x 2085 x 34 without one 11.7 -> 10.6).
+    const int n = n_wave + (q & 1) * 16 + (q >> 1) * 8, next_lane = (((0x0132 >> (q * 4)) & 3) * 16 + r16) * 4;
+    const bool odd_rows = ((p.ldc & 1) | ((size_t)C >> 1 & 1)) != 0;
+    // 8 elements of which left lie inside the row (single ones at indexes kept inside it: behind a branch each would wait for the last)
+    auto load8 = [&](const uint16_t *from, int left) __attribute__((always_inline)) {
+        u32x4_t w = {0u, 0u, 0u, 0u};
+        if (left >= 8) w = *(const u32x4_any *)from;
+        else if (left > 0) {
+            uint32_t x[7];
+#pragma unroll
+            for (int e = 0; e < 7; ++e) x[e] = from[e < left ? e : 0];
+#pragma unroll
+            for (int e = 0; e < 7; ++e) w[e / 2] |= x[e] << (16 * (e & 1));
+        }
+        return w;
+    };
+    u32x4_t bv[HT];
+    if (bias) {
+#pragma unroll
+        for (int jh = 0; jh < HT; ++jh) bv[jh] = load8(bias + n + jh * 32, nout - (n + jh * 32));
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        if (KW > 1 && i % KW != group) continue;
+        const int m = m0 + wm * WTM + i * 16 + r16;
+        const bool live = m < p.M;
+        uint32_t first = 0;
+#pragma unroll
+        for (int jh = HT - 1; jh >= 0; --jh) {
+            const int nj = n + jh * 32, left = nout - nj;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float a0 = acc[i][2 * jh][e], a1 = acc[i][2 * jh + 1][e];
+                const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a0), __builtin_bit_cast(uint32_t, a1), false, false);
+                v[e] = __builtin_bit_cast(float, (uint32_t)sw[0]);
+                v[4 + e] = __builtin_bit_cast(float, (uint32_t)sw[1]);
+            }
+            if (bias) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += in16<F16>(bv[jh][e / 2] >> (16 * (e & 1)) & 0xFFFFu);
+            }
+            if (p.act == ACT_GELU_TANH) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = gelu_tanh(v[e]);
+            }
+            if (res && live) {
+                const u32x4_t w = load8(res + (int64_t)m * p.ldr + nj, left);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += in16<F16>(w[e / 2] >> (16 * (e & 1)) & 0xFFFFu);
+            }
+            u32x4_t o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = out16<F16>(v[2 * e]) | (out16<F16>(v[2 * e + 1]) << 16);
+            uint16_t *at = C + (int64_t)m * p.ldc + nj;
+            if (odd_rows) {
+                const uint32_t follow = (uint32_t)__builtin_amdgcn_ds_bpermute(next_lane, (int)(q == 0 ? first : o[0]));
+                first = o[0];
+                if (live) store8_of_row<true>(at, o, follow, jh == 0 && q == 0, jh == HT - 1 && q == 3, left);
+            } else if (live) {
+                if (left >= 8) *(u32x4_words *)at = o;
+                else store_few(at, o, 0, left);
             }
         }
     }
