@@ -507,7 +507,12 @@ hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int tile, int gri
     switch (tile) {
     case 0: return nt ? launch_tile<1, 1, 4, 4, true, true>(a, grid_z, stream) : launch_tile<1, 1, 4, 4, true, false>(a, grid_z, stream);
     case 1: return nt ? launch_tile<2, 1, 4, 3, true, true>(a, grid_z, stream) : launch_tile<2, 1, 4, 3, true, false>(a, grid_z, stream);
-    case 2: return launch_tile<2, 2, 4, 2, true, false>(a, grid_z, stream);
+    case 2:
+        // Where the work-groups have a compute unit each, two blocks ahead instead of one, from 2048 K-values on (us; one -> two; 256 x 512 x 8192
+        // 16.0 -> 13.3, 96 x 1536 x 4096 10.0 -> 8.5, 64 x 2048 x 2048 6.8 -> 6.2, 300 x 600 x 2048 7.8 -> 7.4; but 256 x 512 x 1024 4.2 -> 4.8, 128 x 1024 x 1024
+        // 4.1 -> 4.8; three: as two.  B as [K][N] has nothing of it: 256 x 512 x 8192 19.6 -> 20.0)
+        if (a.K >= 2048 && groups_of(kTiles[2], a, grid_z) <= 256) return launch_tile<2, 2, 4, 3, true, false>(a, grid_z, stream);
+        return launch_tile<2, 2, 4, 2, true, false>(a, grid_z, stream);
     case 5: return nt ? launch_tile<4, 1, 8, 2, true, true>(a, grid_z, stream) : launch_tile<4, 1, 8, 2, true, false>(a, grid_z, stream);
     case 6: return nt ? launch_tile<2, 2, 4, 4, true, true>(a, grid_z, stream) : launch_tile<2, 2, 4, 4, true, false>(a, grid_z, stream);
     case 7: return nt ? launch_tile<1, 2, 4, 3, true, true>(a, grid_z, stream) : launch_tile<1, 2, 4, 3, true, false>(a, grid_z, stream);
