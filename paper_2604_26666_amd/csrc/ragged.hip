@@ -2,8 +2,8 @@
 // (odd leading dimensions, K or N no multiple of 8, unaligned pointers).  The main kernel moves operands
 // straight from global memory into LDS, which needs 16-byte aligned rows; here they pass through registers,
 // where a 16-byte global load may start at any 2-byte address (the unaligned-access mode that the compiler
-// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured: 2000 x 1999 x 1777 34-35 us (rows that all
-// begin at whole words 29, all at half words 36-40); the main kernel on 2000 x 2000 x 1784 24.4.  Two steps of loads in flight,
+// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured: 2000 x 1999 x 1777 33.6 us (when it was
+// 35, rows that all begin at whole words took 29 and all at half words 36-40); the main kernel on 2000 x 2000 x 1784 24.4.  Two steps of loads in flight,
 // with the order of loads and matrix products fixed, were slower (37.4), so the loop's order is the compiler's.
 #include "launch.h"
 #include "lds_limit.h"
@@ -168,20 +168,37 @@ ragged_kernel(const GemmArgs p)
     const int steps = ((K + 63) / 64 + KW - 1) / KW;         // per group, the same for all
     Step r0, r1;
     load(r0, 0);
-    load(r1, 1);
+    if (steps > 1) load(r1, 1);
     to_lds(r0, 0);
     __syncthreads();
-    for (int i = 0; i < steps; i += 2) {
+    // (The last steps apart, so that nothing past them is loaded: loads are what bounds this kernel, and two steps' worth beyond the
+    // end, with the loop left in the middle, made 2000 x 1999 x 1777 35.2 us for 33.6, 1803 x 2101 x 301 12.6 for 12.0, 1207 x 1032 x 31 5.0
+    // for 4.3; the same with a condition at each load was slower than either, 36.5.)
+    int i = 0;
+    for (; i + 3 < steps; i += 2) {
         load(r0, i + 2);
         compute(0);
         to_lds(r1, i + 1);
         __syncthreads();
-        if (i + 1 >= steps) break;
         load(r1, i + 3);
         compute(1);
         to_lds(r0, i + 2);
         __syncthreads();
     }
+    const int rest = steps - i;                              // 1, 2 or 3
+    if (rest == 3) load(r0, i + 2);
+    compute(0);
+    if (rest > 1) {
+        to_lds(r1, i + 1);
+        __syncthreads();
+        compute(1);
+        if (rest == 3) {
+            to_lds(r0, i + 2);
+            __syncthreads();
+            compute(0);
+        }
+    }
+    __syncthreads();
 
     // ---- sums of the K groups, through LDS: unit (i, j) of a wave tile (its tiles 2 j and 2 j + 1 of row i) is finished by
     // group i mod KW, which adds the groups' sums in ascending order
