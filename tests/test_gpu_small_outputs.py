@@ -23,7 +23,8 @@ CASES = [(1, 8, 8, 0, "1x1"), (5, 216, 264, 0, "1x1"), (22, 168, 424, 0, "1x1"),
          (9, 104, 16, 0, "1x4"), (5, 344, 48, 0, "1x4"), (198, 312, 8, 0, "1x4"),
          (103, 8, 16, 1, "1x1"), (131, 33, 24, 1, "1x1"), (56, 137, 1160, 1, "1x1"),
          (273, 23, 24, 1, "2x1"), (26, 345, 112, 1, "2x1"), (54, 961, 352, 1, "2x1"),
-         (138, 1121, 8, 1, "2x2"), (26, 2705, 104, 1, "2x2"), (300, 481, 584, 1, "2x2"), (512, 512, 512, 0, "2x2")]
+         (138, 1121, 8, 1, "2x2"), (26, 2705, 104, 1, "2x2"), (300, 481, 584, 1, "2x2"), (512, 512, 512, 0, "2x2"),
+         (96, 1535, 2056, 1, "2x2"), (62, 2043, 2048, 1, "2x2")]         # (two blocks ahead)
 
 
 @pytest.mark.parametrize("M,N,K,nk,tile", CASES, ids=str)
