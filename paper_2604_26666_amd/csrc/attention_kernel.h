@@ -199,6 +199,7 @@ attn_fwd_kernel(const AttnArgs p)
     const int nb = (kend + ROWS - 1) / ROWS;
     int kend_w = p.causal && q0w + QW < T ? q0w + QW : T;
     if (q0w >= T) kend_w = 0;
+    const int nbw = (kend_w + BKV - 1) / BKV;                // without key groups: the steps this wave needs
 
     auto make_rsrc = [&](const __bf16 *base, int64_t st) {
         return __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr((const char *)base), 0,
@@ -268,7 +269,7 @@ attn_fwd_kernel(const AttnArgs p)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         const int k0 = j * ROWS + kg * BKV;                      // the wave's key block
-        if (k0 >= kend_w) {                                      // nothing (more) this wave's queries may see
+        if (KG > 1 ? k0 >= kend_w : j >= nbw) {                  // nothing (more) this wave's queries may see
             if (j + 1 < nb) load_block(j + 1, stage ^ 1);
             return;
         }
@@ -416,7 +417,7 @@ attn_fwd_kernel(const AttnArgs p)
                 o[dt] = sum;
             }
     }
-    if (q0w >= T) return;
+    if (KG > 1 ? q0w >= T : nbw == 0) return;
 
     // ---- normalise and store: lane holds d = 32 dt + 8 g + 4 h + 0..3 (g = 0..3) of query q0w + r32; the two
     // lanes of a query trade halves, after which a lane holds 8 consecutive d -----------------------
