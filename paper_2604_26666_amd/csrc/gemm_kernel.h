@@ -851,7 +851,7 @@ gemm_kernel(const GemmArgs p)
                 if constexpr (NT % 4 == 0) {
                     if (gated) { if (edge) reg_epilogue_any(T, T, F); else reg_epilogue_any(T, F, F); return; }
                 }
-                if ((p.ldc & 1) | ((size_t)C >> 1 & 1)) { if (edge) reg_epilogue_any(F, T, T); else reg_epilogue_any(F, F, T); }
+                if (__builtin_expect((p.ldc & 1) | ((size_t)C >> 1 & 1), 0)) { if (edge) reg_epilogue_any(F, T, T); else reg_epilogue_any(F, F, T); }
                 else if (edge) reg_epilogue_any(F, T, F); else reg_epilogue_any(F, F, F);
                 return;
             }
