@@ -237,6 +237,8 @@ size_t fact_block_mlp_workspace_bytes(int64_t T, int64_t d_model, int64_t d_ff, 
  * scale: the softmax scale; <= 0 selects 1 / sqrt(head_dim).
  * Arithmetic: scores and softmax in fp32 (base-2 exponentials), probabilities rounded to bf16
  * for the second contraction, fp32 accumulation, one rounding to bf16 at the store.
+ * Keys whose scaled scores are minus infinity, or below -2^31 / log2(e), weigh nothing, wherever they lie (callers mask
+ * keys through a spare element of the heads); a query of which all keys are such gets NaN.
  * O must not overlap Q, K or V.
  */
 int fact_attention(int64_t batch, int64_t T, int64_t n_q_heads, int64_t n_kv_heads, int64_t head_dim,

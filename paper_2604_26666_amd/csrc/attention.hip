@@ -4,6 +4,7 @@
 #include "attention_kernel.h"
 #include "lds_limit.h"
 
+#include <cfloat>
 #include <cmath>
 #include <cstdlib>
 
@@ -130,6 +131,7 @@ extern "C" int fact_attention(int64_t batch, int64_t T, int64_t n_q_heads, int64
     a.causal = causal;
     const float sc = scale > 0.f ? scale : 1.0f / std::sqrt((float)head_dim);
     a.scale_log2 = sc * 1.4426950408889634f;
+    a.lowest = std::fmax(-0x1p31f / a.scale_log2, -FLT_MAX);
     a.q_blocks = 0; a.total = 0; a.grid_x = 0; a.group = 1; a.fold = 0;
 
     hipStream_t s = (hipStream_t)stream;

@@ -63,6 +63,7 @@ struct AttnArgs {
     int B, T, Hq, Hkv;
     int causal;
     float scale_log2;       // softmax scale * log2(e)
+    float lowest;           // scores below it are masked keys' (see the reference exponent)
     int q_blocks;           // ceil(T / BQ)
     int total;              // q_blocks * Hq * B work-groups
     int grid_x;             // work-groups in a row of the grid, a multiple of 8 where there is more than one row
@@ -258,9 +259,13 @@ attn_fwd_kernel(const AttnArgs p)
     // lane has computed with it add up to more than kMaxSum (or to no number).  None of them is above
     // kMaxSum then, harmless in bf16 and fp32, and most key blocks need neither a maximum nor a rescaling:
     // 26 of 150 vector instructions of a block.  The branch is uniform over the wave.
+    // It is never below p.lowest = -2^31 / c, where m * c is rounded by more than the exponential can hold.  Callers mask keys through
+    // scores of minus infinity or of a type's lowest value, and all keys of a block, or of a key group, may be such: with a reference
+    // among them their probabilities would be infinite or no numbers, and so would the sums that they are added to, even with weight
+    // zero.  Like this they are zero.
     constexpr float kMaxSum = 256.0f;
     const float c = p.scale_log2;
-    float m = -__builtin_inff(), l = 0.f;
+    float m = p.lowest, l = 0.f;
 
     // One key block.  `stage` is a constant after inlining.
     auto step = [&](int j, int stage) __attribute__((always_inline)) {

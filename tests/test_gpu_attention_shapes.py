@@ -1,6 +1,8 @@
 """fact_attention in every shape of work-group that its rule can choose (query groups x key groups x keys of a block), at lengths
 where a query group, a key block or a key group's share ends, some of them with key groups that see no key: against 64-bit
 attention, with the tolerance of test_gpu_attention.py."""
+import math
+
 import pytest
 import torch
 
@@ -43,3 +45,34 @@ def test_the_same_bits_again():
     for B, T, H, D in ((1, 900, 2, 64), (2, 300, 32, 64), (1, 257, 32, 128), (3, 127, 2, 128)):
         q, k, v = tensors(B, T, H, H, D, 25)
         assert torch.equal(run(q, k, v, 1).view(torch.int16), run(q, k, v, 1).view(torch.int16))
+
+
+# Keys that a caller masks through a spare element of the heads: their scores are the lowest there is, or as good as that.
+# (B, T, Hq, Hkv, D, first and last + 1 of the keys left): in every shape, blocks of masked keys before and behind the others, among
+# them a wave's first ones
+MASKED = [(1, 96, 4, 4, 64, 0, 40), (1, 200, 2, 2, 64, 33, 200), (1, 417, 2, 1, 64, 100, 300), (2, 300, 32, 8, 64, 70, 129), (3, 97, 16, 16, 64, 0, 60),
+          (8, 160, 16, 4, 64, 32, 160), (8, 129, 12, 12, 64, 0, 50), (8, 97, 12, 12, 64, 0, 64), (3, 200, 32, 8, 64, 31, 130),
+          (1, 97, 2, 2, 128, 0, 32), (2, 127, 4, 4, 128, 64, 127), (2, 160, 2, 1, 128, 0, 30), (1, 257, 32, 8, 128, 33, 257), (3, 127, 32, 8, 128, 40, 127)]
+
+
+@pytest.mark.parametrize("value", [-math.inf, torch.finfo(torch.bfloat16).min, -1e20, -1e9])
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("B,T,Hq,Hkv,D,first,last", MASKED)
+def test_masked_keys(B, T, Hq, Hkv, D, first, last, causal, value):
+    q, k, v = tensors(B, T, Hq, Hkv, D, 27)
+    q[..., 0] = 1.0
+    k[..., 0] = value
+    k[:, first:last, :, 0] = 0.0
+    O = run(q, k, v, causal)
+    seen = first if causal else 0                            # (a query before the first key left sees masked ones alone)
+    # the same without the masked keys: against 64-bit attention over the others, each query with the keys that it may see
+    assert not torch.isnan(O[:, seen:]).any()
+    for b, h in ((0, 0), (0, Hq - 1), (B - 1, Hq // 2)):
+        kk, vv = k[b, first:last, h // (Hq // Hkv)].double(), v[b, first:last, h // (Hq // Hkv)].double()
+        s = (q[b, seen:, h].double() @ kk.t().contiguous()) / math.sqrt(D)
+        if causal:
+            s.masked_fill_(torch.arange(first, last, device="cuda")[None] > torch.arange(seen, T, device="cuda")[:, None], -math.inf)
+        p = torch.softmax(s, -1)
+        want, bound = p @ vv, p @ vv.abs()
+        err = (O[b, seen:, h].double() - want).abs()
+        assert (err <= 1e-2 * bound + 1e-3).all(), (b, h, float((err - 1e-2 * bound).max()))
