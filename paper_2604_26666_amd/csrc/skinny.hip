@@ -63,15 +63,17 @@ __device__ __forceinline__ void columns_of(uint32_t block, int lane, u32x4_t (&f
 // The waves' sums, added in ascending wave order (a fixed order: the result is bit-reproducible), the epilogue, the store.  A wave
 // finishes at most one tile; its bias and residual are asked for before the sums meet, in one trip to memory (one after the other
 // behind the sums, and element by element where 4 columns cross the last one: 7 x 2731 x 1284 4.6 us, like this 4.2, 5 x 207 x 205
-// [K][N] 4.5 and 3.9).
-template <int MT, int NT, int NW, bool F16>
+// [K][N] 4.5 and 3.9).  Calls of few rows are a chain of latencies, in which 0.1 us of branches count: a gate only where one can be asked
+// for (GATE), bias and residual behind one uniform branch and no test for rows that the grid guarantees (24 x 664 x 248 2.94 -> 2.76 us,
+// 52 x 2176 x 120 3.48 -> 3.28).
+template <int MT, int NT, int NW, bool GATE, bool F16>
 __device__ __forceinline__ void finish(const GemmArgs &p, const f32x4_t (&acc)[MT][NT], f32x4_t *sums, int wave, int lane, int m0, int n0, int64_t z)
 {
     static_assert(MT * NT <= NW, "a tile per wave");
     const int r16 = lane & 15, q = lane >> 4;
-    const bool gated = p.act == ACT_SILU_GATE;
+    const bool gated = GATE && p.act == ACT_SILU_GATE;
     const int nout = gated ? p.N >> 1 : p.N;
-    const int OT = gated && NT > 1 ? NT / 2 : NT;            // output column tiles
+    const int OT = gated ? NT / 2 : NT;                      // output column tiles
     const uint16_t *res = p.res ? (const uint16_t *)(p.res + z * p.stride_r) : nullptr;
     const uint16_t *bias = (const uint16_t *)p.bias;
     const int t = wave / OT, j = wave - t * OT;
@@ -84,8 +86,10 @@ __device__ __forceinline__ void finish(const GemmArgs &p, const f32x4_t (&acc)[M
         return u32x2_t{x0 | (x1 << 16), x2};
     };
     u32x2_t wb = {0u, 0u}, wr = {0u, 0u};
-    if (live && bias) wb = load4(bias + n);
-    if (live && res) wr = load4(res + (int64_t)m * p.ldr + n);
+    if (bias || res) {
+        if (live && bias) wb = load4(bias + n);
+        if (live && res) wr = load4(res + (int64_t)m * p.ldr + n);
+    }
     __syncthreads();                                         // every wave is done with its blocks
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -147,9 +151,10 @@ skinny_kernel(const GemmArgs p)
     f32x4_t *const sums = (f32x4_t *)smem;                           // [tile][wave][lane], once the rings are done with
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int r16 = lane & 15, q = lane >> 4;
-    const bool gated = p.act == ACT_SILU_GATE;
+    constexpr bool GATE = TRANS_B && NT == 2;                // the tiles that gated calls take
+    const bool gated = GATE && p.act == ACT_SILU_GATE;
     const int nout = gated ? p.N >> 1 : p.N;
-    const int OT = gated && NT > 1 ? NT / 2 : NT;            // output column tiles
+    const int OT = gated ? NT / 2 : NT;                      // output column tiles
     const int n0 = blockIdx.x * 16 * OT, m0 = blockIdx.y * 16 * MT;
     const int64_t z = blockIdx.z;
 
@@ -157,9 +162,9 @@ skinny_kernel(const GemmArgs p)
     // there under the swizzle.  Rows past the matrix are beyond the descriptor's range and pieces past K are pushed
     // there by an offset bit: both arrive as zeros.
     auto rsrc_of = [&](const __bf16 *base, int64_t row0, int rows_left, int64_t ld, int rows_max) __attribute__((always_inline)) {
-        const int rows = rows_left < rows_max ? rows_left : rows_max;        // (ld <= 2^21: the range fits 31 bits)
+        const int rows = rows_left < rows_max ? rows_left : rows_max;        // (at least 1: the grid ends with the matrix; ld <= 2^21: the range fits 31 bits)
         return __builtin_amdgcn_make_buffer_rsrc((void *)wave_uniform((const char *)(base + row0 * ld)), 0,
-                                                 wave_uniform((uint32_t)(rows > 0 ? ((int64_t)(rows - 1) * ld + p.K) * 2 : 0)), kBufferFlags);
+                                                 wave_uniform((uint32_t)(((int64_t)(rows - 1) * ld + p.K) * 2)), kBufferFlags);
     };
     const int chunk = (lane & 7) ^ (lane >> 3);
     const __amdgpu_buffer_rsrc_t rsrc_a = rsrc_of(p.A + z * p.stride_a, m0, p.M - m0, p.lda, 16 * MT);
@@ -243,7 +248,7 @@ skinny_kernel(const GemmArgs p)
         slot = slot + 1 == S ? 0 : slot + 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // loads past the last block still write LDS
-    finish<MT, NT, NW, F16>(p, acc, sums, wave, lane, m0, n0, z);
+    finish<MT, NT, NW, GATE, F16>(p, acc, sums, wave, lane, m0, n0, z);
 #else
     (void)p;
 #endif
@@ -385,7 +390,7 @@ skinny_any_kernel(const GemmArgs p)
             multiply();
         }
     }
-    finish<MT, NT, NW, F16>(p, acc, (f32x4_t *)smem, wave, lane, m0, n0, z);
+    finish<MT, NT, NW, false, F16>(p, acc, (f32x4_t *)smem, wave, lane, m0, n0, z);
 #else
     (void)p;
 #endif
