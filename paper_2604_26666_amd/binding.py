@@ -7,6 +7,7 @@ Return codes are returned unchanged by the fact_* functions; `check()` raises on
 """
 import ctypes
 import os
+import sys
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FACT_GEMM_LIB selects another build of the same library (used to compare variants)
@@ -157,21 +158,31 @@ def lib():
     return _lib
 
 
+class _General:
+    """In the place of the C functions where they are not built for this interpreter: every call goes through ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
 _fast = None
+_fast_before_torch = False
 
 
 def _fast_calls():
     """The launching calls' marshalling in C (csrc/pycall.cpp), bound to the loaded library's functions."""
-    global _fast
+    global _fast, _fast_before_torch
     if _fast is None:
         L = lib()
         try:
             from . import _pycall
-        except ImportError as e:
-            raise FactError(f"{e}: build it with `python -m paper_2604_26666_amd.build` (or __graft_entry__.build())") from e
-        import torch
+        except ImportError:
+            _fast = _General()
+            return _fast
+        torch = sys.modules.get("torch")                     # addresses and given streams need no torch
+        _fast_before_torch = torch is None
         try:
-            streams = (torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+            streams = None if torch is None else (torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
         except AttributeError:                               # (not part of torch's public interface)
             streams = None
         names = ("fact_gemm", "fact_gemm_batched", "fact_gemm_splitk", "fact_block_mlp", "fact_block_mlp_f16", "fact_attention", "fact_block_forward")
@@ -191,6 +202,9 @@ def _addr(x):
 def _stream(s):
     if s is None:
         import torch
+        global _fast
+        if _fast_before_torch:                           # bound again by the next call, with torch's streams
+            _fast = None
         # the current stream's handle itself: current_stream() builds a Stream object around it, 2.9 us of the 7.9 that a
         # 512 x 512 x 512 call took to issue (0.2 this way; the call is then bound by the GPU, 5.4 us)
         if torch.cuda.is_initialized():

@@ -2,6 +2,9 @@
 arguments (a recording stand-in here, so no GPU), and what the first does not know goes the second way."""
 import ctypes
 import os
+import subprocess
+import sys
+import textwrap
 
 import numpy as np
 import pytest
@@ -134,3 +137,41 @@ def test_the_same_errors(recorded):
             fact.fact_gemm(*bad, None, S)
     with pytest.raises(TypeError):
         fact.fact_gemm(3, 7, 5, A)
+
+
+def python(code, **env):
+    return subprocess.run([sys.executable, "-c", textwrap.dedent(code)], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                          env={**os.environ, **env}, capture_output=True, text=True, timeout=240)
+
+
+@pytest.mark.parametrize("absent", ["torch", "paper_2604_26666_amd._pycall"])
+def test_addresses_and_streams_need_neither_torch_nor_the_extension(recorded, absent):
+    # a module that is None in sys.modules cannot be imported; the calls are refused by the library, not by the binding
+    r = python(f"""
+        import sys
+        sys.modules[{absent!r}] = None
+        import paper_2604_26666_amd as fact
+        p = 4096
+        assert fact.fact_gemm(0, 8, 8, p, 8, p, 8, 1, p, 8, fact.Epilogue(bias=p), 0) == -2
+        assert fact.fact_attention(0, 8, 1, 1, 64, p, (8, 64, 64), p, (8, 64, 64), p, (8, 64, 64), p, (8, 64, 64), 1, 0.0, 0) == -2
+    """)
+    assert r.returncode == 0, r.stderr
+
+
+def test_torch_that_comes_later_brings_its_streams(recorded):
+    r = python("""
+        import sys
+        import paper_2604_26666_amd as fact
+        p = 4096
+        assert fact.fact_gemm(0, 8, 8, p, 8, p, 8, 1, p, 8, None, 0) == -2 and "torch" not in sys.modules
+        import torch
+        torch.cuda.current_stream = lambda: type("S", (), {"cuda_stream": 0})()
+        assert fact.fact_gemm(0, 8, 8, p, 8, p, 8, 1, p, 8) == -2
+        bound = []
+        from paper_2604_26666_amd import _pycall, binding
+        init = _pycall.init
+        _pycall.init = lambda *a: (bound.append(a[3]), init(*a))
+        assert fact.fact_gemm(0, 8, 8, p, 8, p, 8, 1, p, 8) == -2 and fact.fact_gemm(0, 8, 8, p, 8, p, 8, 1, p, 8) == -2
+        assert len(bound) == 1 and bound[0] is not None
+    """)
+    assert r.returncode == 0, r.stderr
