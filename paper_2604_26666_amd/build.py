@@ -5,6 +5,7 @@ plus the auxiliary kernels and the C ABI.  hipcc cross-compiles without a GPU.
 """
 import os
 import re
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -14,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfact_gemm.so")
-PYCALL = os.path.join(HERE, "_pycall.so")
+PYCALL = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))      # (tagged: another interpreter does not load it)
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -200,9 +201,13 @@ def write_acc_regs(path=os.path.join(CSRC, "acc_regs.inc")):
 
 
 def build_pycall(path=PYCALL):
-    """The binding's argument marshalling (csrc/pycall.cpp): host code for the running interpreter."""
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"],
-          os.path.join(CSRC, "pycall.cpp"), "-o", path])
+    """The binding's argument marshalling (csrc/pycall.cpp): host code for the running interpreter.  None without its headers or a
+    host compiler: the binding's calls then all go through ctypes."""
+    include, cxx = sysconfig.get_paths()["include"], os.environ.get("CXX", "g++")
+    if not os.path.exists(os.path.join(include, "Python.h")) or not shutil.which(cxx):
+        print(f"{os.path.basename(path)} is not built: no Python.h in {include}, or no {cxx}", file=sys.stderr)
+        return None
+    _run([cxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-I", include, os.path.join(CSRC, "pycall.cpp"), "-o", path])
     return path
 
 

@@ -4,6 +4,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import sysconfig
 import textwrap
 
 import numpy as np
@@ -175,3 +176,8 @@ def test_torch_that_comes_later_brings_its_streams(recorded):
         assert len(bound) == 1 and bound[0] is not None
     """)
     assert r.returncode == 0, r.stderr
+
+
+def test_the_extension_carries_its_interpreters_tag(recorded):
+    from paper_2604_26666_amd import _pycall, build
+    assert build.PYCALL.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and os.path.samefile(_pycall.__file__, build.PYCALL)
