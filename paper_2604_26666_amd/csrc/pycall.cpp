@@ -27,7 +27,11 @@ decltype(&fact_block_mlp) p_block_mlp, p_block_mlp_f16;
 decltype(&fact_attention) p_attention;
 decltype(&fact_block_forward) p_block_forward;
 
-// Readers: false (without a Python error) where the argument has to go the general way.
+// Readers: false where the argument has to go the general way, which meets the same error again; false with a Python error set only
+// for what is no error of the argument (an interrupt while an object's own code ran), and that ends the call.
+void forget() { if (PyErr_Occurred() && PyErr_ExceptionMatches(PyExc_Exception)) PyErr_Clear(); }
+PyObject *general() { if (PyErr_Occurred()) return nullptr; Py_RETURN_NONE; }
+
 bool read(PyObject *o, int64_t *v)
 {
     if (!PyLong_Check(o)) return false;
@@ -61,12 +65,12 @@ bool address(PyObject *o, const void **v)                   // None, an address,
     PyObject *r = nullptr;
     if (!PyLong_Check(o)) {
         r = o = PyObject_CallMethodNoArgs(o, n_data_ptr);
-        if (!r) { PyErr_Clear(); return false; }
+        if (!r) { forget(); return false; }
         if (!PyLong_CheckExact(r)) { Py_DECREF(r); return false; }
     }
     const unsigned long long w = PyLong_AsUnsignedLongLong(o);
     const bool ok = !(w == (unsigned long long)-1 && PyErr_Occurred());
-    if (!ok) PyErr_Clear();
+    if (!ok) forget();
     *v = (const void *)(uintptr_t)w;
     Py_XDECREF(r);
     return ok;
@@ -78,7 +82,7 @@ bool read(PyObject *o, void **v) { return address(o, (const void **)v); }
 template <class T> bool attr(PyObject *o, PyObject *name, T *v)
 {
     PyObject *a = PyObject_GetAttr(o, name);
-    if (!a) { PyErr_Clear(); return false; }
+    if (!a) { forget(); return false; }
     const bool ok = read(a, v);
     Py_DECREF(a);
     return ok;
@@ -104,7 +108,7 @@ bool read(PyObject *o, Stream *v)
     if (o != Py_None) {
         if (PyLong_Check(o)) return address(o, (const void **)&v->s);
         PyObject *a = PyObject_GetAttr(o, n_cuda_stream);
-        if (!a) PyErr_Clear();
+        if (!a) forget();
         const bool ok = a && PyLong_Check(a) && address(a, (const void **)&v->s);
         Py_XDECREF(a);
         return ok;
@@ -115,14 +119,14 @@ bool read(PyObject *o, Stream *v)
     if (ready != me) {
         PyObject *r = PyObject_CallNoArgs(g_is_initialized);
         const bool ok = r == Py_True;
-        if (!r) PyErr_Clear();
+        if (!r) forget();
         Py_XDECREF(r);
         if (!ok) return false;
         ready = me;
     }
     PyObject *dev = PyObject_CallNoArgs(g_get_device), *r = dev ? PyObject_CallOneArg(g_raw_stream, dev) : nullptr;
     Py_XDECREF(dev);
-    if (!r) { PyErr_Clear(); return false; }
+    if (!r) { forget(); return false; }
     const bool ok = PyLong_Check(r) && address(r, (const void **)&v->s);
     Py_DECREF(r);
     return ok;
@@ -157,7 +161,7 @@ bool read(PyObject *o, Block *v)
     }
     ok = ok && attr(o, n_norm_rms, &rms) && attr(o, n_act, &act) && attr(o, n_rope, &rope) && attr(o, n_eps, &b.eps) && attr(o, n_rope_base, &b.rope_base);
     b.norm_rms = rms; b.act = act; b.rope = rope;
-    if (PyErr_Occurred()) PyErr_Clear();
+    forget();
     Py_XDECREF(dims); Py_XDECREF(weights);
     return ok;
 }
@@ -173,28 +177,28 @@ template <class... T> bool arguments(PyObject *const *args, Py_ssize_t n, T *...
 PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     int64_t M, N, K, lda, ldb, ldc; const void *A, *B; void *C; int tb; Epilogue ep; Stream s;
-    if (!p_gemm || !arguments(args, n, &M, &N, &K, &A, &lda, &B, &ldb, &tb, &C, &ldc, &ep, &s)) Py_RETURN_NONE;
+    if (!p_gemm || !arguments(args, n, &M, &N, &K, &A, &lda, &B, &ldb, &tb, &C, &ldc, &ep, &s)) return general();
     FACT_CALL(p_gemm(M, N, K, A, lda, B, ldb, tb, C, ldc, ep.p, s.s));
 }
 
 PyObject *gemm_batched(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     int64_t b, M, N, K, lda, ldb, ldc, sa, sb, sc; const void *A, *B; void *C; int tb; Epilogue ep; Stream s;
-    if (!p_gemm_batched || !arguments(args, n, &b, &M, &N, &K, &A, &lda, &sa, &B, &ldb, &sb, &tb, &C, &ldc, &sc, &ep, &s)) Py_RETURN_NONE;
+    if (!p_gemm_batched || !arguments(args, n, &b, &M, &N, &K, &A, &lda, &sa, &B, &ldb, &sb, &tb, &C, &ldc, &sc, &ep, &s)) return general();
     FACT_CALL(p_gemm_batched(b, M, N, K, A, lda, sa, B, ldb, sb, tb, C, ldc, sc, ep.p, s.s));
 }
 
 PyObject *gemm_splitk(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     int64_t M, N, K, lda, ldb, ldc; const void *A, *B; void *C, *ws; int tb, split; size_t bytes; Epilogue ep; Stream s;
-    if (!p_gemm_splitk || !arguments(args, n, &M, &N, &K, &A, &lda, &B, &ldb, &tb, &C, &ldc, &ep, &split, &ws, &bytes, &s)) Py_RETURN_NONE;
+    if (!p_gemm_splitk || !arguments(args, n, &M, &N, &K, &A, &lda, &B, &ldb, &tb, &C, &ldc, &ep, &split, &ws, &bytes, &s)) return general();
     FACT_CALL(p_gemm_splitk(M, N, K, A, lda, B, ldb, tb, C, ldc, ep.p, split, ws, bytes, s.s));
 }
 
 PyObject *mlp(decltype(&fact_block_mlp) call, PyObject *const *args, Py_ssize_t n)
 {
     int64_t T, d, dff; const void *X, *W1, *W1u, *b1, *W2, *b2, *R; void *H, *Y, *ws; int act; size_t bytes; Stream s;
-    if (!call || !arguments(args, n, &T, &d, &dff, &X, &W1, &W1u, &b1, &act, &W2, &b2, &R, &H, &Y, &ws, &bytes, &s)) Py_RETURN_NONE;
+    if (!call || !arguments(args, n, &T, &d, &dff, &X, &W1, &W1u, &b1, &act, &W2, &b2, &R, &H, &Y, &ws, &bytes, &s)) return general();
     FACT_CALL(call(T, d, dff, X, W1, W1u, b1, act, W2, b2, R, H, Y, ws, bytes, s.s));
 }
 PyObject *block_mlp(PyObject *, PyObject *const *args, Py_ssize_t n) { return mlp(p_block_mlp, args, n); }
@@ -203,14 +207,14 @@ PyObject *block_mlp_f16(PyObject *, PyObject *const *args, Py_ssize_t n) { retur
 PyObject *attention(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     int64_t b, T, hq, hkv, D; const void *Q, *K, *V; void *O; Strides qs, ks, vs, os; int causal; float scale; Stream s;
-    if (!p_attention || !arguments(args, n, &b, &T, &hq, &hkv, &D, &Q, &qs, &K, &ks, &V, &vs, &O, &os, &causal, &scale, &s)) Py_RETURN_NONE;
+    if (!p_attention || !arguments(args, n, &b, &T, &hq, &hkv, &D, &Q, &qs, &K, &ks, &V, &vs, &O, &os, &causal, &scale, &s)) return general();
     FACT_CALL(p_attention(b, T, hq, hkv, D, Q, qs.s, K, ks.s, V, vs.s, O, os.s, causal, scale, s.s));
 }
 
 PyObject *block_forward(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     Block blk; const void *X; void *Y, *scratch; size_t bytes; Stream s;
-    if (!p_block_forward || !arguments(args, n, &blk, &X, &Y, &scratch, &bytes, &s)) Py_RETURN_NONE;
+    if (!p_block_forward || !arguments(args, n, &blk, &X, &Y, &scratch, &bytes, &s)) return general();
     FACT_CALL(p_block_forward(&blk.b, X, Y, scratch, bytes, s.s));
 }
 

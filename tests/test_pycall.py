@@ -140,6 +140,27 @@ def test_the_same_errors(recorded):
         fact.fact_gemm(3, 7, 5, A)
 
 
+def test_an_interrupt_ends_the_call(recorded):
+    A = T(4)
+
+    class Interrupted:
+        times = 0
+
+        def data_ptr(self):
+            self.times += 1
+            if self.times == 1:
+                raise KeyboardInterrupt
+            return A.data_ptr()
+
+    i = Interrupted()
+    for call in (lambda: fact.fact_gemm(3, 7, 5, i, 5, A, 7, 1, A, 7, None, S), lambda: fact.fact_gemm(3, 7, 5, A, 5, A, 7, 1, A, 7, fact.Epilogue(bias=i), S),
+                 lambda: fact.fact_block_forward(fact.Block(1, 2, 3, 4, 5, 64, 7, 0, 1, Wqkv=i), A, A, A, 77, S)):
+        i.times = 0
+        with pytest.raises(KeyboardInterrupt):
+            call()
+        assert i.times == 1
+
+
 def python(code, **env):
     return subprocess.run([sys.executable, "-c", textwrap.dedent(code)], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                           env={**os.environ, **env}, capture_output=True, text=True, timeout=240)
