@@ -6,6 +6,7 @@ import subprocess
 import sys
 import sysconfig
 import textwrap
+import threading
 
 import numpy as np
 import pytest
@@ -138,6 +139,44 @@ def test_the_same_errors(recorded):
             fact.fact_gemm(*bad, None, S)
     with pytest.raises(TypeError):
         fact.fact_gemm(3, 7, 5, A)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["default", "side", "nested", "thread", "thread with a stream"])
+def test_no_stream_is_the_current_one(recorded, where):
+    A = T(4)
+    torch.cuda.synchronize()
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    got = []
+
+    def seen(want):
+        one, two = recorded("fact_gemm", 3, 7, 5, A, 5, A, 7, 1, A, 7)
+        blk = recorded("fact_block_forward", fact.Block(1, 2, 3, 4, 5, 64, 7, 0, 1, Wqkv=A), A, A, A, 77)
+        got.extend((x[-1] or 0, want) for x in (one, two, *blk))
+        assert torch.cuda.current_stream().cuda_stream == want and binding._fast.gemm(3, 7, 5, A, 5, A, 7, 1, A, 7, None, None) == 7
+
+    def threads(s):
+        with torch.cuda.stream(s):
+            seen(s.cuda_stream)
+
+    if where == "default":
+        seen(0)
+    elif where == "side":
+        with torch.cuda.stream(side):
+            seen(side.cuda_stream)
+        seen(0)
+    elif where == "nested":
+        with torch.cuda.stream(side):
+            with torch.cuda.stream(other):
+                seen(other.cuda_stream)
+            seen(side.cuda_stream)
+    else:
+        with torch.cuda.stream(side):                       # a new thread starts on the default stream
+            t = threading.Thread(target=seen, args=(0,)) if where == "thread" else threading.Thread(target=threads, args=(other,))
+            t.start()
+            t.join()
+            seen(side.cuda_stream)
+    assert len(got) == (4 if where == "default" else 8) and all(a == b for a, b in got), got
 
 
 def test_an_interrupt_ends_the_call(recorded):
