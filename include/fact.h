@@ -396,15 +396,19 @@ void fact_test_tail_poll_budget(int polls);
 /* Test hook (host logic only: nothing is launched, no pointer is followed, no GPU is needed): the kernels
  * that fact_gemm_ex would launch for these arguments, in order.  ws == NULL: as the entry points
  * without a workspace choose (fact_gemm, fact_gemm_batched, both with split_k = 1).  Writes at most
- * max_launches kinds (FACT_ROUTE_*), tile configurations (-1 where none) and contraction columns
+ * max_launches kinds (FACT_ROUTE_*), tile configurations (for the skinny and ragged kinds the number of
+ * the kernel's own form, below; -1 where none) and contraction columns
  * (arrays, each may be NULL) and returns the number of launches, or the status the call would return. */
 enum {
     FACT_ROUTE_TILES = 0,         /* the tile kernel */
     FACT_ROUTE_TAIL = 1,          /* the tile kernel, its last round split along K */
     FACT_ROUTE_PERSISTENT = 2,    /* the tile kernel's persistent form */
     FACT_ROUTE_REDUCE = 3,        /* the reduction pass behind a split along K */
-    FACT_ROUTE_SKINNY = 4,        /* the kernel for few rows */
-    FACT_ROUTE_RAGGED = 5,        /* the kernel for rows of any alignment */
+    FACT_ROUTE_SKINNY = 4,        /* the kernel whose waves split K, for few rows and small outputs; 16 x 16 tiles of a work-group and
+                                     its LDS stages: 0 1x1 /4, 1 2x1 /3, 2 2x2 /2, 3 1x2 /4, 4 1x4 /3, 5 4x1 /2 (8 waves), 6 2x2 /4,
+                                     7 1x2 /3, 8 2x2 /3 */
+    FACT_ROUTE_RAGGED = 5,        /* rows of any alignment; tile and K groups: 0 128x128 /1, 1 128x128 /2, 2 64x64 /1, 3 64x64 /2,
+                                     4 32x64 /1, 5 32x64 /4; the kernel whose waves split K: 6 16x16, 7 32x32 */
     FACT_ROUTE_GUARDED = 6        /* one thread per element */
 };
 int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
@@ -413,6 +417,11 @@ int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
                     void *C, int64_t ldc, int64_t stride_c,
                     const fact_epilogue *ep, int config_id, int split_k, int group_m,
                     void *ws, size_t ws_bytes, int max_launches, int *kinds, int *configs, int64_t *columns);
+
+/* Test hook (host logic only): the shape of work-group that fact_attention takes, in groups of 32 queries, groups that
+ * share the keys, and keys of a block.  Any out pointer may be NULL. */
+int fact_test_attention_shape(int64_t batch, int64_t T, int64_t n_q_heads, int64_t head_dim, int causal,
+                              int *query_groups, int *key_groups, int *keys);
 
 /*
  * Persistent launches (the grid-level schedule of Section 4.2 Action 2 next to "Data Parallel" and

@@ -141,6 +141,8 @@ def lib():
         L.fact_test_tail_poll_budget.restype = None
         L.fact_test_route.argtypes = L.fact_gemm_ex.argtypes[:-1] + [_int, ip, ip, i64p]
         L.fact_test_route.restype = _int
+        L.fact_test_attention_shape.argtypes = [_i64, _i64, _i64, _i64, _int, ip, ip, ip]
+        L.fact_test_attention_shape.restype = _int
         L.fact_tune_persistent.argtypes = [_int]
         L.fact_tune_persistent.restype = _int
         L.fact_persistent_grid.argtypes = [_i64, _i64, _i64, _i64, _int, _int, _int]
@@ -370,16 +372,26 @@ def fact_test_tail_poll_budget(polls):
 
 
 ROUTES = ("tiles", "tail", "persistent", "reduce", "skinny", "ragged", "guarded")     # FACT_ROUTE_*
+# what the configuration means for two of them: 16 x 16 tiles of a work-group / LDS stages; tile / K groups, then as for skinny
+SKINNY_FORMS = ("1x1/4", "2x1/3", "2x2/2", "1x2/4", "1x4/3", "4x1/2", "2x2/4", "1x2/3", "2x2/3")
+RAGGED_FORMS = ("128x128/1", "128x128/2", "64x64/1", "64x64/2", "32x64/1", "32x64/4", "1x1", "2x2")
 
 
 def fact_test_route(batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b, C, ldc, stride_c, ep,
                     config_id=-1, split_k=1, group_m=0, ws=None, ws_bytes=0):
-    """[(kernel, tile configuration, columns), ...] of the launches that fact_gemm_ex would make (ws None: fact_gemm and
+    """[(kernel, tile configuration or form, columns), ...] of the launches that fact_gemm_ex would make (ws None: fact_gemm and
     fact_gemm_batched), or the negative status it would return."""
     k, c, n = (_int * 4)(), (_int * 4)(), (_i64 * 4)()
     r = lib().fact_test_route(batch, M, N, K, _addr(A), lda, stride_a, _addr(B), ldb, stride_b, int(trans_b), _addr(C), ldc, stride_c,
                               _ep(ep), int(config_id), int(split_k), int(group_m), _addr(ws), int(ws_bytes), 4, k, c, n)
     return r if r < 0 else [(ROUTES[k[i]], c[i], n[i]) for i in range(r)]
+
+
+def fact_test_attention_shape(batch, T, n_q_heads, head_dim, causal):
+    """(groups of 32 queries, key groups, keys of a block) of a work-group, or the negative status."""
+    v = [_int() for _ in range(3)]
+    rc = lib().fact_test_attention_shape(batch, T, n_q_heads, head_dim, int(causal), *[ctypes.byref(x) for x in v])
+    return rc if rc < 0 else tuple(x.value for x in v)
 
 
 def fact_tune_persistent(mode):

@@ -94,6 +94,20 @@ static int choose(const AttnArgs &a, const Shape (&shapes)[N])
 }  // namespace attn
 }  // namespace fact
 
+extern "C" int fact_test_attention_shape(int64_t batch, int64_t T, int64_t n_q_heads, int64_t head_dim, int causal, int *query_groups, int *key_groups, int *keys)
+{
+    using namespace fact::attn;
+    if (batch <= 0 || T <= 0 || n_q_heads <= 0 || batch > 0x7FFFFFFF || T > 0x7FFFFFFF - 1024 || n_q_heads > 0x7FFFFFFF) return FACT_ERR_DIM;
+    if (head_dim != 64 && head_dim != 128) return FACT_ERR_UNSUPPORTED;
+    AttnArgs a;
+    a.B = (int)batch; a.T = (int)T; a.Hq = (int)n_q_heads; a.causal = causal;
+    const Shape &s = head_dim == 128 ? kShapes128[choose(a, kShapes128)] : kShapes64[choose(a, kShapes64)];
+    if (query_groups) *query_groups = s.nw;
+    if (key_groups) *key_groups = s.kg;
+    if (keys) *keys = s.bkv;
+    return FACT_OK;
+}
+
 extern "C" int fact_attention(int64_t batch, int64_t T, int64_t n_q_heads, int64_t n_kv_heads, int64_t head_dim,
                               const void *Q, const int64_t *q_strides, const void *K, const int64_t *k_strides,
                               const void *V, const int64_t *v_strides, void *O, const int64_t *o_strides,

@@ -486,8 +486,9 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     hipError_t e;
     if (pl.cfg < 0) {
         if (cfg_id != FACT_CONFIG_GUARDED && ragged_serves(a, q.trans_b != 0, q.batch)) {
-            if (route) return route->add(FACT_ROUTE_RAGGED, -1, q.N);
-            e = launch_ragged_gemm(a, q.trans_b != 0, (int)q.batch, stream);
+            const int form = ragged_form(a, q.trans_b != 0, q.batch);
+            if (route) return route->add(FACT_ROUTE_RAGGED, form, q.N);
+            e = launch_ragged_gemm(a, q.trans_b != 0, form, (int)q.batch, stream);
             return e == hipSuccess ? FACT_OK : hip_fail(e, "ragged gemm launch");
         }
         if (route) return route->add(FACT_ROUTE_GUARDED, -1, q.N);
@@ -551,8 +552,9 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
             a.out_f32 = 0; a.c_f32 = 1;
         }
         a.splits = 1; a.P = nullptr;
-        if (route) return route->add(FACT_ROUTE_SKINNY, -1, q.N);
-        e = launch_skinny_gemm(a, q.trans_b != 0, tile, (int)q.batch, stream);
+        const int form = skinny_form(a, q.trans_b != 0, q.batch, tile);
+        if (route) return route->add(FACT_ROUTE_SKINNY, form, q.N);
+        e = launch_skinny_gemm(a, q.trans_b != 0, form, (int)q.batch, stream);
         return e == hipSuccess ? FACT_OK : hip_fail(e, "skinny gemm launch");
     }
     // L2 prefetch (see the kernel).  Many work-groups: the ones resident on an XCD (32 CUs) form a

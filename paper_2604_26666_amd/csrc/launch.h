@@ -29,18 +29,21 @@ hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, 
 
 // GEMM of few rows against B as [N][K], and small GEMMs of either layout (skinny.hip): the calls of few rows it can take and
 // their estimated microseconds (whole_lines: every row of B begins on a 128-byte line); the estimate for a small GEMM with the
-// tile that gives it (-1: none serves it); the launch (tile -1: few rows).
+// tile that gives it (-1: none serves it); the form that runs for that tile (-1: few rows), a number of FACT_ROUTE_SKINNY; the launch.
 bool skinny_takes(const GemmArgs &args, bool trans_b);
 double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
 double small_us(const GemmArgs &args, bool trans_b, int64_t batch, int *tile);
-hipError_t launch_skinny_gemm(const GemmArgs &args, bool trans_b, int tile, int grid_z, hipStream_t stream);
+int skinny_form(const GemmArgs &args, bool trans_b, int64_t batch, int tile);
+hipError_t launch_skinny_gemm(const GemmArgs &args, bool trans_b, int form, int grid_z, hipStream_t stream);
 
 // The same kernel's form for operands of any alignment: its estimate with the tile that gives it (-1: none), the launch.
 double small_any_us(const GemmArgs &args, bool trans_b, int64_t batch, int *tile);
 hipError_t launch_small_any(const GemmArgs &args, bool trans_b, int tile, int grid_z, hipStream_t stream);
 
-// GEMM with operands of any alignment and size on the matrix cores (ragged.hip).
+// GEMM with operands of any alignment and size on the matrix cores (ragged.hip): the form that runs, a number of
+// FACT_ROUTE_RAGGED, and the launch.
 bool ragged_serves(const GemmArgs &args, bool trans_b, int64_t batch);
-hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
+int ragged_form(const GemmArgs &args, bool trans_b, int64_t batch);
+hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int form, int grid_z, hipStream_t stream);
 
 }  // namespace fact

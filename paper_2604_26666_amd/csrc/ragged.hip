@@ -390,18 +390,19 @@ bool ragged_serves(const GemmArgs &a, bool trans_b, int64_t batch)
 //   3850 x 1884 x   31   128/1 12.3   128/2 18.8    64/1 12.9
 //    858 x  133 x   33   128/1 11.6    64/1  5.4   32x64/1 4.4   32x64/4  6.5
 struct RaggedTile { int bm, bn, groups; };
-static RaggedTile ragged_tile(const GemmArgs &a, int64_t batch)
+static constexpr RaggedTile kRaggedTiles[6] = {{128, 128, 1}, {128, 128, 2}, {64, 64, 1}, {64, 64, 2}, {32, 64, 1}, {32, 64, 4}};
+static int ragged_tile(const GemmArgs &a, int64_t batch)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return (a.M + bm - 1) / bm * ((a.N + bn - 1) / bn) * batch; };
-    if (tiles(128, 128) >= 160) return {128, 128, a.K >= 512 && tiles(128, 128) < 512 ? 2 : 1};
-    if (tiles(64, 64) >= 160) return {64, 64, a.K >= 256 ? 2 : 1};
-    return {32, 64, a.K >= 768 ? 4 : 1};
+    if (tiles(128, 128) >= 160) return a.K >= 512 && tiles(128, 128) < 512 ? 1 : 0;
+    if (tiles(64, 64) >= 160) return a.K >= 256 ? 3 : 2;
+    return a.K >= 768 ? 5 : 4;
 }
 
 // Its estimated microseconds where there are few work-groups (fitted to the calls of small_any_us, mean error 5 and 8 %).
 static double ragged_us(const GemmArgs &a, bool trans_b, int64_t batch)
 {
-    const RaggedTile t = ragged_tile(a, batch);
+    const RaggedTile t = kRaggedTiles[ragged_tile(a, batch)];
     const double wgs = (double)((a.M + (int64_t)t.bm - 1) / t.bm * ((a.N + (int64_t)t.bn - 1) / t.bn) * batch);
     const int64_t blocks = ((int64_t)a.K + 63) / 64;
     const double load = (wgs > 256 ? wgs / 256.0 : 1.0) * 128.0 * t.groups * (t.bm + t.bn) / (trans_b ? 55.6e3 : 43.7e3);
@@ -412,15 +413,25 @@ static double ragged_us(const GemmArgs &a, bool trans_b, int64_t batch)
 // Small outputs go to the kernel whose waves split K where that is the faster one by its estimate (us, this kernel -> that one; M x N x K: 1 x 34 x 1917
 // [N][K] 11.1 -> 4.9, 9 x 83 x 1443 [N][K] 9.0 -> 4.3, 273 x 53 x 3855 [K][N] 21.5 -> 10.7, 45 x 2916 x 3331 [N][K] 18.0 -> 12.8; but 304 x 3477 x 246 [N][K]
 // 6.4 -> 9.2, 137 x 3402 x 334 [K][N] 6.2 -> 8.6).  Over the 420 calls the choice is 1.23 times as fast, the better kernel of every call 1.25.
-hipError_t launch_ragged_gemm(const GemmArgs &a, bool trans_b, int grid_z, hipStream_t stream)
+static constexpr int kSmallForms = 6;                        // the tiles of small_any_us follow those of kRaggedTiles
+int ragged_form(const GemmArgs &a, bool trans_b, int64_t batch)
 {
     int small = -1;
-    const double us = small_any_us(a, trans_b, grid_z, &small);
-    if (small >= 0 && us < 0.96 * ragged_us(a, trans_b, grid_z)) return launch_small_any(a, trans_b, small, grid_z, stream);
-    const RaggedTile t = ragged_tile(a, grid_z);
-    if (t.bm == 128) return t.groups == 2 ? launch_tile<128, 128, 2, 2, 2>(a, trans_b, grid_z, stream) : launch_tile<128, 128, 2, 2, 1>(a, trans_b, grid_z, stream);
-    if (t.bm == 64) return t.groups == 2 ? launch_tile<64, 64, 2, 2, 2>(a, trans_b, grid_z, stream) : launch_tile<64, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
-    return t.groups == 4 ? launch_tile<32, 64, 2, 2, 4>(a, trans_b, grid_z, stream) : launch_tile<32, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+    const double us = small_any_us(a, trans_b, batch, &small);
+    return small >= 0 && us < 0.96 * ragged_us(a, trans_b, batch) ? kSmallForms + small : ragged_tile(a, batch);
+}
+
+hipError_t launch_ragged_gemm(const GemmArgs &a, bool trans_b, int form, int grid_z, hipStream_t stream)
+{
+    switch (form) {
+    case 0: return launch_tile<128, 128, 2, 2, 1>(a, trans_b, grid_z, stream);
+    case 1: return launch_tile<128, 128, 2, 2, 2>(a, trans_b, grid_z, stream);
+    case 2: return launch_tile<64, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+    case 3: return launch_tile<64, 64, 2, 2, 2>(a, trans_b, grid_z, stream);
+    case 4: return launch_tile<32, 64, 2, 2, 1>(a, trans_b, grid_z, stream);
+    case 5: return launch_tile<32, 64, 2, 2, 4>(a, trans_b, grid_z, stream);
+    default: return launch_small_any(a, trans_b, form - kSmallForms, grid_z, stream);
+    }
 }
 
 }  // namespace fact

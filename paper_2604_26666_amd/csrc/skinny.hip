@@ -438,7 +438,7 @@ static hipError_t launch_tile(const GemmArgs &a, int grid_z, hipStream_t stream)
 }
 
 struct Tile { int mt, nt, waves, stages; };
-static constexpr Tile kTiles[] = {{1, 1, 4, 4}, {2, 1, 4, 3}, {2, 2, 4, 2}, {1, 2, 4, 4}, {1, 4, 4, 3}, {4, 1, 8, 2}, {2, 2, 4, 4}, {1, 2, 4, 3}};
+static constexpr Tile kTiles[] = {{1, 1, 4, 4}, {2, 1, 4, 3}, {2, 2, 4, 2}, {1, 2, 4, 4}, {1, 4, 4, 3}, {4, 1, 8, 2}, {2, 2, 4, 4}, {1, 2, 4, 3}, {2, 2, 4, 3}};
 static int64_t groups_of(const Tile &t, const GemmArgs &a, int64_t batch)
 {
     const bool gated = a.act == ACT_SILU_GATE;
@@ -517,13 +517,21 @@ double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
     return best;
 }
 
-// tile: small_us's choice, or -1 for the tile of few rows (skinny_us)
-hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int tile, int grid_z, hipStream_t stream)
+// The index in kTiles of what runs; tile: small_us's choice, or -1 for the tile of few rows (skinny_us).
+int skinny_form(const GemmArgs &a, bool trans_b, int64_t batch, int tile)
+{
+    if (tile < 0) return row_tile(a);
+    // Where the work-groups have a compute unit each, two blocks ahead instead of one, from 2048 K-values on (us; one -> two; 256 x 512 x 8192
+    // 16.0 -> 13.3, 96 x 1536 x 4096 10.0 -> 8.5, 64 x 2048 x 2048 6.8 -> 6.2, 300 x 600 x 2048 7.8 -> 7.4; but 256 x 512 x 1024 4.2 -> 4.8, 128 x 1024 x 1024
+    // 4.1 -> 4.8; three: as two.  B as [K][N] has nothing of it: 256 x 512 x 8192 19.6 -> 20.0)
+    return trans_b && tile == 2 && a.K >= 2048 && groups_of(kTiles[2], a, batch) <= 256 ? 8 : tile;
+}
+
+hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int form, int grid_z, hipStream_t stream)
 {
     const bool nt = streams(a, grid_z);
-    if (tile < 0) tile = row_tile(a);
     if (!trans_b) {
-        switch (tile) {
+        switch (form) {
         case 0: return launch_tile<1, 1, 4, 4, false, false>(a, grid_z, stream);
         case 2: return launch_tile<2, 2, 4, 2, false, false>(a, grid_z, stream);
         case 3: return launch_tile<1, 2, 4, 4, false, false>(a, grid_z, stream);
@@ -531,15 +539,11 @@ hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int tile, int gri
         default: return hipErrorInvalidConfiguration;
         }
     }
-    switch (tile) {
+    switch (form) {
     case 0: return nt ? launch_tile<1, 1, 4, 4, true, true>(a, grid_z, stream) : launch_tile<1, 1, 4, 4, true, false>(a, grid_z, stream);
     case 1: return nt ? launch_tile<2, 1, 4, 3, true, true>(a, grid_z, stream) : launch_tile<2, 1, 4, 3, true, false>(a, grid_z, stream);
-    case 2:
-        // Where the work-groups have a compute unit each, two blocks ahead instead of one, from 2048 K-values on (us; one -> two; 256 x 512 x 8192
-        // 16.0 -> 13.3, 96 x 1536 x 4096 10.0 -> 8.5, 64 x 2048 x 2048 6.8 -> 6.2, 300 x 600 x 2048 7.8 -> 7.4; but 256 x 512 x 1024 4.2 -> 4.8, 128 x 1024 x 1024
-        // 4.1 -> 4.8; three: as two.  B as [K][N] has nothing of it: 256 x 512 x 8192 19.6 -> 20.0)
-        if (a.K >= 2048 && groups_of(kTiles[2], a, grid_z) <= 256) return launch_tile<2, 2, 4, 3, true, false>(a, grid_z, stream);
-        return launch_tile<2, 2, 4, 2, true, false>(a, grid_z, stream);
+    case 2: return launch_tile<2, 2, 4, 2, true, false>(a, grid_z, stream);
+    case 8: return launch_tile<2, 2, 4, 3, true, false>(a, grid_z, stream);
     case 5: return nt ? launch_tile<4, 1, 8, 2, true, true>(a, grid_z, stream) : launch_tile<4, 1, 8, 2, true, false>(a, grid_z, stream);
     case 6: return nt ? launch_tile<2, 2, 4, 4, true, true>(a, grid_z, stream) : launch_tile<2, 2, 4, 4, true, false>(a, grid_z, stream);
     case 7: return nt ? launch_tile<1, 2, 4, 3, true, true>(a, grid_z, stream) : launch_tile<1, 2, 4, 3, true, false>(a, grid_z, stream);

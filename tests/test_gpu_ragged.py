@@ -11,12 +11,19 @@ from oracle import check, ref
 
 pytestmark = pytest.mark.gpu
 
-# one row per tile shape and K-group count of the dispatch rule (K above and below its line), and the smallest sizes
-# (few rows or columns with a K of up to 13 run on the guarded kernel)
-SHAPES = [(601, 1003, 8), (1003, 601, 9), (1801, 1499, 521), (1801, 1499, 77), (700, 999, 300), (700, 999, 100), (37, 131, 777), (1, 9, 8), (33, 65, 71), (31, 8, 9), (65, 64, 1025)]
+# shape: what serves it with B as [K][N] and as [N][K].  Every tile and K-group count of the dispatch rule in both layouts; steps of K
+# (64 wide, per group) that leave each remainder of the loop, which runs from 4 steps on: 1, 2, 3 steps without it, and with it an
+# even count (2 left) and an odd one (3); 512 tiles of 128 x 128 and more, which keep one K group whatever K is
+FORMS = {(601, 1003, 8): ("64x64/1",) * 2, (1003, 601, 9): ("64x64/1",) * 2, (700, 999, 100): ("64x64/1",) * 2, (700, 999, 150): ("64x64/1",) * 2,
+         (700, 999, 201): ("64x64/1",) * 2, (700, 999, 300): ("64x64/2",) * 2, (700, 999, 777): ("64x64/2",) * 2, (900, 901, 600): ("64x64/2",) * 2,
+         (1801, 1499, 77): ("128x128/1", "2x2"), (1801, 1499, 201): ("128x128/1",) * 2, (2000, 1999, 300): ("128x128/1",) * 2,
+         (2900, 2901, 777): ("128x128/1",) * 2, (1801, 1499, 521): ("128x128/2",) * 2, (1801, 1499, 1000): ("128x128/2",) * 2,
+         (500, 1200, 201): ("32x64/1",) * 2, (500, 1201, 300): ("32x64/1",) * 2, (400, 1001, 600): ("32x64/1",) * 2, (150, 2201, 77): ("32x64/1",) * 2,
+         (350, 1167, 1081): ("32x64/4",) * 2, (401, 1001, 777): ("32x64/4",) * 2,
+         (37, 131, 777): ("1x1",) * 2, (33, 65, 71): ("1x1",) * 2, (65, 64, 1025): ("1x1",) * 2, (1, 9, 8): ("guarded",) * 2, (31, 8, 9): ("guarded",) * 2}
 
 
-def run(A, B, nk, bias=None, res=None, act=fact.ACT_NONE, f16=0):
+def run(A, B, nk, bias=None, res=None, act=fact.ACT_NONE, f16=0, form=None):
     """Rows padded to odd lengths with NaN, pointers 2-byte aligned only; returns the bits of C after checking its surroundings."""
     dt = torch.float16 if f16 else torch.bfloat16
 
@@ -35,6 +42,8 @@ def run(A, B, nk, bias=None, res=None, act=fact.ACT_NONE, f16=0):
     Cb = torch.full((M + 1, ldc), 77.0, dtype=dt, device="cuda")
     keep = [None if t is None else t.cuda() for t in (bias, res)]
     ep = fact.Epilogue(bias=keep[0], residual=keep[1], ldr=nout, act=act, f16=f16)
+    (kind, n, _), = fact.fact_test_route(1, M, N, K, ap, lda, 0, bp, ldb, 0, nk, Cb, ldc, 0, ep)
+    assert form is None or (fact.RAGGED_FORMS[n] if kind == "ragged" else kind) == form, (M, N, K, nk)
     fact.binding.check(fact.fact_gemm(M, N, K, ap, lda, bp, ldb, nk, Cb, ldc, ep), f"{(M, N, K, nk)}")
     torch.cuda.synchronize()
     out = Cb.cpu()
@@ -44,7 +53,7 @@ def run(A, B, nk, bias=None, res=None, act=fact.ACT_NONE, f16=0):
 
 @pytest.mark.parametrize("f16", [0, 1])
 @pytest.mark.parametrize("nk", [0, 1])
-@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("shape", FORMS, ids=str)
 def test_exact_sums_bias_and_residual(shape, nk, f16):
     M, N, K = shape
     ints = wl.small_int_f16 if f16 else wl.small_int
@@ -52,17 +61,19 @@ def test_exact_sums_bias_and_residual(shape, nk, f16):
     A, B = ints((M, K), -4, 4, f"rg.A.{shape}"), ints((N, K) if nk else (K, N), -4, 4, f"rg.B.{shape}.{nk}")
     bias, res = ints((N,), -9, 9, "rg.bias"), ints((M, N), -9, 9, "rg.res")
     rows = wl.choice_rows(M, 48, f"rg.rows.{shape}", edges=(0, 31, 32, 63, 64, 127, 128, M - 1))
-    got = run(A, B, nk, bias, res, f16=f16)
+    got = run(A, B, nk, bias, res, f16=f16, form=FORMS[shape][nk])
     check.assert_bits_equal(got, ref.gemm_epilogue(A, B, nk, bias=bias, residual=res, rows=rows, fmt=fmt), rows="full", what=f"{shape} nk={nk}")
 
 
 @pytest.mark.parametrize("act", [fact.ACT_GELU_TANH, fact.ACT_SILU_GATE])
-@pytest.mark.parametrize("shape", [(1801, 1498, 521), (700, 998, 300), (37, 130, 777), (33, 66, 71)], ids=str)
-def test_activations(shape, act):
+@pytest.mark.parametrize("shape,forms", [((1801, 1498, 521), ("128x128/2",) * 2), ((1801, 1498, 201), ("128x128/1",) * 2), ((700, 998, 300), ("64x64/2",) * 2),
+                                         ((700, 998, 201), ("64x64/1",) * 2), ((400, 1000, 300), ("32x64/1",) * 2), ((401, 1002, 777), ("32x64/4",) * 2),
+                                         ((37, 130, 777), ("1x1", "32x64/4")), ((33, 66, 71), ("1x1", "32x64/1"))], ids=str)
+def test_activations(shape, forms, act):
     M, N, K = shape
     A, B = wl.normal((M, K), 1.0, f"rg.a.{shape}"), wl.normal((N, K), K ** -0.5, f"rg.b.{shape}")
     rows = wl.choice_rows(M, 32, f"rg.r.{shape}", edges=(0, M - 1))
-    got = run(A, B, 1, act=act)
+    got = run(A, B, 1, act=act, form=forms[act == fact.ACT_SILU_GATE])
     check.assert_close(got, ref.gemm_epilogue(A, B, True, act=act, rows=rows), rows="full", what=f"{shape} act={act}")
 
 

@@ -12,24 +12,27 @@ P = 1 << 16
 
 
 def route(M, N, K, nk, batch=1, **ep):
-    r = fact.fact_test_route(batch, M, N, K, P, K, M * K, P, K if nk else N, K * N, nk, P, N, M * N, fact.Epilogue(**ep))
-    return [x[0] for x in r]
+    return [x[0] for x in routes(M, N, K, nk, batch, **ep)]
 
 
-# (M, N, K, B as [N][K], tile); tiles in 16 x 16: what small_us takes for these sizes
-CASES = [(1, 8, 8, 0, "1x1"), (5, 216, 264, 0, "1x1"), (22, 168, 424, 0, "1x1"), (33, 40, 1480, 0, "1x1"),
-         (7, 480, 72, 0, "2x2"), (65, 1000, 136, 0, "2x2"), (26, 2184, 64, 0, "2x2"), (33, 40, 8, 0, "1x4"),
-         (42, 152, 96, 0, "1x2"), (24, 752, 168, 0, "1x2"), (24, 1728, 328, 0, "1x2"),
-         (9, 104, 16, 0, "1x4"), (5, 344, 48, 0, "1x4"), (198, 312, 8, 0, "1x4"),
-         (103, 8, 16, 1, "1x1"), (131, 33, 24, 1, "1x1"), (56, 137, 1160, 1, "1x1"),
-         (273, 23, 24, 1, "2x1"), (26, 345, 112, 1, "2x1"), (54, 961, 352, 1, "2x1"),
-         (138, 1121, 8, 1, "2x2"), (26, 2705, 104, 1, "2x2"), (300, 481, 584, 1, "2x2"), (512, 512, 512, 0, "2x2"),
-         (96, 1535, 2056, 1, "2x2"), (62, 2043, 2048, 1, "2x2")]         # (two blocks ahead)
+def routes(M, N, K, nk, batch=1, **ep):
+    return fact.fact_test_route(batch, M, N, K, P, K, M * K, P, K if nk else N, K * N, nk, P, N, M * N, fact.Epilogue(**ep))
 
 
-@pytest.mark.parametrize("M,N,K,nk,tile", CASES, ids=str)
-def test_route(M, N, K, nk, tile):
-    assert route(M, N, K, nk) == ["skinny"]
+# (M, N, K, B as [N][K], form): the tile in 16 x 16 and the LDS stages of a wave that the rule takes for these sizes
+CASES = [(1, 8, 8, 0, "1x1/4"), (5, 216, 264, 0, "1x1/4"), (22, 168, 424, 0, "1x1/4"), (33, 40, 1480, 0, "1x1/4"),
+         (7, 480, 72, 0, "2x2/2"), (65, 1000, 136, 0, "2x2/2"), (26, 2184, 64, 0, "2x2/2"), (33, 40, 8, 0, "1x4/3"),
+         (42, 152, 96, 0, "1x2/4"), (24, 752, 168, 0, "1x2/4"), (24, 1728, 328, 0, "1x2/4"),
+         (9, 104, 16, 0, "1x4/3"), (5, 344, 48, 0, "1x4/3"), (198, 312, 8, 0, "1x4/3"),
+         (103, 8, 16, 1, "1x1/4"), (131, 33, 24, 1, "1x1/4"), (56, 137, 1160, 1, "1x1/4"),
+         (273, 23, 24, 1, "2x1/3"), (26, 345, 112, 1, "2x1/3"), (54, 961, 352, 1, "4x1/2"), (126, 525, 1896, 1, "2x1/3"),
+         (138, 1121, 8, 1, "2x2/2"), (26, 2705, 104, 1, "2x1/3"), (58, 2547, 1840, 1, "2x2/2"), (300, 481, 584, 1, "2x2/2"), (512, 512, 512, 0, "2x2/2"),
+         (96, 1535, 2056, 1, "2x2/3"), (62, 2043, 2048, 1, "2x2/3")]         # (two blocks ahead)
+
+
+@pytest.mark.parametrize("M,N,K,nk,form", CASES, ids=str)
+def test_route(M, N, K, nk, form):
+    assert [(k, fact.SKINNY_FORMS[n]) for k, n, _ in routes(M, N, K, nk)] == [("skinny", form)]
 
 
 def test_where_the_tile_kernel_stays():
@@ -41,8 +44,8 @@ def test_where_the_tile_kernel_stays():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("f16", [0, 1])
-@pytest.mark.parametrize("M,N,K,nk,tile", CASES, ids=str)
-def test_exact_sums(M, N, K, nk, tile, f16):
+@pytest.mark.parametrize("M,N,K,nk,form", CASES, ids=str)
+def test_exact_sums(M, N, K, nk, form, f16):
     dt, ints = (torch.float16, wl.small_int_f16) if f16 else (torch.bfloat16, wl.small_int)
     A, B = ints((M, K), -4, 4, f"so.A.{M}.{K}"), ints((N, K) if nk else (K, N), -4, 4, f"so.B.{N}.{K}")
     bias, res = ints((N,), -9, 9, "so.b"), ints((M, N), -9, 9, "so.r")
