@@ -498,6 +498,10 @@ double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
     for (int i = 0; i < 5; ++i) {
         const Tile &t = kTiles[i];
         if (trans_b ? t.nt > t.mt : i == 1) continue;
+        // (32 columns for at most 32 rows of weights as [N][K] only where 16 give more work-groups than compute units: up to there the estimates of
+        // the two are level, and half of the chip fetches what all of it could: 27 x 3248 x 1864 cold 9.4 and 7.2 us, warm 7.1 and 5.6,
+        // 30 x 3800 x 880 6.3 and 5.3, 24 x 3504 x 328 4.5 and 3.8; but 26 x 4856 x 2336, 304 work-groups of 16 columns, 9.8 and 11.9)
+        if (trans_b && i == 2 && a.M <= 32 && groups_of(kTiles[1], a, batch) <= 256) continue;
         const int64_t wgs = groups_of(t, a, batch);
         const int fit = resident(t);
         if (wgs > 256 * fit || ((int64_t)a.M + 16 * t.mt - 1) / (16 * t.mt) > 65535) continue;

@@ -91,6 +91,12 @@ def test_few_rows_only_where_nothing_else_was_asked_for():
     assert kernels(16, 4096, 4096, 1, a=P + 2) == ["ragged"]
 
 
+# at most 32 rows: tiles of 32 columns only where tiles of 16 are more than compute units (203, 211 and 256 work-groups; 257 and 304)
+@pytest.mark.parametrize("M,N,K,form", [(27, 3248, 1864, "2x1/3"), (30, 3376, 880, "2x1/3"), (32, 4096, 624, "2x1/3"), (25, 4112, 624, "2x2/2"), (26, 4856, 2336, "2x2/3")])
+def test_half_the_chip_does_not_fetch_the_weights_of_few_rows(M, N, K, form):
+    assert [(k, fact.SKINNY_FORMS[c]) for k, c, _ in route(M, N, K, 1)] == [("skinny", form)]
+
+
 def test_few_rows_of_more_columns_than_a_grid_counts():
     # (such weights would be 500 GB and more: the pricing alone does not rule them out)
     assert kernels(1, 2 ** 27 - 16, 2048, 1) == ["skinny"]
