@@ -361,6 +361,9 @@ skinny_any_kernel(const GemmArgs p)
                 for (int j = 0; j < NT; ++j) acc[t][j] = mfma_skinny<F16>(b[j], a[t], acc[t][j]);
         }
     };
+    // The lanes read what other lanes of the wave have stored.  The hardware keeps a wave's LDS accesses in order; this keeps the
+    // compiler, which reasons per lane, from moving one over another that only a different lane's address makes depend on it.
+    auto in_order = []() __attribute__((always_inline)) { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); };
     if (mine > D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) fetch(r[d], d);
@@ -368,8 +371,10 @@ skinny_any_kernel(const GemmArgs p)
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 put(r[d], i + d);
+                in_order();
                 fetch(r[d], i + d + D);
                 multiply();
+                in_order();
             }
         }
     } else {
@@ -381,12 +386,16 @@ skinny_any_kernel(const GemmArgs p)
             fetch(r[0], 0);
             fetch(r[1], 1);
             put(r[0], 0);
+            in_order();
             multiply();
+            in_order();
             put(r[1], 1);
+            in_order();
             multiply();
         } else if (mine == 1) {
             fetch(r[0], 0);
             put(r[0], 0);
+            in_order();
             multiply();
         }
     }
