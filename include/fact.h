@@ -333,7 +333,8 @@ int fact_select_config(int64_t batch, int64_t M, int64_t N, int64_t K, int trans
  * Entries of another rule, data type or architecture, and entries naming a configuration this
  * build does not have (or one that cannot serve the layout), are skipped.  Of several entries for
  * one shape the first applies; a call that brings no workspace takes the first one with
- * split_k == 1.  Host only, callable from any thread; affects calls made after it returns.
+ * split_k == 1.  An entry that says what the compiled-in table says changes nothing.  Host only, callable from any
+ * thread; affects calls made after it returns.
  * path: host pointer to a NUL-terminated file name, read during the call, not kept.
  * Returns the number of entries taken (>= 0), FACT_ERR_NULL for a NULL path,
  * FACT_ERR_UNSUPPORTED if the file cannot be read or is not a version-1 registry.

@@ -125,8 +125,7 @@ struct Plan {
     int cfg = -1;      // -1: no tile configuration of the main kernel serves it (ragged or guarded kernel)
     int split = 1;
     int group_m = 4;
-    bool listed = false;   // from the registry or the table
-    bool loaded = false;   // from a registry file read at run time
+    bool loaded = false;   // from a registry file read at run time that says another thing than the compiled-in table
 };
 
 // Estimated microseconds of a launch, for shapes the registry does not list.  A 64-deep K step of a
@@ -164,15 +163,20 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
         pl.cfg = r.cfg;
         pl.split = r.split == 0 ? 1 : r.split;             // negative: a tail split, which needs a workspace as well
         pl.group_m = r.group_m > 0 ? r.group_m : 4;
-        pl.listed = true;
     };
+    const TableRow *listed = g_table;
+    while (listed->cfg >= 0 && !matches(*listed)) ++listed;
     {
         std::lock_guard<std::mutex> lock(g_registry_mutex);
         for (const TableRow &r : g_registry)
-            if (matches(r)) { take(r); pl.loaded = true; return pl; }
+            if (matches(r)) {
+                take(r);
+                // (the file that the table is generated from changes nothing when it is loaded)
+                pl.loaded = listed->cfg < 0 || r.cfg != listed->cfg || r.split != listed->split || r.group_m != listed->group_m;
+                return pl;
+            }
     }
-    for (const TableRow *r = g_table; r->cfg >= 0; ++r)
-        if (matches(*r)) { take(*r); return pl; }
+    if (listed->cfg >= 0) { take(*listed); return pl; }
     const int64_t nout = gated ? N / 2 : N;
     const bool all_fit = any_grid_fits(M, nout);
     double best = 0;

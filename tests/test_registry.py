@@ -86,6 +86,43 @@ def test_runtime_loader_overrides_the_compiled_table(tmp_path):
     assert fact.fact_registry_size() == 0 and fact.fact_select_config(*shape)[1:] == (cfg0, split0)
 
 
+def test_loading_the_shipped_registry_changes_no_route():
+    p = 0x10000                                   # never dereferenced
+
+    def routes():
+        out = {}
+        for e in registry.read():
+            act = fact.ACT_SILU_GATE if e.gated else fact.ACT_NONE
+            nout = e.N // 2 if e.gated else e.N
+            for split, ws in ((1, None), (0, p)):          # without and with a workspace
+                if ws is None or e.batch == 1:
+                    out[e.name, split] = fact.fact_test_route(e.batch, e.M, e.N, e.K, p, e.K, e.M * e.K, p, e.K if e.trans_b else e.N, e.K * e.N, e.trans_b, p, nout,
+                                                              e.M * nout, fact.Epilogue(act=act), -1, split, 0, ws, 1 << 40 if ws else 0)
+        return out
+
+    fact.fact_registry_clear()
+    compiled = routes()
+    assert compiled["c1.square512", 1][0][0] == "skinny" and len(compiled["c5.gate_up_silu", 1]) == 2
+    try:
+        assert fact.fact_registry_load(registry.DEFAULT) > 0
+        assert routes() == compiled
+    finally:
+        fact.fact_registry_clear()
+
+
+def test_a_loaded_entry_of_its_own_is_taken_as_it_stands(tmp_path):
+    p = 0x10000
+    route = lambda: fact.fact_test_route(1, 512, 512, 512, p, 512, 0, p, 512, 0, 0, p, 512, 0, None)
+    f = tmp_path / "other.reg"
+    f.write_text("# fact-registry 1\ngemm bf16 gfx950 1 512 512 512 kn plain 6 1 2\n")          # (the table's, with another group of tile rows)
+    try:
+        assert fact.fact_registry_load(str(f)) == 1
+        assert route() == [("tiles", 6, 512)]
+    finally:
+        fact.fact_registry_clear()
+    assert route()[0][0] == "skinny"
+
+
 def test_runtime_loader_refusals(tmp_path):
     assert fact.fact_registry_load(None) == -1
     assert fact.fact_registry_load(str(tmp_path / "missing.reg")) == -7
