@@ -113,9 +113,10 @@ typedef struct fact_epilogue {
  * registry lookup, Section 4.2 Action 6).  One launch, or two over the columns where the last
  * round of tiles would be nearly empty (the columns of the full rounds on the table's configuration,
  * the others on one that spreads them over the GPU; same bits as one launch; not for an entry of a
- * registry file loaded at run time).  Calls of at most 64 rows with trans_b == 1 that no registry or
- * table entry names take a kernel of their own for few rows where it is estimated to be faster.
- * Both hold in every entry point that leaves the configuration to the library.
+ * registry file loaded at run time).  Few rows (at most 64, gated 32, with trans_b == 1) and small outputs of either
+ * layout take a kernel whose waves split K where it is estimated to be faster, also in place of an entry of the
+ * compiled-in table, not of one of a file loaded at run time; operands of any alignment have theirs.
+ * All of it holds in every entry point that leaves the configuration to the library.
  */
 int fact_gemm(int64_t M, int64_t N, int64_t K,
               const void *A, int64_t lda,
@@ -143,8 +144,8 @@ int fact_gemm_batched(int64_t batch, int64_t M, int64_t N, int64_t K,
  * order; W is 1, 2, 4 or 8, the least that puts some 2048 waves to work on the M x N output
  * with at least four ranges each: a function of M, N and split_k alone), applies the epilogue
  * and rounds once.  split_k == 0 lets the table choose; split_k == 1 (or a
- * choice of 1) runs the plain kernel and needs no workspace.  Few rows may keep K whole on the kernel
- * for few rows (see fact_gemm) although the table splits it; the workspace is asked for all the same.
+ * choice of 1) runs the plain kernel and needs no workspace.  Few rows and small outputs may keep K whole on the
+ * kernel whose waves split it (see fact_gemm) although the table splits it; the workspace is asked for all the same.
  * Bit-reproducible: the order of additions is fixed.
  * ws: device pointer, 16-byte aligned, at least
  * fact_gemm_splitk_workspace_bytes(M, N, K, split_k) bytes; contents are scratch.
@@ -312,7 +313,7 @@ int fact_config_info(int id, int *tile_m, int *tile_n, int *waves_m, int *waves_
  * fact_gemm_ex).  batch >= 1.  Returns FACT_OK, or an
  * error if the shape is invalid.  config_id is -1 when no tile configuration serves the
  * shape (unaligned dimensions: the kernel for rows of any alignment, or one element per thread).
- * Where a call takes the kernel for few rows, or runs as two launches (see fact_gemm), this is
+ * Where a call takes the kernel for few rows and small outputs, or runs as two launches (see fact_gemm), this is
  * the choice that it was weighed against; fact_test_route names the kernels that run. */
 int fact_select_config(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act,
                        int *config_id, int *split_k);
@@ -438,7 +439,7 @@ int fact_test_attention_shape(int64_t batch, int64_t T, int64_t n_q_heads, int64
 int fact_tune_persistent(int mode);
 /* Work-groups a launch of this problem with K whole uses when it is persistent, else 0 (config_id < 0:
  * the table's or the model's configuration; 0 as well when that choice splits K).  While mode 1 is
- * set such a launch takes the place of the kernel for few rows and of two launches over the columns. */
+ * set such a launch takes the place of the kernel for few rows and small outputs and of two launches over the columns. */
 int fact_persistent_grid(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, int config_id);
 
 /* ---- misc ------------------------------------------------------------------------------- */
