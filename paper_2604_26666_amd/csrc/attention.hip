@@ -57,13 +57,14 @@ static hipError_t launch(AttnArgs a, hipStream_t stream)
 // which the last walks all the keys, a launch lasts as long as its longest work-group, at one wave per SIMD: key groups shorten
 // that chain and put more waves on a compute unit, fewer queries per work-group make more of them; each costs more K and V from
 // the L2 per query.  Key blocks of 32 leave four waves per SIMD at head_dim 64 in place of three.  us, 4 x 1 x 64 -> the choice
-// (batch x tokens, query heads): head_dim 64 causal 1 x 616, 12 10.6 -> 6.8 (1 x 4 x 32), 1 x 2656, 16 36.2 -> 24.1 (2 x 2 x 64), 36 x 208, 12 14.7 -> 11.8
-// (4 x 1 x 32), full 1 x 509, 16 9.2 -> 6.5; head_dim 128 causal 1 x 1172, 16 24.1 -> 19.1, 1 x 1152, 32 27.0 -> 22.6 (2 x 2 x 32).
+// (batch x tokens, query heads): head_dim 64 causal 1 x 616, 12 10.6 -> 6.8 (1 x 4 x 32), 7 x 2049, 2 26.7 -> 18.2 (2 x 2 x 64), 36 x 208, 12 14.7 -> 11.8
+// (4 x 1 x 32), full 1 x 509, 16 9.2 -> 6.5 (1 x 4 x 32); head_dim 128 causal 1 x 1172, 16 24.1 -> 19.1, 1 x 393, 32 10.9 -> 9.5 (2 x 2 x 32).
 // The estimate in us: a start, then the longer of one chain (`chain` per step of the longest work-group) and the chip's throughput
 // (`step` and `group` per step and work-group, over 256 compute units); with one key group, where work-groups of all lengths
-// share a compute unit, the two overlap badly (the fourth root of the fourth powers' sum).  Fitted to 460 calls, mean error
-// 6-8 %; a shape other than 4 x 1 x 64 is taken where it is 3 % below: over those calls 5.4 % (head_dim 64) and 1.5 % (128) faster, 10 % slower at
-// worst.  `resident`: work-groups of the chip at once (LDS); beyond that shapes with key groups do not serve.
+// share a compute unit, the two overlap badly (the fourth root of the fourth powers' sum).  Fitted to 262 calls of head_dim 64 and 202 of
+// 128 (profiles/attention_shape_calls.csv), mean error 6-8 %; a shape other than 4 x 1 x 64 is taken where it is 3 % below: over those calls 5.2 %
+// and 1.6 % faster, the best shape of each 7.2 % and 2.3 %, the worst choice 7 % slower.  `resident`: work-groups of the chip at once
+// (LDS); beyond that shapes with key groups do not serve.
 struct Shape { int nw, kg, bkv, resident; double start, chain, step, group; };
 static constexpr Shape kShapes64[4] = {{4, 1, 64, 0, 3.52, 0.775, 0.56, 1.36}, {4, 1, 32, 0, 3.46, 0.45, 0.289, 1.12},
                                        {2, 2, 64, 512, 3.63, 0.932, 0.592, 1.734}, {1, 4, 32, 512, 3.4, 0.86, 0.404, 1.511}};

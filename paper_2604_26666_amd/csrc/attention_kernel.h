@@ -113,7 +113,7 @@ __device__ __forceinline__ s16x4_t read_transposed(const char *lds)
 #endif
 }
 
-// LDS layout of a key or value block: [64 rows][D] bf16, the 16-byte chunk c of row r stored at
+// LDS layout of a step's keys or values: [rows = keys of all key groups][D] bf16, the 16-byte chunk c of row r stored at
 // chunk position c ^ swz(r).
 //  K (read as MFMA A operand: 32 consecutive rows x 2 consecutive chunks per instruction): the
 //    XOR puts 16 consecutive rows into the 16 chunks of the 256 bytes that the banks span: with the row number

@@ -329,16 +329,6 @@ static double few_rows_us(const ConfigDesc &c, int64_t batch, int64_t M, int64_t
     return (chain > memory ? chain : memory) + (splits > 1 ? 5.0 + (double)M * N * 8.0 * splits / 1e7 : 0.0);
 }
 
-// Where the skinny kernel's estimate is below the plan's.  Both estimates were fitted to 1100 calls of 1 to 64 rows, 16 to
-// 36000 columns, K of 64 to 131072 and batches up to 128, with and without a workspace, operands from HBM; the choice costs
-// 0.4 % over the better kernel of every call on average; in 28 of them the one it takes is more than 3 % slower, by 25 % at most
-// but for two (46 and 49 %).  Some of the calls (us, plan -> skinny; * the plan is kept):
-//    M x N x K:  16 x 4096 x 14336  59.6 -> 25.6     16 x 768 x 3072  9.5 -> 6.3       64 x 3072 x 768  5.3 -> 4.4
-//                16 x 16384 x 8192  62.6 -> 52.0     16 x 16384 x 256  5.4 -> 6.6 *    32 x 16384 x 1024  9.6 -> 11.2 *
-//    with a workspace, so that the plan may split K:
-//                16 x 64 x 8192  11.7 -> 10.3        16 x 64 x 32768  12.0 -> 34.9 *   64 x 64 x 131072  16.6 -> 315 *
-//    without:    16 x 64 x 8192  23.7 -> 10.4        64 x 64 x 32768  134 -> 51        64 x 64 x 131072  559 -> 318
-//    batches:    8 x (16 x 256 x 1024)  6.7 -> 4.1   128 x (32 x 64 x 4096)  24.8 -> 37.2 *   128 x (64 x 512 x 1024)  33.1 -> 75.4 *
 // The plan's time where the chip has few work-groups of it: model_time prices full chips.  Fitted to the same calls as
 // small_us, of which those with more than 64 rows or B as [K][N] ran the tile kernel (mean error 13 and 6 %).
 static double small_plan_us(const ConfigDesc &c, bool trans_b, int64_t batch, int64_t M, int64_t N, int64_t K, int splits)
@@ -358,11 +348,22 @@ static double small_plan_us(const ConfigDesc &c, bool trans_b, int64_t batch, in
 }
 
 // Which form of the skinny kernel runs in the plan's place: kFewRows, a tile of small_us, or kNoSkinny.
+// Few rows where the skinny kernel's estimate (skinny_us) is below the plan's (few_rows_us).  Both were fitted to 1100 calls of 1 to 64 rows, 16 to
+// 36000 columns, K of 64 to 131072 and batches up to 128, with and without a workspace, operands from HBM; the choice costs
+// 0.4 % over the better kernel of every call on average; in 28 of them the one it takes is more than 3 % slower, by 25 % at most
+// but for two (46 and 49 %).  Some of the calls (us, plan -> skinny; * the plan is kept):
+//    M x N x K:  16 x 4096 x 14336  59.6 -> 25.6     16 x 768 x 3072  9.5 -> 6.3       64 x 3072 x 768  5.3 -> 4.4
+//                16 x 16384 x 8192  62.6 -> 52.0     16 x 16384 x 256  5.4 -> 6.6 *    32 x 16384 x 1024  9.6 -> 11.2 *
+//    with a workspace, so that the plan may split K:
+//                16 x 64 x 8192  11.7 -> 10.3        16 x 64 x 32768  12.0 -> 34.9 *   64 x 64 x 131072  16.6 -> 315 *
+//    without:    16 x 64 x 8192  23.7 -> 10.4        64 x 64 x 32768  134 -> 51        64 x 64 x 131072  559 -> 318
+//    batches:    8 x (16 x 256 x 1024)  6.7 -> 4.1   128 x (32 x 64 x 4096)  24.8 -> 37.2 *   128 x (64 x 512 x 1024)  33.1 -> 75.4 *
 // Small outputs (small_us) where the estimate is 8 % below the plan's (us, plan -> skinny; M x N x K): B as [K][N] 43 x 2736 x 80 5.3 -> 3.6, 1 x 32 x 3688
 // 15.0 -> 5.7, 22 x 176 x 3920 16.0 -> 7.6, 120 x 112 x 6280 31.3 -> 13.3, 610 x 344 x 7272 36.3 -> 23.7; but 159 x 5840 x 928 12.2 -> 16.8; [N][K]
 // 67 x 56 x 256 4.7 -> 3.3, 425 x 104 x 1352 7.2 -> 4.5, 180 x 1920 x 600 6.0 -> 5.1; but 572 x 1552 x 2128 14.8 -> 25.  Over the 650 calls with more than 64
 // rows or B as [K][N] the choice is 1.29 and 1.50 times as fast as the plan alone, the better kernel of every call 1.34 and 1.55 times;
-// 4 of them lose more than 3 %, 12 % at most.
+// 4 of them lose more than 3 %, 12 % at most.  The estimates of small outputs are of operands in the memory-side cache; cold ones (60 random calls each,
+// caches filled with other data) are 1.62 and 1.33 times as fast as the plan, warm ones 1.66 and 1.28 times.
 static constexpr int kNoSkinny = -2, kFewRows = -1;
 static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c)
 {

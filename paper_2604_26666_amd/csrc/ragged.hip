@@ -2,7 +2,7 @@
 // (odd leading dimensions, K or N no multiple of 8, unaligned pointers).  The main kernel moves operands
 // straight from global memory into LDS, which needs 16-byte aligned rows; here they pass through registers,
 // where a 16-byte global load may start at any 2-byte address (the unaligned-access mode that the compiler
-// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured: 2000 x 1999 x 1777 33.6 us (when it was
+// targets on this architecture), and go to LDS in the same swizzled layouts.  Measured: 2000 x 1999 x 1777 33.6 us = 423 TFLOP/s (when it was
 // 35, rows that all begin at whole words took 29 and all at half words 36-40); the main kernel on 2000 x 2000 x 1784 24.4.  Two steps of loads in flight,
 // with the order of loads and matrix products fixed, were slower (37.4), so the loop's order is the compiler's.
 #include "launch.h"
@@ -27,7 +27,7 @@ __device__ __forceinline__ s16x4_t read_tr16(const char *lds)
 // A work-group owns a BM x BN tile; its 4 KW waves form KW groups of WGM x WGN waves, and group g takes the 64-deep
 // K steps g, g + KW, ...  Each group keeps two LDS stages and two further steps of operands in registers on their
 // way there (the K loop is bound by the loads' latency: with one step in flight and one group per compute unit
-// 2000 x 1999 x 1777 took 45 us, as it stands 33.0 us = 430 TFLOP/s; the one-thread-per-element kernel 3416 us).  A 16-byte piece that would cross the end of a row (K-contiguous operand) or of the
+// 2000 x 1999 x 1777 took 45 us, as it stands 33.6; the one-thread-per-element kernel 3416 us).  A 16-byte piece that would cross the end of a row (K-contiguous operand) or of the
 // matrix's columns (B as [K][N]) is loaded so that it ends there and shifted into place, so nothing outside the
 // matrices is ever read; a step past the end of K brings zeros.
 template <int BM, int BN, int WGM, int WGN, int KW, bool TRANS_B, bool F16>
@@ -357,8 +357,9 @@ static hipError_t launch_tile(GemmArgs a, bool trans_b, int grid_z, hipStream_t 
 }
 
 // Operands whose rows hold at least one 16-byte piece; shorter ones stay with the guarded kernel.  So do sizes of which the
-// edge of a last tile, or the step that a last K group loads ahead (3 x 4 x 64 past K), would leave the kernel's 32-bit
-// indexes: a wrapped one is negative, which its clamps take for inside.
+// edge of a last tile, or K-values past the end, would leave the 32-bit indexes: a last K group's step begins up to 3 x 64 past
+// the last block of 64, and a wave of the kernel whose waves split K loads up to 3 turns of 4 waves (12 blocks) past it.  A wrapped
+// index is negative, which the clamps take for inside.
 // And so does a K of a few elements where the guarded kernel has little to do, or where a tile here is mostly edge (us, guarded
 // and this kernel, K = 9 unless said): 8 x 8 2.1 / 2.7, 1 x 1000 2.5 / 3.3, 300 x 300 2.8 / 3.3 (K = 13 3.2 / 3.2, 17 3.7 / 3.3),
 // 100000 x 9 8.7 / 17.2 (K = 17 13.5 / 17.3, with [N][K] 20.4 / 16.6), 9 x 100000 12.4 / 13.6 (K = 13 16.0 / 13.7);
@@ -412,7 +413,7 @@ static double ragged_us(const GemmArgs &a, bool trans_b, int64_t batch)
 
 // Small outputs go to the kernel whose waves split K where that is the faster one by its estimate (us, this kernel -> that one; M x N x K: 1 x 34 x 1917
 // [N][K] 11.1 -> 4.9, 9 x 83 x 1443 [N][K] 9.0 -> 4.3, 273 x 53 x 3855 [K][N] 21.5 -> 10.7, 45 x 2916 x 3331 [N][K] 18.0 -> 12.8; but 304 x 3477 x 246 [N][K]
-// 6.4 -> 9.2, 137 x 3402 x 334 [K][N] 6.2 -> 8.6).  Over the 420 calls the choice is 1.23 times as fast, the better kernel of every call 1.25.
+// 6.4 -> 9.2, 137 x 3402 x 334 [K][N] 6.2 -> 8.6).  Over the 420 calls of profiles/gemm_small_odd_calls.csv the choice is 1.23 times as fast, the better kernel of every call 1.25.
 static constexpr int kSmallForms = 6;                        // the tiles of small_any_us follow those of kRaggedTiles
 int ragged_form(const GemmArgs &a, bool trans_b, int64_t batch)
 {

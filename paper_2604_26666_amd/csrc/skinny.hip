@@ -433,10 +433,15 @@ static hipError_t launch_skinny_as(const GemmArgs &a, int grid_z, hipStream_t st
     return hipGetLastError();
 }
 
-// B larger than this is asked for as non-temporal data (us per feed-forward block of 16 rows, three sets of weights in turn,
-// cached -> non-temporal; megabytes of the two products' weights: 24 x 2 4096 x 14336, 352 MB: 73.3 -> 70.7; 2048 x 5632, 69 MB: 17.7 ->
-// 23.0; 1024 x 4096, 17 MB: 10.4 -> 12.0; 768 x 3072: 8.8 -> 10.4).  A fourth of the memory-side cache: several such matrices
-// are found there again, larger ones push each other out.
+// B larger than this is asked for as non-temporal data, which leaves no copy of it in the memory-side cache (us per
+// feed-forward block of 16 rows, three sets of weights in turn, cached -> non-temporal; megabytes of the products' weights: 4096 x
+// 14336, 352 MB: 73.3 -> 70.7; 2048 x 5632, 69 MB: 17.7 -> 23.0; 1024 x 4096, 17 MB: 10.4 -> 12.0; 768 x 3072: 8.8 -> 10.4).  A fourth of the
+// memory-side cache: several such matrices are found there again, larger ones push each other out.  Where a program has so many that
+// none is (the caches filled with other data before every call), ordinary loads cost next to nothing up to 23 MB and a few
+// per cent above, and where they are they gain up to a third (GEMM of 16 rows, us, ordinary / non-temporal, cold; the same warm):
+//    N x K  768 x 3072  6.6 / 6.6; 4.9 / 6.2      2048 x 5632 (23 MB)  9.9 / 9.9; 6.9 / 9.8     4096 x 4096 (34 MB)  9.1 / 9.0; 8.4 / 8.9
+//          6144 x 4096 (50 MB) 14.0 / 13.8; 11.0 / 13.3    7168 x 4096 (59 MB) 14.7 / 14.3; 11.5 / 13.6    4096 x 7168 13.5 / 13.0; 11.1 / 12.5
+//    (the worst cold: 4096 x 7168 of 1 row 12.3 / 11.5).
 constexpr int64_t kStreamBytes = (int64_t)64 << 20;
 static bool streams(const GemmArgs &a, int64_t batch) { return (int64_t)a.N * a.K * 2 * batch > kStreamBytes; }
 
@@ -496,7 +501,7 @@ double skinny_us(const GemmArgs &a, int64_t batch, bool whole_lines)
 // there are more of them.  The estimate: 3 us, the K steps one after the other at 84 (B as [K][N]) or 108 GB/s per compute unit;
 // never faster than the 8.2 or 11.2 TB/s at which the L2s deliver what the work-groups ask for together, nor than B arrives
 // once in each XCD that asks for a piece of its lines (as [K][N], a work-group's 16 NT columns are a part of 128-byte lines).
-// Fitted to 900 calls of 1 to 1536 rows, 32 to 8192 columns, K of 64 to 8192 (mean error 9 and 12 %).
+// Fitted to 900 calls of 1 to 1536 rows, 32 to 8192 columns, K of 64 to 8192 (profiles/gemm_small_calls.csv; mean error 9 and 12 %).
 double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
 {
     double best = 0.0;
@@ -565,8 +570,8 @@ hipError_t launch_skinny_gemm(const GemmArgs &a, bool trans_b, int form, int gri
 }
 
 // Operands of any alignment: the estimate of small_us with what loads at odd addresses reach (16 bytes per lane from half a
-// word run at 36 GB/s per compute unit, from whole words at 99), for a tile of 16 x 16 and one of 32 x 32; fitted to 445 calls of 1 to 3000
-// rows, 16 to 4096 columns, K of 16 to 4096 (mean error 6-9 %).
+// word run at 36 GB/s per compute unit, from whole words at 99), for a tile of 16 x 16 and one of 32 x 32; fitted to 420 calls of 1 to 3000
+// rows, 16 to 4096 columns, K of 16 to 4096 (profiles/gemm_small_odd_calls.csv; mean error 6-9 %).
 struct AnyTile { int mt, nt; double start[2], group[2], latency[2], rate[2], pull[2]; };       // [B as [K][N], as [N][K]]
 static constexpr AnyTile kAnyTiles[2] = {{1, 1, {3.38, 3.25}, {0.0006, 0.0007}, {0.255, 0.196}, {42.6e3, 78.3e3}, {6.26e6, 10.5e6}},
                                          {2, 2, {4.33, 3.87}, {0.0009, 0.0014}, {0.025, 0.012}, {59.1e3, 75.0e3}, {6.76e6, 9.6e6}}};

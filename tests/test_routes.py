@@ -45,14 +45,14 @@ def test_a_call_that_is_refused_has_no_route():
     assert route(0, 8, 8, 1) == -2 and route(8, 8, 8, 1, cfg=99) == -7 and route(8, 8, 8, 1, a=None) == -1
 
 
-# 32-bit indexes: a step loaded ahead, or a tile's edge, must not pass 2^31 (the guarded kernel counts K one by one)
+# 32-bit indexes: a block of K loaded past the last one, or a tile's edge, must not pass 2^31 (the guarded kernel counts K one by one)
 @pytest.mark.parametrize("nk", [0, 1])
 def test_ragged_kernel_keeps_its_indexes_in_range(nk):
     top, last = 2 ** 31 - 1, 2 ** 31 - 1 - 4096
     for K in (top, top - 63, top - 960, last + 1):
         assert kernels(1, 8, K, nk) == ["guarded"], K
-    # groups x steps ahead x depth, all below the margin, and a tile's edge
-    assert 3 * 4 * 64 + 4 * 64 + 64 < 4096 and kernels(1, 8, last, nk) == ["ragged"]
+    # (12 blocks of 64 past the last, with the waves that split K, are well below the margin, and so is a tile's edge)
+    assert kernels(1, 8, last, nk) == ["ragged"]
     for K in (25, 999, 2 ** 21 + 8):              # odd rows, and aligned ones past the tile kernel's leading dimensions
         assert kernels(3, 9, K, nk) == ["ragged"], K
     assert kernels(last + 1, 9, 25, nk) == ["guarded"] and kernels(1, last + 2, 25, nk) == ["guarded"] and kernels(1, last, 25, nk) == ["ragged"]
