@@ -164,19 +164,20 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
         pl.split = r.split == 0 ? 1 : r.split;             // negative: a tail split, which needs a workspace as well
         pl.group_m = r.group_m > 0 ? r.group_m : 4;
     };
-    const TableRow *listed = g_table;
-    while (listed->cfg >= 0 && !matches(*listed)) ++listed;
     {
         std::lock_guard<std::mutex> lock(g_registry_mutex);
         for (const TableRow &r : g_registry)
             if (matches(r)) {
                 take(r);
                 // (the file that the table is generated from changes nothing when it is loaded)
-                pl.loaded = listed->cfg < 0 || r.cfg != listed->cfg || r.split != listed->split || r.group_m != listed->group_m;
+                const TableRow *t = g_table;
+                while (t->cfg >= 0 && !matches(*t)) ++t;
+                pl.loaded = t->cfg < 0 || r.cfg != t->cfg || r.split != t->split || r.group_m != t->group_m;
                 return pl;
             }
     }
-    if (listed->cfg >= 0) { take(*listed); return pl; }
+    for (const TableRow *r = g_table; r->cfg >= 0; ++r)
+        if (matches(*r)) { take(*r); return pl; }
     const int64_t nout = gated ? N / 2 : N;
     const bool all_fit = any_grid_fits(M, nout);
     double best = 0;
