@@ -220,22 +220,19 @@ def build(jobs=None, verbose=False, extra_flags=(), lib=LIB, obj_dir=OBJ):
     FLAGS = list(globals()["FLAGS"]) + list(extra_flags)
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
-    units = []
+    units, asm_units = [], []
     for (cid, bm, bn, wm, wn, bk, st) in configs():
-        obj = os.path.join(OBJ, f"inst{cid}.o")
-        units.append((obj, [HIPCC] + FLAGS + ["-Rpass-analysis=kernel-resource-usage", f"-DFACT_ID={cid}", f"-DFACT_BM={bm}", f"-DFACT_BN={bn}",
-                                              f"-DFACT_WM={wm}", f"-DFACT_WN={wn}", f"-DFACT_BK={bk}", f"-DFACT_STAGES={st}",
-                                              "-c", os.path.join(CSRC, "inst.hip"), "-o", obj]))
+        # (the kernels for rows of C at half a word are a unit of their own; 8-wave and 192-wide configurations have none)
+        for name, odd in [(f"inst{cid}", [])] + ([(f"inst{cid}_odd", ["-DFACT_ODD_ROWS"])] if wm * wn <= 4 and bn != 192 else []):
+            cmd = [HIPCC] + FLAGS + [f"-DFACT_ID={cid}", f"-DFACT_BM={bm}", f"-DFACT_BN={bn}", f"-DFACT_WM={wm}", f"-DFACT_WN={wn}",
+                                     f"-DFACT_BK={bk}", f"-DFACT_STAGES={st}", *odd, os.path.join(CSRC, "inst.hip"), "-o"]
+            obj, asm = os.path.join(OBJ, name + ".o"), os.path.join(OBJ, name + ".s")
+            units.append((obj, cmd + [obj, "-Rpass-analysis=kernel-resource-usage", "-c"]))
+            # the same kernels once more as assembly text, for the check of the inline-asm MFMAs below
+            asm_units.append((asm, "gemm_kernel", cmd + [asm, "--cuda-device-only", "-S"]))
     for name in ("aux_kernels", "ragged", "skinny", "fact_api", "attention", "block"):
         obj = os.path.join(OBJ, name + ".o")
         units.append((obj, [HIPCC] + FLAGS + ["-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(CSRC, name + ".hip"), "-o", obj]))
-    # the same kernels once more as assembly text, for the check of the inline-asm MFMAs below
-    asm_units = []
-    for (cid, bm, bn, wm, wn, bk, st) in configs():
-        asm_units.append((os.path.join(OBJ, f"inst{cid}.s"), "gemm_kernel",
-                          [HIPCC] + FLAGS + [f"-DFACT_ID={cid}", f"-DFACT_BM={bm}", f"-DFACT_BN={bn}", f"-DFACT_WM={wm}", f"-DFACT_WN={wn}",
-                                             f"-DFACT_BK={bk}", f"-DFACT_STAGES={st}", "--cuda-device-only", "-S",
-                                             os.path.join(CSRC, "inst.hip"), "-o", os.path.join(OBJ, f"inst{cid}.s")]))
     asm_units.append((os.path.join(OBJ, "attention.s"), "attn_fwd_kernel",
                       [HIPCC] + FLAGS + ["--cuda-device-only", "-S", os.path.join(CSRC, "attention.hip"), "-o", os.path.join(OBJ, "attention.s")]))
     usage = {}

@@ -349,7 +349,12 @@ __device__ __forceinline__ GemmArgs fresh_args()
 // PERSIST: the work-group walks several work items (persistent launch; 4-wave configurations only).  The
 // ordinary kernel is a separate instantiation in which the loop below is gone at compile time.
 // F16: the operands, bias, residual and the 16-bit output are IEEE binary16 instead of bf16.
-template <int BM, int BN, int WGM, int WGN, bool TRANS_B, int BK, int STAGES, bool PERSIST, bool F16 = false>
+// ODD: for plain outputs with rows that begin at half a word (store8_of_row).  Instantiations of their own, since their epilogues
+// in the common kernels, reached or not, cost every other call with a short K its share of the code's fetch: 5504 x 7624 x 104
+// [K][N] 33.2 us for 32.3, 5384 x 1704 x 80 16.8 for 16.3, 19 such calls on 256 x 256 tiles 1.9 % on average.  Not for 192-wide tiles:
+// with those epilogues inside, their other calls are 3-4 % faster (12 of K up to 1000; where the code lies, like the order of their common forms).
+constexpr bool odd_rows_apart(int bn) { return bn != 192; }
+template <int BM, int BN, int WGM, int WGN, bool TRANS_B, int BK, int STAGES, bool PERSIST, bool F16 = false, bool ODD = false>
 __global__ void __launch_bounds__(WGM * WGN * 64)
 gemm_kernel(const GemmArgs p)
 {
@@ -404,6 +409,7 @@ gemm_kernel(const GemmArgs p)
     // Tiles of a C whose rows are not 16-byte aligned, and interior ones that are not written through, take a register path of their own
     // (8-wave work-groups and persistent launches do not have it: guarded path, or write-through stores).
     constexpr bool REG_ANY = NWAVES <= 4 && !PERSIST;
+    static_assert((REG_ANY && odd_rows_apart(BN)) || !ODD, "rows at half a word leave through the register path");
 
     // ---- epilogue ---------------------------------------------------------------------------
     // Accumulator tile (mt, nt), lane (r16, q): output row mt*16 + r16, output columns
@@ -425,9 +431,9 @@ gemm_kernel(const GemmArgs p)
     // operand ring may be filling for the next tile while it runs.  Otherwise the LDS-staged passes.
     auto epilogue = [&](auto in_regs_tag) __attribute__((always_inline)) {
     constexpr bool IN_REGS = decltype(in_regs_tag)::value;
-    const bool gated = (p.act == ACT_SILU_GATE);
+    const bool gated = !ODD && p.act == ACT_SILU_GATE;
     const int nout = gated ? (p.N >> 1) : p.N;
-    const bool partial = p.splits > 1 || p.out_f32;
+    const bool partial = !ODD && (p.splits > 1 || p.out_f32);
     // The lane's position is derived anew here, so that nothing of it stays live in a vector register
     // across the K loop (the 8-wave kernels have no register to spare for that).
     const int tid = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) + wave * 64;
@@ -743,10 +749,9 @@ gemm_kernel(const GemmArgs p)
     // Edge tiles of such a C take it too, with every access guarded.  (In the LDS-staged general path, which a launch's interior
     // tiles do not run, they fetched cold code of their own: 3547 x 2369 x 328, of which a seventh of the tiles are edges, 31.9 us
     // when all tiles took that path, 33.7 when the edges alone did, 24.1 like this; 2726 x 30276 x 376 204, 156 and 124 us.)
-    // (Rows at half a word run through instances of their own, not gated, the columns in descending order so that a lane's next
-    // element is there: as a branch of one instance they cost 4648 x 7208 x 64 on whole words 34.5 us for 32.7.)
+    // (Rows at half a word: the columns in descending order so that a lane's next element is there.)
     auto reg_epilogue_any = [&](auto gated_tag, auto edge_tag, auto odd_tag) __attribute__((always_inline)) {
-        constexpr bool GATED = decltype(gated_tag)::value, EDGE = decltype(edge_tag)::value, ODD = decltype(odd_tag)::value;
+        constexpr bool GATED = decltype(gated_tag)::value, EDGE = decltype(edge_tag)::value, ODD_ROWS = decltype(odd_tag)::value;
         constexpr int OT = GATED ? NT / 2 : NT, NP = OT / 2;
         static_assert(OT % 2 == 0, "tiles are exchanged in pairs");
         const int n = n_wave + (q & 1) * 16 + (q >> 1) * 8;
@@ -787,7 +792,7 @@ gemm_kernel(const GemmArgs p)
             if constexpr (mt + 1 < MT) load_res(mt + 1);
             uint32_t first = 0;
             static_for<NP>([&](auto pr_) __attribute__((always_inline)) {
-                constexpr int pr = ODD ? NP - 1 - decltype(pr_)::value : decltype(pr_)::value;
+                constexpr int pr = ODD_ROWS ? NP - 1 - decltype(pr_)::value : decltype(pr_)::value;
                 if constexpr (EDGE && BN != 192) { if (n_wave + 32 * pr >= nout) return; }      // (columns likewise)
                 f32x4_t x0 = AccTile<mt * NT + 2 * pr>::get(), x1 = AccTile<mt * NT + 2 * pr + 1>::get();
                 if constexpr (GATED) {
@@ -825,7 +830,7 @@ gemm_kernel(const GemmArgs p)
                 uint16_t *at = (uint16_t *)(crow + pr * 32);
                 const int left = EDGE ? nout - (n + pr * 32) : 9;
                 const bool live = !EDGE || row + 16 * mt < p.M;
-                if constexpr (ODD) {
+                if constexpr (ODD_ROWS) {
                     // (column order of the lanes: q = 0, 2, 1, 3, past the last one the next 32 columns' first, which is done already)
                     const uint32_t follow = (uint32_t)__builtin_amdgcn_ds_bpermute(next_lane, (int)(q == 0 ? first : o[0]));
                     first = o[0];
@@ -838,7 +843,11 @@ gemm_kernel(const GemmArgs p)
             crow += 16 * p.ldc;
         });
     };
-    if constexpr (IN_REGS) {
+    if constexpr (IN_REGS && ODD) {
+        const bool edge = e_m0 + BM > p.M || e_n0 + BN > nout;
+        if (edge) reg_epilogue_any(std::false_type{}, std::true_type{}, std::true_type{});
+        else reg_epilogue_any(std::false_type{}, std::false_type{}, std::true_type{});
+    } else if constexpr (IN_REGS) {
         if constexpr (REG_ANY) {
             // (192-wide tiles: laid out behind the common forms, whose code then follows the K loop's; 3547 x 2368 x 328 15.9 -> 15.5 us,
             // 610 x 68608 x 840 gated 153.7 -> 150.5; the other widths do not gain by it, and it costs gated tiles of unaligned rows 3 %.)
@@ -851,7 +860,9 @@ gemm_kernel(const GemmArgs p)
                 if constexpr (NT % 4 == 0) {
                     if (gated) { if (edge) reg_epilogue_any(T, T, F); else reg_epilogue_any(T, F, F); return; }
                 }
-                if (__builtin_expect((p.ldc & 1) | ((size_t)C >> 1 & 1), 0)) { if (edge) reg_epilogue_any(F, T, T); else reg_epilogue_any(F, F, T); }
+                bool odd = false;
+                if constexpr (!odd_rows_apart(BN)) odd = __builtin_expect((p.ldc & 1) | ((size_t)C >> 1 & 1), 0);
+                if (odd) { if constexpr (!odd_rows_apart(BN)) { if (edge) reg_epilogue_any(F, T, T); else reg_epilogue_any(F, F, T); } }
                 else if (edge) reg_epilogue_any(F, T, F); else reg_epilogue_any(F, F, F);
                 return;
             }
@@ -1113,9 +1124,9 @@ gemm_kernel(const GemmArgs p)
     // by-value copy, whose fields stay in registers across the K loop as far as it needs them.
     auto tile_args = [&]() __attribute__((always_inline)) -> GemmArgs { if constexpr (PERSIST) return fresh_args(); else return p_launch; };
     const GemmArgs p = tile_args();
-    const bool gated = (p.act == ACT_SILU_GATE);
+    const bool gated = !ODD && p.act == ACT_SILU_GATE;
     const int nout = gated ? (p.N >> 1) : p.N;
-    const bool partial = p.splits > 1 || p.out_f32;
+    const bool partial = !ODD && (p.splits > 1 || p.out_f32);
     const int tid = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) + wave * 64;      // == threadIdx.x
     const int lane = tid & 63;
     const int r16 = lane & 15, q = lane >> 4;

@@ -1,5 +1,6 @@
 // One tile configuration's kernels (both B layouts).  Built once per row of configs.def with
-// -DFACT_ID=.. -DFACT_BM=.. -DFACT_BN=.. -DFACT_WM=.. -DFACT_WN=.. -DFACT_BK=.. -DFACT_STAGES=..
+// -DFACT_ID=.. -DFACT_BM=.. -DFACT_BN=.. -DFACT_WM=.. -DFACT_WN=.. -DFACT_BK=.. -DFACT_STAGES=.., and for 4-wave
+// configurations (but 192-wide ones) once more with -DFACT_ODD_ROWS: the kernels for plain outputs with rows at half a word.
 #include "launch.h"
 #include "lds_limit.h"
 
@@ -7,6 +8,13 @@ namespace fact {
 
 #define FACT_CAT2(a, b) a##b
 #define FACT_CAT(a, b) FACT_CAT2(a, b)
+
+#ifdef FACT_ODD_ROWS
+constexpr bool ODD = true;
+#else
+constexpr bool ODD = false;
+#endif
+hipError_t FACT_CAT(fact_launch_odd_cfg, FACT_ID)(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream);
 
 template <bool TRANS_B>
 static hipError_t launch_one(const GemmArgs &args, int grid_z, hipStream_t stream)
@@ -16,9 +24,13 @@ static hipError_t launch_one(const GemmArgs &args, int grid_z, hipStream_t strea
         return hipErrorInvalidConfiguration;          // (the host side never selects such a tile for this layout)
     } else {
     constexpr bool CAN_PERSIST = FACT_WM * FACT_WN <= 4;      // the persistent form exists for 4-wave configurations
-    auto kern = gemm_kernel<FACT_BM, FACT_BN, FACT_WM, FACT_WN, TRANS_B, FACT_BK, FACT_STAGES, false>;
-    auto kern_p = gemm_kernel<FACT_BM, FACT_BN, FACT_WM, FACT_WN, TRANS_B, FACT_BK, FACT_STAGES, CAN_PERSIST>;
-    auto kern_h = gemm_kernel<FACT_BM, FACT_BN, FACT_WM, FACT_WN, TRANS_B, FACT_BK, FACT_STAGES, false, true>;      // binary16 operands (ordinary launches only)
+    auto kern = gemm_kernel<FACT_BM, FACT_BN, FACT_WM, FACT_WN, TRANS_B, FACT_BK, FACT_STAGES, false, false, ODD>;
+    auto kern_p = gemm_kernel<FACT_BM, FACT_BN, FACT_WM, FACT_WN, TRANS_B, FACT_BK, FACT_STAGES, CAN_PERSIST && !ODD, false, ODD>;
+    auto kern_h = gemm_kernel<FACT_BM, FACT_BN, FACT_WM, FACT_WN, TRANS_B, FACT_BK, FACT_STAGES, false, true, ODD>;      // binary16 operands (ordinary launches only)
+    if constexpr (CAN_PERSIST && odd_rows_apart(FACT_BN) && !ODD)
+        if (args.act != ACT_SILU_GATE && args.splits <= 1 && !args.out_f32 && !args.c_f32 && args.persist_items <= 0 &&
+            ((args.ldc & 1) || ((uintptr_t)args.C & 2) || (grid_z > 1 && (args.stride_c & 1))))
+            return FACT_CAT(fact_launch_odd_cfg, FACT_ID)(args, TRANS_B, grid_z, stream);
     const bool persist = CAN_PERSIST && args.persist_items > 0;
     if (args.persist_items > 0 && (!CAN_PERSIST || args.f16)) return hipErrorInvalidConfiguration;     // (the host side never asks for it)
     constexpr int lds = lds_total(FACT_BM, FACT_BN, FACT_WM, FACT_WN, FACT_BK, FACT_STAGES);
@@ -37,7 +49,12 @@ static hipError_t launch_one(const GemmArgs &args, int grid_z, hipStream_t strea
     }
 }
 
-hipError_t FACT_CAT(fact_launch_cfg, FACT_ID)(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream)
+#ifdef FACT_ODD_ROWS
+#define FACT_LAUNCH fact_launch_odd_cfg
+#else
+#define FACT_LAUNCH fact_launch_cfg
+#endif
+hipError_t FACT_CAT(FACT_LAUNCH, FACT_ID)(const GemmArgs &args, bool trans_b, int grid_z, hipStream_t stream)
 {
     return trans_b ? launch_one<true>(args, grid_z, stream) : launch_one<false>(args, grid_z, stream);
 }
