@@ -84,6 +84,13 @@ def test_few_rows(M, N, K, batch, ws, want):
     assert got == (["skinny"] if want == "skinny" else ["tiles", "reduce"] if ws and plan[2] > 1 else ["tiles"])
 
 
+# small outputs with a workspace, where the plan splits K: the kernel whose waves split it for the shorter ones
+@pytest.mark.parametrize("M,N,K,nk,want", [(280, 120, 7232, 1, ["skinny"]), (80, 304, 15168, 1, ["tiles", "reduce"]), (352, 328, 6848, 1, ["tiles", "reduce"]),
+                                           (72, 64, 5888, 0, ["skinny"]), (160, 64, 7680, 0, ["tiles", "reduce"]), (256, 64, 8192, 0, ["tiles", "reduce"])])
+def test_small_outputs_whose_plan_splits_k(M, N, K, nk, want):
+    assert kernels(M, N, K, nk, ws=True) == want and kernels(M, N, K, nk) == ["skinny"]
+
+
 def test_few_rows_only_where_nothing_else_was_asked_for():
     assert kernels(16, 4096, 4096, 1) == ["skinny"]
     assert kernels(16, 4096, 4096, 0) == ["tiles"] and kernels(65, 4096, 4096, 1) == ["tiles"]
