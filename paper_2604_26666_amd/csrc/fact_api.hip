@@ -374,7 +374,7 @@ static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const C
     const double small = small_us(a, trans_b, batch, &tile);
     // (A plan that splits K is quicker than its estimate, by what its reduction became, and a K as long as that longer here: with a workspace us, plan and
     // this kernel at their estimates' ratio: [N][K] 80 x 304 x 15168 13.1 / 13.8 at 0.86, 352 x 328 x 6848 13.2 / 14.7 at 0.90, but 280 x 120 x 7232 13.1 / 8.7 at
-    // 0.77; [K][N] 256 x 64 x 8192 11.4 / 13.5 at 0.87, 160 x 64 x 7680 13.4 / 13.6 at 0.67, but 72 x 64 x 5888 11.7 / 10.3 at 0.62.)
+    // 0.77; [K][N] 256 x 64 x 8192 10.4 / 14.0 at 0.87, 160 x 64 x 7680 13.4 / 13.6 at 0.67, but 72 x 64 x 5888 11.7 / 10.3 at 0.62.)
     const double line = a.splits <= 1 ? 0.92 : trans_b ? 0.8 : 0.65;
     if (!few) return tile >= 0 && small < line * small_plan_us(c, trans_b, batch, a.M, a.N, a.K, a.splits) ? tile : kNoSkinny;
     const double rows = skinny_us(a, batch, lines), plan = few_rows_us(c, batch, a.M, a.N, gated ? a.N / 2 : a.N, a.K, gated, a.splits, lines);
