@@ -493,6 +493,11 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     const int unit = gated ? 64 : 32;                 // elements of C between the addresses that rows may begin at (see kStoreThrough)
     a.store_through = ((uintptr_t)q.C & (uintptr_t)(2 * unit - 1)) == 0 && q.ldc % unit == 0 && (q.batch == 1 || q.stride_c % unit == 0);
 
+    // (see kStoreThrough; with A they have to leave the memory-side cache room for a step of the program: 8000 x 1024 x 4096 behind its up projection, 16 + 65 MB,
+    // the block 128 us as streaming stores and 131 without)
+    const int64_t c_bytes = q.batch * q.M * nout * 2;
+    a.store_stream = c_bytes > (int64_t)40 << 20 || c_bytes + q.batch * q.M * q.K * 2 > (int64_t)64 << 20;
+
     hipError_t e;
     if (pl.cfg < 0) {
         if (cfg_id != FACT_CONFIG_GUARDED && ragged_serves(a, q.trans_b != 0, q.batch)) {

@@ -84,6 +84,7 @@ struct GemmArgs {
     int group_m;            // tile rows walked together (L2 reuse)
     int vec_store;          // 1: C / residual / bias allow 16-byte vector access
     int store_through;      // 1: 16-byte stores of C are written through the L2 (see kStoreThrough)
+    int store_stream;       // 1: and past the memory-side cache
     int pf_sa, pf_sb;       // L2 prefetch: work-groups that share an A row-panel / a B column-panel (0: off; else a power of two)
     int pf_dist;            // L2 prefetch: K steps ahead of the step being loaded into LDS (>= 1)
     // Tail split (the last, partly filled round of tiles): work-groups [0, tail_first) own one tile
@@ -398,7 +399,12 @@ gemm_kernel(const GemmArgs p)
     // memory-side cache / rotated out of it: 8192 x 2304 x 768 + bias 37.5 -> 36.6 / 48.1 -> 40.2 us,
     // 8192 x 3072 x 768 + bias + GELU 45.3 -> 41.6 / 48.0 -> 41.7 us, 128 x 512^3 43.5 -> 42.5 / 51.5 -> 48.5 us,
     // 8192^3 713 -> 708 us; no shape slower.  (Write-through alone: better from the cache, worse from HBM.)
-    constexpr int kStoreThrough = 19;
+    // Outputs of up to 40 MB, 64 MB with A (p.store_stream == 0), without nt, so that the memory-side cache keeps them: the next launch of a program reads them, and
+    // from HBM a K step of it takes as long as the loads' latency (down projection of 1024 <- 4096 after an up projection of 384 tokens 19.5 us, by itself,
+    // from the cache, 14.3).  Feed-forward blocks, 19 -> 17: 3000 tokens of 768 x 3072 (hidden tensor 18 MB) 56.0 -> 46.8 us, 4000 of 1024 x 4096 (33 MB)
+    // 76.8 -> 66.3, 2000 of 2048 x 5632 (23 MB) 140 -> 136; but 8000 of 768 x 3072 (49 MB) 82.8 -> 85.0, 8192 x 8192 x 512 (134 MB) 75 -> 88.
+    // Single GEMMs of up to 40 MB: level.  Stores that stay in the L2s: 48.5, 67.7 and 136 us, and 90.9 beyond.
+    constexpr int kStoreThrough = 17, kStoreStream = 19;
     // ... where every row of C begins on a 64-byte boundary.  Rows at other addresses would send the lines at the tiles' edges to
     // memory in pieces of 16 or 32 bytes: plain stores then, which the L2 joins (us, through -> plain; 1024 x 50256 x 768 147 ->
     // 92.7, 1611 x 9840 x 456 41.7 -> 28.8; but rows at odd multiples of 64 bytes 2726 x 30304 x 376 98 -> 122, 4096 x 4128 x 4096
@@ -645,6 +651,8 @@ gemm_kernel(const GemmArgs p)
     // C and the residual are addressed through buffer descriptors of the wave's tile with one
     // lane-offset register each (32-bit offsets: the host sets vec_store only if a tile's rows span
     // less than 2^31 bytes), a tile row adds one vector add, a pair an immediate offset.
+    // The stores' cache policy is chosen per tile row; 192-wide tiles have one for outputs of any size (3000 x 4000 x 512: 19.2 us with the choice in the
+    // code, 18.0 with an instance for either, 17.2 like this; 8000 x 3072 x 768 + GELU, 49 MB, 2 % slower than as streaming stores; the other widths are level).
     auto reg_epilogue = [&](auto gated_tag, auto bias_tag, auto gelu_tag, auto res_tag) __attribute__((always_inline)) {
         constexpr bool GATED = decltype(gated_tag)::value, BIAS = decltype(bias_tag)::value;
         constexpr bool GELU = decltype(gelu_tag)::value, RES = decltype(res_tag)::value;
@@ -693,6 +701,7 @@ gemm_kernel(const GemmArgs p)
             if constexpr (LEAN) load_res(mt);
             else if constexpr (mt + 1 < MT) load_res(mt + 1);
             const uint32_t vo = voff_c + mt * row_c;
+            u32x4_t out[NP];
             static_for<NP>([&](auto pr_) __attribute__((always_inline)) {
                 constexpr int pr = decltype(pr_)::value;
                 f32x4_t x0 = AccTile<mt * NT + 2 * pr>::get(), x1 = AccTile<mt * NT + 2 * pr + 1>::get();
@@ -727,15 +736,22 @@ gemm_kernel(const GemmArgs p)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { z[2 * e] += in16<F16>(r4[e] & 0xFFFFu); z[2 * e + 1] += in16<F16>(r4[e] >> 16); }
                 }
-                u32x4_t o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const f32x2_t f2 = {z[2 * e], z[2 * e + 1]};
-                    o[e] = pack2<F16>(f2);     // round to nearest even
+                    out[pr][e] = pack2<F16>(f2);     // round to nearest even
                 }
                 // (scalar offset operand: the constant 0, see the note at the partial-tile stores below)
-                __builtin_amdgcn_raw_buffer_store_b128(o, rsrc_c, vo + pr * 64, 0, kStoreThrough);
+                if constexpr (BN == 192) __builtin_amdgcn_raw_buffer_store_b128(out[pr], rsrc_c, vo + pr * 64, 0, kStoreThrough);
             });
+            if constexpr (BN == 192) return;
+            if (p.store_stream) {
+#pragma unroll
+                for (int pr = 0; pr < NP; ++pr) __builtin_amdgcn_raw_buffer_store_b128(out[pr], rsrc_c, vo + pr * 64, 0, kStoreStream);
+            } else {
+#pragma unroll
+                for (int pr = 0; pr < NP; ++pr) __builtin_amdgcn_raw_buffer_store_b128(out[pr], rsrc_c, vo + pr * 64, 0, kStoreThrough);
+            }
         });
     };
     // The register path for C, bias or residual rows at any 2-byte address (odd leading dimensions such as a
