@@ -6,6 +6,7 @@
 // attention and SwiGLU); fact_block_forward is that composition with every stage on the GPU.
 #include "../../include/fact.h"
 
+#include "launch.h"
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -206,7 +207,7 @@ static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 static size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t n1, qkv, a, x1, n2, h, ws, ws_bytes, total;
+    size_t n1, qkv, a, x1, n2, h, ws, ws_bytes, least, total;
 };
 
 static int plan(const fact_block *b, Layout &L)
@@ -237,12 +238,15 @@ static int plan(const fact_block *b, Layout &L)
     L.x1 = off; off += up256((size_t)T * d * 2);
     L.n2 = off; off += up256((size_t)T * d * 2);
     L.h = off; off += up256((size_t)T * b->d_ff * 2);
-    size_t w = fact_gemm_splitk_workspace_bytes(T, nqkv, d, 0);
-    const size_t w2 = fact_gemm_splitk_workspace_bytes(T, d, nq, 0), w3 = fact_block_mlp_workspace_bytes(T, d, b->d_ff, b->act);
-    if (w2 > w) w = w2;
-    if (w3 > w) w = w3;
-    L.ws = off; L.ws_bytes = w; off += up256(w);
-    L.total = off;
+    const Workspace parts[3] = {splitk_workspace(T, nqkv, d), splitk_workspace(T, d, nq), mlp_workspace(T, d, b->d_ff, b->act)};
+    size_t least = 0, full = 0;
+    for (const Workspace &w : parts) {
+        if (w.least > least) least = w.least;
+        if (w.full > full) full = w.full;
+    }
+    L.ws = off; L.ws_bytes = full;
+    L.least = off + up256(least);       // (a scratch buffer of that size serves as well)
+    L.total = off + up256(full);
     return FACT_OK;
 }
 
@@ -352,7 +356,8 @@ int fact_block_forward(const fact_block *blk, const void *X, void *Y, void *scra
     int rc = plan(blk, L);
     if (rc != FACT_OK) return rc;
     if (!X || !Y || !scratch) return FACT_ERR_NULL;
-    if (scratch_bytes < L.total) return FACT_ERR_WORKSPACE;
+    if (scratch_bytes < L.least) return FACT_ERR_WORKSPACE;
+    if (scratch_bytes < L.total) L.ws_bytes = scratch_bytes - L.ws;
     if (!aligned16(X) || !aligned16(Y) || ((uintptr_t)scratch & 255u)) return FACT_ERR_ALIGN;
     const fact_block &b = *blk;
     const int64_t T = b.batch * b.tokens, d = b.d_model, D = b.head_dim, nq = b.n_q_heads * D;

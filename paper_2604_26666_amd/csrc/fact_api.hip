@@ -126,6 +126,11 @@ struct Plan {
     int split = 1;
     int group_m = 4;
     bool loaded = false;   // from a registry file read at run time that says another thing than the compiled-in table
+    // plan_one_round's choice, where it has one: it runs in the place of the above where the workspace of the call has room for its ranges.  (The call is
+    // refused by the above's need alone: callers may have sized their workspaces by it.)
+    int near_cfg = -1, near_split = 1;
+    double near_us = 0.0;
+    int most_ranges() const { return near_cfg >= 0 && near_split > split ? near_split : split; }
 };
 
 // Estimated microseconds of a launch, for shapes the registry does not list.  A 64-deep K step of a
@@ -135,6 +140,7 @@ struct Plan {
 // exhaustive timing of every configuration on 24 unlisted shapes: the choice costs 0.6 % on average
 // and at most 8 % (the model it replaces, which counted the fixed cost in K steps and priced small
 // tiles by a formula: 5.4 % and 30 %).
+static constexpr int kModelConfigs = 16;         // the configurations it was fitted to; the others are plan_one_round's alone
 static double model_time(const ConfigDesc &c, int64_t batch, int64_t M, int64_t nout, int64_t K, bool gated, int split)
 {
     const int64_t bn_out = gated ? c.bn / 2 : c.bn;
@@ -150,7 +156,94 @@ static double model_time(const ConfigDesc &c, int64_t batch, int64_t M, int64_t 
     return (double)(rounds - 1) * tile_us + tile_us * (1.0 - 0.2 * (1.0 - last));
 }
 
-static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, bool allow_split)
+// The plan of a launch of about one round of work-groups, K split or not, by the least estimated microseconds: what a step takes there is not the full
+// chip's figure.  A compute unit's work-groups walk their K steps, each of them the longest of a latency (lat: an own one per tile), what the
+// compute unit can pull of operands, and what the L2s deliver to all compute units together; then an epilogue; never faster than HBM
+// delivers the operands; split K costs a launch and its planes.  Fitted to 62000 timed launches (1900 shapes of 65 to 8192 rows, 64 to 28672 columns,
+// K of 64 to 131072, one to 256 ranges; mean error 9 %).  Its choice against the best of all configurations and ranges, geometric mean over the
+// shapes at which model_time chooses at most one round: K whole 1.5 %, with ranges 2.4 % ([N][K] 1.3 and 2.6; K of 8192 and more 2.4) where model_time's choice is
+// 5.9, 8.0 and 15 % behind.  Beyond a round it is the other way round (4.8 and 1.6 %): epilogues run under other work-groups' steps there.
+// ranges_asked: the ranges that the caller asks for (0: none asked for).
+// Three sets: B as [K][N], as [N][K], and as [N][K] from 32 MB on, which a program with several such matrices finds in HBM (fitted to 28000 launches of 320
+// shapes of 65 to 2048 rows whose weights were rotated out of the memory-side cache, plain and gated; mean error 5 %; the choice 1.2 % behind the best with K
+// whole and 1.4 % with ranges; by the second set 2.7 and 5.8, by model_time 6.6 and 4.9).
+struct RoundRates { double start, pull, chip, epilogue, memory, more, unaligned, reduce, planes; };
+static constexpr RoundRates kRoundRates[3] = {{3.12, 117.2e3, 30.3e6, 10.4, 5.37e6, 1.157, 1.555, 5.3, 5.18e6}, {2.32, 95.3e3, 58.9e6, 10.4, 5.37e6, 1.157, 1.555, 5.3, 5.18e6},
+                                              {1.0, 67.3e3, 48.1e6, 8.69, 5.31e6, 0.926, 1.622, 5.2, 6.56e6}};
+struct StepLatency { int fit; bool choose; double lat[3]; };   // by configuration; fit: work-groups of a compute unit; us.  (What the ones not chosen from would add: 0.2 %.)
+static constexpr StepLatency kStepLatency[] = {{1, true, {0.999, 0.975, 1.179}}, {1, false, {0.515, 0.530, 0.643}}, {1, true, {0.556, 0.542, 0.734}}, {2, false, {0.575, 0.566, 0.81}},
+    {1, false, {0.505, 0.471, 0.641}}, {1, true, {0.510, 0.471, 0.742}}, {2, true, {0.194, 0.153, 0.065}}, {1, false, {0.358, 0.318, 0.506}}, {1, true, {0.338, 0.316, 0.513}},
+    {1, false, {0.701, 0.670, 0.90}}, {1, false, {0.693, 0.687, 0.92}}, {1, false, {0.970, 0.927, 1.15}}, {1, false, {0.950, 0.920, 1.15}}, {1, true, {0.804, 0.804, 1.082}},
+    {1, true, {0.450, 0.450, 0.629}}, {2, false, {0.645, 0.645, 0.90}}, {1, true, {0.249, 0.219, 0.263}}, {1, true, {0.275, 0.199, 0.341}}};
+static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a row for every configuration");
+// The plan stays model_time's unless this is a tenth below what the same estimate says of that one: of the shapes above 0 to 8 % then run more than 2 % slower
+// than by model_time in place of 1 to 16, and of the gain (2.5 to 5.6 % over all those shapes) 0 to 1 % is lost.
+static constexpr double kClear = 0.9;
+
+static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t K, int trans_b, bool gated, bool allow_split, int ranges_asked)
+{
+    static constexpr int kRanges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
+    const int set = !trans_b ? 0 : N * K < 1 << 24 ? 1 : 2;
+    const RoundRates &rates = kRoundRates[set];
+    const int all_steps = ((int)K + 63) / 64;
+    const double plane = (double)M * N * 8.0 / rates.planes, memory = rates.start + ((double)M * K + (double)N * K + (double)M * N) * 2.0 / rates.memory;
+    struct Ranges { int asked, ksteps, count; double after; } ranges[sizeof(kRanges) / sizeof(kRanges[0])];
+    auto in_ranges = [&](int asked) {
+        Ranges r;
+        r.asked = asked;
+        r.ksteps = (all_steps + asked - 1) / asked;
+        r.count = (all_steps + r.ksteps - 1) / r.ksteps;
+        r.after = r.count > 1 ? rates.reduce + r.count * plane : 0.0;      // the reduction's launch, and its planes
+        return r;
+    };
+    int choices = 0;
+    for (const int s : kRanges) {
+        if (s > 1 && (ranges_asked > 0 || !allow_split || all_steps < 4 * s)) break;
+        ranges[choices++] = in_ranges(ranges_asked > 0 ? ranges_asked : s);
+    }
+    auto tiles_in = [&](const ConfigDesc &c) {
+        const int bn_out = gated ? c.bn / 2 : c.bn;
+        return ((int)M + c.bm - 1) / c.bm * (((int)nout + bn_out - 1) / bn_out);
+    };
+    auto estimate = [&](int cfg, int tiles, const Ranges &r) {
+        const ConfigDesc &c = g_configs[cfg];
+        const StepLatency &l = kStepLatency[cfg];
+        const int slots = 256 * l.fit;
+        const double area = rates.epilogue * (c.bm * c.bn) / 65536.0, lat = l.lat[set];
+        const double bytes = 128.0 * ((M < c.bm ? M : c.bm) + (N < c.bn ? N : c.bn)) * (K % 64 ? rates.unaligned : 1.0);      // (rows that are no whole lines)
+        const double own_us = bytes / rates.pull, all_us = bytes / rates.chip;
+        auto step = [&](int sharing, int active) {
+            const double own = sharing * own_us, all = active * all_us, most = own > all ? own : all;
+            return most > lat ? most : lat;
+        };
+        int rem = tiles * r.count;
+        double us = rates.start + 0.00555 * rem;
+        if (rem > slots) {
+            const int before = (rem - 1) / slots;
+            rem -= before * slots;
+            us += before * rates.more * (r.ksteps * step(l.fit, slots) + area * l.fit);
+        }
+        const int sharing = (rem + 255) / 256;
+        us += r.ksteps * step(sharing, rem) + area * sharing;
+        // (from HBM the two add up as much as they overlap)
+        return (set == 2 ? std::sqrt(us * us + memory * memory) : us > memory ? us : memory) + r.after;
+    };
+    for (int cfg = 0; cfg < kNumConfigs; ++cfg) {
+        const ConfigDesc &c = g_configs[cfg];
+        if (!kStepLatency[cfg].choose || !c.serves(trans_b)) continue;
+        const int tiles = tiles_in(c);
+        for (int i = 0; i < choices && (i == 0 || tiles * ranges[i].asked <= 512); ++i) {
+            const double us = estimate(cfg, tiles, ranges[i]);
+            if (pl.near_cfg < 0 || us < pl.near_us) { pl.near_us = us; pl.near_cfg = cfg; pl.near_split = ranges[i].asked; }
+        }
+    }
+    if (pl.near_cfg >= 0 && pl.near_us >= kClear * estimate(pl.cfg, tiles_in(g_configs[pl.cfg]), in_ranges(ranges_asked > 0 ? ranges_asked : pl.split))) {
+        pl.near_cfg = -1;
+        pl.near_split = 1;
+    }
+}
+
+static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, bool allow_split, int ranges_asked = 0)
 {
     Plan pl;
     const bool gated = act == FACT_ACT_SILU_GATE;
@@ -180,8 +273,9 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
         if (matches(*r)) { take(*r); return pl; }
     const int64_t nout = gated ? N / 2 : N;
     const bool all_fit = any_grid_fits(M, nout);
-    double best = 0;
-    for (int i = 0; i < kNumConfigs; ++i) {
+    double best = 0, whole = 0;
+    int whole_cfg = -1;
+    for (int i = 0; i < kModelConfigs; ++i) {
         const ConfigDesc &c = g_configs[i];
         if (gated && !c.gate_capable()) continue;
         if (!c.serves(trans_b) || (!all_fit && !grid_fits(c, tiles_of(c, M, nout, gated)))) continue;
@@ -193,10 +287,17 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
         }
         for (int s = 1; s <= max_split; s *= 2) {
             double t = model_time(c, batch, M, nout, K, gated, s);
+            if (s == 1 && (whole_cfg < 0 || t < whole)) { whole = t; whole_cfg = i; }
             if (s > 1) t += 4.0 + 2.0 * s * (double)M * N * 4.0 / 4.0e6;     // the reduction launch; partials written and read back at ~4 TB/s
             if (pl.cfg < 0 || t < best) { best = t; pl.cfg = i; pl.split = s; }
         }
     }
+    // (Small ones for calls without K ranges are left to model_time: the choice is level, 0.5 and 0.7 % behind the best below 1 GFLOP, and takes a fraction of a microsecond
+    // less; few rows have estimates of their own, few_rows_us.  A K of up to three steps is start and epilogue, which the estimate has the least of: 2368 x 2688 x 128
+    // [K][N] 9.1 -> 10.7 us, 7715 x 560 x 184 8 % slower, others of [N][K] up to 3 % faster.)
+    if (batch == 1 && M > 64 && K >= 256 && all_fit && whole_cfg >= 0 && (allow_split || (double)M * N * K >= 0.5e9) &&
+        tiles_of(g_configs[whole_cfg], M, nout, gated) <= kNumCU * wgs_per_cu(g_configs[whole_cfg]))
+        plan_one_round(pl, M, N, nout, K, trans_b, gated, allow_split, ranges_asked);
     pl.group_m = 4;
     return pl;
 }
@@ -301,7 +402,7 @@ static ColumnSplit column_split(const Plan &pl, int64_t M, int64_t nout, int64_t
     if (n1 <= 0 || n1 >= nout) return sp;
     const bool all_fit = any_grid_fits(M, nout);
     double rest = 0;
-    for (int i = 0; i < kNumConfigs; ++i) {
+    for (int i = 0; i < kModelConfigs; ++i) {
         const ConfigDesc &d = g_configs[i];
         if ((gated && !d.gate_capable()) || !d.serves(trans_b) || (wgs_per_cu(d) > 1 && d.bm * d.bn > 64 * 64)) continue;
         if (!all_fit && !grid_fits(d, tiles_of(d, M, nout - n1, gated))) continue;
@@ -366,12 +467,15 @@ static double small_plan_us(const ConfigDesc &c, bool trans_b, int64_t batch, in
 // 4 of them lose more than 3 %, 12 % at most.  The estimates of small outputs are of operands in the memory-side cache; cold ones (60 random calls each,
 // caches filled with other data) are 1.62 and 1.33 times as fast as the plan, warm ones 1.66 and 1.28 times.
 static constexpr int kNoSkinny = -2, kFewRows = -1;
-static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c)
+static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c, double plan_us)
 {
     const bool gated = a.act == FACT_ACT_SILU_GATE, few = skinny_takes(a, trans_b);
     const bool lines = ((uintptr_t)a.B & 127u) == 0 && a.ldb % 64 == 0 && (batch == 1 || a.stride_b % 64 == 0);
     int tile = -1;
-    const double small = small_us(a, trans_b, batch, &tile);
+    const double small = small_us(a, trans_b, batch, plan_us > 0.0, &tile);
+    // More than 64 rows, the plan priced by plan_one_round and the small tiles of [N][K] by rates of the same measurements: over 2400 shapes the choice costs
+    // 0.6 % over the best kernel of each with K whole, 2.5 % ([K][N]) and 2.1 % ([N][K]) with ranges; with lines of 1.0 in place of these 1.0, 3.6 and 2.4.
+    if (plan_us > 0.0) return tile >= 0 && small < (a.splits <= 1 ? 1.1 : trans_b ? 0.9 : 0.83) * plan_us ? tile : kNoSkinny;
     // (A plan that splits K is quicker than its estimate, by what its reduction became, and a K as long as that longer here: with a workspace us, plan and
     // this kernel at their estimates' ratio: [N][K] 80 x 304 x 15168 13.1 / 13.8 at 0.86, 352 x 328 x 6848 13.2 / 14.7 at 0.90, but 280 x 120 x 7232 13.1 / 8.7 at
     // 0.77; [K][N] 256 x 64 x 8192 10.4 / 14.0 at 0.87, 160 x 64 x 7680 13.4 / 13.6 at 0.67, but 72 x 64 x 5888 11.7 / 10.3 at 0.62.)
@@ -401,7 +505,12 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     const bool gated = q.ep.act == FACT_ACT_SILU_GATE;
     const int64_t nout = gated ? q.N / 2 : q.N;
 
-    Plan pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split);
+    Plan pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split, split > 0 ? split : 0);
+    double near_us = 0.0;
+    if (pl.near_cfg >= 0 && cfg_id < 0 && split >= 0) {
+        auto has_room = [&](int ranges) { return ranges <= 1 || (ws && aligned16(ws) && ws_bytes >= splitk_ws_bytes(q.M, q.N, ranges)); };
+        if (split > 0 || (has_room(pl.split) && has_room(pl.near_split))) { pl.cfg = pl.near_cfg; pl.split = pl.near_split; near_us = q.trans_b && q.N * q.K >= 1 << 24 ? 0.0 : pl.near_us; }      // (skinny_choice's lines for it are of warm operands)
+    }
     if (cfg_id == FACT_CONFIG_GUARDED) {              // the guarded kernel on request: the sweep's reference result
         if (split > 1 || split < 0 || q.ep.out_f32) return FACT_ERR_UNSUPPORTED;
         pl.cfg = -1; pl.split = 1;
@@ -556,7 +665,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     // checked above all the same.  (Persistent launches where they are asked for, and a registry file's choice, are taken as
     // they stand; a row of the compiled-in table names the best tile configuration: 512^3 5.5 us there, 4.0 here.)
     if (!(a.splits <= 1 && !a.f16 && persistent_grid(c, tiles_m * tiles_n * q.batch) > 0) && cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.loaded && tail_g <= 1)
-        if (const int tile = skinny_choice(a, q.trans_b != 0, q.batch, c); tile != kNoSkinny) {
+        if (const int tile = skinny_choice(a, q.trans_b != 0, q.batch, c, near_us); tile != kNoSkinny) {
         if (out_f32) {
             if (a.splits <= 1) {
                 const size_t need = (size_t)q.M * (size_t)q.N * sizeof(float);
@@ -682,35 +791,54 @@ static size_t plan_ws_bytes(const Plan &pl, int64_t M, int64_t N, int64_t K, boo
     return 0;
 }
 
+}  // extern "C"
+
+namespace fact {
+
+Workspace splitk_workspace(int64_t M, int64_t N, int64_t K)
+{
+    size_t least = 0, full = 0;
+    // the table's choice may depend on layout and epilogue (gated or not); report the largest over them
+    for (int tb = 0; tb < 2; ++tb)
+        for (int gated = 0; gated < 2; ++gated) {
+            if (gated && (!tb || N % 2)) continue;
+            const Plan pl = make_plan(1, M, N, K, tb, gated ? FACT_ACT_SILU_GATE : FACT_ACT_NONE, true);
+            const size_t b = plan_ws_bytes(pl, M, N, K, gated != 0), near = splitk_ws_bytes(M, N, pl.near_split);
+            if (b > least) least = b;
+            if (near > full) full = near;
+        }
+    return {least, full > least ? full : least};
+}
+
+Workspace mlp_workspace(int64_t T, int64_t d_model, int64_t d_ff, int act)
+{
+    const bool gated = act == FACT_ACT_SILU_GATE;
+    const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
+    const Plan p2 = make_plan(1, T, d_model, d_ff, 1, FACT_ACT_NONE, true);
+    const size_t b1 = p1.split < -1 ? plan_ws_bytes(p1, T, gated ? 2 * d_ff : d_ff, d_model, gated) : 0;   // GEMM 1 never splits K
+    const size_t b2 = plan_ws_bytes(p2, T, d_model, d_ff, false), near = splitk_ws_bytes(T, d_model, p2.near_split);
+    const size_t least = b1 > b2 ? b1 : b2;
+    return {least, near > least ? near : least};
+}
+
+}  // namespace fact
+
+extern "C" {
+
 size_t fact_gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, int split_k)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    if (split_k < 0) {
-        // forced tail split (fact_gemm_ex): the largest need over the tile configurations
-        size_t need = 0;
-        for (int i = 0; i < kNumConfigs; ++i)
-            for (int gated = 0; gated < 2; ++gated) {
-                Plan pl; pl.cfg = i; pl.split = split_k;
-                const size_t b = plan_ws_bytes(pl, M, N, K, gated != 0);
-                if (b > need) need = b;
-            }
-        return need;
-    }
-    int s = split_k;
-    size_t tail_need = 0;
-    if (s == 0) {
-        // the table's choice may depend on layout and epilogue; report the largest over them
-        for (int tb = 0; tb < 2; ++tb)
-            for (int act = 0; act < 3; ++act) {
-                if (act == FACT_ACT_SILU_GATE && (!tb || N % 2)) continue;
-                Plan pl = make_plan(1, M, N, K, tb, act, true);
-                if (pl.cfg >= 0 && pl.split > s) s = pl.split;
-                const size_t b = pl.split < -1 ? plan_ws_bytes(pl, M, N, K, act == FACT_ACT_SILU_GATE) : 0;
-                if (b > tail_need) tail_need = b;
-            }
-    }
-    const size_t sk = splitk_ws_bytes(M, N, s);
-    return sk > tail_need ? sk : tail_need;
+    if (split_k == 0) return splitk_workspace(M, N, K).full;
+    if (split_k > 0) return splitk_ws_bytes(M, N, split_k);
+    // forced tail split (fact_gemm_ex): the largest need over the tile configurations
+    size_t need = 0;
+    for (int i = 0; i < kNumConfigs; ++i)
+        for (int gated = 0; gated < 2; ++gated) {
+            Plan pl; pl.cfg = i; pl.split = split_k;
+            const size_t b = plan_ws_bytes(pl, M, N, K, gated != 0);
+            if (b > need) need = b;
+        }
+    return need;
 }
 
 size_t fact_gemm_f32out_workspace_bytes(int64_t M, int64_t N, int64_t K, int split_k)
@@ -720,7 +848,7 @@ size_t fact_gemm_f32out_workspace_bytes(int64_t M, int64_t N, int64_t K, int spl
     if (s == 0)                                       // the table's split-K factor, over both layouts (tail splits do not apply)
         for (int tb = 0; tb < 2; ++tb) {
             const Plan pl = make_plan(1, M, N, K, tb, FACT_ACT_NONE, true);
-            if (pl.cfg >= 0 && pl.split > s) s = pl.split;
+            if (pl.cfg >= 0 && pl.most_ranges() > s) s = pl.most_ranges();
         }
     return splitk_ws_bytes(M, N, s);                  // nothing when K stays whole: the main kernel writes the fp32 result
 }
@@ -759,12 +887,7 @@ size_t fact_block_mlp_workspace_bytes(int64_t T, int64_t d_model, int64_t d_ff, 
 {
     if (T <= 0 || d_model <= 0 || d_ff <= 0) return 0;
     if (act < 0 || act > 2) return 0;
-    const bool gated = act == FACT_ACT_SILU_GATE;
-    const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
-    const Plan p2 = make_plan(1, T, d_model, d_ff, 1, FACT_ACT_NONE, true);
-    const size_t b1 = p1.split < -1 ? plan_ws_bytes(p1, T, gated ? 2 * d_ff : d_ff, d_model, gated) : 0;   // GEMM 1 never splits K
-    const size_t b2 = plan_ws_bytes(p2, T, d_model, d_ff, false);
-    return b1 > b2 ? b1 : b2;
+    return mlp_workspace(T, d_model, d_ff, act).full;
 }
 
 static int block_mlp_impl(int f16, int64_t T, int64_t d_model, int64_t d_ff,
@@ -801,14 +924,14 @@ static int block_mlp_impl(int f16, int64_t T, int64_t d_model, int64_t d_ff,
     int rc = validate(q1);
     if (rc == FACT_OK) rc = validate(q2);
     if (rc != FACT_OK) return rc;
-    const size_t need = fact_block_mlp_workspace_bytes(T, d_model, d_ff, act);
+    const size_t need = mlp_workspace(T, d_model, d_ff, act).least;
     if (need > 0 && (!ws || ws_bytes < need)) return FACT_ERR_WORKSPACE;
     if (need > 0 && !aligned16(ws)) return FACT_ERR_ALIGN;
     // (the first GEMM never splits K into planes, but its last round of tiles may be split)
     const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
     rc = run(q1, -1, p1.split < -1 ? 0 : 1, 0, p1.split < -1, ws, ws_bytes, (hipStream_t)stream);
     if (rc != FACT_OK) return rc;
-    return run(q2, -1, 0, 0, need > 0, ws, ws_bytes, (hipStream_t)stream);
+    return run(q2, -1, 0, 0, need > 0 || ws, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int fact_block_mlp(int64_t T, int64_t d_model, int64_t d_ff,
@@ -848,9 +971,9 @@ int fact_select_config(int64_t batch, int64_t M, int64_t N, int64_t K, int trans
     if (trans_b != 0 && trans_b != 1) return FACT_ERR_LAYOUT;
     if (act < 0 || act > 2) return FACT_ERR_EPILOGUE;
     if (act == FACT_ACT_SILU_GATE && (N % 2 || !trans_b)) return FACT_ERR_EPILOGUE;
-    Plan pl = make_plan(batch, M, N, K, trans_b, act, true);
-    if (config_id) *config_id = pl.cfg;
-    if (split_k) *split_k = pl.split;
+    const Plan pl = make_plan(batch, M, N, K, trans_b, act, true);
+    if (config_id) *config_id = pl.near_cfg >= 0 ? pl.near_cfg : pl.cfg;
+    if (split_k) *split_k = pl.near_cfg >= 0 ? pl.near_split : pl.split;
     return FACT_OK;
 }
 
@@ -860,7 +983,7 @@ int fact_persistent_grid(int64_t batch, int64_t M, int64_t N, int64_t K, int tra
     if (config_id < 0) {
         Plan pl = make_plan(batch, M, N, K, trans_b, act, false);
         if (pl.split != 1) return 0;
-        config_id = pl.cfg;
+        config_id = pl.near_cfg >= 0 ? pl.near_cfg : pl.cfg;
     }
     if (config_id < 0 || config_id >= kNumConfigs) return 0;
     const ConfigDesc &c = g_configs[config_id];

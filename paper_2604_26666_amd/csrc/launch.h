@@ -32,7 +32,7 @@ hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, 
 // tile that gives it (-1: none serves it); the form that runs for that tile (-1: few rows), a number of FACT_ROUTE_SKINNY; the launch.
 bool skinny_takes(const GemmArgs &args, bool trans_b);
 double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
-double small_us(const GemmArgs &args, bool trans_b, int64_t batch, int *tile);
+double small_us(const GemmArgs &args, bool trans_b, int64_t batch, bool many_rows, int *tile);
 int skinny_form(const GemmArgs &args, bool trans_b, int64_t batch, int tile);
 hipError_t launch_skinny_gemm(const GemmArgs &args, bool trans_b, int form, int grid_z, hipStream_t stream);
 
@@ -45,5 +45,10 @@ hipError_t launch_small_any(const GemmArgs &args, bool trans_b, int tile, int gr
 bool ragged_serves(const GemmArgs &args, bool trans_b, int64_t batch);
 int ragged_form(const GemmArgs &args, bool trans_b, int64_t batch);
 hipError_t launch_ragged_gemm(const GemmArgs &args, bool trans_b, int form, int grid_z, hipStream_t stream);
+
+// Workspace of fact_gemm_splitk (any layout and epilogue) and of fact_block_mlp: the least that a call takes, and what the query reports.
+struct Workspace { size_t least, full; };
+Workspace splitk_workspace(int64_t M, int64_t N, int64_t K);
+Workspace mlp_workspace(int64_t T, int64_t d_model, int64_t d_ff, int act);
 
 }  // namespace fact

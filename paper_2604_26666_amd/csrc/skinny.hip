@@ -502,8 +502,13 @@ double skinny_us(const GemmArgs &a, int64_t batch, bool whole_lines)
 // never faster than the 8.2 or 11.2 TB/s at which the L2s deliver what the work-groups ask for together, nor than B arrives
 // once in each XCD that asks for a piece of its lines (as [K][N], a work-group's 16 NT columns are a part of 128-byte lines).
 // Fitted to 900 calls of 1 to 1536 rows, 32 to 8192 columns, K of 64 to 8192 (profiles/gemm_small_calls.csv; mean error 9 and 12 %).
-double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
+struct SmallRates { double start, group, rate, memory_start, memory, pull; };
+// B as [K][N], as [N][K], and the latter of many rows: fitted, with plan_one_round, to 1050 calls of up to 8192 rows whose operands lie in the memory-side cache (mean
+// error 10 %, the second's there 13: 111 x 2048 x 5632 takes 11.9 us, priced at 15.9 and 19.5)
+static constexpr SmallRates kSmallRates[3] = {{3.07, 0.002, 83.6e3, 3.0, 5.38e6, 8.2e6}, {3.07, 0.0015, 107.7e3, 3.0, 4.42e6, 11.2e6}, {3.15, 0.002, 95.1e3, 3.15, 5.27e6, 13.8e6}};
+double small_us(const GemmArgs &a, bool trans_b, int64_t batch, bool many_rows, int *tile)
 {
+    const SmallRates &r = kSmallRates[!trans_b ? 0 : many_rows ? 2 : 1];
     double best = 0.0;
     *tile = -1;
     if (a.act == ACT_SILU_GATE || a.N > 8192 || streams(a, batch)) return best;
@@ -522,12 +527,12 @@ double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int *tile)
         const double sharing = wgs > 256 ? wgs / 256.0 : 1.0;
         const double rows_a = 0.5 * (16 * t.mt + (a.M < 16 * t.mt ? a.M : 16 * t.mt));
         const double cols = 16 * t.nt * (trans_b ? 1.0 : t.nt == 1 ? 1.48 : t.nt == 2 ? 1.25 : 1.0);       // (a line's lookups for less than a line)
-        double step = sharing * 128.0 * (blocks < t.waves ? blocks : t.waves) * (rows_a + cols) / (trans_b ? 107.7e3 : 83.6e3);
+        double step = sharing * 128.0 * (blocks < t.waves ? blocks : t.waves) * (rows_a + cols) / r.rate;
         if (!trans_b && step < 0.2) step = 0.2;
-        const double chain = 3.07 + (trans_b ? 0.0015 : 0.002) * wgs + (blocks + t.waves - 1) / t.waves * step;
+        const double chain = r.start + r.group * wgs + (blocks + t.waves - 1) / t.waves * step;
         const int64_t wx = ((int64_t)a.N + 16 * t.nt - 1) / (16 * t.nt);
-        const double memory = 3.0 + (double)batch * a.K * 2.0 * (a.N * (trans_b ? 1.0 : 4.0 / t.nt) + (wx < 8 ? wx : 8) * (double)a.M) / (trans_b ? 4.42e6 : 5.38e6);
-        const double pull = 3.0 + (double)wgs * blocks * 128.0 * (rows_a + cols) / (trans_b ? 11.2e6 : 8.2e6);
+        const double memory = r.memory_start + (double)batch * a.K * 2.0 * (a.N * (trans_b ? 1.0 : 4.0 / t.nt) + (wx < 8 ? wx : 8) * (double)a.M) / r.memory;
+        const double pull = r.memory_start + (double)wgs * blocks * 128.0 * (rows_a + cols) / r.pull;
         double us = chain > memory ? chain : memory;
         if (pull > us) us = pull;
         if (*tile < 0 || us < best) { best = us; *tile = i; }

@@ -1,0 +1,69 @@
+"""What a call with a workspace takes and refuses (host logic, no GPU): a plan that wants more K ranges than the caller's workspace holds gives way to the one
+that fits, and the least that is accepted is what it was before such plans (sizes that callers may have kept)."""
+import os
+
+import pytest
+
+import paper_2604_26666_amd as fact
+
+P = 0x10000          # a 128-byte aligned address; never dereferenced
+WORKSPACE = -6
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    if not os.path.exists(fact.lib_path()):
+        from paper_2604_26666_amd import build
+        build.build()
+
+
+def route(M, N, K, nk, ws, ws_bytes, split=0):
+    return fact.fact_test_route(1, M, N, K, P, K, M * K, P, K if nk else N, K * N, nk, P, N, M * N, fact.Epilogue(), -1, split, 0, P if ws else None, ws_bytes)
+
+
+# (M, N, K, least bytes): the second kind needs none
+@pytest.mark.parametrize("nk", [0, 1])
+@pytest.mark.parametrize("M,N,K,least", [(162, 888, 3056, 1150848), (398, 2056, 35648, 26185216), (213, 96, 9264, 654336), (851, 144, 32656, 7842816), (73, 168, 3672, 98112),
+                                         (600, 2048, 5632, 9830400), (1032, 1024, 4096, 8454144)])
+def test_least_workspace(M, N, K, least, nk):
+    full = fact.fact_gemm_splitk_workspace_bytes(M, N, K, 0)
+    assert full >= least
+    # (the query is the largest over layouts: a call of one of them may take less, but never less than its own plan's planes)
+    split = next(s for s in (2, 4, 8, 16, 32, 64) if s * M * N * 4 >= least)
+    assert split * M * N * 4 == least
+    for have in (least, (least + full) // 32 * 16, full, 1 << 40):
+        r = route(M, N, K, nk, True, have)
+        assert isinstance(r, list) and r, (have, r)
+    assert route(M, N, K, nk, True, least - 16) == WORKSPACE
+
+
+@pytest.mark.parametrize("M,N,K", [(610, 5040, 13784), (1131, 3640, 12576), (2074, 1824, 44312)])
+def test_no_workspace_where_none_was_needed(M, N, K):
+    # the plan has ranges where there is room for them, and none otherwise: nothing is refused
+    full = fact.fact_gemm_splitk_workspace_bytes(M, N, K, 0)
+    assert full > 0
+    with_room = [x[0] for x in route(M, N, K, 1, True, full)]
+    for have in (0, 16, full - 16):
+        without = route(M, N, K, 1, True, have)
+        assert isinstance(without, list) and "reduce" not in [x[0] for x in without], (have, without)
+    assert with_room == ["tiles", "reduce"] or with_room == [x[0] for x in route(M, N, K, 1, True, 0)]
+
+
+@pytest.mark.parametrize("T,d,dff,act,least", [(384, 1024, 4096, 1, 6291456), (105, 4096, 14336, 2, 13762560), (600, 2048, 5632, 2, 9830400), (610, 5040, 13784, 1, 0)])
+def test_mlp_query_is_never_below_what_it_was(T, d, dff, act, least):
+    assert fact.fact_block_mlp_workspace_bytes(T, d, dff, act) >= least
+
+
+def test_ranges_that_the_caller_asks_for_stay():
+    for split in (1, 2, 3, 5):
+        r = route(600, 2048, 5632, 1, True, 1 << 40, split=split)
+        assert [x[0] for x in r] == (["tiles"] if split == 1 else ["tiles", "reduce"])
+    assert route(600, 2048, 5632, 1, True, 3 * 600 * 2048 * 4 - 16, split=3) == WORKSPACE
+
+
+# outputs of half a chip of 128 x 128 tiles, and what lies beside them
+@pytest.mark.parametrize("M,N,K,nk,tile", [(512, 4096, 14336, 1, (128, 64)), (4096, 512, 4096, 0, (64, 128)), (3136, 488, 3200, 0, (64, 128)), (419, 4096, 1024, 1, (64, 128)),
+                                           (256, 4096, 14336, 1, (64, 64)), (2904, 768, 3072, 1, (128, 128)), (4096, 4096, 2048, 1, (256, 256))])
+def test_tiles(M, N, K, nk, tile):
+    (kind, cfg, _), = route(M, N, K, nk, False, 0, split=1)
+    assert kind == "tiles" and tuple(sorted(fact.fact_config_info(cfg)[:2])) == tuple(sorted(tile))
