@@ -22,14 +22,14 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float lo16(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi16(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-__device__ __forceinline__ uint32_t bf16_rne(float x)
-{
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ __forceinline__ uint32_t pack2(float a, float b) { return bf16_rne(a) | (bf16_rne(b) << 16); }
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+// two values rounded to nearest even, low half first: one instruction.  Rounding in integer arithmetic took about ten for a pair, a third of all
+// that a norm issues, and that work is not hidden: every wave of a launch loads, then sums, then rounds at about the same time (us, before ->
+// now, operands from the memory-side cache: norms of 8192 x 768 7.9 -> 6.7, 2048 x 4096 8.0 -> 7.2, 16 x 4096 2.56 -> 2.37, 65536 x 64
+// 17.4 -> 13.0; rotary embedding of 2048 tokens of 40 heads of 128 9.0 -> 7.5, 16 tokens 3.5 -> 3.1; above 100 MB, bound by HBM,
+// within 2 %: norms of 65536 x 2040 100.3 -> 98.6, 262144 x 1152 204 -> 209).
+__device__ __forceinline__ uint32_t pack2(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t)); }
 // sum over the wave, the same in every lane: rotations inside each 16-lane row, then exchanges of rows and halves, all on
 // the vector ALU (through LDS permutes the six dependent steps of a sum took 0.35 us)
 template <int CTRL>
@@ -55,9 +55,11 @@ __device__ __forceinline__ float wave_sum(float v)
 // d <= 8192, a multiple of 8.  Bound by memory traffic where there are many rows and by one row's chain of latencies
 // where there are few, so gamma and beta are asked for before the sums need them, and a wide row is shared by the four
 // waves of a work-group (their sums meet in LDS; the launch says which rows).  Operands
-// from HBM: 2048 x 4096 12.4 -> 8.6 us (3.9 TB/s), 16 x 4096 5.6 -> 2.2 us, 32768 x 4096 113 -> 92 us (5.8 TB/s), 8192 x 768
-// 9.9 -> 8.5 us (against a wave per row that asked for gamma and beta after its sums).
-// Narrower rows take a wave each.  The number of 512-element pieces per wave is a template parameter.
+// from HBM: 2048 x 4096 7.6 us (4.4 TB/s; 12.4 with a wave per row that asked for gamma and beta after its sums), 32768 x 4096 89 us
+// (6.0 TB/s; 113), 8192 x 768 7.8 us (9.9).
+// Narrower rows take a wave each, in pieces of 8 columns a lane also where half of the last one is idle (768 = 1.5 pieces): with pieces of 4
+// columns 8192 x 768 took 8.2 us, 65536 x 768 39.6 (35.8), 16384 x 1280 18.7 (16.9): more, smaller requests cost what the idle lanes did.
+// The number of 512-element pieces per wave is a template parameter.
 constexpr int kMaxWidth = 8192;
 template <bool RMS, int WPR, int PIECES>
 __global__ void __launch_bounds__(256)
@@ -128,8 +130,9 @@ norm_kernel(const uint16_t *X, int64_t ldx, const uint16_t *gamma, const uint16_
 // Rotary embedding in place, "rotate-half" pairing.  A work-group takes a few tokens and up to 256 of their angles
 // (blockIdx.y: further angles of a wider head); each thread computes one sine and cosine, once per token, into
 // LDS - the precise functions cost more than the traffic - and then walks 16-byte pieces of its heads: the piece at i
-// and the one at i + D/2.  Many heads of few tokens are shared by several work-groups (4096 heads of 128, one token: 100 -> 3.7 us).  2048 tokens of 40 heads of 128: 15.1 -> 11.4 us (3.7 TB/s), 16 tokens: 6.3 -> 3.1 us (against a
-// thread that computed eight angles and walked eight heads).
+// and the one at i + D/2.  Many heads of few tokens are shared by several work-groups (4096 heads of 128, one token: 100 -> 3.7 us).
+// 2048 tokens of 40 heads of 128, from HBM: 8.6 us (4.9 TB/s), 16 tokens 3.1 us (15.1 and 6.3 with a thread that computed eight angles and
+// walked eight heads).
 template <bool GROUPS>
 __global__ void __launch_bounds__(256)
 rope_kernel(uint16_t *X, int64_t sb, int64_t st, int64_t sh, int64_t tokens, int T, int H, int D, int per_wg, int per_group, float log2_base)
