@@ -183,7 +183,9 @@ size_t fact_gemm_splitk_static_capacity(void);   /* bytes of the static array */
 /* Bytes of workspace fact_gemm_splitk needs for this shape and split_k (0 = the table's
  * choice, which may also be a tail split, see fact_gemm_ex; negative = a forced tail split
  * of -split_k ranges, largest need over the tile configurations).  Returns 0 when no
- * workspace is needed or the arguments are invalid. */
+ * workspace is needed or the arguments are invalid.  Where K may be split in two ways (a launch of at most one
+ * round) this is the larger need; a call with less room for its ranges takes the other way, and only one without
+ * room for that is refused. */
 size_t fact_gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, int split_k);
 /* Workspace of the same call with ep->out_f32 = 1: the fp32 partial planes when K is split
  * (split_k > 1, or 0 and the table splits this shape), else 0. */

@@ -7,6 +7,7 @@ namespace fact {
 // 16-bit pattern <-> fp32 in the launch's format (these kernels are bound by memory traffic: a run-time choice)
 __device__ __forceinline__ float in16_rt(int f16, uint32_t bits) { return f16 ? f16_bits_to_f32(bits) : bf16_bits_to_f32(bits); }
 __device__ __forceinline__ uint32_t out16_rt(int f16, float x) { return f16 ? f32_to_f16_bits(x) : f32_to_bf16_bits(x); }
+__device__ __forceinline__ uint32_t pack2_rt(int f16, float a, float b) { return f16 ? pack2<true>(pk_f32_t{a, b}) : pack2<false>(pk_f32_t{a, b}); }
 
 // ---- split-K reduction -----------------------------------------------------------------
 // P holds `splits` fp32 partial products [M][N].  A lane owns 4 consecutive output columns of
@@ -119,7 +120,7 @@ __global__ void __launch_bounds__(64 * kReduceWaves) splitk_reduce_kernel(const 
             } else {
                 __bf16 *cp = p.C + (int64_t)m * p.ldc + n;
                 if (vec_e) {
-                    *(u32x2_t *)cp = u32x2_t{out16_rt(p.f16, v[0]) | (out16_rt(p.f16, v[1]) << 16), out16_rt(p.f16, v[2]) | (out16_rt(p.f16, v[3]) << 16)};
+                    *(u32x2_t *)cp = u32x2_t{pack2_rt(p.f16, v[0], v[1]), pack2_rt(p.f16, v[2], v[3])};
                 } else {
                     uint16_t *cs = (uint16_t *)cp;
                     for (int e = 0; e < 4; ++e)

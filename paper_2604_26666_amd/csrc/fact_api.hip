@@ -163,7 +163,6 @@ static double model_time(const ConfigDesc &c, int64_t batch, int64_t M, int64_t 
 // K of 64 to 131072, one to 256 ranges; mean error 9 %).  Its choice against the best of all configurations and ranges, geometric mean over the
 // shapes at which model_time chooses at most one round: K whole 1.5 %, with ranges 2.4 % ([N][K] 1.3 and 2.6; K of 8192 and more 2.4) where model_time's choice is
 // 5.9, 8.0 and 15 % behind.  Beyond a round it is the other way round (4.8 and 1.6 %): epilogues run under other work-groups' steps there.
-// ranges_asked: the ranges that the caller asks for (0: none asked for).
 // Three sets: B as [K][N], as [N][K], and as [N][K] from 32 MB on, which a program with several such matrices finds in HBM (fitted to 28000 launches of 320
 // shapes of 65 to 2048 rows whose weights were rotated out of the memory-side cache, plain and gated; mean error 5 %; the choice 1.2 % behind the best with K
 // whole and 1.4 % with ranges; by the second set 2.7 and 5.8, by model_time 6.6 and 4.9).
@@ -180,6 +179,7 @@ static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a 
 // than by model_time in place of 1 to 16, and of the gain (2.5 to 5.6 % over all those shapes) 0 to 1 % is lost.
 static constexpr double kClear = 0.9;
 
+// ranges_asked: the ranges that the caller asks for (0: none asked for).
 static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t K, int trans_b, bool gated, bool allow_split, int ranges_asked)
 {
     static constexpr int kRanges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};

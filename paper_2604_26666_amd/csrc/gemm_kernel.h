@@ -143,22 +143,8 @@ __device__ __forceinline__ uint32_t wave_uniform(uint32_t v) { return __builtin_
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h16) { return __uint_as_float(h16 << 16); }
 
-// fp32 -> bf16 bit pattern, round to nearest even; NaN -> quiet NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float x)
-{
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-
-__device__ __forceinline__ u32x2_t pack4_bf16(float a, float b, float c, float d)
-{
-    u32x2_t r;
-    r.x = f32_to_bf16_bits(a) | (f32_to_bf16_bits(b) << 16);
-    r.y = f32_to_bf16_bits(c) | (f32_to_bf16_bits(d) << 16);
-    return r;
-}
+// fp32 -> bf16 bit pattern, round to nearest even; NaN -> quiet NaN (the hardware's conversion)
+__device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)x); }
 
 // The two 16-bit formats a launch may compute in.  F16 = false: bf16 (the workload definition's); F16 = true: IEEE
 // binary16, the precision of the paper's own kernels (Listing 1; Sections 5.2.3 - 5.2.5).  Either way the
@@ -1087,7 +1073,7 @@ gemm_kernel(const GemmArgs p)
                 if (whole[j]) {
                     u32x4_t o;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = out16<F16>(z[2 * e]) | (out16<F16>(z[2 * e + 1]) << 16);
+                    for (int e = 0; e < 4; ++e) o[e] = pack2<F16>(pk_f32_t{z[2 * e], z[2 * e + 1]});
                     *(u32x4_any *)cp = o;
                 } else {
                     uint16_t *cs = (uint16_t *)cp;

@@ -250,7 +250,7 @@ ragged_kernel(const GemmArgs p)
                     if (n + e < nout) v[e] += in16<F16>(rp[e]);
             }
             uint16_t *cp = C + (int64_t)m * p.ldc + n;
-            if (full) *(u32x2_any *)cp = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
+            if (full) *(u32x2_any *)cp = u32x2_t{pack2<F16>(pk_f32_t{v[0], v[1]}), pack2<F16>(pk_f32_t{v[2], v[3]})};
             else {
 #pragma unroll
                 for (int e = 0; e < 3; ++e)
@@ -314,7 +314,7 @@ ragged_kernel(const GemmArgs p)
             }
             u32x4_t o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = out16<F16>(v[2 * e]) | (out16<F16>(v[2 * e + 1]) << 16);
+            for (int e = 0; e < 4; ++e) o[e] = pack2<F16>(pk_f32_t{v[2 * e], v[2 * e + 1]});
             uint16_t *at = C + (int64_t)m * p.ldc + nj;
             if (odd_rows) {
                 const uint32_t follow = (uint32_t)__builtin_amdgcn_ds_bpermute(next_lane, (int)(q == 0 ? first : o[0]));

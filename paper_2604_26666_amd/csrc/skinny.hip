@@ -127,7 +127,7 @@ __device__ __forceinline__ void finish(const GemmArgs &p, const f32x4_t (&acc)[M
         } else {
             uint16_t *c = (uint16_t *)(p.C + z * p.stride_c) + (int64_t)m * p.ldc + n;
             if (full) {
-                *(u32x2_any *)c = u32x2_t{out16<F16>(v[0]) | (out16<F16>(v[1]) << 16), out16<F16>(v[2]) | (out16<F16>(v[3]) << 16)};
+                *(u32x2_any *)c = u32x2_t{pack2<F16>(pk_f32_t{v[0], v[1]}), pack2<F16>(pk_f32_t{v[2], v[3]})};
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
