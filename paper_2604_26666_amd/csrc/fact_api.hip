@@ -602,10 +602,13 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     const int unit = gated ? 64 : 32;                 // elements of C between the addresses that rows may begin at (see kStoreThrough)
     a.store_through = ((uintptr_t)q.C & (uintptr_t)(2 * unit - 1)) == 0 && q.ldc % unit == 0 && (q.batch == 1 || q.stride_c % unit == 0);
 
-    // (see kStoreThrough; with A they have to leave the memory-side cache room for a step of the program: 8000 x 1024 x 4096 behind its up projection, 16 + 65 MB,
-    // the block 128 us as streaming stores and 131 without)
+    // Up to 56 MB of A and C together, C stays in the memory-side cache (see kStoreThrough); beyond, a program that walks a few such sets of buffers overflows it,
+    // and the launches that would have found their operands there lose more (us, streamed / kept, three sets in turn: feed-forward 768 x 3072 of 7288 tokens, 11 + 45 MB,
+    // 84.7 / 78.5, 7800 tokens, 12 + 48 MB, 88.3 / 89.5, 8192 tokens, 13 + 50 MB, 81.6 / 88.6; 1024 x 4096 of 5000 tokens, 10 + 41 MB, 98.4 / 98.7, 5600, 11 + 46 MB,
+    // 114.7 / 110.7, 6400 118.0 / 119.5; 48 and 64 x 512^3, 25 + 25 and 34 + 34 MB, 18.0 / 17.8 and 20.9 / 26.0, 256 x 256^3, 34 + 34 MB, 19.1 / 22.6).  The other way round where
+    // one set serves every layer: a block of 16 x 1024 tokens of 768, 25 + 100 MB, 311 / 302.
     const int64_t c_bytes = q.batch * q.M * nout * 2;
-    a.store_stream = c_bytes > (int64_t)40 << 20 || c_bytes + q.batch * q.M * q.K * 2 > (int64_t)64 << 20;
+    a.store_stream = c_bytes + q.batch * q.M * q.K * 2 > (int64_t)56 << 20;
 
     hipError_t e;
     if (pl.cfg < 0) {

@@ -341,7 +341,7 @@ __device__ __forceinline__ GemmArgs fresh_args()
 // [K][N] 33.2 us for 32.3, 5384 x 1704 x 80 16.8 for 16.3, 19 such calls on 256 x 256 tiles 1.9 % on average.  Not for 192-wide tiles:
 // with those epilogues inside, their other calls are 3-4 % faster (12 of K up to 1000; where the code lies, like the order of their common forms).
 constexpr bool odd_rows_apart(int bn) { return bn != 192; }
-template <int BM, int BN, int WGM, int WGN, bool TRANS_B, int BK, int STAGES, bool PERSIST, bool F16 = false, bool ODD = false>
+template <int BM, int BN, int WGM, int WGN, bool TRANS_B, int BK, int STAGES, bool PERSIST, bool F16 = false, bool ODD = false, bool STREAM = false>
 __global__ void __launch_bounds__(WGM * WGN * 64)
 gemm_kernel(const GemmArgs p)
 {
@@ -385,10 +385,10 @@ gemm_kernel(const GemmArgs p)
     // memory-side cache / rotated out of it: 8192 x 2304 x 768 + bias 37.5 -> 36.6 / 48.1 -> 40.2 us,
     // 8192 x 3072 x 768 + bias + GELU 45.3 -> 41.6 / 48.0 -> 41.7 us, 128 x 512^3 43.5 -> 42.5 / 51.5 -> 48.5 us,
     // 8192^3 713 -> 708 us; no shape slower.  (Write-through alone: better from the cache, worse from HBM.)
-    // Outputs of up to 40 MB, 64 MB with A (p.store_stream == 0), without nt, so that the memory-side cache keeps them: the next launch of a program reads them, and
+    // Outputs of up to 56 MB with A (p.store_stream == 0) without nt, so that the memory-side cache keeps them: the next launch of a program reads them, and
     // from HBM a K step of it takes as long as the loads' latency (down projection of 1024 <- 4096 after an up projection of 384 tokens 19.5 us, by itself,
     // from the cache, 14.3).  Feed-forward blocks, 19 -> 17: 3000 tokens of 768 x 3072 (hidden tensor 18 MB) 56.0 -> 46.8 us, 4000 of 1024 x 4096 (33 MB)
-    // 76.8 -> 66.3, 2000 of 2048 x 5632 (23 MB) 140 -> 136; but 8000 of 768 x 3072 (49 MB) 82.8 -> 85.0, 8192 x 8192 x 512 (134 MB) 75 -> 88.
+    // 76.8 -> 66.3, 2000 of 2048 x 5632 (23 MB) 140 -> 136; but 8192 of 768 x 3072 (50 MB) 81.6 -> 88.6, 8192 x 8192 x 512 (134 MB) 75 -> 88.
     // Single GEMMs of up to 40 MB: level.  Stores that stay in the L2s: 48.5, 67.7 and 136 us, and 90.9 beyond.
     constexpr int kStoreThrough = 17, kStoreStream = 19;
     // ... where every row of C begins on a 64-byte boundary.  Rows at other addresses would send the lines at the tiles' edges to
@@ -637,8 +637,8 @@ gemm_kernel(const GemmArgs p)
     // C and the residual are addressed through buffer descriptors of the wave's tile with one
     // lane-offset register each (32-bit offsets: the host sets vec_store only if a tile's rows span
     // less than 2^31 bytes), a tile row adds one vector add, a pair an immediate offset.
-    // The stores' cache policy is chosen per tile row; 192-wide tiles have one for outputs of any size (3000 x 4000 x 512: 19.2 us with the choice in the
-    // code, 18.0 with an instance for either, 17.2 like this; 8000 x 3072 x 768 + GELU, 49 MB, 2 % slower than as streaming stores; the other widths are level).
+    // The stores' cache policy is chosen per tile row; 192-wide tiles have a kernel for either (3000 x 4000 x 512: 19.2 us with the choice in the
+    // code, 17.2 without; the other widths are level).
     auto reg_epilogue = [&](auto gated_tag, auto bias_tag, auto gelu_tag, auto res_tag) __attribute__((always_inline)) {
         constexpr bool GATED = decltype(gated_tag)::value, BIAS = decltype(bias_tag)::value;
         constexpr bool GELU = decltype(gelu_tag)::value, RES = decltype(res_tag)::value;
@@ -728,9 +728,9 @@ gemm_kernel(const GemmArgs p)
                     out[pr][e] = pack2<F16>(f2);     // round to nearest even
                 }
                 // (scalar offset operand: the constant 0, see the note at the partial-tile stores below)
-                if constexpr (BN == 192) __builtin_amdgcn_raw_buffer_store_b128(out[pr], rsrc_c, vo + pr * 64, 0, kStoreThrough);
+                if constexpr (BN == 192) __builtin_amdgcn_raw_buffer_store_b128(out[pr], rsrc_c, vo + pr * 64, 0, STREAM ? kStoreStream : kStoreThrough);
             });
-            if constexpr (BN == 192) return;
+            if constexpr (BN == 192) return;                 // (the launch picks the kernel by p.store_stream)
             if (p.store_stream) {
 #pragma unroll
                 for (int pr = 0; pr < NP; ++pr) __builtin_amdgcn_raw_buffer_store_b128(out[pr], rsrc_c, vo + pr * 64, 0, kStoreStream);

@@ -1,4 +1,4 @@
-"""Outputs on either side of the 40 MB from which on C's stores pass the memory-side cache: the same bits, through every form of the register
+"""Outputs on either side of the 56 MB (with A) from which on C's stores pass the memory-side cache: the same bits, through every form of the register
 epilogue and the edge tiles' one, and read back by the launch that follows."""
 import pytest
 import torch
@@ -6,7 +6,7 @@ import torch
 import paper_2604_26666_amd as fact
 
 pytestmark = pytest.mark.gpu
-LINE = (40 << 20) // 2           # elements of C
+LINE = (56 << 20) // 2           # elements of A and C
 
 
 def gemm(A, B, C, **ep):
@@ -20,7 +20,7 @@ def gemm(A, B, C, **ep):
 def test_both_sides_of_the_line(form, nout):
     g = torch.Generator(device="cuda").manual_seed(5)
     K, N = 64, 2 * nout if form == "gated" else nout
-    few = LINE // nout                                              # the last row count without the policy; one more has it
+    few = LINE // (nout + K)                                              # the last row count without the policy; one more has it
     A = torch.randn(few + 1, K, generator=g, device="cuda").bfloat16()
     B = torch.randn(N, K, generator=g, device="cuda").mul_(K ** -0.5).bfloat16()
     R = torch.randn(few + 1, nout, generator=g, device="cuda").bfloat16()
@@ -53,3 +53,24 @@ def test_both_sides_of_the_line(form, nout):
     err = (outs[1].float() - z).abs()
     # one rounding to bf16 (2^-9 of the value), and fp32 sums of 64 products of the operands' size
     assert bool((err <= z.abs() * 2.0 ** -8 + 2e-5 * (1 + z.abs())).all()), float(err.max())
+
+
+@pytest.mark.parametrize("config", [13, 14, 15])                    # the 192-wide tiles, with a kernel for either policy
+def test_both_sides_of_the_line_192_wide(config):
+    g = torch.Generator(device="cuda").manual_seed(6)
+    K, N = 64, 7688
+    few = LINE // (N + K)
+    A = torch.randn(few + 1, K, generator=g, device="cuda").bfloat16()
+    B = torch.randn(N, K, generator=g, device="cuda").mul_(K ** -0.5).bfloat16()
+    bias = torch.randn(N, generator=g, device="cuda").bfloat16()
+    outs = []
+    for M in (few, few + 1):
+        C = torch.full((M + 1, N), 77.0, dtype=torch.bfloat16, device="cuda")
+        fact.binding.check(fact.fact_gemm_ex(1, M, N, K, A, K, 0, B, K, 0, 1, C, N, 0, fact.Epilogue(bias=bias, act=fact.ACT_GELU_TANH), config, 1, 4, None, 0))
+        torch.cuda.synchronize()
+        assert (C[M] == 77.0).all(), "wrote past C"
+        outs.append(C[:M])
+    assert torch.equal(outs[0], outs[1][:few])
+    ref = torch.nn.functional.gelu(A.float() @ B.float().t() + bias.float(), approximate="tanh")
+    # one rounding to bfloat16 (2^-9) of sums and a tanh that differ in the last places of fp32
+    assert ((outs[1].float() - ref).abs() <= ref.abs() * 2.0 ** -8 + 2.0 ** -16).all()
