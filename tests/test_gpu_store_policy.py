@@ -56,21 +56,23 @@ def test_both_sides_of_the_line(form, nout):
 
 
 @pytest.mark.parametrize("config", [13, 14, 15])                    # the 192-wide tiles, with a kernel for either policy
-def test_both_sides_of_the_line_192_wide(config):
+@pytest.mark.parametrize("f16", [0, 1])
+def test_both_sides_of_the_line_192_wide(config, f16):
+    dtype = torch.float16 if f16 else torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(6)
     K, N = 64, 7688
     few = LINE // (N + K)
-    A = torch.randn(few + 1, K, generator=g, device="cuda").bfloat16()
-    B = torch.randn(N, K, generator=g, device="cuda").mul_(K ** -0.5).bfloat16()
-    bias = torch.randn(N, generator=g, device="cuda").bfloat16()
+    A = torch.randn(few + 1, K, generator=g, device="cuda").to(dtype)
+    B = torch.randn(N, K, generator=g, device="cuda").mul_(K ** -0.5).to(dtype)
+    bias = torch.randn(N, generator=g, device="cuda").to(dtype)
     outs = []
     for M in (few, few + 1):
-        C = torch.full((M + 1, N), 77.0, dtype=torch.bfloat16, device="cuda")
-        fact.binding.check(fact.fact_gemm_ex(1, M, N, K, A, K, 0, B, K, 0, 1, C, N, 0, fact.Epilogue(bias=bias, act=fact.ACT_GELU_TANH), config, 1, 4, None, 0))
+        C = torch.full((M + 1, N), 77.0, dtype=dtype, device="cuda")
+        fact.binding.check(fact.fact_gemm_ex(1, M, N, K, A, K, 0, B, K, 0, 1, C, N, 0, fact.Epilogue(bias=bias, act=fact.ACT_GELU_TANH, f16=f16), config, 1, 4, None, 0))
         torch.cuda.synchronize()
         assert (C[M] == 77.0).all(), "wrote past C"
         outs.append(C[:M])
     assert torch.equal(outs[0], outs[1][:few])
     ref = torch.nn.functional.gelu(A.float() @ B.float().t() + bias.float(), approximate="tanh")
-    # one rounding to bfloat16 (2^-9) of sums and a tanh that differ in the last places of fp32
+    # one rounding to bfloat16 (2^-9) or binary16 (2^-12, subnormal below 2^-14) of sums and a tanh that differ in the last places of fp32
     assert ((outs[1].float() - ref).abs() <= ref.abs() * 2.0 ** -8 + 2.0 ** -16).all()
