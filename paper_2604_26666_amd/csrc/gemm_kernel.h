@@ -548,7 +548,7 @@ gemm_kernel(const GemmArgs p)
     // pieces that do not overlap (3547 x 2368 x 328: 15.0 -> 16.1 us), so there is an instance for either.
     auto compact_pass = [&](int pass, auto gated_tag, auto through_tag) __attribute__((always_inline)) {
         constexpr bool GATED = decltype(gated_tag)::value;
-        constexpr int kStore = decltype(through_tag)::value ? kStoreThrough : 0;
+        constexpr int kStore = decltype(through_tag)::value ? (STREAM ? kStoreStream : kStoreThrough) : 0;
         constexpr int OUT_W = GATED ? WTN / 2 : WTN;
         constexpr int LPR_USED = OUT_W / 8;
         constexpr int LPR = LPR_USED <= 1 ? 1 : LPR_USED <= 2 ? 2 : LPR_USED <= 4 ? 4 : LPR_USED <= 8 ? 8 : LPR_USED <= 16 ? 16 : 32;
