@@ -179,7 +179,7 @@ static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a 
 // than by model_time in place of 1 to 16, and of the gain (2.5 to 5.6 % over all those shapes) 0 to 1 % is lost.
 static constexpr double kClear = 0.9;
 
-// ranges_asked: the ranges that the caller asks for (0: none asked for).
+// ranges_asked: the ranges that the caller asks for (0: none asked for), at most kMaxGridZ: the launches counted here, of 4096 tiles at most, fit 32 bits.
 static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t K, int trans_b, bool gated, bool allow_split, int ranges_asked)
 {
     static constexpr int kRanges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
@@ -243,6 +243,8 @@ static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t
     }
 }
 
+// (ranges_asked: as above, or kPlanned where the caller names a configuration or a tail split, so that only the plan's other parts are of use)
+static constexpr int kPlanned = -1;
 static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, bool allow_split, int ranges_asked = 0)
 {
     Plan pl;
@@ -295,7 +297,7 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
     // (Small ones for calls without K ranges are left to model_time: the choice is level, 0.5 and 0.7 % behind the best below 1 GFLOP, and takes a fraction of a microsecond
     // less; few rows have estimates of their own, few_rows_us.  A K of up to three steps is start and epilogue, which the estimate has the least of: 2368 x 2688 x 128
     // [K][N] 9.1 -> 10.7 us, 7715 x 560 x 184 8 % slower, others of [N][K] up to 3 % faster.)
-    if (batch == 1 && M > 64 && K >= 256 && all_fit && whole_cfg >= 0 && (allow_split || (double)M * N * K >= 0.5e9) &&
+    if (ranges_asked != kPlanned && batch == 1 && M > 64 && K >= 256 && all_fit && whole_cfg >= 0 && (allow_split || (double)M * N * K >= 0.5e9) &&
         tiles_of(g_configs[whole_cfg], M, nout, gated) <= kNumCU * wgs_per_cu(g_configs[whole_cfg]))
         plan_one_round(pl, M, N, nout, K, trans_b, gated, allow_split, ranges_asked);
     pl.group_m = 4;
@@ -502,12 +504,13 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
 {
     int rc = validate(q);
     if (rc != FACT_OK) return rc;
+    if (split > kMaxGridZ) return FACT_ERR_UNSUPPORTED;
     const bool gated = q.ep.act == FACT_ACT_SILU_GATE;
     const int64_t nout = gated ? q.N / 2 : q.N;
 
-    Plan pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split, split > 0 ? split : 0);
+    Plan pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split, cfg_id >= 0 || cfg_id == FACT_CONFIG_GUARDED || split < 0 ? kPlanned : split);
     double near_us = 0.0;
-    if (pl.near_cfg >= 0 && cfg_id < 0 && split >= 0) {
+    if (pl.near_cfg >= 0) {
         auto has_room = [&](int ranges) { return ranges <= 1 || (ws && aligned16(ws) && ws_bytes >= splitk_ws_bytes(q.M, q.N, ranges)); };
         if (split > 0 || (has_room(pl.split) && has_room(pl.near_split))) { pl.cfg = pl.near_cfg; pl.split = pl.near_split; near_us = q.trans_b && q.N * q.K >= 1 << 24 ? 0.0 : pl.near_us; }      // (skinny_choice's lines for it are of warm operands)
     }
@@ -530,7 +533,6 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     if (pl.split < 0) { tail_g = -pl.split; pl.split = 1; }
     if (tail_g > 1 && q.batch != 1) { if (split < 0) return FACT_ERR_UNSUPPORTED; tail_g = 0; }
     if (pl.split > 1 && q.batch != 1) return FACT_ERR_UNSUPPORTED;
-    if (pl.split > kMaxGridZ) return FACT_ERR_UNSUPPORTED;
 
     // operands the MFMA kernel reads with 16-byte loads
     // (leading dimensions are bounded so that per-lane byte offsets inside one tile panel fit 31 bits)

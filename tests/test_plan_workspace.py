@@ -7,7 +7,7 @@ import pytest
 import paper_2604_26666_amd as fact
 
 P = 0x10000          # a 128-byte aligned address; never dereferenced
-WORKSPACE = -6
+WORKSPACE, UNSUPPORTED = -6, -7
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -17,8 +17,8 @@ def _built():
         build.build()
 
 
-def route(M, N, K, nk, ws, ws_bytes, split=0):
-    return fact.fact_test_route(1, M, N, K, P, K, M * K, P, K if nk else N, K * N, nk, P, N, M * N, fact.Epilogue(), -1, split, 0, P if ws else None, ws_bytes)
+def route(M, N, K, nk, ws, ws_bytes, split=0, cfg=-1):
+    return fact.fact_test_route(1, M, N, K, P, K, M * K, P, K if nk else N, K * N, nk, P, N, M * N, fact.Epilogue(), cfg, split, 0, P if ws else None, ws_bytes)
 
 
 # (M, N, K, least bytes): the second kind needs none
@@ -59,6 +59,20 @@ def test_ranges_that_the_caller_asks_for_stay():
         r = route(600, 2048, 5632, 1, True, 1 << 40, split=split)
         assert [x[0] for x in r] == (["tiles"] if split == 1 else ["tiles", "reduce"])
     assert route(600, 2048, 5632, 1, True, 3 * 600 * 2048 * 4 - 16, split=3) == WORKSPACE
+
+
+# more K ranges than a grid counts, on shapes with a plan for one round, with a long K, and on few rows
+@pytest.mark.parametrize("M,N,K", [(600, 2048, 5632), (4096, 512, 4096), (65, 8, 2 ** 21), (64, 4096, 4096)])
+@pytest.mark.parametrize("cfg", [-1, -2, 6])
+@pytest.mark.parametrize("split", [65536, 2 ** 31 - 88, 2 ** 31 - 1])
+def test_more_ranges_than_there_can_be_are_refused(M, N, K, cfg, split):
+    for nk in (0, 1):
+        assert route(M, N, K, nk, True, 1 << 62, split=split, cfg=cfg) == UNSUPPORTED
+
+
+@pytest.mark.parametrize("M,N", [(65, 8), (4096, 4096)])
+def test_as_many_ranges_as_there_can_be(M, N):
+    assert [x[0] for x in route(M, N, 2 ** 21, 1, True, 1 << 62, split=65535)] == ["tiles", "reduce"]
 
 
 # outputs of half a chip of 128 x 128 tiles, and what lies beside them
