@@ -146,7 +146,8 @@ int fact_gemm_batched(int64_t batch, int64_t M, int64_t N, int64_t K,
  * and rounds once.  split_k == 0 lets the table choose; split_k == 1 (or a
  * choice of 1) runs the plain kernel and needs no workspace.  Few rows and small outputs may keep K whole on the
  * kernel whose waves split it (see fact_gemm) although the table splits it; the workspace is asked for all the same.
- * Bit-reproducible: the order of additions is fixed.
+ * Bit-reproducible: the order of additions is fixed; with split_k == 0 it may be another one for a workspace of less than
+ * the queried size (see there), and is the same for every workspace of that size or more.
  * ws: device pointer, 16-byte aligned, at least
  * fact_gemm_splitk_workspace_bytes(M, N, K, split_k) bytes; contents are scratch.
  */
@@ -160,7 +161,7 @@ int fact_gemm_splitk(int64_t M, int64_t N, int64_t K,
 /*
  * fact_gemm_splitk for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation.  Same arguments, same results (bit for
- * bit) and same error codes as fact_gemm_splitk, without ws / ws_bytes: the fp32 partial sums (or
+ * bit) and same error codes as fact_gemm_splitk with a workspace of the queried size, without ws / ws_bytes: the fp32 partial sums (or
  * the hand-over tiles of a tail split) live in a static device array inside the library, of
  * fact_gemm_splitk_static_capacity() bytes (32 MiB: 128 K ranges of a 256 x 256 problem).  Every
  * GPU the library runs on holds its own copy of the array until the process ends.  The call
@@ -204,7 +205,8 @@ size_t fact_gemm_f32out_workspace_bytes(int64_t M, int64_t N, int64_t K, int spl
  * R  : residual bf16 [T][d_model] or NULL (Y may alias R).
  * All matrices dense (leading dimension = row length).
  * ws : workspace for a split-K second GEMM or a tail split of either GEMM,
- *      fact_block_mlp_workspace_bytes() bytes (may be NULL when that returns 0).
+ *      fact_block_mlp_workspace_bytes() bytes (may be NULL when that returns 0).  A smaller one, or none, is taken where
+ *      a K that is split less, or not at all, makes do with it: the same sums in another order.
  */
 int fact_block_mlp(int64_t T, int64_t d_model, int64_t d_ff,
                    const void *X, const void *W1, const void *W1u, const void *b1, int act,

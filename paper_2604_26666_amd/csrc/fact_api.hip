@@ -26,6 +26,7 @@ static constexpr int kNumConfigs = (int)(sizeof(g_configs) / sizeof(g_configs[0]
 static constexpr int kNumCU = 256;
 static constexpr int kLdsPerCU = 160 * 1024;
 static constexpr int kMaxGridZ = 65535;
+static constexpr size_t kStaticScratchBytes = (size_t)32 << 20;       // the array of fact_gemm_splitk_static
 
 static thread_local char g_last_error[256] = "";
 
@@ -180,7 +181,8 @@ static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a 
 static constexpr double kClear = 0.9;
 
 // ranges_asked: the ranges that the caller asks for (0: none asked for), at most kMaxGridZ: the launches counted here, of 4096 tiles at most, fit 32 bits.
-static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t K, int trans_b, bool gated, bool allow_split, int ranges_asked)
+// planes_held: the bytes of planes that this plan may choose ranges for.
+static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t K, int trans_b, bool gated, bool allow_split, int ranges_asked, size_t planes_held)
 {
     static constexpr int kRanges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
     const int set = !trans_b ? 0 : N * K < 1 << 24 ? 1 : 2;
@@ -198,7 +200,7 @@ static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t
     };
     int choices = 0;
     for (const int s : kRanges) {
-        if (s > 1 && (ranges_asked > 0 || !allow_split || all_steps < 4 * s)) break;
+        if (s > 1 && (ranges_asked > 0 || !allow_split || all_steps < 4 * s || (size_t)s * M * N * sizeof(float) > planes_held)) break;
         ranges[choices++] = in_ranges(ranges_asked > 0 ? ranges_asked : s);
     }
     auto tiles_in = [&](const ConfigDesc &c) {
@@ -245,7 +247,11 @@ static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t
 
 // (ranges_asked: as above, or kPlanned where the caller names a configuration or a tail split, so that only the plan's other parts are of use)
 static constexpr int kPlanned = -1;
-static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, bool allow_split, int ranges_asked = 0)
+// planes_held: fact_gemm_splitk_static gives fact_gemm_splitk's results bit for bit, so where neither is asked for ranges both plan for what the static array
+// holds (us, any number of planes -> 32 MiB of them, [N][K]: 962 x 5464 x 14040 203 -> 230, 1369 x 3656 x 13456 187 -> 215, 370 x 464 x 89168 73.3 -> 75.5,
+// but 1067 x 6704 x 64504 1353 -> 1242).  The feed-forward block has no such twin and takes what it asks its caller for (1100 x 4096 x 14336 155 -> 137).
+static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_b, int act, bool allow_split, int ranges_asked = 0,
+                      size_t planes_held = kStaticScratchBytes)
 {
     Plan pl;
     const bool gated = act == FACT_ACT_SILU_GATE;
@@ -299,7 +305,7 @@ static Plan make_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int trans_
     // [K][N] 9.1 -> 10.7 us, 7715 x 560 x 184 8 % slower, others of [N][K] up to 3 % faster.)
     if (ranges_asked != kPlanned && batch == 1 && M > 64 && K >= 256 && all_fit && whole_cfg >= 0 && (allow_split || (double)M * N * K >= 0.5e9) &&
         tiles_of(g_configs[whole_cfg], M, nout, gated) <= kNumCU * wgs_per_cu(g_configs[whole_cfg]))
-        plan_one_round(pl, M, N, nout, K, trans_b, gated, allow_split, ranges_asked);
+        plan_one_round(pl, M, N, nout, K, trans_b, gated, allow_split, ranges_asked, planes_held);
     pl.group_m = 4;
     return pl;
 }
@@ -490,6 +496,9 @@ static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const C
 
 // ---- the one launch path every entry point goes through ----------------------------------------
 
+// The second GEMM of the feed-forward block: as many planes as its own workspace query asks for.
+static Plan down_plan(int64_t T, int64_t d_model, int64_t d_ff) { return make_plan(1, T, d_model, d_ff, 1, FACT_ACT_NONE, true, 0, SIZE_MAX); }
+
 // How a call runs, for fact_test_route: with one of these run() notes each launch in place of making it.
 struct Route {
     static constexpr int kMax = 4;
@@ -500,7 +509,7 @@ struct Route {
 };
 
 static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_table_split,
-               void *ws, size_t ws_bytes, hipStream_t stream, Route *route = nullptr)
+               void *ws, size_t ws_bytes, hipStream_t stream, Route *route = nullptr, const Plan *given = nullptr)
 {
     int rc = validate(q);
     if (rc != FACT_OK) return rc;
@@ -508,7 +517,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     const bool gated = q.ep.act == FACT_ACT_SILU_GATE;
     const int64_t nout = gated ? q.N / 2 : q.N;
 
-    Plan pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split, cfg_id >= 0 || cfg_id == FACT_CONFIG_GUARDED || split < 0 ? kPlanned : split);
+    Plan pl = given ? *given : make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split, cfg_id >= 0 || cfg_id == FACT_CONFIG_GUARDED || split < 0 ? kPlanned : split);
     double near_us = 0.0;
     if (pl.near_cfg >= 0) {
         auto has_room = [&](int ranges) { return ranges <= 1 || (ws && aligned16(ws) && ws_bytes >= splitk_ws_bytes(q.M, q.N, ranges)); };
@@ -819,7 +828,7 @@ Workspace mlp_workspace(int64_t T, int64_t d_model, int64_t d_ff, int act)
 {
     const bool gated = act == FACT_ACT_SILU_GATE;
     const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
-    const Plan p2 = make_plan(1, T, d_model, d_ff, 1, FACT_ACT_NONE, true);
+    const Plan p2 = down_plan(T, d_model, d_ff);
     const size_t b1 = p1.split < -1 ? plan_ws_bytes(p1, T, gated ? 2 * d_ff : d_ff, d_model, gated) : 0;   // GEMM 1 never splits K
     const size_t b2 = plan_ws_bytes(p2, T, d_model, d_ff, false), near = splitk_ws_bytes(T, d_model, p2.near_split);
     const size_t least = b1 > b2 ? b1 : b2;
@@ -936,7 +945,9 @@ static int block_mlp_impl(int f16, int64_t T, int64_t d_model, int64_t d_ff,
     const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
     rc = run(q1, -1, p1.split < -1 ? 0 : 1, 0, p1.split < -1, ws, ws_bytes, (hipStream_t)stream);
     if (rc != FACT_OK) return rc;
-    return run(q2, -1, 0, 0, need > 0 || ws, ws, ws_bytes, (hipStream_t)stream);
+    if (need == 0 && !ws) return run(q2, -1, 0, 0, false, nullptr, 0, (hipStream_t)stream);
+    const Plan p2 = down_plan(T, d_model, d_ff);
+    return run(q2, -1, 0, 0, true, ws, ws_bytes, (hipStream_t)stream, nullptr, &p2);
 }
 
 int fact_block_mlp(int64_t T, int64_t d_model, int64_t d_ff,
@@ -1019,7 +1030,6 @@ const char *fact_status_string(int status)
 // copy, at its own address, until the process ends.  Host code never uses the array's name as an
 // address (on the host it is a stand-in for the symbol): the address is asked for once per device,
 // with that device current, and kept.
-static constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 static constexpr int kMaxDevices = 64;
 static std::atomic<void *> g_scratch_ptr[kMaxDevices];

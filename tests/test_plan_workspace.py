@@ -1,6 +1,8 @@
 """What a call with a workspace takes and refuses (host logic, no GPU): a plan that wants more K ranges than the caller's workspace holds gives way to the one
 that fits, and the least that is accepted is what it was before such plans (sizes that callers may have kept)."""
+import math
 import os
+import random
 
 import pytest
 
@@ -37,16 +39,15 @@ def test_least_workspace(M, N, K, least, nk):
     assert route(M, N, K, nk, True, least - 16) == WORKSPACE
 
 
-@pytest.mark.parametrize("M,N,K", [(610, 5040, 13784), (1131, 3640, 12576), (2074, 1824, 44312)])
+@pytest.mark.parametrize("M,N,K", [(610, 5040, 13784), (1131, 3640, 12576), (2309, 1552, 63840)])
 def test_no_workspace_where_none_was_needed(M, N, K):
     # the plan has ranges where there is room for them, and none otherwise: nothing is refused
     full = fact.fact_gemm_splitk_workspace_bytes(M, N, K, 0)
     assert full > 0
-    with_room = [x[0] for x in route(M, N, K, 1, True, full)]
+    assert [x[0] for x in route(M, N, K, 1, True, full)] == ["tiles", "reduce"]
     for have in (0, 16, full - 16):
         without = route(M, N, K, 1, True, have)
         assert isinstance(without, list) and "reduce" not in [x[0] for x in without], (have, without)
-    assert with_room == ["tiles", "reduce"] or with_room == [x[0] for x in route(M, N, K, 1, True, 0)]
 
 
 @pytest.mark.parametrize("T,d,dff,act,least", [(384, 1024, 4096, 1, 6291456), (105, 4096, 14336, 2, 13762560), (600, 2048, 5632, 2, 9830400), (610, 5040, 13784, 1, 0)])
@@ -59,6 +60,27 @@ def test_ranges_that_the_caller_asks_for_stay():
         r = route(600, 2048, 5632, 1, True, 1 << 40, split=split)
         assert [x[0] for x in r] == (["tiles"] if split == 1 else ["tiles", "reduce"])
     assert route(600, 2048, 5632, 1, True, 3 * 600 * 2048 * 4 - 16, split=3) == WORKSPACE
+
+
+def test_no_ranges_beyond_the_static_array():
+    # (three ranges of 15 MB would be the quicker plan, and two are no clear gain)
+    assert fact.fact_gemm_splitk_workspace_bytes(2074, 1824, 44312, 0) == 0
+    assert [x[0] for x in route(2074, 1824, 44312, 1, True, 1 << 40)] == ["tiles"]
+
+
+def test_the_static_array_has_the_room_of_any_workspace():
+    # fact_gemm_splitk_static promises fact_gemm_splitk's bits: one plan for the array's size and for all beyond, wherever the array serves the call
+    rng = random.Random(7)
+    size = lambda lo, hi: int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+    cap = fact.fact_gemm_splitk_static_capacity()
+    shapes = [(1067, 6704, 64504), (370, 464, 89168), (1100, 4096, 14336)] + [(size(65, 8192), size(8, 1024) * 8, size(32, 16384) * 8) for _ in range(3000)]
+    split = 0
+    for M, N, K in shapes:
+        for nk in (0, 1):
+            here, beyond = route(M, N, K, nk, True, cap), route(M, N, K, nk, True, 1 << 40)
+            assert here == WORKSPACE or here == beyond, (M, N, K, nk, here, beyond)
+            split += len(beyond) > 1
+    assert split > 500
 
 
 # more K ranges than a grid counts, on shapes with a plan for one round, with a long K, and on few rows

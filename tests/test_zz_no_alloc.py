@@ -83,3 +83,10 @@ def test_static_scratch_refuses_what_does_not_fit_and_launches_nothing():
     torch.cuda.synchronize()
     assert (C == 0).all()
     assert fact.fact_gemm_splitk_static(M, N, K, A, K, B, N, 0, C, N, None, -2) == -7      # as fact_gemm_splitk: no forced tail split here
+
+
+# K ranges left to the plan: outputs whose planes would fill more than the array at the ranges that a launch of one round is best at
+@pytest.mark.parametrize("M,N,K", [(370, 464, 89168), (962, 5464, 14040)])
+@pytest.mark.parametrize("trans_b", [0, 1])
+def test_the_plan_is_the_one_of_a_workspace(M, N, K, trans_b):
+    _both(M, N, K, trans_b, 0, f"plan.{M}.{K}", oracle=False)
