@@ -128,7 +128,8 @@ struct Plan {
     int group_m = 4;
     bool loaded = false;   // from a registry file read at run time that says another thing than the compiled-in table
     // plan_one_round's choice, where it has one: it runs in the place of the above where the workspace of the call has room for its ranges.  (The call is
-    // refused by the above's need alone: callers may have sized their workspaces by it.)
+    // refused by the above's need alone: callers may have sized their workspaces by it.  Where that is nothing, a call without room for this one's ranges
+    // is planned as one without a workspace.)
     int near_cfg = -1, near_split = 1;
     double near_us = 0.0;
     int most_ranges() const { return near_cfg >= 0 && near_split > split ? near_split : split; }
@@ -521,7 +522,12 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     double near_us = 0.0;
     if (pl.near_cfg >= 0) {
         auto has_room = [&](int ranges) { return ranges <= 1 || (ws && aligned16(ws) && ws_bytes >= splitk_ws_bytes(q.M, q.N, ranges)); };
-        if (split > 0 || (has_room(pl.split) && has_room(pl.near_split))) { pl.cfg = pl.near_cfg; pl.split = pl.near_split; near_us = q.trans_b && q.N * q.K >= 1 << 24 ? 0.0 : pl.near_us; }      // (skinny_choice's lines for it are of warm operands)
+        if (split == 0 && pl.split <= 1 && !has_room(pl.near_split)) pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, false);
+        if (pl.near_cfg >= 0 && (split > 0 || (has_room(pl.split) && has_room(pl.near_split)))) {
+            pl.cfg = pl.near_cfg;
+            pl.split = pl.near_split;
+            near_us = q.trans_b && q.N * q.K >= 1 << 24 ? 0.0 : pl.near_us;      // (skinny_choice's lines for it are of warm operands)
+        }
     }
     if (cfg_id == FACT_CONFIG_GUARDED) {              // the guarded kernel on request: the sweep's reference result
         if (split > 1 || split < 0 || q.ep.out_f32) return FACT_ERR_UNSUPPORTED;

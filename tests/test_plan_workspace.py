@@ -62,6 +62,14 @@ def test_ranges_that_the_caller_asks_for_stay():
     assert route(600, 2048, 5632, 1, True, 3 * 600 * 2048 * 4 - 16, split=3) == WORKSPACE
 
 
+@pytest.mark.parametrize("M,N,K", [(235, 7744, 3736), (192, 8136, 3760), (374, 5416, 6304), (610, 5040, 13784)])
+def test_too_small_a_workspace_is_planned_as_none(M, N, K):
+    full, none = fact.fact_gemm_splitk_workspace_bytes(M, N, K, 0), route(M, N, K, 1, False, 0)
+    assert len(route(M, N, K, 1, True, full)) == 2 and len(none) == 1
+    for have in (0, 16, full // 32 * 16, full - 16):
+        assert route(M, N, K, 1, True, have) == none, have
+
+
 def test_no_ranges_beyond_the_static_array():
     # (three ranges of 15 MB would be the quicker plan, and two are no clear gain)
     assert fact.fact_gemm_splitk_workspace_bytes(2074, 1824, 44312, 0) == 0
