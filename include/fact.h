@@ -423,6 +423,9 @@ int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
                     void *C, int64_t ldc, int64_t stride_c,
                     const fact_epilogue *ep, int config_id, int split_k, int group_m,
                     void *ws, size_t ws_bytes, int max_launches, int *kinds, int *configs, int64_t *columns);
+/* ... and of the calling thread's last successful fact_test_route, launch by launch: 1 where the tile kernel's 16-byte stores of C pass the memory-side cache.
+ * Returns the number of launches. */
+int fact_test_route_streams(int max_launches, int *streams);
 
 /* Test hook (host logic only): the shape of work-group that fact_attention takes, in groups of 32 queries, groups that
  * share the keys, and keys of a block.  Any out pointer may be NULL. */

@@ -141,6 +141,8 @@ def lib():
         L.fact_test_tail_poll_budget.restype = None
         L.fact_test_route.argtypes = L.fact_gemm_ex.argtypes[:-1] + [_int, ip, ip, i64p]
         L.fact_test_route.restype = _int
+        L.fact_test_route_streams.argtypes = [_int, ip]
+        L.fact_test_route_streams.restype = _int
         L.fact_test_attention_shape.argtypes = [_i64, _i64, _i64, _i64, _int, ip, ip, ip]
         L.fact_test_attention_shape.restype = _int
         L.fact_tune_persistent.argtypes = [_int]
@@ -385,6 +387,12 @@ def fact_test_route(batch, M, N, K, A, lda, stride_a, B, ldb, stride_b, trans_b,
     r = lib().fact_test_route(batch, M, N, K, _addr(A), lda, stride_a, _addr(B), ldb, stride_b, int(trans_b), _addr(C), ldc, stride_c,
                               _ep(ep), int(config_id), int(split_k), int(group_m), _addr(ws), int(ws_bytes), 4, k, c, n)
     return r if r < 0 else [(ROUTES[k[i]], c[i], n[i]) for i in range(r)]
+
+
+def fact_test_route_streams():
+    """Of the thread's last fact_test_route that was not refused, launch by launch: whether C's stores pass the memory-side cache."""
+    v = (_int * 4)()
+    return [bool(v[i]) for i in range(lib().fact_test_route_streams(4, v))]
 
 
 def fact_test_attention_shape(batch, T, n_q_heads, head_dim, causal):

@@ -320,6 +320,7 @@ struct Problem {
     const void *B_up;     // gated with separate weights, else nullptr
     void *C; int64_t ldc, stride_c;
     fact_epilogue ep;
+    int store_stream = -1;    // of the call that this is a part of, -1: the call's own
 };
 
 static int validate(const Problem &q)
@@ -504,10 +505,12 @@ static Plan down_plan(int64_t T, int64_t d_model, int64_t d_ff) { return make_pl
 struct Route {
     static constexpr int kMax = 4;
     int launches = 0;
-    int kind[kMax], cfg[kMax];
+    int kind[kMax], cfg[kMax], streams[kMax];
     int64_t columns[kMax];           // contraction columns of the launch
-    int add(int k, int c, int64_t n) { if (launches < kMax) { kind[launches] = k; cfg[launches] = c; columns[launches] = n; } ++launches; return FACT_OK; }
+    int add(int k, int c, int64_t n, int stream = 0) { if (launches < kMax) { kind[launches] = k; cfg[launches] = c; columns[launches] = n; streams[launches] = stream; } ++launches; return FACT_OK; }
 };
+
+static thread_local Route g_last_route;      // of the thread's last fact_test_route
 
 static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_table_split,
                void *ws, size_t ws_bytes, hipStream_t stream, Route *route = nullptr, const Plan *given = nullptr)
@@ -570,6 +573,14 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
         else if (q.batch != 1 || !allow_table_split) return FACT_ERR_UNSUPPORTED;
     }
 
+    // Up to 56 MB of A and C together, C stays in the memory-side cache (see kStoreThrough); beyond, a program that walks a few such sets of buffers overflows it,
+    // and the launches that would have found their operands there lose more (us, streamed / kept, three sets in turn: feed-forward 768 x 3072 of 7288 tokens, 11 + 45 MB,
+    // 84.7 / 78.5, 7800 tokens, 12 + 48 MB, 88.3 / 89.5, 8192 tokens, 13 + 50 MB, 81.6 / 88.6; 1024 x 4096 of 5000 tokens, 10 + 41 MB, 98.4 / 98.7, 5600, 11 + 46 MB,
+    // 114.7 / 110.7, 6400 118.0 / 119.5; 48 and 64 x 512^3, 25 + 25 and 34 + 34 MB, 18.0 / 17.8 and 20.9 / 26.0, 256 x 256^3, 34 + 34 MB, 19.1 / 22.6).  The other way round where
+    // one set serves every layer: a block of 16 x 1024 tokens of 768, 25 + 100 MB, 311 / 302.  Of the whole call: the parts of a column split store alike (25 calls of two
+    // parts above the line, each part by its own line or both by the call's: level, 0.99-1.01).
+    const int store_stream = q.store_stream >= 0 ? q.store_stream : (double)q.batch * q.M * (nout + q.K) * 2.0 > 56.0 * (1 << 20);
+
     // (a registry file's choice, and persistent launches where they are asked for, are taken as they stand)
     if (cfg_id < 0 && pl.cfg >= 0 && !pl.loaded && (split == 0 || split == 1) && group_m <= 0 && pl.split == 1 && tail_g <= 1 && q.batch == 1 &&
         q.M > 64 && !g_persistent.load(std::memory_order_relaxed)) {
@@ -579,6 +590,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
             const uint16_t *B = (const uint16_t *)q.B, *up = gated ? (q.B_up ? (const uint16_t *)q.B_up : B + nout * q.ldb) : nullptr;
             const int64_t skip = q.trans_b ? sp.n1 * q.ldb : sp.n1;
             Problem first = q, rest = q;
+            first.store_stream = rest.store_stream = store_stream;
             first.N = gated ? 2 * sp.n1 : sp.n1;
             first.B_up = up;
             rest.N = gated ? 2 * n2 : n2;
@@ -619,13 +631,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     const int unit = gated ? 64 : 32;                 // elements of C between the addresses that rows may begin at (see kStoreThrough)
     a.store_through = ((uintptr_t)q.C & (uintptr_t)(2 * unit - 1)) == 0 && q.ldc % unit == 0 && (q.batch == 1 || q.stride_c % unit == 0);
 
-    // Up to 56 MB of A and C together, C stays in the memory-side cache (see kStoreThrough); beyond, a program that walks a few such sets of buffers overflows it,
-    // and the launches that would have found their operands there lose more (us, streamed / kept, three sets in turn: feed-forward 768 x 3072 of 7288 tokens, 11 + 45 MB,
-    // 84.7 / 78.5, 7800 tokens, 12 + 48 MB, 88.3 / 89.5, 8192 tokens, 13 + 50 MB, 81.6 / 88.6; 1024 x 4096 of 5000 tokens, 10 + 41 MB, 98.4 / 98.7, 5600, 11 + 46 MB,
-    // 114.7 / 110.7, 6400 118.0 / 119.5; 48 and 64 x 512^3, 25 + 25 and 34 + 34 MB, 18.0 / 17.8 and 20.9 / 26.0, 256 x 256^3, 34 + 34 MB, 19.1 / 22.6).  The other way round where
-    // one set serves every layer: a block of 16 x 1024 tokens of 768, 25 + 100 MB, 311 / 302.
-    const int64_t c_bytes = q.batch * q.M * nout * 2;
-    a.store_stream = c_bytes + q.batch * q.M * q.K * 2 > (int64_t)56 << 20;
+    a.store_stream = store_stream;
 
     hipError_t e;
     if (pl.cfg < 0) {
@@ -745,7 +751,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     // (the kernel numbers (K range or batch entry, tile) pairs with 32-bit integers)
     if (tiles_m * tiles_n * (a.splits > 1 ? (int64_t)a.splits : q.batch) > INT32_MAX / 2) return FACT_ERR_DIM;
     if (route) {
-        route->add(a.tail_g > 1 ? FACT_ROUTE_TAIL : a.persist_items > 0 ? FACT_ROUTE_PERSISTENT : FACT_ROUTE_TILES, pl.cfg, q.N);
+        route->add(a.tail_g > 1 ? FACT_ROUTE_TAIL : a.persist_items > 0 ? FACT_ROUTE_PERSISTENT : FACT_ROUTE_TILES, pl.cfg, q.N, a.store_stream);
         return a.splits > 1 || out_f32 ? route->add(FACT_ROUTE_REDUCE, -1, q.N) : FACT_OK;
     }
     e = c.launch(a, q.trans_b != 0, a.splits > 1 ? a.splits : (int)q.batch, stream);
@@ -895,11 +901,20 @@ int fact_test_route(int64_t batch, int64_t M, int64_t N, int64_t K,
     Route route;
     const int rc = run(q, config_id, split_k, group_m, ws != nullptr, ws, ws_bytes, nullptr, &route);
     if (rc != FACT_OK) return rc;
+    g_last_route = route;
     for (int i = 0; i < route.launches && i < max_launches && i < Route::kMax; ++i) {
         if (kinds) kinds[i] = route.kind[i];
         if (configs) configs[i] = route.cfg[i];
         if (columns) columns[i] = route.columns[i];
     }
+    return route.launches;
+}
+
+int fact_test_route_streams(int max_launches, int *streams)
+{
+    const Route &route = g_last_route;
+    for (int i = 0; i < route.launches && i < max_launches && i < Route::kMax; ++i)
+        if (streams) streams[i] = route.streams[i];
     return route.launches;
 }
 

@@ -1,5 +1,7 @@
 """Which kernels a GEMM call runs on (host logic, no GPU): the launches that each rule of the dispatch gives, around its lines."""
+import math
 import os
+import random
 
 import pytest
 
@@ -39,6 +41,21 @@ def test_column_split(M, N, K, nk, act):
     assert [x[0] for x in route(M, n1, K, nk, act)] == ["tiles"]
     assert [x[0] for x in route(M, N, K, nk, act, cfg=c1)] == ["tiles"]
     assert [x[0] for x in route(M, N, K, nk, act, batch=2)] == ["tiles"]
+
+
+# A and C above 56 MB: C passes the memory-side cache, in both parts of a call or in neither
+def test_both_parts_of_a_column_split_store_alike():
+    rng, seen = random.Random(3), [0, 0]
+    size = lambda lo, hi: int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+    shapes = [(6521, 3008, 1904, 0, 0), (3300, 5592, 4968, 1, 0), (4907, 7800, 1088, 1, 0), (1024, 50257, 768, 1, 0), (2048, 28672, 4096, 1, 2), (1, 64, 64, 1, 0)]
+    shapes += [(size(1024, 8192), size(128, 1024) * 8, size(32, 1024) * 8, 1, 0) for _ in range(4000)]
+    for M, N, K, nk, act in shapes:
+        r = route(M, N, K, nk, act)
+        if len(r) == 2:
+            past = M * ((N // 2 if act else N) + K) * 2 > 56 << 20
+            assert fact.fact_test_route_streams() == [past, past], (M, N, K, nk, act)
+            seen[past] += 1
+    assert seen[0] > 5 and seen[1] > 100
 
 
 def test_a_call_that_is_refused_has_no_route():
