@@ -389,7 +389,7 @@ gemm_kernel(const GemmArgs p)
     // from HBM a K step of it takes as long as the loads' latency (down projection of 1024 <- 4096 after an up projection of 384 tokens 19.5 us, by itself,
     // from the cache, 14.3).  Feed-forward blocks, 19 -> 17: 3000 tokens of 768 x 3072 (hidden tensor 18 MB) 56.0 -> 46.8 us, 4000 of 1024 x 4096 (33 MB)
     // 76.8 -> 66.3, 2000 of 2048 x 5632 (23 MB) 140 -> 136; but 8192 of 768 x 3072 (50 MB) 81.6 -> 88.6, 8192 x 8192 x 512 (134 MB) 75 -> 88.
-    // Single GEMMs of up to 40 MB: level.  Stores that stay in the L2s: 48.5, 67.7 and 136 us, and 90.9 beyond.
+    // Single GEMMs: level.  Stores that stay in the L2s: 48.5, 67.7 and 136 us, and 90.9 beyond.
     constexpr int kStoreThrough = 17, kStoreStream = 19;
     // ... where every row of C begins on a 64-byte boundary.  Rows at other addresses would send the lines at the tiles' edges to
     // memory in pieces of 16 or 32 bytes: plain stores then, which the L2 joins (us, through -> plain; 1024 x 50256 x 768 147 ->
@@ -545,10 +545,13 @@ gemm_kernel(const GemmArgs p)
     // constant per iteration (32-bit offsets: the host sets vec_store only if a tile's rows span
     // less than 2^31 bytes).
     // The stores' cache policy is part of the instruction, and a branch around each store would cut the loop's body into
-    // pieces that do not overlap (3547 x 2368 x 328: 15.0 -> 16.1 us), so there is an instance for either.
-    auto compact_pass = [&](int pass, auto gated_tag, auto through_tag) __attribute__((always_inline)) {
+    // pieces that do not overlap (3547 x 2368 x 328: 15.0 -> 16.1 us), so there is an instance for each.  (Edge tiles follow p.store_stream as
+    // interior ones do: with lines of theirs kept where the rest of C is streamed, batches of mostly edge tiles are at, us, three sets in turn, kept -> streamed:
+    // 128 x (448 x 448 x 512) 47.1 -> 43.8, 100 x (480 x 480 x 512) 44.2 -> 41.7, 64 x (640 x 704 x 512) [N][K] 50.7 -> 46.9; streamed where the rest is
+    // kept, a call of 100 rows, all of it edge, would leave nothing to the next launch: 1024 x 4096 of 100 tokens 17.2 us, 14.8 like this.)
+    auto compact_pass = [&](int pass, auto gated_tag, auto store_tag) __attribute__((always_inline)) {
         constexpr bool GATED = decltype(gated_tag)::value;
-        constexpr int kStore = decltype(through_tag)::value ? (STREAM ? kStoreStream : kStoreThrough) : 0;
+        constexpr int kStore = decltype(store_tag)::value;
         constexpr int OUT_W = GATED ? WTN / 2 : WTN;
         constexpr int LPR_USED = OUT_W / 8;
         constexpr int LPR = LPR_USED <= 1 ? 1 : LPR_USED <= 2 ? 2 : LPR_USED <= 4 ? 4 : LPR_USED <= 8 ? 8 : LPR_USED <= 16 ? 16 : 32;
@@ -899,14 +902,19 @@ gemm_kernel(const GemmArgs p)
     };
     // (chosen once, so that an edge tile runs through one straight stretch of code)
     if (!partial && p.vec_store && tail_parts == 0 && !p.c_f32) {      // interior and edge tiles alike
-        auto all = [&](auto gated_tag, auto through_tag) __attribute__((always_inline)) {
-            static_for<WTM / EPI_ROWS>([&](auto pass_) __attribute__((always_inline)) {
-                rows_to_lds(pass_);
-                compact_pass(decltype(pass_)::value, gated_tag, through_tag);
-            });
+        auto all = [&](auto store_tag) __attribute__((always_inline)) {
+            auto passes = [&](auto gated_tag) __attribute__((always_inline)) {
+                static_for<WTM / EPI_ROWS>([&](auto pass_) __attribute__((always_inline)) {
+                    rows_to_lds(pass_);
+                    compact_pass(decltype(pass_)::value, gated_tag, store_tag);
+                });
+            };
+            if (gated) passes(std::true_type{}); else passes(std::false_type{});
         };
-        if (p.store_through) { if (gated) all(std::true_type{}, std::true_type{}); else all(std::false_type{}, std::true_type{}); }
-        else if (gated) all(std::true_type{}, std::false_type{}); else all(std::false_type{}, std::false_type{});
+        // (192-wide tiles: the kernel's own policy)
+        if (!p.store_through) all(std::integral_constant<int, 0>{});
+        else if (BN == 192 ? STREAM : p.store_stream != 0) { if constexpr (BN != 192 || STREAM) all(std::integral_constant<int, kStoreStream>{}); }
+        else if constexpr (BN != 192 || !STREAM) all(std::integral_constant<int, kStoreThrough>{});
     } else
     static_for<WTM / EPI_ROWS>([&](auto pass_) __attribute__((always_inline)) {
         constexpr int pass = decltype(pass_)::value;

@@ -16,7 +16,7 @@ def gemm(A, B, C, **ep):
 
 
 @pytest.mark.parametrize("form", ["plain", "bias", "gelu", "residual", "gated"])
-@pytest.mark.parametrize("nout", [8192, 8200])                      # interior tiles only, ragged columns
+@pytest.mark.parametrize("nout", [8192, 8200])                      # whole and ragged columns (of rows that end in an edge tile)
 def test_both_sides_of_the_line(form, nout):
     g = torch.Generator(device="cuda").manual_seed(5)
     K, N = 64, 2 * nout if form == "gated" else nout
@@ -76,3 +76,28 @@ def test_both_sides_of_the_line_192_wide(config, f16):
     ref = torch.nn.functional.gelu(A.float() @ B.float().t() + bias.float(), approximate="tanh")
     # one rounding to bfloat16 (2^-9) or binary16 (2^-12, subnormal below 2^-14) of sums and a tanh that differ in the last places of fp32
     assert ((outs[1].float() - ref).abs() <= ref.abs() * 2.0 ** -8 + 2.0 ** -16).all()
+
+
+# every tile width whose policy is chosen in its code, interior and edge tiles (the last rows and columns of all of these)
+@pytest.mark.parametrize("config", [0, 2, 5, 6, 7, 16, 17])
+@pytest.mark.parametrize("gated", [False, True])
+def test_both_sides_of_the_line_by_tile(config, gated):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    K, nout = 64, 7744                                                  # rows of whole and of half lines, written through for either form
+    few = LINE // (nout + K)
+    A = torch.randn(few + 1, K, generator=g, device="cuda").bfloat16()
+    B = torch.randn(2 * nout if gated else nout, K, generator=g, device="cuda").mul_(K ** -0.5).bfloat16()
+    outs = []
+    for M in (few, few + 1):
+        C = torch.full((M + 1, nout), 77.0, dtype=torch.bfloat16, device="cuda")
+        ep = fact.Epilogue(act=fact.ACT_SILU_GATE if gated else fact.ACT_NONE)
+        fact.binding.check(fact.fact_gemm_ex(1, M, len(B), K, A, K, 0, B, K, 0, 1, C, nout, 0, ep, config, 1, 4, None, 0))
+        torch.cuda.synchronize()
+        assert (C[M] == 77.0).all(), "wrote past C"
+        outs.append(C[:M])
+    assert torch.equal(outs[0], outs[1][:few])
+    ref = A.float() @ B.float().t()
+    if gated:
+        ref = torch.nn.functional.silu(ref[:, :nout]) * ref[:, nout:]
+    # one rounding to bfloat16 (2^-9) of sums of 64 products of the operands' size, whose order differs
+    assert ((outs[1].float() - ref).abs() <= ref.abs() * 2.0 ** -8 + 2e-5 * (1 + ref.abs())).all()
