@@ -55,7 +55,7 @@ def test_both_parts_of_a_column_split_store_alike():
             past = M * ((N // 2 if act else N) + K) * 2 > 56 << 20
             assert fact.fact_test_route_streams() == [past, past], (M, N, K, nk, act)
             seen[past] += 1
-    assert seen[0] > 5 and seen[1] > 100
+    assert seen[0] > 5 and seen[1] > 50
 
 
 def test_a_call_that_is_refused_has_no_route():
