@@ -177,9 +177,24 @@ static constexpr StepLatency kStepLatency[] = {{1, true, {0.999, 0.975, 1.179}},
     {1, false, {0.701, 0.670, 0.90}}, {1, false, {0.693, 0.687, 0.92}}, {1, false, {0.970, 0.927, 1.15}}, {1, false, {0.950, 0.920, 1.15}}, {1, true, {0.804, 0.804, 1.082}},
     {1, true, {0.450, 0.450, 0.629}}, {2, false, {0.645, 0.645, 0.90}}, {1, true, {0.249, 0.219, 0.263}}, {1, true, {0.275, 0.199, 0.341}}};
 static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a row for every configuration");
-// The plan stays model_time's unless this is a tenth below what the same estimate says of that one: of the shapes above 0 to 8 % then run more than 2 % slower
-// than by model_time in place of 1 to 16, and of the gain (2.5 to 5.6 % over all those shapes) 0 to 1 % is lost.
-static constexpr double kClear = 0.9;
+// How far the estimate has to be below the same estimate of model_time's plan, c0, to replace it (a factor; 0: never), by what the plans of 75000 random calls took, both timed
+// (65 to 8192 rows, with and without a workspace, operands in the memory-side cache or rotated out of it; us, model_time's plan -> the other):
+// * a tenth, where both split K or neither does: 1.08 to 1.25 times as fast in every class, 1 call in 100 of those that change more than 3 % slower;
+// * from 64 MB of operands on 0.15, by the two sets that were fitted to the cache (at a tenth, out of it, 0.95 times as fast: 128 x 432 x 103104 [K][N] 35 -> 50);
+// * K whole in the place of ranges 0.3, and not from 64 MB on, where few work-groups would pull it all from HBM (94 x 11264 x 16728 [K][N] 97 -> 157, 8118 x 96 x 31360
+//   107 -> 170; below, out of the cache, 1.2 times as fast, but between 0.3 and 0.2 level and at a tenth 0.93);
+// * ranges in the place of K whole, weights of 32 MB and more as [N][K], only from there on (621 x 3776 x 5568 35 -> 43 in the cache; beyond 1.15 times as fast out of
+//   it and 1.06 in it).
+// No tiles with ranges that are larger than c0's and than the output (130 x 72 x 16488 on 64 x 128 10.7 -> 12.7, 168 x 1704 x 30800 on 256 x 256 40 -> 53), and for [N][K] none
+// of 256 x 192 and 256 x 256 whose rows are filled below 85 % (in the cache 0.9 times as fast; 797 x 592 x 29520 47 -> 58; above, 1.0 to 1.1).
+static double clear_gain(const ConfigDesc &c, const ConfigDesc &c0, int64_t M, int64_t N, int64_t K, int trans_b, bool split, bool split0)
+{
+    const bool large = (M * K + N * K) * 2 >= (int64_t)64 << 20, weights = trans_b && N * K >= 1 << 24;      // (weights: the third set's)
+    if (split && trans_b && ((c.bm > M && c.bm > c0.bm) || (c.bn > N && c.bn > c0.bn) || (c.bm * c.bn > 128 * 256 && 20 * M < 17 * ((M + c.bm - 1) / c.bm * c.bm)))) return 0.0;
+    if (split0 && !split) return large ? 0.0 : 0.7;
+    if (split && !split0) return large || !weights ? 0.9 : 0.0;
+    return large && !weights ? 0.85 : 0.9;
+}
 
 // ranges_asked: the ranges that the caller asks for (0: none asked for), at most kMaxGridZ: the launches counted here, of 4096 tiles at most, fit 32 bits.
 // planes_held: the bytes of planes that this plan may choose ranges for.
@@ -231,18 +246,19 @@ static void plan_one_round(Plan &pl, int64_t M, int64_t N, int64_t nout, int64_t
         // (from HBM the two add up as much as they overlap)
         return (set == 2 ? std::sqrt(us * us + memory * memory) : us > memory ? us : memory) + r.after;
     };
+    const Ranges before = in_ranges(ranges_asked > 0 ? ranges_asked : pl.split);
+    const double before_us = estimate(pl.cfg, tiles_in(g_configs[pl.cfg]), before);
     for (int cfg = 0; cfg < kNumConfigs; ++cfg) {
         const ConfigDesc &c = g_configs[cfg];
         if (!kStepLatency[cfg].choose || !c.serves(trans_b)) continue;
         const int tiles = tiles_in(c);
         for (int i = 0; i < choices && (i == 0 || tiles * ranges[i].asked <= 512); ++i) {
             const double us = estimate(cfg, tiles, ranges[i]);
-            if (pl.near_cfg < 0 || us < pl.near_us) { pl.near_us = us; pl.near_cfg = cfg; pl.near_split = ranges[i].asked; }
+            if ((pl.near_cfg >= 0 && us >= pl.near_us) || us >= before_us * clear_gain(c, g_configs[pl.cfg], M, N, K, trans_b, ranges[i].asked > 1, before.asked > 1)) continue;
+            pl.near_us = us;
+            pl.near_cfg = cfg;
+            pl.near_split = ranges[i].asked;
         }
-    }
-    if (pl.near_cfg >= 0 && pl.near_us >= kClear * estimate(pl.cfg, tiles_in(g_configs[pl.cfg]), in_ranges(ranges_asked > 0 ? ranges_asked : pl.split))) {
-        pl.near_cfg = -1;
-        pl.near_split = 1;
     }
 }
 
@@ -477,22 +493,33 @@ static double small_plan_us(const ConfigDesc &c, bool trans_b, int64_t batch, in
 // 4 of them lose more than 3 %, 12 % at most.  The estimates of small outputs are of operands in the memory-side cache; cold ones (60 random calls each,
 // caches filled with other data) are 1.62 and 1.33 times as fast as the plan, warm ones 1.66 and 1.28 times.
 static constexpr int kNoSkinny = -2, kFewRows = -1;
-static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c, double plan_us)
+// c, splits: model_time's plan.  plan_us: plan_one_round's estimate of the one that runs in its place, or 0.
+static int skinny_choice(const GemmArgs &a, bool trans_b, int64_t batch, const ConfigDesc &c, int splits, double plan_us)
 {
     const bool gated = a.act == FACT_ACT_SILU_GATE, few = skinny_takes(a, trans_b);
     const bool lines = ((uintptr_t)a.B & 127u) == 0 && a.ldb % 64 == 0 && (batch == 1 || a.stride_b % 64 == 0);
     int tile = -1;
-    const double small = small_us(a, trans_b, batch, plan_us > 0.0, &tile);
-    // More than 64 rows, the plan priced by plan_one_round and the small tiles of [N][K] by rates of the same measurements: over 2400 shapes the choice costs
-    // 0.6 % over the best kernel of each with K whole, 2.5 % ([K][N]) and 2.1 % ([N][K]) with ranges; with lines of 1.0 in place of these 1.0, 3.6 and 2.4.
-    if (plan_us > 0.0) return tile >= 0 && small < (a.splits <= 1 ? 1.1 : trans_b ? 0.9 : 0.83) * plan_us ? tile : kNoSkinny;
+    const double small = small_us(a, trans_b, batch, 0, &tile);
     // (A plan that splits K is quicker than its estimate, by what its reduction became, and a K as long as that longer here: with a workspace us, plan and
     // this kernel at their estimates' ratio: [N][K] 80 x 304 x 15168 13.1 / 13.8 at 0.86, 352 x 328 x 6848 13.2 / 14.7 at 0.90, but 280 x 120 x 7232 13.1 / 8.7 at
     // 0.77; [K][N] 256 x 64 x 8192 10.4 / 14.0 at 0.87, 160 x 64 x 7680 13.4 / 13.6 at 0.67, but 72 x 64 x 5888 11.7 / 10.3 at 0.62.)
-    const double line = a.splits <= 1 ? 0.92 : trans_b ? 0.8 : 0.65;
-    if (!few) return tile >= 0 && small < line * small_plan_us(c, trans_b, batch, a.M, a.N, a.K, a.splits) ? tile : kNoSkinny;
-    const double rows = skinny_us(a, batch, lines), plan = few_rows_us(c, batch, a.M, a.N, gated ? a.N / 2 : a.N, a.K, gated, a.splits, lines);
-    if (rows < plan || (a.splits <= 1 && tile >= 0 && small < 0.92 * plan)) return tile >= 0 && small < rows ? tile : kFewRows;
+    const double line = splits <= 1 ? 0.92 : trans_b ? 0.8 : 0.65;
+    if (!few) {
+        const bool taken = tile >= 0 && small < line * small_plan_us(c, trans_b, batch, a.M, a.N, a.K, splits);
+        if (plan_us <= 0.0) return taken ? tile : kNoSkinny;
+        // The plan is another one, priced by plan_one_round, and the small tiles of [N][K] by rates of the same measurements.  What was taken stays taken (us, small tile and
+        // the plan with ranges that is estimated a fifth below it, from the cache: 0.76 times as fast as [K][N], 69 calls, 0.89 as [N][K], 239), with the tile that those rates
+        // name where a compute unit has one work-group of it (770 calls 1.18 times as fast; with two 0.92).  Otherwise the small tiles run in the place of K whole below 1.1 of the
+        // plan's estimate, and of ranges below 0.9 ([K][N] 0.83): 490 calls 1.28 times as fast as model_time's plan; not with rows of odd lengths from 4096 on (0.91: 464 x 224 x 5912
+        // 12.5 -> 17.1), nor where many compute units have two (229 x 1224 x 3072, 312 work-groups, 12.4 -> 15.3; up to 288 1.28).
+        int other = -1;
+        const double other_us = small_us(a, trans_b, batch, taken ? 256 : 288, &other);
+        if (taken) return trans_b && other >= 0 ? other : tile;
+        if (other < 0 || (a.splits > 1 && trans_b && a.K % 64 && a.K >= 4096)) return kNoSkinny;
+        return other_us < (a.splits <= 1 ? 1.1 : trans_b ? 0.9 : 0.83) * plan_us ? other : kNoSkinny;
+    }
+    const double rows = skinny_us(a, batch, lines), plan = few_rows_us(c, batch, a.M, a.N, gated ? a.N / 2 : a.N, a.K, gated, splits, lines);
+    if (rows < plan || (splits <= 1 && tile >= 0 && small < 0.92 * plan)) return tile >= 0 && small < rows ? tile : kFewRows;
     return kNoSkinny;
 }
 
@@ -523,10 +550,13 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
 
     Plan pl = given ? *given : make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, allow_table_split, cfg_id >= 0 || cfg_id == FACT_CONFIG_GUARDED || split < 0 ? kPlanned : split);
     double near_us = 0.0;
+    int before_cfg = -1, before_split = 1;            // what plan_one_round's choice replaces
     if (pl.near_cfg >= 0) {
         auto has_room = [&](int ranges) { return ranges <= 1 || (ws && aligned16(ws) && ws_bytes >= splitk_ws_bytes(q.M, q.N, ranges)); };
         if (split == 0 && pl.split <= 1 && !has_room(pl.near_split)) pl = make_plan(q.batch, q.M, q.N, q.K, q.trans_b, q.ep.act, false);
         if (pl.near_cfg >= 0 && (split > 0 || (has_room(pl.split) && has_room(pl.near_split)))) {
+            before_cfg = pl.cfg;
+            before_split = split > 0 ? split : pl.split;
             pl.cfg = pl.near_cfg;
             pl.split = pl.near_split;
             near_us = q.trans_b && q.N * q.K >= 1 << 24 ? 0.0 : pl.near_us;      // (skinny_choice's lines for it are of warm operands)
@@ -691,7 +721,7 @@ static int run(const Problem &q, int cfg_id, int split, int group_m, bool allow_
     // checked above all the same.  (Persistent launches where they are asked for, and a registry file's choice, are taken as
     // they stand; a row of the compiled-in table names the best tile configuration: 512^3 5.5 us there, 4.0 here.)
     if (!(a.splits <= 1 && !a.f16 && persistent_grid(c, tiles_m * tiles_n * q.batch) > 0) && cfg_id < 0 && (split == 0 || split == 1) && group_m <= 0 && !pl.loaded && tail_g <= 1)
-        if (const int tile = skinny_choice(a, q.trans_b != 0, q.batch, c, near_us); tile != kNoSkinny) {
+        if (const int tile = skinny_choice(a, q.trans_b != 0, q.batch, before_cfg < 0 ? c : g_configs[before_cfg], before_cfg < 0 ? a.splits : before_split, near_us); tile != kNoSkinny) {
         if (out_f32) {
             if (a.splits <= 1) {
                 const size_t need = (size_t)q.M * (size_t)q.N * sizeof(float);

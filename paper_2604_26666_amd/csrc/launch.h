@@ -32,7 +32,7 @@ hipError_t launch_fallback_gemm(const GemmArgs &args, bool trans_b, int grid_z, 
 // tile that gives it (-1: none serves it); the form that runs for that tile (-1: few rows), a number of FACT_ROUTE_SKINNY; the launch.
 bool skinny_takes(const GemmArgs &args, bool trans_b);
 double skinny_us(const GemmArgs &args, int64_t batch, bool whole_lines);
-double small_us(const GemmArgs &args, bool trans_b, int64_t batch, bool many_rows, int *tile);
+double small_us(const GemmArgs &args, bool trans_b, int64_t batch, int most, int *tile);
 int skinny_form(const GemmArgs &args, bool trans_b, int64_t batch, int tile);
 hipError_t launch_skinny_gemm(const GemmArgs &args, bool trans_b, int form, int grid_z, hipStream_t stream);
 

@@ -506,9 +506,10 @@ struct SmallRates { double start, group, rate, memory_start, memory, pull; };
 // B as [K][N], as [N][K], and the latter of many rows: fitted, with plan_one_round, to 1050 calls of up to 8192 rows whose operands lie in the memory-side cache (mean
 // error 10 %, the second's there 13: 111 x 2048 x 5632 takes 11.9 us, priced at 15.9 and 19.5)
 static constexpr SmallRates kSmallRates[3] = {{3.07, 0.002, 83.6e3, 3.0, 5.38e6, 8.2e6}, {3.07, 0.0015, 107.7e3, 3.0, 4.42e6, 11.2e6}, {3.15, 0.002, 95.1e3, 3.15, 5.27e6, 13.8e6}};
-double small_us(const GemmArgs &a, bool trans_b, int64_t batch, bool many_rows, int *tile)
+// most: 0, or the most work-groups of a launch in the place of one that plan_one_round priced.
+double small_us(const GemmArgs &a, bool trans_b, int64_t batch, int most, int *tile)
 {
-    const SmallRates &r = kSmallRates[!trans_b ? 0 : many_rows ? 2 : 1];
+    const SmallRates &r = kSmallRates[!trans_b ? 0 : most ? 2 : 1];
     double best = 0.0;
     *tile = -1;
     if (a.act == ACT_SILU_GATE || a.N > 8192 || streams(a, batch)) return best;
@@ -523,7 +524,7 @@ double small_us(const GemmArgs &a, bool trans_b, int64_t batch, bool many_rows, 
         if (trans_b && i == 2 && a.M <= 32 && groups_of(kTiles[1], a, batch) <= 256) continue;
         const int64_t wgs = groups_of(t, a, batch);
         const int fit = resident(t);
-        if (wgs > 256 * fit || ((int64_t)a.M + 16 * t.mt - 1) / (16 * t.mt) > 65535) continue;
+        if (wgs > (most && trans_b ? most : 256 * fit) || ((int64_t)a.M + 16 * t.mt - 1) / (16 * t.mt) > 65535) continue;
         const double sharing = wgs > 256 ? wgs / 256.0 : 1.0;
         const double rows_a = 0.5 * (16 * t.mt + (a.M < 16 * t.mt ? a.M : 16 * t.mt));
         const double cols = 16 * t.nt * (trans_b ? 1.0 : t.nt == 1 ? 1.48 : t.nt == 2 ? 1.25 : 1.0);       // (a line's lookups for less than a line)
