@@ -866,16 +866,20 @@ Workspace splitk_workspace(int64_t M, int64_t N, int64_t K)
     return {least, full > least ? full : least};
 }
 
-Workspace mlp_workspace(int64_t T, int64_t d_model, int64_t d_ff, int act)
+// The two GEMMs of the feed-forward block as planned for any workspace, and what they need.
+struct MlpPlans { Plan up, down; Workspace need; };
+static MlpPlans mlp_plans(int64_t T, int64_t d_model, int64_t d_ff, int act)
 {
     const bool gated = act == FACT_ACT_SILU_GATE;
-    const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
-    const Plan p2 = down_plan(T, d_model, d_ff);
-    const size_t b1 = p1.split < -1 ? plan_ws_bytes(p1, T, gated ? 2 * d_ff : d_ff, d_model, gated) : 0;   // GEMM 1 never splits K
-    const size_t b2 = plan_ws_bytes(p2, T, d_model, d_ff, false), near = splitk_ws_bytes(T, d_model, p2.near_split);
-    const size_t least = b1 > b2 ? b1 : b2;
-    return {least, near > least ? near : least};
+    MlpPlans p{make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true), down_plan(T, d_model, d_ff), {}};
+    const size_t up = p.up.split < -1 ? plan_ws_bytes(p.up, T, gated ? 2 * d_ff : d_ff, d_model, gated) : 0;   // GEMM 1 never splits K
+    const size_t down = plan_ws_bytes(p.down, T, d_model, d_ff, false), near = splitk_ws_bytes(T, d_model, p.down.near_split);
+    p.need.least = up > down ? up : down;
+    p.need.full = near > p.need.least ? near : p.need.least;
+    return p;
 }
+
+Workspace mlp_workspace(int64_t T, int64_t d_model, int64_t d_ff, int act) { return mlp_plans(T, d_model, d_ff, act).need; }
 
 }  // namespace fact
 
@@ -989,16 +993,16 @@ static int block_mlp_impl(int f16, int64_t T, int64_t d_model, int64_t d_ff,
     int rc = validate(q1);
     if (rc == FACT_OK) rc = validate(q2);
     if (rc != FACT_OK) return rc;
-    const size_t need = mlp_workspace(T, d_model, d_ff, act).least;
+    const MlpPlans plans = mlp_plans(T, d_model, d_ff, act);
+    const size_t need = plans.need.least;
     if (need > 0 && (!ws || ws_bytes < need)) return FACT_ERR_WORKSPACE;
     if (need > 0 && !aligned16(ws)) return FACT_ERR_ALIGN;
     // (the first GEMM never splits K into planes, but its last round of tiles may be split)
-    const Plan p1 = make_plan(1, T, gated ? 2 * d_ff : d_ff, d_model, 1, act, true);
-    rc = run(q1, -1, p1.split < -1 ? 0 : 1, 0, p1.split < -1, ws, ws_bytes, (hipStream_t)stream);
+    const bool tail = plans.up.split < -1;
+    rc = run(q1, -1, tail ? 0 : 1, 0, tail, ws, ws_bytes, (hipStream_t)stream);
     if (rc != FACT_OK) return rc;
     if (need == 0 && !ws) return run(q2, -1, 0, 0, false, nullptr, 0, (hipStream_t)stream);
-    const Plan p2 = down_plan(T, d_model, d_ff);
-    return run(q2, -1, 0, 0, true, ws, ws_bytes, (hipStream_t)stream, nullptr, &p2);
+    return run(q2, -1, 0, 0, true, ws, ws_bytes, (hipStream_t)stream, nullptr, &plans.down);
 }
 
 int fact_block_mlp(int64_t T, int64_t d_model, int64_t d_ff,
