@@ -162,7 +162,7 @@ static double model_time(const ConfigDesc &c, int64_t batch, int64_t M, int64_t 
 // chip's figure.  A compute unit's work-groups walk their K steps, each of them the longest of a latency (lat: an own one per tile), what the
 // compute unit can pull of operands, and what the L2s deliver to all compute units together; then an epilogue; never faster than HBM
 // delivers the operands; split K costs a launch and its planes.  Fitted to 62000 timed launches (1900 shapes of 65 to 8192 rows, 64 to 28672 columns,
-// K of 64 to 131072, one to 256 ranges; mean error 9 %).  Its choice against the best of all configurations and ranges, geometric mean over the
+// K of 64 to 131072, one to 256 ranges; mean error 9 %; on an independent sample 8 to 12 %, profiles/gemm_one_round_calls.csv).  Its choice against the best of all configurations and ranges, geometric mean over the
 // shapes at which model_time chooses at most one round: K whole 1.5 %, with ranges 2.4 % ([N][K] 1.3 and 2.6; K of 8192 and more 2.4) where model_time's choice is
 // 5.9, 8.0 and 15 % behind.  Beyond a round it is the other way round (4.8 and 1.6 %): epilogues run under other work-groups' steps there.
 // Three sets: B as [K][N], as [N][K], and as [N][K] from 32 MB on, which a program with several such matrices finds in HBM (fitted to 28000 launches of 320
@@ -181,17 +181,21 @@ static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a 
 // (65 to 8192 rows, with and without a workspace, operands in the memory-side cache or rotated out of it; us, model_time's plan -> the other):
 // * a tenth, where both split K or neither does: 1.08 to 1.25 times as fast in every class, 1 call in 100 of those that change more than 3 % slower;
 // * from 64 MB of operands on 0.15, by the two sets that were fitted to the cache (at a tenth, out of it, 0.95 times as fast: 128 x 432 x 103104 [K][N] 35 -> 50);
-// * K whole in the place of ranges 0.3, and not from 64 MB on, where few work-groups would pull it all from HBM (94 x 11264 x 16728 [K][N] 97 -> 157, 8118 x 96 x 31360
-//   107 -> 170; below, out of the cache, 1.2 times as fast, but between 0.3 and 0.2 level and at a tenth 0.93);
+// * K whole in the place of ranges not from 64 MB on, where few work-groups would pull it all from HBM (94 x 11264 x 16728 [K][N] 97 -> 157, 8118 x 96 x 31360
+//   107 -> 170).  Below, of 300 random calls and 47 feed-forward blocks that change between a tenth and 0.3: 0.3 with K of 4096 and more, outputs below 0.6 M elements and operands
+//   of 8 MB and more (at a tenth 1.01 times as fast in the cache and 0.90 out of it; blocks 320 x 1024 x 4096 22.3 -> 23.9 and 27.3 -> 33.3), 0.2 from 32 MB on (at a tenth 1.02
+//   and 0.94), and a tenth elsewhere: 1.10 and 1.03; blocks of 65 to 2048 tokens 1.08 and 1.00 (320 x 768 x 3072 19.1 -> 14.5 and 23.5 -> 17.6, 1237 x 1024 x 4096
+//   44.2 -> 39.2 and 49.2 -> 48.0, 512 x 2048 x 5632 58.2 -> 52.6 and 59.4 -> 59.9);
 // * ranges in the place of K whole, weights of 32 MB and more as [N][K], only from there on (621 x 3776 x 5568 35 -> 43 in the cache; beyond 1.15 times as fast out of
 //   it and 1.06 in it).
 // No tiles with ranges that are larger than c0's and than the output (130 x 72 x 16488 on 64 x 128 10.7 -> 12.7, 168 x 1704 x 30800 on 256 x 256 40 -> 53), and for [N][K] none
 // of 256 x 192 and 256 x 256 whose rows are filled below 85 % (in the cache 0.9 times as fast; 797 x 592 x 29520 47 -> 58; above, 1.0 to 1.1).
 static double clear_gain(const ConfigDesc &c, const ConfigDesc &c0, int64_t M, int64_t N, int64_t K, int trans_b, bool split, bool split0)
 {
-    const bool large = (M * K + N * K) * 2 >= (int64_t)64 << 20, weights = trans_b && N * K >= 1 << 24;      // (weights: the third set's)
+    const int64_t bytes = (M * K + N * K) * 2;
+    const bool large = bytes >= (int64_t)64 << 20, weights = trans_b && N * K >= 1 << 24;      // (weights: the third set's)
     if (split && trans_b && ((c.bm > M && c.bm > c0.bm) || (c.bn > N && c.bn > c0.bn) || (c.bm * c.bn > 128 * 256 && 20 * M < 17 * ((M + c.bm - 1) / c.bm * c.bm)))) return 0.0;
-    if (split0 && !split) return large ? 0.0 : 0.7;
+    if (split0 && !split) return large ? 0.0 : K >= 4096 && M * N < 600000 && bytes >= 8000000 ? 0.7 : bytes >= (int64_t)32 << 20 ? 0.8 : 0.9;
     if (split && !split0) return large || !weights ? 0.9 : 0.0;
     return large && !weights ? 0.85 : 0.9;
 }

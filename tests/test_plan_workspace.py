@@ -115,13 +115,20 @@ def test_tiles(M, N, K, nk, tile):
     assert kind == "tiles" and tuple(sorted(fact.fact_config_info(cfg)[:2])) == tuple(sorted(tile))
 
 
+# K whole in the place of the ranges that model_time splits it in: by a clear gain, a clearer one where few compute units read much, and never from 64 MB on
+@pytest.mark.parametrize("M,N,K,kinds", [(320, 768, 3072, ["skinny"]), (320, 2048, 5632, ["tiles"]), (1237, 1024, 4096, ["tiles"]), (229, 1224, 3072, ["tiles"]),
+                                         (320, 1024, 4096, ["tiles", "reduce"]), (256, 2048, 5632, ["tiles", "reduce"]), (8118, 96, 31360, ["tiles", "reduce"])])
+def test_whole_k_in_the_place_of_ranges(M, N, K, kinds):
+    assert [x[0] for x in route(M, N, K, 1, True, 1 << 40)] == kinds
+
+
 # calls with a workspace at which model_time's plan is the quicker one, each for a reason of its own (at clear_gain and skinny_choice): where the estimate for one
 # round says otherwise it stays.  (M, N, K, B as [N][K], kinds of launch, tile)
 @pytest.mark.parametrize("M,N,K,nk,kinds,tile", [
     (94, 11264, 16728, 0, ["tiles", "reduce"], (128, 256)), (8118, 96, 31360, 0, ["tiles", "reduce"], (256, 128)), (7002, 128, 20864, 1, ["tiles", "reduce"], (128, 128)),
     (128, 432, 103104, 0, ["tiles", "reduce"], (128, 128)), (130, 72, 16488, 1, ["tiles", "reduce"], (64, 64)), (168, 1704, 30800, 1, ["tiles", "reduce"], (128, 128)),
     (797, 592, 29520, 1, ["tiles", "reduce"], (128, 192)), (621, 3776, 5568, 1, ["tiles"], (128, 128)), (464, 224, 5912, 1, ["tiles", "reduce"], (64, 64)),
-    (229, 1224, 3072, 1, ["tiles", "reduce"], (64, 64)), (208, 80, 6784, 0, ["skinny"], None), (128, 96, 11008, 1, ["skinny"], None)])
+    (208, 80, 6784, 0, ["skinny"], None), (128, 96, 11008, 1, ["skinny"], None)])
 def test_model_times_plan_stays(M, N, K, nk, kinds, tile):
     r = route(M, N, K, nk, True, 1 << 40)
     assert [x[0] for x in r] == kinds
