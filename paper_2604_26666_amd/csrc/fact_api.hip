@@ -180,7 +180,8 @@ static_assert(sizeof(kStepLatency) / sizeof(kStepLatency[0]) == kNumConfigs, "a 
 // How far the estimate has to be below the same estimate of model_time's plan, c0, to replace it (a factor; 0: never), by what the plans of 75000 random calls took, both timed
 // (65 to 8192 rows, with and without a workspace, operands in the memory-side cache or rotated out of it; us, model_time's plan -> the other):
 // * a tenth, where both split K or neither does: 1.08 to 1.25 times as fast in every class, 1 call in 100 of those that change more than 3 % slower;
-// * from 64 MB of operands on 0.15, by the two sets that were fitted to the cache (at a tenth, out of it, 0.95 times as fast: 128 x 432 x 103104 [K][N] 35 -> 50);
+// * 0.15 from 64 MB of operands on where B is [K][N] and the output at most 512 x 512 (45 calls that change between the two, at a tenth 1.08 times as fast in the cache and 0.93
+//   out of it: 128 x 432 x 103104 35 -> 50; as [N][K] 36 calls 1.15 and 0.93, 424 x 112 x 71104 24.9 -> 21.0 and 28.0 -> 29.0; larger outputs, 68 calls, 1.15 and 1.21);
 // * K whole in the place of ranges not from 64 MB on, where few work-groups would pull it all from HBM (94 x 11264 x 16728 [K][N] 97 -> 157, 8118 x 96 x 31360
 //   107 -> 170).  Below, of 300 random calls and 47 feed-forward blocks that change between a tenth and 0.3: 0.3 with K of 4096 and more, outputs below 0.6 M elements and operands
 //   of 8 MB and more (at a tenth 1.01 times as fast in the cache and 0.90 out of it; blocks 320 x 1024 x 4096 22.3 -> 23.9 and 27.3 -> 33.3), 0.2 from 32 MB on (at a tenth 1.02
@@ -197,7 +198,7 @@ static double clear_gain(const ConfigDesc &c, const ConfigDesc &c0, int64_t M, i
     if (split && trans_b && ((c.bm > M && c.bm > c0.bm) || (c.bn > N && c.bn > c0.bn) || (c.bm * c.bn > 128 * 256 && 20 * M < 17 * ((M + c.bm - 1) / c.bm * c.bm)))) return 0.0;
     if (split0 && !split) return large ? 0.0 : K >= 4096 && M * N < 600000 && bytes >= 8000000 ? 0.7 : bytes >= (int64_t)32 << 20 ? 0.8 : 0.9;
     if (split && !split0) return large || !weights ? 0.9 : 0.0;
-    return large && !weights ? 0.85 : 0.9;
+    return large && !trans_b && M * N <= 512 * 512 ? 0.85 : 0.9;
 }
 
 // ranges_asked: the ranges that the caller asks for (0: none asked for), at most kMaxGridZ: the launches counted here, of 4096 tiles at most, fit 32 bits.

@@ -122,6 +122,13 @@ def test_whole_k_in_the_place_of_ranges(M, N, K, kinds):
     assert [x[0] for x in route(M, N, K, 1, True, 1 << 40)] == kinds
 
 
+# ranges of another tile from 64 MB on: by the same gain as below but for small outputs of B as [K][N]
+@pytest.mark.parametrize("M,N,K,nk,tile", [(424, 112, 71104, 1, (64, 64)), (128, 432, 103104, 0, (128, 128))])
+def test_ranges_of_large_operands(M, N, K, nk, tile):
+    r = route(M, N, K, nk, True, 1 << 40)
+    assert [x[0] for x in r] == ["tiles", "reduce"] and tuple(fact.fact_config_info(r[0][1])[:2]) == tile
+
+
 # calls with a workspace at which model_time's plan is the quicker one, each for a reason of its own (at clear_gain and skinny_choice): where the estimate for one
 # round says otherwise it stays.  (M, N, K, B as [N][K], kinds of launch, tile)
 @pytest.mark.parametrize("M,N,K,nk,kinds,tile", [
